@@ -152,18 +152,11 @@ size_t bpc_workspace_status_offset(const bpc_params_t *params, uint64_t D) {
   return ws_layout(params, D).status;
 }
 
-// Workspace of an update call: LANS with caller-defined blocks keeps three f64 sums per block
-// where the layout has room for three per partition.
+// Workspace of an update call: LANS with caller-defined blocks needs room for them where the
+// layout ends.
 static size_t update_ws_bytes(const WsLayout &lay, bool caller_blocks, uint64_t n_blocks, uint64_t D) {
-  size_t need = lay.total;
-  if (caller_blocks) {
-    // three f64 sums per block (the two-launch form) or the tables of the one-pass form
-    size_t with_blocks = lay.norms + (sizeof(double) * 3 * (size_t)n_blocks + 255) / 256 * 256;
-    const size_t one_pass = lay.norms + block_ws(nullptr, n_blocks, cdiv(D, kSTile)).bytes;
-    if (one_pass > with_blocks) with_blocks = one_pass;
-    if (with_blocks > need) need = with_blocks;
-  }
-  return need;
+  const size_t with_blocks = caller_blocks ? lay.norms + lans_blocks_room(n_blocks, cdiv(D, kSTile)) : 0;
+  return with_blocks > lay.total ? with_blocks : lay.total;
 }
 
 size_t bpc_update_workspace_bytes(const bpc_params_t *params, uint64_t D, uint64_t n_blocks) {

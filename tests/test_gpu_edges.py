@@ -512,3 +512,39 @@ def test_lans_blocks_of_every_shape_in_one_call(gu, orc, kind, lr):
     assert np.array_equal(mg.view(np.uint32), m.view(np.uint32))
     assert np.array_equal(vg.view(np.uint32), v.view(np.uint32))
     assert gu.lans_step_close(xg, x, x0, blocks)
+
+
+@pytest.mark.parametrize("kind", ["sign", "dither15", "topk16", "randk"])
+@pytest.mark.parametrize("shape", ["one_element", "one_block_ragged", "whole_tiles", "a_block_an_element", "many_blocks_and_a_long_one"])
+def test_lans_blocks_at_the_edges_of_tiles_and_of_the_block_search(gu, orc, kind, shape):
+    """LANS over caller-defined blocks at the ends of what its passes walk: a single element; one
+    block over everything, ragged; blocks that are exactly tiles of 8192 elements; 8193 blocks of
+    one element (the block search goes three levels deep); 70000 blocks, so that a workgroup of
+    the totals pass takes several groups of 64, then one block over many tiles and partitions."""
+    import torch
+    bpc = gu.bpc
+    pe = 65536
+    offs = {"one_element": [0, 1], "one_block_ragged": [0, 2 * pe + 8191], "whole_tiles": list(range(0, 2 * pe + 1, 8192)),
+            "a_block_an_element": list(range(8194)),
+            "many_blocks_and_a_long_one": list(range(70001)) + [4 * pe + 8193]}[shape]
+    blocks = np.array(offs, dtype=np.uint64)
+    D = int(blocks[-1])
+    kind, kw = ("dither", dict(levels=15, seed=5, stream_id=2)) if kind == "dither15" else (kind, KW[kind])
+    po, pb = gu.both_params(orc, kind, pe, **kw)
+    rs = np.random.default_rng(78)
+    payload = orc.compress(po, (rs.standard_t(3.0, D) * 1e-2).astype(np.float32), None)
+    x0 = (rs.standard_normal(D) * 0.02).astype(np.float32)
+    m0 = (rs.standard_normal(D) * 1e-3).astype(np.float32)
+    v0 = (rs.random(D) * 1e-5).astype(np.float32)
+    oo = orc.make_opt(orc.OPT_LANS, 0.5, 0.9, 0.999, 1e-8, 0.01, 4, block_offsets=blocks)
+    ob = bpc.make_opt(bpc.OPT_LANS, 0.5, 0.9, 0.999, 1e-8, 0.01, 4,
+                      block_offsets=torch.from_numpy(blocks.astype(np.int64)).to(gu.DEV))
+    x, m, v = x0.copy(), m0.copy(), v0.copy()
+    orc.adaptive_update(po, payload, D, x, m, v, oo)
+    xg, mg, vg = gu.gpu_update(pb, payload, x0, m0, v0, ob)
+    if kind == "randk":   # repeated draws add up in a free order
+        assert gu.close(mg, m, 1e-6) and gu.close(vg, v, 2e-6)
+    else:
+        assert np.array_equal(mg.view(np.uint32), m.view(np.uint32))
+        assert np.array_equal(vg.view(np.uint32), v.view(np.uint32))
+    assert gu.lans_step_close(xg, x, x0, blocks)
