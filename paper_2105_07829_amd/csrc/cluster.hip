@@ -1,6 +1,9 @@
 // Host-side support of the cluster kernels (see cluster.hpp).
+#include <atomic>
 #include <mutex>
 #include <stdlib.h>
+#include <time.h>
+#include <unistd.h>
 #include "cluster.hpp"
 
 namespace bpc {
@@ -37,6 +40,24 @@ bool g_have[kMaxDevices];
 // nodes, and an event recorded during capture is not one a later eager launch could wait for.
 // Keeping replays of such a graph apart from cluster kernels launched elsewhere at the same
 // time is then up to the caller.
+// A number no other launch gets: a counter that starts somewhere else in every process, through a
+// bijection of the 64-bit numbers (Steele, Lea and Flood's SplitMix64 finaliser), so that two tags
+// differ in about half their bits.
+static uint64_t next_tag() {
+  static std::atomic<uint64_t> counter{[] {
+    struct timespec ts = {};
+    clock_gettime(CLOCK_REALTIME, &ts);
+    return ((uint64_t)ts.tv_sec * 1000000007ull) ^ ((uint64_t)ts.tv_nsec << 33) ^ ((uint64_t)getpid() << 20);
+  }()};
+  for (;;) {
+    uint64_t z = counter.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    if (z != 0) return z;
+  }
+}
+
 static bool is_capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &st) != hipSuccess) return false;
@@ -47,8 +68,10 @@ static bool is_capturing(hipStream_t stream) {
 // one before, on that earlier stream (it then covers the earlier kernel and whatever that
 // stream was given since, which is more than needed and never less).  Recording one after
 // every launch cost each call some microseconds of idle device time.
-hipError_t cluster_launch_begin(hipStream_t stream) {
+hipError_t cluster_launch_begin(hipStream_t stream, uint64_t *tag) {
+  if (tag) *tag = 0;
   if (is_capturing(stream)) return hipSuccess;
+  if (tag) *tag = next_tag();
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;

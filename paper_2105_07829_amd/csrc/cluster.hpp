@@ -11,6 +11,15 @@
 //     status word and carries on with the values it has, so the kernel always terminates;
 //   - partial results are combined in slot order, so the total does not depend on timing.
 //
+// The preset is a launch of its own in front of the kernel (2 to 3 us of a call, whatever its
+// size), so calls of few tiles do without it: such a launch gets a 64-bit TAG of its own from the host, a
+// slot is two words (value bits, value bits ^ tag) and counts as published when their exclusive
+// or is the tag.  What an earlier call or anything else left in the workspace has another
+// exclusive or (tags are never handed out twice; arbitrary bytes match one time in 2^64), and a
+// pair of which only one word has arrived reads as unpublished in the same way.  A launch that is
+// being captured into a graph would carry the same tag at every replay: it takes the preset form
+// (tag 0).
+//
 // Two drivers share this exchange.  Both are LAGGED: a workgroup publishes the partial of
 // tile k, then finishes tile k-1 (collects its partition's total and writes its outputs), then
 // goes on to tile k+1.  Tile k-1 was published a whole phase 1 earlier, so the other tiles of
@@ -104,7 +113,8 @@ inline SplitGeo split_geo(const Geo &g, uint32_t tile, bool ragged_ok) {
 // kernels running concurrently (different streams) would share the device, so launches are
 // chained: a launch on another stream than the one before first waits for an event recorded
 // on that earlier stream.
-hipError_t cluster_launch_begin(hipStream_t stream);
+// `tag` (if given) receives this launch's tag, 0 while the stream is being captured.
+hipError_t cluster_launch_begin(hipStream_t stream, uint64_t *tag = nullptr);
 hipError_t cluster_launch_end(hipStream_t stream);
 // Creates the current device's event now rather than at the first launch that needs it.
 hipError_t cluster_prepare_device();
@@ -145,6 +155,37 @@ __device__ inline bool slot_published(double x) { return __double_as_longlong(x)
 __device__ inline void slot_publish(double *slot, double value) {
   __hip_atomic_store(slot, value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Slot number `item` of a launch with this tag (0: the preset form).
+__device__ inline void slot_publish(double *slots, uint32_t item, double value, uint64_t tag) {
+  if (tag == 0) {
+    slot_publish(slots + item, value);
+  } else {
+    uint64_t *w = reinterpret_cast<uint64_t *>(slots) + 2ull * item;
+    const uint64_t bits = (uint64_t)__double_as_longlong(value);
+    __hip_atomic_store(w, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 1, bits ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+
+// The status word of a launch with a tag is not cleared by an earlier kernel; its first workgroup
+// does it, and the word next to it says for which launch: a workgroup that gave up before the
+// first one got to run is not forgotten.
+__device__ inline void status_open(uint32_t *status, uint64_t tag) {
+  if (tag == 0 || blockIdx.x != 0 || threadIdx.x != 0) return;
+  unsigned long long *w = reinterpret_cast<unsigned long long *>(status);
+  const unsigned long long mine = (unsigned long long)(uint32_t)tag << 32;
+  unsigned long long cur = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+  for (int tries = 0; tries < 64 && (uint32_t)(cur >> 32) != (uint32_t)tag; ++tries) {
+    const unsigned long long seen = atomicCAS(w, cur, mine);
+    if (seen == cur) break;
+    cur = seen;
+  }
+}
+__device__ inline void status_give_up(uint32_t *status, uint64_t tag) {
+  if (tag == 0) atomicOr(status, 1u);
+  else atomicExch(reinterpret_cast<unsigned long long *>(status), ((unsigned long long)(uint32_t)tag << 32) | 1ull);
+}
 
 // Two neighbouring slots in one 16-byte load that goes to the memory side like the atomic loads
 // (each slot is written with one 8-byte store, so either half is a whole old or new value);
@@ -157,32 +198,55 @@ __device__ inline void slot_pair(const TileBuf &b, uint32_t pair, double *x0, do
   *x1 = __longlong_as_double((long long)(((unsigned long long)w.w << 32) | w.z));
 }
 
-// Called by the first wave of a workgroup.  Polls the `count` slots starting at `slots`
+// Slots 2 `pair` and 2 `pair` + 1 of a partition whose slots start at `b` (which ends with them):
+// adds the published ones to *v (in this order) and says whether both are.  `tag`: see above;
+// slots past the partition's count as published and add nothing.
+template <bool MAX>
+__device__ inline bool slots_add(const TileBuf &b, uint32_t pair, uint32_t count, uint64_t tag, double *v) {
+  double x[2];
+  bool pub[2];
+  if (tag == 0) {
+    slot_pair(b, pair, &x[0], &x[1]);
+    pub[0] = slot_published(x[0]);
+    pub[1] = slot_published(x[1]);
+  } else {
+    u32x4 w[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) w[h] = b.load16<kMemorySide>((2 * pair + h) * 16, 0);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      x[h] = __longlong_as_double((long long)(((unsigned long long)w[h].y << 32) | w[h].x));
+      pub[h] = ((w[h].x ^ w[h].z) == (uint32_t)tag && (w[h].y ^ w[h].w) == (uint32_t)(tag >> 32)) || 2 * pair + h >= count;
+    }
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const double y = pub[h] ? x[h] : 0.0;
+    *v = MAX ? fmax(*v, y) : *v + y;
+  }
+  return pub[0] && pub[1];
+}
+// The slots of a partition, `first` the number of its first one.
+__device__ inline TileBuf slots_buf(const double *slots, uint32_t first, uint32_t count, uint64_t tag) {
+  return tag == 0 ? TileBuf(slots + first, count * 8) : TileBuf(slots + 2ull * first, count * 16);
+}
+
+// Called by the first wave of a workgroup.  Polls the `count` slots from number `first`
 // until all are published, then returns their sum (MAX = false) or maximum (MAX = true),
 // combined in a fixed order, in every lane.
 template <bool MAX>
-__device__ inline double slots_collect(const double *slots, uint32_t count, uint32_t *status) {
+__device__ inline double slots_collect(const double *slots, uint32_t first, uint32_t count, uint32_t *status, uint64_t tag) {
   const uint32_t lane = threadIdx.x & 63;
-  const TileBuf b(slots, count * 8);
+  const TileBuf b = slots_buf(slots, first, count, tag);
   double v;
   int spins = 0;
   for (;;) {
     bool ok = true;
     v = 0.0;
-    for (uint32_t s = lane; 2 * s < count; s += 64) {
-      double x[2];
-      slot_pair(b, s, &x[0], &x[1]);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bool pub = slot_published(x[h]);
-        ok = ok && pub;
-        const double y = pub ? x[h] : 0.0;
-        v = MAX ? fmax(v, y) : v + y;
-      }
-    }
+    for (uint32_t s = lane; 2 * s < count; s += 64) ok = slots_add<MAX>(b, s, count, tag, &v) && ok;
     if (__all(ok)) break;
     if (++spins > kSpinLimit) {
-      if (lane == 0) atomicOr(status, 1u);
+      if (lane == 0) status_give_up(status, tag);
       break;
     }
     __builtin_amdgcn_s_sleep(16);
@@ -199,32 +263,27 @@ __device__ inline double slots_collect(const double *slots, uint32_t count, uint
 // waiting for the values (the loads stay in flight under whatever the caller does next), and
 // slots_finish() uses them if all were published, else falls back to slots_collect().  Both
 // combine in the same order, so the result does not depend on which one produced it.  A probe
-// covers partitions of up to 256 tiles.
+// covers partitions of up to 256 tiles, of up to 128 with a tag (the same number of loads).
 struct SlotProbe { double v; bool ok; };
 template <bool MAX>
-__device__ inline SlotProbe slots_probe(const double *slots, uint32_t count) {
+__device__ inline SlotProbe slots_probe(const double *slots, uint32_t first, uint32_t count, uint64_t tag) {
   const uint32_t lane = threadIdx.x & 63;
-  SlotProbe r{0.0, count <= 256u};
-  if (count <= 256u) {
-    const TileBuf b(slots, count * 8);
+  SlotProbe r{0.0, count <= (tag == 0 ? 256u : 128u)};
+  if (r.ok) {
+    const TileBuf b = slots_buf(slots, first, count, tag);
+    if (tag == 0) {
 #pragma unroll
-    for (uint32_t j = 0; j < 2; ++j) {
-      double x[2];
-      slot_pair(b, lane + 64 * j, &x[0], &x[1]);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const bool pub = slot_published(x[h]);
-        r.ok = r.ok && pub;
-        const double y = pub ? x[h] : 0.0;
-        r.v = MAX ? fmax(r.v, y) : r.v + y;
-      }
+      for (uint32_t j = 0; j < 2; ++j) r.ok = slots_add<MAX>(b, lane + 64 * j, count, 0, &r.v) && r.ok;
+    } else {
+      r.ok = slots_add<MAX>(b, lane, count, tag, &r.v);
     }
   }
   return r;
 }
 template <bool MAX>
-__device__ inline double slots_finish(const SlotProbe &probe, const double *slots, uint32_t count, uint32_t *status) {
-  if (!__all(probe.ok)) return slots_collect<MAX>(slots, count, status);
+__device__ inline double slots_finish(const SlotProbe &probe, const double *slots, uint32_t first, uint32_t count,
+                                      uint32_t *status, uint64_t tag) {
+  if (!__all(probe.ok)) return slots_collect<MAX>(slots, first, count, status, tag);
   double v = probe.v;
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -286,9 +345,10 @@ struct has_init { static constexpr bool value = false; };
 template <class Op>
 struct has_init<Op, std::void_t<decltype(std::declval<const Op &>().init((float *)nullptr))>> { static constexpr bool value = true; };
 
-// Ticketed driver.
+// Ticketed driver.  A launch with a tag has no counters (nobody cleared them): its workgroups take
+// tiles w, w+G, ... as in the persistent driver, whose progress argument then holds.
 template <class Op>
-__device__ inline void cluster_run_ticketed(const Op &op, float *table, double *slots, uint32_t *status, uint32_t *tickets) {
+__device__ inline void cluster_run_ticketed(const Op &op, float *table, double *slots, uint32_t *status, uint32_t *tickets, uint64_t tag) {
   constexpr int kT = Op::kThreads;
   constexpr uint32_t kNone = 0xffffffffu;
   __shared__ double red[kT / 64];
@@ -300,7 +360,7 @@ __device__ inline void cluster_run_ticketed(const Op &op, float *table, double *
   const uint32_t n_classes = gridDim.x < (uint32_t)kTicketClasses ? gridDim.x : (uint32_t)kTicketClasses;
   const uint32_t cls = blockIdx.x % n_classes;
   uint32_t *counter = tickets + cls * (kTicketStride / 4);
-  if (threadIdx.x == 0) item_sh = atomicAdd(counter, 1u) * n_classes + cls;
+  if (threadIdx.x == 0) item_sh = tag ? blockIdx.x : atomicAdd(counter, 1u) * n_classes + cls;
   if constexpr (has_init<Op>::value) op.init(table);
   __syncthreads();
   uint32_t item = __builtin_amdgcn_readfirstlane(item_sh);
@@ -312,7 +372,7 @@ __device__ inline void cluster_run_ticketed(const Op &op, float *table, double *
       typename Op::Raw raw;
       double part = op.phase1(item, raw, held, table);
       part = cluster_block_reduce<Op::kMax, kT>(part, red);
-      if (threadIdx.x == 0 && op.needs_total()) slot_publish(slots + item, part);
+      if (threadIdx.x == 0 && op.needs_total()) slot_publish(slots, item, part, tag);
     }
     uint32_t ticket = kNone;
     // (reading the older tile's slots before phase 1, as the persistent driver does,
@@ -322,12 +382,12 @@ __device__ inline void cluster_run_ticketed(const Op &op, float *table, double *
       if (op.needs_total()) {
         uint32_t first, count;
         op.slots_of(prev, &first, &count);
-        total = slots_collect<Op::kMax>(slots + first, count, status);
+        total = slots_collect<Op::kMax>(slots, first, count, status, tag);
       }
       if (threadIdx.x == 0) scale_sh = op.scale_of(prev, total);
     }
     // the next ticket is on its way while the older tile is written out
-    if (have && threadIdx.x == 0) ticket = atomicAdd(counter, 1u) * n_classes + cls;
+    if (have && threadIdx.x == 0) ticket = tag ? item + gridDim.x : atomicAdd(counter, 1u) * n_classes + cls;
     if (have) op.early(item, held);
     __syncthreads();
     if (prev != kNone) {
@@ -347,7 +407,7 @@ __device__ inline void cluster_run_ticketed(const Op &op, float *table, double *
 // Persistent driver.  The older tile's slots are read before phase 1 of the current tile and
 // looked at after it, so that read is off the critical path as well.
 template <class Op>
-__device__ inline void cluster_run_persistent(const Op &op, float *table, double *slots, uint32_t *status, uint32_t *) {
+__device__ inline void cluster_run_persistent(const Op &op, float *table, double *slots, uint32_t *status, uint64_t tag) {
   constexpr int kT = Op::kThreads;
   constexpr uint32_t kNone = 0xffffffffu;
   __shared__ double red[kT / 64];
@@ -369,7 +429,7 @@ __device__ inline void cluster_run_persistent(const Op &op, float *table, double
     uint32_t first = 0, count = 0;
     if (collects) {
       op.slots_of(prev, &first, &count);
-      probe = slots_probe<Op::kMax>(slots + first, count);
+      probe = slots_probe<Op::kMax>(slots, first, count, tag);
     }
     double part = op.phase1(item, raw, held, table);
     const uint32_t next = __builtin_amdgcn_readfirstlane(item + gridDim.x);
@@ -379,10 +439,10 @@ __device__ inline void cluster_run_persistent(const Op &op, float *table, double
       for (int u = 0; u < Op::kRowsPerTile; ++u) op.issue_row(next, u, raw);
     }
     part = cluster_block_reduce<Op::kMax, kT>(part, red);
-    if (threadIdx.x == 0 && op.needs_total()) slot_publish(slots + item, part);
+    if (threadIdx.x == 0 && op.needs_total()) slot_publish(slots, item, part, tag);
     if (prev != kNone && threadIdx.x < 64) {
       double total = 0.0;
-      if (collects) total = slots_finish<Op::kMax>(probe, slots + first, count, status);
+      if (collects) total = slots_finish<Op::kMax>(probe, slots, first, count, status, tag);
       if (threadIdx.x == 0) scale_sh = op.scale_of(prev, total);
     }
     op.early(item, held);
@@ -405,7 +465,7 @@ __device__ inline void cluster_run_persistent(const Op &op, float *table, double
     if (op.needs_total()) {
       uint32_t first, count;
       op.slots_of(prev, &first, &count);
-      total = slots_collect<Op::kMax>(slots + first, count, status);
+      total = slots_collect<Op::kMax>(slots, first, count, status, tag);
     }
     if (threadIdx.x == 0) scale_sh = op.scale_of(prev, total);
   }

@@ -13,23 +13,29 @@ struct waves_per_simd { static constexpr int value = 4; };
 template <class Op>
 struct waves_per_simd<Op, std::void_t<decltype(Op::kWavesPerSimd)>> { static constexpr int value = Op::kWavesPerSimd; };
 
-template <class Op>
-__device__ inline void cluster_run(const Op &op, float *table, double *slots, uint32_t *status, uint32_t *tickets) {
-  if constexpr (Op::kPersistent) cluster_run_persistent(op, table, slots, status, tickets);
-  else cluster_run_ticketed(op, table, slots, status, tickets);
-}
-
-template <class Op>
-__global__ __launch_bounds__(Op::kThreads, waves_per_simd<Op>::value) void cluster_kernel(const Op op, double *slots, uint32_t *status, uint32_t *tickets) {
+// TAGGED: the launch has a tag and no preset in front of it (cluster.hpp); without it `tag` is the
+// constant 0 and none of that is compiled in.
+template <class Op, bool TAGGED>
+__global__ __launch_bounds__(Op::kThreads, waves_per_simd<Op>::value) void cluster_kernel(const Op op, double *slots, uint32_t *status, uint32_t *tickets, uint64_t launch_tag) {
   __shared__ __attribute__((aligned(16))) float table[Op::kTableFloats];
-  cluster_run(op, table, slots, status, tickets);
+  const uint64_t tag = TAGGED ? launch_tag : 0;
+  status_open(status, tag);
+  if constexpr (Op::kPersistent) cluster_run_persistent(op, table, slots, status, tag);
+  else cluster_run_ticketed(op, table, slots, status, tickets, tag);
 }
 
-// Same, with the operator's LDS scratch allocated at launch (sizes above the static limit).
-template <class Op>
-__global__ __launch_bounds__(Op::kThreads, waves_per_simd<Op>::value) void cluster_kernel_dyn(const Op op, double *slots, uint32_t *status, uint32_t *tickets) {
-  extern __shared__ __attribute__((aligned(16))) float dyn_table[];
-  cluster_run(op, dyn_table, slots, status, tickets);
+// Calls of up to this many tiles per workgroup of the grid go without the preset launch.  Beyond
+// it that launch is small beside the kernel and the second word of every slot costs as much or
+// more (110 M / 336 M elements, always with a tag: sign worker 195 against 188 us, dithering
+// worker 705 against 632, sign server 232 against 216, dithering server 1143 against 1065); below
+// it a call gains what the launch costs (a step of 4 workers on 1 M elements, sign: 73 -> 60 us; of
+// 8 workers on 12.3 M elements, dithering, 3 tiles a workgroup: 428 -> 410 us).
+constexpr uint32_t kTaggedTiles = 4;
+
+template <class Op, bool TAGGED>
+static int resident_workgroups() {
+  static PerDevice cache;  // resident workgroups of this kernel on each device
+  return cache.get([] { return cluster_capacity(reinterpret_cast<const void *>(&cluster_kernel<Op, TAGGED>), Op::kThreads); });
 }
 
 // Launches `op` over the tiles of `cg`.  *used = false (and nothing is enqueued) when the
@@ -37,29 +43,26 @@ __global__ __launch_bounds__(Op::kThreads, waves_per_simd<Op>::value) void clust
 // workgroups at once.
 template <class Op>
 static hipError_t launch_cluster(const Op &op, const ClusterGeo &cg, double *slots, uint32_t *status, uint32_t *tickets,
-                                 hipStream_t stream, bool *used, size_t dyn_lds = 0) {
-  const void *fn = dyn_lds ? reinterpret_cast<const void *>(&cluster_kernel_dyn<Op>)
-                           : reinterpret_cast<const void *>(&cluster_kernel<Op>);
-  static PerDevice cache;  // resident workgroups of this kernel on each device
-  const size_t max_dyn = dyn_lds ? (size_t)Op::kMaxDynLds : 0;
-  const int capacity = cache.get([&]() -> int {
-    if (max_dyn && hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)max_dyn) != hipSuccess) {
-      (void)hipGetLastError();
-      return 0;
-    }
-    return cluster_capacity(fn, Op::kThreads, max_dyn);
-  });
+                                 hipStream_t stream, bool *used) {
   *used = false;
+  const int capacity = resident_workgroups<Op, false>(), capacity_tagged = resident_workgroups<Op, true>();
   if (capacity <= 0) return hipSuccess;
   if (cg.tiles_per_part > (uint32_t)capacity) return hipSuccess;
-  // the whole grid is resident at once
-  const uint32_t grid = cg.n_items > (uint32_t)capacity ? (uint32_t)capacity : cg.n_items;
   *used = true;
-  hipError_t e = cluster_launch_begin(stream);
+  const bool small = capacity_tagged > 0 && cg.tiles_per_part <= (uint32_t)capacity_tagged &&
+                     cg.n_items <= kTaggedTiles * (uint64_t)capacity_tagged;
+  uint64_t tag = 0;
+  hipError_t e = cluster_launch_begin(stream, small ? &tag : nullptr);
   if (e != hipSuccess) return e;
-  slots_reset_kernel<<<(uint32_t)cdiv(cg.n_items, 256), 256, 0, stream>>>(slots, cg.n_items, status, tickets);
-  if (dyn_lds) cluster_kernel_dyn<Op><<<grid, Op::kThreads, dyn_lds, stream>>>(op, slots, status, tickets);
-  else cluster_kernel<Op><<<grid, Op::kThreads, 0, stream>>>(op, slots, status, tickets);
+  // the whole grid is resident at once
+  const uint32_t most = (uint32_t)(tag ? capacity_tagged : capacity);
+  const uint32_t grid = cg.n_items > most ? most : cg.n_items;
+  if (tag) {
+    cluster_kernel<Op, true><<<grid, Op::kThreads, 0, stream>>>(op, slots, status, tickets, tag);
+  } else {
+    slots_reset_kernel<<<(uint32_t)cdiv(cg.n_items, 256), 256, 0, stream>>>(slots, cg.n_items, status, tickets);
+    cluster_kernel<Op, false><<<grid, Op::kThreads, 0, stream>>>(op, slots, status, tickets, 0);
+  }
   e = hipGetLastError();
   if (e != hipSuccess) return e;
   return cluster_launch_end(stream);

@@ -31,7 +31,6 @@ struct DitherWorkerOp {
   static constexpr bool kMax = LINF;
   static constexpr int kRowsPerTile = kDRows;
   static constexpr int kTableFloats = 64;   // decoded magnitudes of the levels 0..s
-  static constexpr size_t kMaxDynLds = 0;
   static constexpr int kThreads = kDWThreads;
   static constexpr bool kPersistent = true;
   struct Ctx { float nu, top_over_nu; int mode; const float *mag; };

@@ -62,7 +62,6 @@ struct DitherServerOp {
   static constexpr int kSpreadAt = kMaxWorkers * 16 + 16;
   static constexpr int kTableFloats = kSpreadAt + (WIDE ? 512 : 0);
   static_assert(!WIDE || (NW > 0 && NW * 32 <= kMaxWorkers * 16), "tables of the wide form must fit");
-  static constexpr size_t kMaxDynLds = 0;
   static constexpr bool kPersistent = false;
   static constexpr int kWavesPerSimd = (NW > 8 && !WIDE) ? 6 : 4;
 

@@ -24,7 +24,6 @@ struct SignWorkerOp {
   static constexpr bool kMax = false;
   static constexpr int kRowsPerTile = kRows;
   static constexpr int kTableFloats = 1;
-  static constexpr size_t kMaxDynLds = 0;
   static constexpr int kThreads = kSWThreads;
   static constexpr bool kPersistent = true;
   struct Ctx { float sigma; };

@@ -87,7 +87,6 @@ struct SignServerOp {
   static constexpr int kThreads = kSSThreads;
   static constexpr int kWavesPerSimd = 6;   // 80 registers a lane, three workgroups a CU
   static constexpr bool kPersistent = false;
-  static constexpr size_t kMaxDynLds = 0;
   struct Ctx { float sigma; };
 
   Geo g;
