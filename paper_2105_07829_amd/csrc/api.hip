@@ -98,6 +98,21 @@ static Geo run_geo(const bpc_params_t &sub, const Run &r) {
   return g;
 }
 
+// FP16 calls with several runs go in one launch (its kernels pick the class per workgroup).
+static bool one_launch(const bpc_params_t *prm, const Runs &runs) { return prm->kind == BPC_FP16 && runs.n > 1; }
+static RecordMap record_map(const bpc_params_t *prm, const Runs &runs) {
+  RecordMap m{};
+  m.n = (uint32_t)runs.n;
+  for (int k = 0; k < runs.n; ++k) {
+    m.p0[k] = runs.r[k].p0;
+    m.off[k] = runs.r[k].pay_off;
+    m.bypass |= (uint64_t)(runs.r[k].bypass ? 1 : 0) << k;
+  }
+  m.stride = stride_of(prm);
+  m.identity_stride = identity_stride(prm->part_elems);
+  return m;
+}
+
 // Every run's own workspace layout fits in ws_bytes (they all do when ws_bytes covers the layout
 // of the whole call, which is what the entry points ask for; checked all the same).
 static bool runs_fit(const bpc_params_t *prm, const Runs &runs, size_t ws_bytes) {
@@ -227,6 +242,14 @@ bpc_status_t bpc_compress(const bpc_params_t *params, const void *grad, bpc_dtyp
   if (!make_runs(params, D, &runs)) return BPC_ERR_UNSUPPORTED;
   if (!runs_fit(params, runs, ws_bytes)) return BPC_ERR_WORKSPACE;
   const size_t gbytes = dtype == BPC_F16 ? 2 : 4;
+  if (one_launch(params, runs)) {
+    Source src{};
+    src.grad = grad;
+    src.dtype = (int)dtype;
+    src.residual = residual;
+    return hip_status(fp16_encode_map(make_geo(params, D), record_map(params, runs), src, (uint8_t *)payload,
+                                      Workspace{(uint8_t *)ws, lay, 0}, (hipStream_t)hip_stream));
+  }
   for (int k = 0; k < runs.n; ++k) {
     const Run &r = runs.r[k];
     const bpc_params_t sub = run_params(params, r);
@@ -313,6 +336,15 @@ bpc_status_t bpc_server_aggregate(const bpc_params_t *in, const void *const *pay
       for (uint64_t p = 0; p < P; ++p)
         if ((in[i].bypass[p] != 0) != (out->bypass[p] != 0)) return BPC_ERR_INVALID_ARG;
   }
+  if (one_launch(out, runs)) {
+    Source src{};
+    src.residual = server_residual;
+    src.msgs.n = n;
+    src.msgs.inv_n = 1.0f / (float)n;
+    for (int i = 0; i < n; ++i) src.msgs.ptr[i] = (const uint8_t *)payloads[i];
+    return hip_status(fp16_encode_map(make_geo(out, D), record_map(out, runs), src, (uint8_t *)out_payload,
+                                      Workspace{(uint8_t *)ws, lay, 0}, (hipStream_t)hip_stream));
+  }
   for (int k = 0; k < runs.n; ++k) {
     const Run &r = runs.r[k];
     const bpc_params_t sub = run_params(out, r);
@@ -361,6 +393,9 @@ bpc_status_t bpc_adaptive_update(const bpc_params_t *params, const void *payload
   // (caller-defined LANS blocks may reach from one run into the next: not built)
   if (runs.n > 1 && opt->kind == BPC_OPT_LANS && opt->block_offsets) return BPC_ERR_UNSUPPORTED;
   if (!runs_fit(params, runs, ws_bytes)) return BPC_ERR_WORKSPACE;
+  if (one_launch(params, runs) && opt->kind == BPC_OPT_ADAM)
+    return hip_status(adam_update_fp16_map(make_geo(params, D), record_map(params, runs), (const uint8_t *)payload, param, m, v,
+                                           *opt, Workspace{(uint8_t *)ws, lay, 0}, (hipStream_t)hip_stream));
   for (int k = 0; k < runs.n; ++k) {
     const Run &r = runs.r[k];
     const bpc_params_t sub = run_params(params, r);

@@ -92,12 +92,9 @@ __device__ inline void cast_store_row(const CastTile &t, int u, const float q[4]
   if (EF) row_buf(residual + t.base, t.valid, u * kCRowElems, kCRowElems).store16<kNonTemporal>(as_u32x4(r[0], r[1], r[2], r[3]), threadIdx.x * 16);
 }
 
+// `rec`: the tile's partition's record.
 template <class GT, bool EF, class FMT>
-__global__ __launch_bounds__(kThreads) void cast_worker_kernel(Geo g, const GT *grad, float *residual, uint8_t *payload,
-                                                               uint32_t *status) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;   // no wait in this call: the word reads "none gave up"
-  const CastTile t = cast_tile<FMT>(g);
-  uint8_t *rec = payload + (uint64_t)t.p * g.stride;
+__device__ inline void cast_worker_tile(const CastTile &t, const GT *grad, float *residual, uint8_t *rec) {
   if (t.j0 == 0 && threadIdx.x < 4) reinterpret_cast<uint32_t *>(rec)[threadIdx.x] = 0;
   const TileBuf gb(grad + t.base, t.valid * (uint32_t)sizeof(GT));
   const TileBuf eb(residual + (EF ? t.base : 0), EF ? t.valid * 4 : 0);
@@ -123,6 +120,27 @@ __global__ __launch_bounds__(kThreads) void cast_worker_kernel(Geo g, const GT *
   }
 }
 
+template <class GT, bool EF, class FMT>
+__global__ __launch_bounds__(kThreads) void cast_worker_kernel(Geo g, const GT *grad, float *residual, uint8_t *payload,
+                                                               uint32_t *status) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;   // no wait in this call: the word reads "none gave up"
+  const CastTile t = cast_tile<FMT>(g);
+  cast_worker_tile<GT, EF, FMT>(t, grad, residual, payload + (uint64_t)t.p * g.stride);
+}
+// FP16 with bypassed partitions: the class is the same for a whole workgroup, so one launch takes
+// all partitions (one launch per run of a class left the chip idle between runs and in short
+// ones: a step of 4 workers on 12.6 M f16 elements in four runs took 244 us with its 24 launches
+// and takes 205 us with 6).
+template <class GT, bool EF>
+__global__ __launch_bounds__(kThreads) void cast_worker_map_kernel(Geo g, RecordMap map, const GT *grad, float *residual,
+                                                                   uint8_t *payload, uint32_t *status) {
+  if (blockIdx.x == 0 && threadIdx.x < map.n) status[4 * threadIdx.x] = 0;   // the words of all runs
+  bool as_is;
+  const uint64_t rec = map.record(__builtin_amdgcn_readfirstlane(blockIdx.x / g.tiles_per_part), &as_is);
+  if (as_is) cast_worker_tile<GT, EF, FloatFmt>(cast_tile<FloatFmt>(g), grad, residual, payload + rec);
+  else cast_worker_tile<GT, EF, HalfFmt>(cast_tile<HalfFmt>(g), grad, residual, payload + rec);
+}
+
 struct CastMsgs {
   const uint8_t *ptr[kMaxWorkers];
   int n;
@@ -130,14 +148,13 @@ struct CastMsgs {
 };
 
 // NW > 0: number of workers known at compile time; NW == 0: any number, four at a time.
+// `rec_at`: offset of the tile's partition's record in every message and in the payload.
 template <bool EF, int NW, class FMT>
-__global__ __launch_bounds__(kThreads) void cast_server_kernel(Geo g, CastMsgs msgs, float *residual, uint8_t *payload,
-                                                               uint32_t *status) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;
-  const CastTile t = cast_tile<FMT>(g);
-  uint8_t *rec = payload + (uint64_t)t.p * g.stride;
+__device__ inline void cast_server_tile(const CastTile &t, const CastMsgs &msgs, float *residual, uint8_t *payload,
+                                        uint64_t rec_at) {
+  uint8_t *rec = payload + rec_at;
   if (t.j0 == 0 && threadIdx.x < 4) reinterpret_cast<uint32_t *>(rec)[threadIdx.x] = 0;
-  const uint64_t rec_off = uniform_off((uint64_t)t.p * g.stride + kHeaderBytes + (uint64_t)FMT::kBytes * t.j0);
+  const uint64_t rec_off = uniform_off(rec_at + kHeaderBytes + (uint64_t)FMT::kBytes * t.j0);
   const TileBuf eb(residual + (EF ? t.base : 0), EF ? t.valid * 4 : 0);
   constexpr int kPair = FMT::kPair;   // rows whose loads are in flight together
   using Vec = typename FMT::Vec;
@@ -210,12 +227,34 @@ __global__ __launch_bounds__(kThreads) void cast_server_kernel(Geo g, CastMsgs m
   }
 }
 
+template <bool EF, int NW, class FMT>
+__global__ __launch_bounds__(kThreads) void cast_server_kernel(Geo g, CastMsgs msgs, float *residual, uint8_t *payload,
+                                                               uint32_t *status) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;
+  const CastTile t = cast_tile<FMT>(g);
+  cast_server_tile<EF, NW, FMT>(t, msgs, residual, payload, (uint64_t)t.p * g.stride);
+}
+template <bool EF, int NW>
+__global__ __launch_bounds__(kThreads) void cast_server_map_kernel(Geo g, RecordMap map, CastMsgs msgs, float *residual,
+                                                                   uint8_t *payload, uint32_t *status) {
+  if (blockIdx.x == 0 && threadIdx.x < map.n) status[4 * threadIdx.x] = 0;
+  bool as_is;
+  const uint64_t rec = map.record(__builtin_amdgcn_readfirstlane(blockIdx.x / g.tiles_per_part), &as_is);
+  if (as_is) cast_server_tile<EF, NW, FloatFmt>(cast_tile<FloatFmt>(g), msgs, residual, payload, rec);
+  else cast_server_tile<EF, NW, HalfFmt>(cast_tile<HalfFmt>(g), msgs, residual, payload, rec);
+}
+
+static CastMsgs cast_msgs(const WorkerMsgs &msgs) {
+  CastMsgs m;
+  for (int i = 0; i < kMaxWorkers; ++i) m.ptr[i] = i < msgs.n ? msgs.ptr[i] : nullptr;
+  m.n = msgs.n;
+  m.inv_n = msgs.inv_n;
+  return m;
+}
+
 template <bool EF, class FMT>
 static hipError_t launch_cast_server(const Geo &g, const Source &src, uint8_t *payload, uint32_t *status, hipStream_t stream) {
-  CastMsgs m;
-  for (int i = 0; i < kMaxWorkers; ++i) m.ptr[i] = i < src.msgs.n ? src.msgs.ptr[i] : nullptr;
-  m.n = src.msgs.n;
-  m.inv_n = src.msgs.inv_n;
+  const CastMsgs m = cast_msgs(src.msgs);
   switch (m.n) {
     case 4: cast_server_kernel<EF, 4, FMT><<<g.n_tiles, kThreads, 0, stream>>>(g, m, src.residual, payload, status); break;
     case 8: cast_server_kernel<EF, 8, FMT><<<g.n_tiles, kThreads, 0, stream>>>(g, m, src.residual, payload, status); break;
@@ -245,6 +284,30 @@ static hipError_t cast_encode(const Geo &g, const Source &src, uint8_t *payload,
 hipError_t fp16_encode(const Geo &g, const bpc_params_t &, const Source &src, uint8_t *payload, const Workspace &ws,
                        hipStream_t stream) {
   return cast_encode<HalfFmt>(g, src, payload, ws, stream);
+}
+
+template <bool EF>
+static hipError_t launch_cast_map(const Geo &g, const RecordMap &map, const Source &src, uint8_t *payload, uint32_t *status,
+                                  hipStream_t stream) {
+  float *res = src.residual;
+  if (src.grad) {
+    if (src.dtype == BPC_F16) cast_worker_map_kernel<__half, EF><<<g.n_tiles, kThreads, 0, stream>>>(g, map, (const __half *)src.grad, res, payload, status);
+    else cast_worker_map_kernel<float, EF><<<g.n_tiles, kThreads, 0, stream>>>(g, map, (const float *)src.grad, res, payload, status);
+    return hipGetLastError();
+  }
+  const CastMsgs m = cast_msgs(src.msgs);
+  switch (m.n) {
+    case 4: cast_server_map_kernel<EF, 4><<<g.n_tiles, kThreads, 0, stream>>>(g, map, m, res, payload, status); break;
+    case 8: cast_server_map_kernel<EF, 8><<<g.n_tiles, kThreads, 0, stream>>>(g, map, m, res, payload, status); break;
+    case 16: cast_server_map_kernel<EF, 16><<<g.n_tiles, kThreads, 0, stream>>>(g, map, m, res, payload, status); break;
+    default: cast_server_map_kernel<EF, 0><<<g.n_tiles, kThreads, 0, stream>>>(g, map, m, res, payload, status); break;
+  }
+  return hipGetLastError();
+}
+hipError_t fp16_encode_map(const Geo &g, const RecordMap &map, const Source &src, uint8_t *payload, const Workspace &ws,
+                           hipStream_t stream) {
+  return src.residual ? launch_cast_map<true>(g, map, src, payload, ws.status(), stream)
+                      : launch_cast_map<false>(g, map, src, payload, ws.status(), stream);
 }
 
 hipError_t identity_encode(const Geo &g, const bpc_params_t &, const Source &src, uint8_t *payload, const Workspace &ws,

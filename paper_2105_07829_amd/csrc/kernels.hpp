@@ -35,6 +35,26 @@ struct Workspace {
   uint32_t *tickets() const { return reinterpret_cast<uint32_t *>(base + lay.tickets); }
 };
 
+// Where the records of a payload with bypassed partitions lie: the runs of partitions of one class.
+struct RecordMap {
+  uint32_t n;               // runs
+  uint32_t p0[kMaxRuns];    // first partition of a run
+  uint64_t off[kMaxRuns];   // where its records start
+  uint64_t bypass;          // bit r: run r carries its partitions as they are
+  uint64_t stride, identity_stride;
+  // Offset of partition p's record (p the same in every lane); *as_is: an identity record.
+  __device__ uint64_t record(uint32_t p, bool *as_is) const {
+    uint32_t a = 0, b = n;   // p0[a] <= p < p0[b]
+    while (b - a > 1) {
+      const uint32_t m = (a + b) >> 1;
+      if (p0[m] <= p) a = m; else b = m;
+    }
+    a = __builtin_amdgcn_readfirstlane(a);
+    *as_is = (bypass >> a) & 1;
+    return off[a] + (uint64_t)(p - p0[a]) * (*as_is ? identity_stride : stride);
+  }
+};
+
 hipError_t fill_zero(void *ptr, size_t bytes, hipStream_t stream);
 // Streaming kernels with a stage's memory traffic and no arithmetic (bpc_stream_probe).
 hipError_t stream_probe(int mix, const void *a, const void *b, void *c, uint64_t n, hipStream_t stream);
@@ -58,6 +78,9 @@ hipError_t dither_encode(const Geo &g, const bpc_params_t &prm, const Source &sr
                          const Workspace &ws, hipStream_t stream);
 hipError_t fp16_encode(const Geo &g, const bpc_params_t &prm, const Source &src, uint8_t *payload,
                        const Workspace &ws, hipStream_t stream);
+// FP16 with bypassed partitions in one launch; `ws` is that of run 0.
+hipError_t fp16_encode_map(const Geo &g, const RecordMap &map, const Source &src, uint8_t *payload, const Workspace &ws,
+                           hipStream_t stream);
 hipError_t identity_encode(const Geo &g, const bpc_params_t &prm, const Source &src, uint8_t *payload,
                            const Workspace &ws, hipStream_t stream);
 hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t *in_prm, const Source &src,
@@ -97,5 +120,9 @@ hipError_t decode_dense(const Geo &g, const bpc_params_t &prm, const uint8_t *pa
 // decoded into the workspace first.
 hipError_t adaptive_update(const Geo &g, const bpc_params_t &prm, const uint8_t *payload, float *x, float *m,
                            float *v, const bpc_opt_t &opt, const Workspace &ws, hipStream_t stream);
+
+// Adam-style update from an FP16 payload with bypassed partitions in one launch.
+hipError_t adam_update_fp16_map(const Geo &g, const RecordMap &map, const uint8_t *payload, float *x, float *m, float *v,
+                                const bpc_opt_t &opt, const Workspace &ws, hipStream_t stream);
 
 }  // namespace bpc

@@ -199,6 +199,21 @@ struct Fp16Dec {
     decode4(load4(g, p, j, row), j, 0.0f, lds, out);
   }
 };
+// FP16 with bypassed partitions (the Adam-style kernel only): which of the two a record is, is the
+// same for a whole workgroup.
+struct Fp16MapDec {
+  const uint8_t *payload;
+  RecordMap map;
+  __device__ const float *dense_base() const { return nullptr; }
+  static constexpr int kLdsFloats = 1;
+  __device__ void begin(uint32_t, float *) const {}
+  __device__ void at4(const Geo &g, uint32_t p, uint32_t j, const TileBuf &row, const float *lds, float out[4]) const {
+    bool as_is;
+    const uint8_t *rec = payload + map.record(p, &as_is);
+    if (as_is) IdentityDec{rec, 0}.at4(g, 0, j, row, lds, out);
+    else Fp16Dec{rec, 0}.at4(g, 0, j, row, lds, out);
+  }
+};
 struct DenseDec {
   const float *dense;
   __device__ const float *dense_base() const { return dense; }
@@ -394,7 +409,13 @@ constexpr int kURows = kTile / kURow;
 template <class DEC>
 __global__ __launch_bounds__(kThreads) void adam_update_kernel(Geo g, DEC dec, float *x, float *m, float *v, OptArgs o) {
   __shared__ __align__(16) float lds[DEC::kLdsFloats];
-  if (blockIdx.x == 0 && threadIdx.x == 0) o.status[0] = 0;   // no wait in this call
+  if (blockIdx.x == 0) {   // no wait in this call
+    if constexpr (std::is_same_v<DEC, Fp16MapDec>) {
+      if (threadIdx.x < dec.map.n) o.status[4 * threadIdx.x] = 0;
+    } else {
+      if (threadIdx.x == 0) o.status[0] = 0;
+    }
+  }
   const uint32_t p = __builtin_amdgcn_readfirstlane(blockIdx.x / g.tiles_per_part);
   const uint32_t tile = __builtin_amdgcn_readfirstlane(blockIdx.x % g.tiles_per_part);
   const uint32_t d = g.part_size(p);
@@ -1042,6 +1063,14 @@ static hipError_t run_update(const Geo &g, DEC dec, float *x, float *m, float *v
   if (e != hipSuccess) return e;
   update_moments_kernel<DEC, true><<<g.n_tiles, kThreads, 0, stream>>>(g, dec, x, m, v, o, norms);
   lans_apply_kernel<DEC><<<g.n_tiles, kThreads, 0, stream>>>(g, dec, x, m, v, o, norms);
+  return hipGetLastError();
+}
+
+hipError_t adam_update_fp16_map(const Geo &g, const RecordMap &map, const uint8_t *payload, float *x, float *m, float *v,
+                                const bpc_opt_t &opt, const Workspace &ws, hipStream_t stream) {
+  const OptArgs o{opt.lr, opt.beta1, opt.beta2, opt.eps, opt.weight_decay, opt.bias_corr1, opt.bias_corr2,
+                  opt.phi_lo, opt.phi_hi, opt.block_offsets, opt.n_blocks, ws.status()};
+  adam_update_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, Fp16MapDec{payload, map}, x, m, v, o);
   return hipGetLastError();
 }
 

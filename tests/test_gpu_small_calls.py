@@ -1,0 +1,144 @@
+"""Calls of few tiles per workgroup go without the launch that presets the slots of the
+single-pass kernels (the slots carry a tag of the launch instead); calls recorded into a graph and
+large calls take the preset form.  Both give the same bits, whatever an earlier call left in the
+workspace."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available()
+    import gpu_util
+    gpu_util.bpc.lib()
+    return gpu_util
+
+
+# one tile; a partition and a ragged one; several tiles a workgroup; the sizes around the rule's
+# line (512 or 768 workgroups of 8192 elements, four tiles each), where the large form begins
+@pytest.mark.parametrize("D", [777, 140_001, 6_000_003, 16_777_216, 16_785_409, 25_170_000])
+@pytest.mark.parametrize("kind,n,dtype", [("sign", 4, "float32"), ("sign", 3, "float16"), ("dither", 8, "float32"),
+                                          ("dither", 3, "float16"), ("natdither", 16, "float32"), ("dither5", 4, "float32")])
+def test_tagged_and_preset_forms_agree(gu, kind, n, dtype, D):
+    import torch
+    bpc, dev = gu.bpc, gu.DEV
+    pe = 2_097_152 if dtype == "float16" else 1_048_576
+    kw = dict(levels=15 if kind == "dither5" else 4, seed=5) if kind != "sign" else {}
+    code = gu.KIND_B["dither" if kind == "dither5" else kind]
+    D &= ~1   # (an odd number of halves would send the last partition to the other kernels)
+    prm = bpc.make_params(code, pe, **kw)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(D + n)
+    g = (torch.randn(D, generator=gen, device=dev) * 1e-3).to(getattr(torch, dtype))
+    e0 = torch.randn(D, generator=gen, device=dev) * 1e-4
+    s0 = torch.randn(D, generator=gen, device=dev) * 1e-4
+    e, s = e0.clone(), s0.clone()
+    pay = torch.zeros(bpc.payload_bytes(prm, D), dtype=torch.uint8, device=dev)
+    out = torch.zeros_like(pay)
+    ws = torch.full((bpc.workspace_bytes(prm, D, n),), 0xFF, dtype=torch.uint8, device=dev)
+
+    def calls():
+        bpc.bpc_compress(prm, g, e, pay, ws)
+        bpc.bpc_server_aggregate([prm] * n, [pay] * n, prm, s, D, out, ws)
+
+    def restore():
+        e.copy_(e0); s.copy_(s0); pay.zero_(); out.zero_()
+
+    def snapshot():
+        torch.cuda.synchronize()
+        bpc.workspace_check(prm, D, ws)
+        return [t.clone() for t in (e, s, pay, out)]
+
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        calls()   # on a workspace of arbitrary bytes
+    torch.cuda.current_stream().wait_stream(side)
+    first = snapshot()
+    restore()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for _ in range(2):
+        restore()
+        graph.replay()
+        for a, b in zip(snapshot(), first):
+            assert torch.equal(a, b)
+    for _ in range(2):   # eager again, over slots that hold the very values to come
+        restore()
+        calls()
+        for a, b in zip(snapshot(), first):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("kind", ["topk", "topk16"])
+def test_topk_many_partitions(gu, orc, kind):
+    """More partitions than the device holds workgroups of the select kernel; some of them, spread
+    over the range, are left to the long form."""
+    pe = 4096
+    D = 1300 * pe + 1001
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=0.01)
+    rs = np.random.default_rng(23)
+    g = rs.standard_normal(D).astype(np.float32)
+    e = (0.3 * rs.standard_normal(D)).astype(np.float32)
+    for p in (3, 200, 257, 700, 1299):
+        g[p * pe:(p + 1) * pe] = np.where(rs.random(pe) < 0.5, -0.5, 0.5)
+        e[p * pe:(p + 1) * pe] = 0.0
+    g[800 * pe:801 * pe] = 0.0
+    e[800 * pe:801 * pe] = 0.0
+    res_ref = e.copy()
+    pay_ref = orc.compress(po, g, res_ref)
+    pay_gpu, res_gpu = gu.gpu_compress(pb, g, e.copy())
+    assert np.array_equal(res_gpu.view(np.uint32), res_ref.view(np.uint32))
+    stride = orc.partition_stride(po)
+    for p in range(1301):
+        k = max(1, int(0.01 * min(pe, D - p * pe)))
+        a, b = pay_gpu[p * stride:(p + 1) * stride], pay_ref[p * stride:(p + 1) * stride]
+        assert np.array_equal(a[:16 + 4 * k], b[:16 + 4 * k]), p
+
+
+@pytest.mark.parametrize("n,dtype", [(1, np.float16), (4, np.float32), (8, np.float16), (16, np.float32)])
+@pytest.mark.parametrize("pe", [1024, 5120])
+def test_fp16_with_the_most_runs_in_one_launch(gu, orc, n, dtype, pe):
+    """64 runs of alternating class (partitions smaller than a tile and of a tile and a remainder, an
+    odd last one): messages, residuals and an Adam-style step against the oracle, bit for bit."""
+    import torch
+    bpc = gu.bpc
+    D = 70 * pe - 3
+    mask = np.array([0] * 4 + [1] * 4 + [0, 1] * 31, np.uint8)
+    assert len(mask) == 70 and 1 + np.count_nonzero(np.diff(mask)) == 64
+    po, pb = gu.both_params(orc, "fp16", pe, bypass=mask)
+    rs = np.random.default_rng(pe + n)
+    ws = gu.new_ws(pb, D, n)
+    ws.fill_(0xFF)
+    pays_ref, pays = [], []
+    for i in range(n):
+        g = (rs.standard_t(3.0, D) * 1e-3).astype(dtype)
+        e = (rs.standard_normal(D) * 3e-4).astype(np.float32)
+        rd = gu.to_dev(e)
+        pays.append(gu.new_payload(pb, D))
+        bpc.bpc_compress(pb, gu.to_dev(g), rd, pays[i], ws)
+        bpc.workspace_check(pb, D, ws)
+        pays_ref.append(orc.compress_bypass(po, mask, g, e))
+        assert np.array_equal(gu.to_host(rd), e)
+    s = (rs.standard_normal(D) * 1e-4).astype(np.float32)
+    sd, out = gu.to_dev(s), gu.new_payload(pb, D)
+    bpc.bpc_server_aggregate([pb] * n, pays, pb, sd, D, out, ws)
+    bpc.workspace_check(pb, D, ws)
+    out_ref = orc.server_aggregate_bypass([po] * n, pays_ref, po, mask, s, D)
+    assert np.array_equal(gu.to_host(sd), s)
+    dense = torch.zeros(D, device=gu.DEV)
+    bpc.bpc_decompress(pb, out, dense)
+    assert np.array_equal(gu.to_host(dense), orc.decompress_bypass(po, mask, out_ref, D))
+    x, m, v = [(rs.standard_normal(D) * c).astype(np.float32) for c in (0.02, 3e-4, 1e-3)]
+    v = v * v
+    dx, dm, dv = gu.to_dev(x), gu.to_dev(m), gu.to_dev(v)
+    hyper = (1e-3, 0.9, 0.999, 1e-8, 0.01, 3)
+    bpc.bpc_adaptive_update(pb, out, dx, dm, dv, bpc.make_opt(bpc.OPT_ADAM, *hyper), ws)
+    bpc.workspace_check(pb, D, ws)
+    orc.adaptive_update_bypass(po, mask, out_ref, D, x, m, v, orc.make_opt(orc.OPT_ADAM, *hyper))
+    for a, b in ((dx, x), (dm, m), (dv, v)):
+        assert np.array_equal(gu.to_host(a), b)
