@@ -56,6 +56,7 @@ constexpr int kBits1 = 11, kBits23 = 10;
 constexpr int kTpgLoad = 2, kTpgHist2 = 4, kTpgHist3 = 1, kTpgCount = 1;
 constexpr int kSelThreads = 1024;                       // workgroup of the select pass
 constexpr int kSelPer = kTopkListCap / kSelThreads;     // list entries a thread of it keeps
+constexpr uint32_t kSelGrid = 256;                      // workgroups the select pass is spread over when there are few partitions
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr int kSamplePer = 16;                          // sampled elements per thread of the sample pass
 constexpr uint32_t kSample = kThreads * kSamplePer;     // per partition: 4096
@@ -143,10 +144,10 @@ __device__ inline void level1_in_registers(const uint32_t (&bits)[PER], uint32_t
   __syncthreads();
   pick_bin<kBins1, kBits1, THREADS>(h, rank, 0, scan, sel);
 }
-// Levels 2 and 3, given level 1's (b1, k_rem1): the key in sel[0], the rank left among the keys
-// equal to it in sel[1].
+// Level 2, given level 1's (b1, k_rem1): the key's first 21 bits in sel[0], the rank left among the
+// keys that share them in sel[1].
 template <int PER, int THREADS>
-__device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
+__device__ inline void level2_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
                                              uint32_t k_rem1, uint32_t *h, uint32_t *scan, uint32_t *sel) {
   for (int b = threadIdx.x; b < kBins23; b += THREADS) h[b] = 0;
   __syncthreads();
@@ -158,6 +159,12 @@ __device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32
   }
   __syncthreads();
   pick_bin<kBins23, kBits23, THREADS>(h, k_rem1, b1, scan, sel);
+}
+// Levels 2 and 3: the key in sel[0], the rank left among the keys equal to it in sel[1].
+template <int PER, int THREADS>
+__device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
+                                             uint32_t k_rem1, uint32_t *h, uint32_t *scan, uint32_t *sel) {
+  level2_in_registers<PER, THREADS>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
   const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
   __syncthreads();
   for (int b = threadIdx.x; b < kBins23; b += THREADS) h[b] = 0;
@@ -407,8 +414,9 @@ __global__ __launch_bounds__(kThreads) void topk_sample_kernel(Geo g, SRC src, u
   level1_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, rank, h, scan, sel);
   const uint32_t b1 = sel[0], k_rem1 = sel[1];
   __syncthreads();
-  levels23_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, b1, k_rem1, h, scan, sel);
-  if (threadIdx.x == 0) guess[p] = sel[0];
+  // (the lower end of the level-2 bin will do for a guess: it holds a thousandth of an octave)
+  level2_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, b1, k_rem1, h, scan, sel);
+  if (threadIdx.x == 0) guess[p] = sel[0] << kShift2;
 }
 
 template <class SRC, class = void>
@@ -768,11 +776,15 @@ __device__ inline void topk_write_entry(const Geo &g, uint8_t *rec, uint32_t pos
 // lanes read neighbouring words), and keeps their values in registers throughout; positions in
 // the record follow from the counts of the waves before, of the rounds before and of the lanes
 // before.  A list shorter than k or longer than its room leaves the partition to the long form.
+// Where there are fewer partitions than compute units, `shares` workgroups take a partition: each
+// works the selection out for itself and writes its share of the rounds (with the guess taken two
+// levels deep and the runs requested before the list's length is looked at: a step of 3 workers on
+// 0.3 M elements 153 -> 146 us, of 8 workers on 25.6 M elements 927 -> 911 us).
 template <bool HALF>
 __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, uint32_t *state,
                                                                        const uint32_t *hist, const uint32_t *groupcnt,
                                                                        const uint32_t *cand_idx, const uint32_t *cand_val,
-                                                                       uint8_t *payload, int zero_selected) {
+                                                                       uint8_t *payload, int zero_selected, uint32_t shares) {
   constexpr int kWaves = kSelThreads / 64;
   __shared__ uint32_t h[kBins23];
   __shared__ uint32_t vstart[kSelThreads + 1];  // entries of the list before group t's run
@@ -780,25 +792,29 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   __shared__ uint32_t scan[kWaves];
   __shared__ uint32_t sel[2];
   __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
-  const uint32_t p = blockIdx.x;
+  const uint32_t p = __builtin_amdgcn_readfirstlane(blockIdx.x / shares), share = __builtin_amdgcn_readfirstlane(blockIdx.x % shares);
+  const uint32_t groups_per_part = (uint32_t)cdiv(g.tiles_per_part, kTpgLoad);            // at most kSelThreads
+  const uint32_t n_groups_p = (uint32_t)cdiv(cdiv(g.part_size(p), kTile), kTpgLoad);
+  // (the runs are requested together with the length, before the check of it)
+  uint2 run = make_uint2(0u, 0u);
+  if (threadIdx.x < n_groups_p) run = reinterpret_cast<const uint2 *>(groupcnt)[(uint64_t)p * groups_per_part + threadIdx.x];
   const uint32_t n = __builtin_amdgcn_readfirstlane(state[p * 8 + kStListLen]);
   const uint32_t k = (uint32_t)k_of_device(g, p);
   if (n < k || n > kTopkListCap) {
     if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
     return;
   }
-  const uint32_t groups_per_part = (uint32_t)cdiv(g.tiles_per_part, kTpgLoad);            // at most kSelThreads
-  const uint32_t n_groups_p = (uint32_t)cdiv(cdiv(g.part_size(p), kTile), kTpgLoad);
   {
-    const uint64_t t = (uint64_t)p * groups_per_part + threadIdx.x;
-    const uint32_t c = threadIdx.x < n_groups_p ? groupcnt[2 * t + 1] : 0u;
-    goff[threadIdx.x] = threadIdx.x < n_groups_p ? groupcnt[2 * t] : 0u;
+    const uint32_t c = run.y;
+    goff[threadIdx.x] = run.x;
     uint32_t total;
     vstart[threadIdx.x] = block_exclusive_scan<kSelThreads>(c, scan, &total);
     if (threadIdx.x == 0) vstart[kSelThreads] = n;
   }
   __syncthreads();
   const uint32_t rounds = (uint32_t)cdiv(n, kSelThreads);  // at most kSelPer
+  const uint32_t emit_lo = __builtin_amdgcn_readfirstlane(rounds * share / shares);
+  const uint32_t emit_hi = __builtin_amdgcn_readfirstlane(rounds * (share + 1) / shares);   // the rounds this workgroup writes
   const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t first = wave * rounds * 64 + lane;        // the thread's entries: first + 64 i, i < rounds
   const uint32_t cnt = first < n ? (uint32_t)cdiv(n - first, 64) < rounds ? (uint32_t)cdiv(n - first, 64) : rounds : 0u;
@@ -841,7 +857,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
       if ((uint32_t)i >= rounds) continue;   // (the same for all threads)
       const uint32_t at = (uint32_t)i < cnt ? walk_to(w, first + 64 * i) : 0u;
       bits[i] = cand_val[list + at];
-      where[i] = cand_idx[list + at];
+      if ((uint32_t)i >= emit_lo && (uint32_t)i < emit_hi) where[i] = cand_idx[list + at];
     }
   }
   // level 1 is known from the histogram of the whole partition
@@ -850,7 +866,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   __syncthreads();
   levels23_in_registers<kSelPer, kSelThreads>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
   const uint32_t T = sel[0], r = sel[1];
-  if (threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
+  if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
   // keys above T and equal to T in the waves before this one
   {
     uint32_t n_gt = 0, n_eq = 0;
@@ -877,7 +893,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   // which entries are kept and where they go
 #pragma unroll
   for (int i = 0; i < kSelPer; ++i) {
-    if ((uint32_t)i < rounds) {   // (the same for all threads)
+    if ((uint32_t)i < emit_hi) {   // (the same for all threads)
       const bool valid = (uint32_t)i < cnt;
       const uint64_t gtm = __ballot(valid && key(i) > T), eqm = __ballot(valid && key(i) == T);
       const uint32_t gt_before = gt_base + __popcll(gtm & lanes_before);
@@ -885,7 +901,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
       const bool t = valid && (key(i) > T || (key(i) == T && eq_before < r));
       gt_base += __popcll(gtm);
       eq_base += __popcll(eqm);
-      if (t) topk_write_entry<HALF>(g, rec, gt_before + (eq_before < r ? eq_before : r), where[i], __uint_as_float(bits[i]), buf_part, zero_selected);
+      if (t && (uint32_t)i >= emit_lo) topk_write_entry<HALF>(g, rec, gt_before + (eq_before < r ? eq_before : r), where[i], __uint_as_float(bits[i]), buf_part, zero_selected);
     }
   }
 }
@@ -1098,8 +1114,10 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   }
   const int zero_selected = src.residual != nullptr;
   if (short_list) {
-    if (half) topk_list_select_kernel<true><<<g.P, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected);
-    else topk_list_select_kernel<false><<<g.P, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected);
+    // (as many workgroups as one round of them over the compute units takes, at most four a partition)
+    const uint32_t shares = 4 * g.P <= kSelGrid ? 4 : 2 * g.P <= kSelGrid ? 2 : 1;
+    if (half) topk_list_select_kernel<true><<<g.P * shares, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected, shares);
+    else topk_list_select_kernel<false><<<g.P * shares, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected, shares);
   }
   const uint32_t n2 = group_count(g, kTpgHist2), n3 = group_count(g, kTpgHist3), nc = group_count(g, kTpgCount);
   const uint32_t ne = g.P * g.tiles_per_part;
