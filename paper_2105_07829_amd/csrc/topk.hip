@@ -188,6 +188,11 @@ __device__ inline uint32_t sample_chunk(uint32_t c, uint32_t stride) { return c 
 // Sample chunks and their spacing for a partition of d elements.
 __device__ inline uint32_t sample_chunks(uint32_t d) { return d / 8 < kSample / 8 ? d / 8 : kSample / 8; }
 
+// Workgroup of the load pass: 16 elements a thread (of 256 threads, 32 elements each: 91 registers
+// a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
+// 135 us, of 8 workers on 25.6 M elements 911 -> 892 us, of 16 workers on 110 M f16 elements 4275 ->
+// 4202 us.
+constexpr int kLoadThreads = 512;
 constexpr uint32_t kGroupElems = kTpgLoad * kTile;   // elements a workgroup of the load pass takes: 8192
 static_assert(kGroupElems == 8192, "the workspace is laid out for groups of 8192 elements");
 
@@ -283,7 +288,7 @@ struct TopkMsgsGroupSource : TopkMsgs {
       range[2 * threadIdx.x] = s;
       range[2 * threadIdx.x + 1] = e < s ? s : e;
     }
-    for (uint32_t q = threadIdx.x; q < kGroupElems / 4; q += kThreads) reinterpret_cast<float4 *>(lds)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (uint32_t q = threadIdx.x; q < kGroupElems / 4; q += kLoadThreads) reinterpret_cast<float4 *>(lds)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     __syncthreads();
     // entries of the group before worker i's, over all workers
     uint32_t *cum = range + 2 * kMaxWorkers;
@@ -295,15 +300,15 @@ struct TopkMsgsGroupSource : TopkMsgs {
     }
     __syncthreads();
     const uint32_t total = cum[msgs.n];
-    constexpr int kMine = 4;   // entries a thread takes
-    if (total <= (uint32_t)(kMine * kThreads)) {
+    constexpr int kMine = 2;   // entries a thread takes
+    if (total <= (uint32_t)(kMine * kLoadThreads)) {
       // all the group's entries are requested at once (worker-major, so a thread's entries come
       // in worker order), then added worker by worker with a barrier in between
       uint32_t rel[kMine], who[kMine];
       float val[kMine];
 #pragma unroll
       for (int r = 0; r < kMine; ++r) {
-        const uint32_t q = r * kThreads + threadIdx.x;
+        const uint32_t q = r * kLoadThreads + threadIdx.x;
         who[r] = 0xffffffffu;
         rel[r] = 0;
         val[r] = 0.0f;
@@ -332,7 +337,7 @@ struct TopkMsgsGroupSource : TopkMsgs {
     } else {
       for (int i = 0; i < msgs.n; ++i) {
         const uint32_t s = range[2 * i], e = range[2 * i + 1];
-        for (uint32_t q = s + threadIdx.x; q < e; q += kThreads) {
+        for (uint32_t q = s + threadIdx.x; q < e; q += kLoadThreads) {
           const uint32_t r = idx(i, p)[q] - lo;
           if (r < kGroupElems) lds[r] = lds[r] + value(i, p, q);
         }
@@ -437,28 +442,28 @@ struct has_begin_group<SRC, std::void_t<decltype(&SRC::begin_group)>> : std::tru
 // workgroup: a fourth workgroup per compute unit on the server side); the rare key beyond them
 // goes to the partition's histogram directly.
 constexpr int kNearBins = 64;
-// The group is taken as 8 rows of 1024 elements, 4 consecutive elements a thread and row: every
+// The group is taken as 4 rows of 2048 elements, 4 consecutive elements a thread and row: every
 // 16-byte access of a wave to the gradient, the residual and the buffer covers whole cache lines
 // and is marked non-temporal; everything goes through descriptors of the elements that exist
 // (the rest read as zero and are not written).  All loads of the group are requested before the
 // first is used.  Index order in the list is row, thread, element: a thread's place in its
 // row comes from the wave's ballots, the places of the rows and waves from one scan of their
 // 32 counts.
-constexpr int kLoadRowElems = kThreads * 4;
+constexpr int kLoadRowElems = kLoadThreads * 4;
 constexpr int kLoadRows = kGroupElems / kLoadRowElems;
 template <class SRC, bool LISTED>
-__global__ __launch_bounds__(kThreads) void topk_load_hist1_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state,
+__global__ __launch_bounds__(kLoadThreads) void topk_load_hist1_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state,
                                                                    const uint32_t *guess, uint32_t *groupcnt,
                                                                    uint32_t *cand_idx, uint32_t *cand_val) {
   __shared__ __align__(16) float lds[SRC::kLdsFloats];
   constexpr int kLocalBins = LISTED ? kNearBins : kBins1;
-  constexpr int kWaves = kThreads / 64;
+  constexpr int kWaves = kLoadThreads / 64;
   static_assert(kLoadRows * kWaves <= 64, "one wave scans the counts of all rows and waves");
   __shared__ uint32_t h[kLocalBins];
   __shared__ uint32_t run_cnt[kLoadRows * kWaves];   // listed elements per row and wave, then how many come before them
   __shared__ uint32_t off_sh;
   const GroupOf w = group_of<kTpgLoad>(g, blockIdx.x);
-  for (int b = threadIdx.x; b < kLocalBins; b += kThreads) h[b] = 0;
+  for (int b = threadIdx.x; b < kLocalBins; b += kLoadThreads) h[b] = 0;
   src.begin(g, w.p, lds);
   __syncthreads();
   if (w.tile_lo >= w.tile_hi) return;  // (uniform) past the end of a shorter last partition
@@ -478,7 +483,7 @@ __global__ __launch_bounds__(kThreads) void topk_load_hist1_kernel(Geo g, SRC sr
     src.begin_group(g, w.p, w.tile_lo / kTpgLoad, lds);
 #pragma unroll
     for (int u = 0; u < kLoadRows; ++u) {
-      const float4 sum = reinterpret_cast<const float4 *>(lds)[u * kThreads + threadIdx.x];
+      const float4 sum = reinterpret_cast<const float4 *>(lds)[u * kLoadThreads + threadIdx.x];
       const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
       float e[4];
       widen4(er[u], e);
@@ -582,7 +587,7 @@ __global__ __launch_bounds__(kThreads) void topk_load_hist1_kernel(Geo g, SRC sr
   }
   __syncthreads();
   uint32_t *gh = hist + (uint64_t)w.p * kTopkHistWords + kHist1 + (LISTED ? (G >> kShift1) : 0u);
-  for (int b = threadIdx.x; b < kLocalBins; b += kThreads)
+  for (int b = threadIdx.x; b < kLocalBins; b += kLoadThreads)
     if (h[b]) atomicAdd(&gh[b], h[b]);   // (LISTED: bins past the last one hold nothing)
 }
 
@@ -1091,8 +1096,8 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   auto first_two = [&](auto s_sample, auto s_load) {
     topk_sample_kernel<<<sample_grid, kThreads, 0, stream>>>(g, s_sample, hist, state, guess, short_list, ws.status());
     using Load = decltype(s_load);
-    if (short_list) topk_load_hist1_kernel<Load, true><<<load_grid, kThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
-    else topk_load_hist1_kernel<Load, false><<<load_grid, kThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
+    if (short_list) topk_load_hist1_kernel<Load, true><<<load_grid, kLoadThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
+    else topk_load_hist1_kernel<Load, false><<<load_grid, kLoadThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
   };
   if (src.grad) {
     if (src.dtype == BPC_F16) {
