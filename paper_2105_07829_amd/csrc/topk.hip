@@ -191,7 +191,7 @@ __device__ inline uint32_t sample_chunks(uint32_t d) { return d / 8 < kSample / 
 // Workgroup of the load pass: 16 elements a thread (of 256 threads, 32 elements each: 91 registers
 // a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
 // 135 us, of 8 workers on 25.6 M elements 911 -> 892 us, of 16 workers on 110 M f16 elements 4275 ->
-// 4202 us.
+// 4202 us.  (1024 threads: 131, 908 and 4402 us.)
 constexpr int kLoadThreads = 512;
 constexpr uint32_t kGroupElems = kTpgLoad * kTile;   // elements a workgroup of the load pass takes: 8192
 static_assert(kGroupElems == 8192, "the workspace is laid out for groups of 8192 elements");
