@@ -25,10 +25,11 @@ hipError_t fill_zero(void *ptr, size_t bytes, hipStream_t stream) {
 // Decode of the bit-packed kinds and of the identity record.  A thread owns 4 consecutive
 // elements per row of 1024, so the 16-byte stores of a wave cover whole cache lines and can be
 // non-temporal; the output goes through a descriptor that ends with the partition (stores
-// past it are dropped).  The records are padded to a full partition, so reads stay inside.
+// past it are dropped) and the message is read through row_in_record().
 template <int KIND>
 __global__ __launch_bounds__(kThreads) void decode_packed_kernel(Geo g, uint32_t levels, bool natural, const uint8_t *payload, float *out) {
   constexpr int kRow = kThreads * 4, kRows = kTile / kRow;
+  static_assert(kRow == kPartUnit, "a record is whole rows");
   const uint32_t p = __builtin_amdgcn_readfirstlane(blockIdx.x / g.tiles_per_part);
   const uint32_t tile = __builtin_amdgcn_readfirstlane(blockIdx.x % g.tiles_per_part);
   const uint32_t d = g.part_size(p);
@@ -44,7 +45,7 @@ __global__ __launch_bounds__(kThreads) void decode_packed_kernel(Geo g, uint32_t
   }
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
-    const uint32_t j = tile * kTile + u * kRow + threadIdx.x * 4;   // partition-local, a multiple of 4
+    const uint32_t j = row_in_record(tile * kTile + u * kRow, g.part_elems) + threadIdx.x * 4;   // partition-local, a multiple of 4
     float v[4];
     if (KIND == BPC_SIGN) {
       const uint32_t nib = body[j >> 3] >> (j & 4);
@@ -80,6 +81,7 @@ __global__ __launch_bounds__(kThreads) void decode_packed_kernel(Geo g, uint32_t
 // (nu * level) / s as the format defines it.
 __global__ __launch_bounds__(kThreads) void decode_dither_wide_kernel(Geo g, uint32_t levels, const uint8_t *payload, float *out) {
   constexpr int kRow = kThreads * 4, kRows = kTile / kRow;
+  static_assert(kRow == kPartUnit, "a record is whole rows");
   const uint32_t p = __builtin_amdgcn_readfirstlane(blockIdx.x / g.tiles_per_part);
   const uint32_t tile = __builtin_amdgcn_readfirstlane(blockIdx.x % g.tiles_per_part);
   const uint32_t d = g.part_size(p);
@@ -93,7 +95,7 @@ __global__ __launch_bounds__(kThreads) void decode_dither_wide_kernel(Geo g, uin
   float *tile_out = out + g.part_base(p) + (uint64_t)tile * kTile;
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
-    const uint32_t j = tile * kTile + u * kRow + threadIdx.x * 4;   // partition-local, a multiple of 4
+    const uint32_t j = row_in_record(tile * kTile + u * kRow, g.part_elems) + threadIdx.x * 4;   // partition-local, a multiple of 4
     const uint32_t half = reinterpret_cast<const uint16_t *>(body)[j >> 2];
     uint32_t hi[4] = {0, 0, 0, 0};
     for (uint32_t t = 0; t < planes; ++t) {

@@ -17,6 +17,7 @@ namespace bpc {
 constexpr int kMaxWorkers = 64;      // most worker messages one aggregate call accepts
 constexpr int kTile = 4096;          // elements one workgroup handles in the streaming kernels
 constexpr int kThreads = 256;        // workgroup size of the streaming kernels
+constexpr uint32_t kPartUnit = 1024; // partitions hold a multiple of this many elements
 constexpr int kSThreads = 256;       // workgroup size of the server-side kernels when the number of workers is not one they are compiled for
 constexpr int kWTile = 8192;         // tile of the worker-side single-pass kernels (512 threads x 16 elements)
 constexpr int kSTile = 8192;         // tile of the server-side single-pass kernels and of single-pass LANS
@@ -62,7 +63,7 @@ struct Geo {
 inline bool params_valid(const bpc_params_t *p) {
   if (!p) return false;
   // (2^28 elements at most: byte offsets inside a partition's record and arrays fit 32 bits everywhere)
-  if (p->part_elems == 0 || p->part_elems % 1024 != 0 || p->part_elems > (1ull << 28)) return false;
+  if (p->part_elems == 0 || p->part_elems % kPartUnit != 0 || p->part_elems > (1ull << 28)) return false;
   switch (p->kind) {
     case BPC_IDENTITY: case BPC_SIGN: case BPC_FP16: return true;
     case BPC_TOPK: case BPC_TOPK16: case BPC_RANDK: return p->k_ratio > 0.0 && p->k_ratio <= 1.0;
@@ -72,6 +73,15 @@ inline bool params_valid(const bpc_params_t *p) {
       return p->levels >= 1 && p->levels <= 7 && (p->norm == BPC_NORM_L2 || p->norm == BPC_NORM_LINF);
     default: return false;
   }
+}
+
+// A record has room for part_elems elements, also that of a shorter last partition.  That is whole
+// rows of kPartUnit elements but not always whole tiles: kernels that read a message a row at a
+// time, 4 elements a thread, read the record's last row again in place of the rows of a tile past
+// its end (what they make of those is not stored).  `row0`: the row's first element in the partition.
+BPC_HD inline uint32_t row_in_record(uint32_t row0, uint64_t part_elems) {
+  const uint32_t last = (uint32_t)part_elems - kPartUnit;
+  return row0 < last ? row0 : last;
 }
 
 // Bit planes that follow the nibbles of a linear-dithering record: level bits 3, 4, 5.

@@ -159,7 +159,7 @@ struct IdentityDec {
   __device__ float at(const Geo &, uint32_t p, uint32_t j, const float *) const {
     return reinterpret_cast<const float *>(payload + (uint64_t)p * stride + kHeaderBytes)[j];
   }
-  // the record is padded to a full partition, so the 16 bytes are always inside it
+  // (j inside a full partition, which the record is padded to)
   __device__ void at4(const Geo &, uint32_t p, uint32_t j, const TileBuf &, const float *, float out[4]) const {
     const float4 a = reinterpret_cast<const float4 *>(payload + (uint64_t)p * stride + kHeaderBytes)[j >> 2];
     out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
@@ -185,7 +185,7 @@ struct Fp16Dec {
   using R4 = u32x2;
   __device__ float header(uint32_t) const { return 0.0f; }
   __device__ void table(float, float *) const {}
-  // the record is padded to a full partition, so the 8 bytes are always inside it
+  // (j inside a full partition, which the record is padded to)
   __device__ R4 load4(const Geo &, uint32_t p, uint32_t j, const TileBuf &) const {
     return reinterpret_cast<const u32x2 *>(payload + (uint64_t)p * stride + kHeaderBytes)[j >> 2];
   }
@@ -403,8 +403,9 @@ __global__ __launch_bounds__(kThreads) void update_moments_kernel(Geo g, DEC dec
 // access of a wave covers whole cache lines (which is what lets the stores be non-temporal);
 // all loads of a tile are requested before the first is used.  x, m and v go through buffer
 // descriptors that end with the partition: reads past it return 0 and stores past it are
-// dropped, so a ragged last tile needs no other care.
+// dropped.  The message is read through row_in_record(): a partition need not be whole tiles.
 constexpr int kURow = kThreads * 4;
+static_assert(kURow == kPartUnit, "a record is whole rows");
 constexpr int kURows = kTile / kURow;
 template <class DEC>
 __global__ __launch_bounds__(kThreads) void adam_update_kernel(Geo g, DEC dec, float *x, float *m, float *v, OptArgs o) {
@@ -443,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void adam_update_kernel(Geo g, DEC dec, f
       vr[u] = row_buf(v + tile_base, valid, u * kURow, kURow).load16<kNonTemporal>(threadIdx.x * 16, 0);
       xr[u] = row_buf(x + tile_base, valid, u * kURow, kURow).load16<kNonTemporal>(threadIdx.x * 16, 0);
     }
-    const uint32_t j = tile * kTile + u * kURow + threadIdx.x * 4;
+    const uint32_t j = row_in_record(tile * kTile + u * kURow, g.part_elems) + threadIdx.x * 4;
     dec.at4(g, p, j, row_buf(dec.dense_base() + tile_base, valid, u * kURow, kURow), lds, gr[u]);
   }
 #pragma unroll
