@@ -186,6 +186,28 @@ inline size_t lans_blocks_room(uint64_t n_blocks, uint64_t tiles) {
   return a > b ? a : b;
 }
 
+// LANS with caller-defined blocks.  The offsets lie in device memory, so nothing on the host can look
+// at them: whatever they are, the kernels stay inside the pairs (block number < n_blocks, tile
+// inside the gradient).  The tiles of block [lo, hi), which ends with the gradient at the latest:
+// the first one and how many (0: none).
+struct BlockTiles { uint64_t t0, n; };
+BPC_HD inline BlockTiles block_tiles(uint64_t lo, uint64_t hi, uint64_t D) {
+  hi = hi < D ? hi : D;
+  BlockTiles t{lo / kSTile, 0};
+  if (hi > lo) t.n = (hi - 1) / kSTile - t.t0 + 1;
+  return t;
+}
+// A block ends inside a tile that ends at tile_end if it ends at or before this.
+BPC_HD inline uint64_t tile_edge(uint64_t tile_end, uint64_t D) { return tile_end < D ? tile_end : ~0ull; }
+// One step of the search for the block that holds an element, among the n blocks from *lo: of the
+// first elements of the blocks *lo, *lo + stride, ... the first c are at or before it (none: the
+// element lies before the first block, which is then the answer).
+BPC_HD inline void narrow_blocks(uint32_t c, uint64_t stride, uint64_t *lo, uint64_t *n) {
+  const uint64_t skip = c ? (uint64_t)(c - 1) * stride : 0;
+  *lo += skip;
+  *n = *n - skip < stride ? *n - skip : stride;
+}
+
 BPC_HD inline uint64_t k_of_device(const Geo &g, uint32_t p) { return k_rule(g.k_ratio, g.part_size(p)); }
 
 }  // namespace bpc

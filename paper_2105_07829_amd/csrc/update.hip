@@ -769,10 +769,7 @@ __device__ inline uint32_t find_block_wave(const uint64_t *offs, uint64_t n_bloc
     const uint64_t stride = (n + 63) / 64;
     const bool in = lane * stride < n;
     const uint64_t off = offs[lo + (in ? lane * stride : 0)];
-    const uint32_t c = (uint32_t)__popcll(__ballot(in && off <= i));   // at least 1: offs[lo] <= i
-    const uint64_t skip = (uint64_t)(c - 1) * stride;
-    lo += skip;
-    n = n - skip < stride ? n - skip : stride;
+    narrow_blocks((uint32_t)__popcll(__ballot(in && off <= i)), stride, &lo, &n);
   }
   return __builtin_amdgcn_readfirstlane((uint32_t)lo);
 }
@@ -894,6 +891,7 @@ __global__ __launch_bounds__(kBThreads) void lans_norms_kernel(Geo g, ClusterGeo
     row_buf(m + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(mo[0], mo[1], mo[2], mo[3]), threadIdx.x * 16);
     row_buf(v + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(vo[0], vo[1], vo[2], vo[3]), threadIdx.x * 16);
   }
+  const uint64_t edge = tile_edge(tile_end, g.D);
 #pragma unroll 1
   for (uint64_t b = b0; b < o.n_blocks; ++b) {
     const uint64_t lo = uniform_off(o.block_offsets[b]), hi = uniform_off(o.block_offsets[b + 1]);
@@ -902,7 +900,7 @@ __global__ __launch_bounds__(kBThreads) void lans_norms_kernel(Geo g, ClusterGeo
     const uint32_t rhi = (uint32_t)((hi < tile_end ? hi : tile_end) - tile_first);
     const double s = rlo == 0 && rhi == (uint32_t)kSTile ? lans_tile_sum<true>(h, rlo, rhi, red) : lans_tile_sum<false>(h, rlo, rhi, red);
     double *pair = pairs + 3 * (item + b);
-    if (lo < tile_first || hi > tile_end) {
+    if (lo < tile_first || hi > edge) {
       if (threadIdx.x < 3) pair[threadIdx.x] = s;
     } else {
       if (threadIdx.x < 3) tot[threadIdx.x] = s;
@@ -917,22 +915,19 @@ __global__ __launch_bounds__(kBThreads) void lans_norms_kernel(Geo g, ClusterGeo
 // there are many, most of which lie inside a tile and need nothing here).
 constexpr int kTotThreads = 1024;
 constexpr uint32_t kTotGrid = 1024;
-__global__ __launch_bounds__(kTotThreads) void lans_totals_kernel(OptArgs o, double *pairs, uint32_t chunk) {
+__global__ __launch_bounds__(kTotThreads) void lans_totals_kernel(OptArgs o, uint64_t D, double *pairs, uint32_t chunk) {
   __shared__ double red[kTotThreads / 64];
   for (uint64_t c0 = (uint64_t)blockIdx.x * chunk; c0 < o.n_blocks; c0 += (uint64_t)gridDim.x * chunk) {
     const uint64_t mine = c0 + (threadIdx.x & 63);
     bool far = false;
-    if ((threadIdx.x & 63) < chunk && mine < o.n_blocks) {
-      const uint64_t lo = o.block_offsets[mine], hi = o.block_offsets[mine + 1];
-      far = hi > lo && lo / kSTile != (hi - 1) / kSTile;
-    }
+    if ((threadIdx.x & 63) < chunk && mine < o.n_blocks) far = block_tiles(o.block_offsets[mine], o.block_offsets[mine + 1], D).n > 1;
     unsigned long long todo = __ballot(far);   // (the same in every wave)
     while (todo) {
       const uint64_t b = c0 + (uint32_t)__builtin_ctzll(todo);
       todo &= todo - 1;
-      const uint64_t lo = uniform_off(o.block_offsets[b]), hi = uniform_off(o.block_offsets[b + 1]);
-      double *first = pairs + 3 * (lo / kSTile + b);
-      const uint32_t n = (uint32_t)((hi - 1) / kSTile - lo / kSTile + 1);
+      const BlockTiles t = block_tiles(uniform_off(o.block_offsets[b]), uniform_off(o.block_offsets[b + 1]), D);
+      double *first = pairs + 3 * (t.t0 + b);
+      const uint32_t n = (uint32_t)t.n;
       double a0 = 0.0, a1 = 0.0, a2 = 0.0;
       for (uint32_t k = threadIdx.x; k < n; k += kTotThreads) {
         a0 += first[3 * (uint64_t)k];
@@ -1007,7 +1002,7 @@ static hipError_t run_lans_blocks(const Geo &g, DEC dec, float *x, float *m, flo
   if (g.part_elems % kSTile != 0) return hipSuccess;
   const ClusterGeo cg = make_cluster_geo(g, kSTile);
   *used = true;
-  // the pairs: three doubles each, one more than tiles + blocks of them at most; they start where
+  // the pairs: three doubles each, fewer of them than tiles + blocks; they start where
   // the slots of the single-pass kernels do (three doubles a tile) and reach into the room for the
   // blocks that follows (three doubles a block, see update_ws_bytes())
   double *pairs = ws.at<double>(ws.lay.slots);
@@ -1015,7 +1010,7 @@ static hipError_t run_lans_blocks(const Geo &g, DEC dec, float *x, float *m, flo
   const uint32_t chunk = per < 64 ? (uint32_t)per : 64u;
   const uint64_t chunks = cdiv(o.n_blocks, chunk);
   lans_norms_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs);
-  lans_totals_kernel<<<chunks < kTotGrid ? (uint32_t)chunks : kTotGrid, kTotThreads, 0, stream>>>(o, pairs, chunk);
+  lans_totals_kernel<<<chunks < kTotGrid ? (uint32_t)chunks : kTotGrid, kTotThreads, 0, stream>>>(o, g.D, pairs, chunk);
   lans_step_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs);
   return hipGetLastError();
 }

@@ -17,7 +17,10 @@ def geo(tmp_path_factory):
                     os.path.join(HERE, "host_geometry.cpp")], check=True)
     L = C.CDLL(so)
     for name, args, res in [("geo_tiles", [C.c_uint64], C.c_uint32), ("geo_tile_elems", [], C.c_uint32),
-                            ("geo_row_elems", [], C.c_uint32), ("geo_row_in_record", [C.c_uint32, C.c_uint64], C.c_uint32)]:
+                            ("geo_row_elems", [], C.c_uint32), ("geo_row_in_record", [C.c_uint32, C.c_uint64], C.c_uint32),
+                            ("geo_lans_tile", [], C.c_uint32), ("geo_find_block", [C.c_void_p, C.c_uint64, C.c_uint64], C.c_int64),
+                            ("geo_tile_edge", [C.c_uint64, C.c_uint64], C.c_uint64),
+                            ("geo_block_tiles", [C.c_uint64, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p], None)]:
         getattr(L, name).argtypes, getattr(L, name).restype = args, res
     return L
 
@@ -54,3 +57,45 @@ def test_update_and_decode_read_inside_the_record(geo, kind, pe):
     assert last(read) <= stride
     if pe % tile:   # (the reads that this is about)
         assert last(rows) > stride
+
+
+def _offsets(name, D):
+    rng = np.random.default_rng(5)
+    inner = np.sort(rng.integers(0, D, 300))
+    return {"as_stated": np.concatenate([[0], inner, [D]]), "one_block": [0, D],
+            "starts_late": np.concatenate([[9000], 9000 + inner, [D + 9000]]),   # (its last one ends past D, too)
+            "one_block_starts_late": [20000, D], "ends_late": np.concatenate([[0], inner, [D + 5 * 8192]]),
+            "ends_early": [0, 100, D // 2], "ends_far_beyond": [0, 17, 1 << 60],
+            "descending": np.arange(D, 0, -100), "any_words": rng.integers(0, 1 << 63, 200)}[name]
+
+
+@pytest.mark.parametrize("name", ["as_stated", "one_block", "starts_late", "one_block_starts_late", "ends_late", "ends_early",
+                                  "ends_far_beyond", "descending", "any_words"])
+@pytest.mark.parametrize("D", [777, 40_000, 150_001])
+def test_lans_blocks_stay_inside_their_pairs_whatever_the_offsets(geo, name, D):
+    """LANS over caller-defined blocks: tile t and block b meet at pair t + b.  The workspace has
+    room for tiles + blocks - 1 pairs; offsets are data of the caller's that no host code sees."""
+    offs = np.ascontiguousarray(_offsets(name, D), dtype=np.uint64)
+    n_blocks, T = len(offs) - 1, geo.geo_lans_tile()
+    tiles = -(-D // T)
+    touched = []
+    t0, n = C.c_uint64(), C.c_uint64()
+    for t in range(tiles):      # norms and step pass: the blocks of a tile, from the one that holds its first element
+        tile_end = min(D, (t + 1) * T)
+        b0 = geo.geo_find_block(offs.ctypes.data, n_blocks, t * T)
+        assert 0 <= b0 < n_blocks
+        if name in ("as_stated", "one_block", "ends_late"):
+            assert b0 == np.searchsorted(offs, t * T, side="right") - 1
+        for b in range(b0, n_blocks):
+            if int(offs[b]) >= tile_end:
+                break
+            touched += [t + b, int(offs[b]) // T + b]
+            # what the norms pass leaves unfinished is what the totals pass finishes
+            geo.geo_block_tiles(int(offs[b]), int(offs[b + 1]), D, C.byref(t0), C.byref(n))
+            if int(offs[b + 1]) > max(int(offs[b]), t * T):
+                assert (int(offs[b]) < t * T or int(offs[b + 1]) > geo.geo_tile_edge(tile_end, D)) == (n.value > 1)
+    for b in range(n_blocks):   # totals pass
+        geo.geo_block_tiles(int(offs[b]), int(offs[b + 1]), D, C.byref(t0), C.byref(n))
+        if n.value > 1:
+            touched += [t0.value + b, t0.value + n.value - 1 + b]
+    assert not touched or (min(touched) >= 0 and max(touched) <= tiles + n_blocks - 2)
