@@ -24,13 +24,20 @@ __global__ __launch_bounds__(Op::kThreads, waves_per_simd<Op>::value) void clust
   else cluster_run_ticketed(op, table, slots, status, tickets, tag);
 }
 
-// Calls of up to this many tiles per workgroup of the grid go without the preset launch.  Beyond
-// it that launch is small beside the kernel and the second word of every slot costs as much or
-// more (110 M / 336 M elements, always with a tag: sign worker 195 against 188 us, dithering
+// Calls of up to this many tenths of a tile per workgroup of the grid go without the preset launch.
+// Beyond four tiles that launch is small beside the kernel and the second word of every slot costs
+// as much or more (110 M / 336 M elements, always with a tag: sign worker 195 against 188 us, dithering
 // worker 705 against 632, sign server 232 against 216, dithering server 1143 against 1065); below
-// it a call gains what the launch costs (a step of 4 workers on 1 M elements, sign: 73 -> 60 us; of
-// 8 workers on 12.3 M elements, dithering, 3 tiles a workgroup: 428 -> 410 us).
-constexpr uint32_t kTaggedTiles = 4;
+// it a call gains what the launch costs (f16, with a tag against without: sign worker 5.1 against 7.1 us
+// at 1 M elements, 10.0 against 10.6 at 4 M, 29.4 against 30.9 at 16.8 M; dithering server of 8 workers
+// on 12 M f32 elements 1.04 times as fast).  Servers of 16 workers with three workgroups a compute
+// unit set their own: their tiles are the longest, and with a tag they come at a fixed stride instead of
+// as workgroups become free, which loses more than the launch costs from 2.7 tiles a workgroup on
+// (17 M elements: 0.93 to 0.94 times as fast, 24 M: 0.94 to 0.97; 16 M, 2.5 tiles: 1.03 to 1.05).
+template <class Op, class = void>
+struct tagged_tenths { static constexpr uint64_t value = 40; };
+template <class Op>
+struct tagged_tenths<Op, std::void_t<decltype(Op::kTaggedTenths)>> { static constexpr uint64_t value = Op::kTaggedTenths; };
 
 template <class Op, bool TAGGED>
 static int resident_workgroups() {
@@ -50,7 +57,7 @@ static hipError_t launch_cluster(const Op &op, const ClusterGeo &cg, double *slo
   if (cg.tiles_per_part > (uint32_t)capacity) return hipSuccess;
   *used = true;
   const bool small = capacity_tagged > 0 && cg.tiles_per_part <= (uint32_t)capacity_tagged &&
-                     cg.n_items <= kTaggedTiles * (uint64_t)capacity_tagged;
+                     10ull * cg.n_items <= tagged_tenths<Op>::value * (uint64_t)capacity_tagged;
   uint64_t tag = 0;
   hipError_t e = cluster_launch_begin(stream, small ? &tag : nullptr);
   if (e != hipSuccess) return e;

@@ -64,6 +64,7 @@ struct DitherServerOp {
   static_assert(!WIDE || (NW > 0 && NW * 32 <= kMaxWorkers * 16), "tables of the wide form must fit");
   static constexpr bool kPersistent = false;
   static constexpr int kWavesPerSimd = (NW > 8 && !WIDE) ? 6 : 4;
+  static constexpr uint64_t kTaggedTenths = (NW > 8 && !WIDE) ? 26 : 40;
 
   Geo g;
   ClusterGeo cg;

@@ -87,6 +87,7 @@ struct SignServerOp {
   static constexpr int kThreads = kSSThreads;
   static constexpr int kWavesPerSimd = 6;   // 80 registers a lane, three workgroups a CU
   static constexpr bool kPersistent = false;
+  static constexpr uint64_t kTaggedTenths = NW == 16 ? 26 : 40;
   struct Ctx { float sigma; };
 
   Geo g;

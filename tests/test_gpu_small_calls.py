@@ -2,6 +2,8 @@
 single-pass kernels (the slots carry a tag of the launch instead); calls recorded into a graph and
 large calls take the preset form.  Both give the same bits, whatever an earlier call left in the
 workspace."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -72,6 +74,29 @@ def test_tagged_and_preset_forms_agree(gu, kind, n, dtype, D):
         calls()
         for a, b in zip(snapshot(), first):
             assert torch.equal(a, b)
+
+
+# tiles of 8192 elements over 768 resident workgroups (16 workers) or 512 (8 workers, bit planes)
+@pytest.mark.parametrize("kind,n,D,tagged", [("sign", 16, 6_291_456, True), ("sign", 16, 16_000_000, True), ("sign", 16, 17_000_000, False),
+                                             ("sign", 4, 17_000_000, True), ("sign", 4, 25_165_825, False),
+                                             ("natdither", 16, 16_000_000, True), ("natdither", 16, 17_000_000, False),
+                                             ("dither", 16, 24_000_000, False), ("dither5", 16, 16_000_000, True),
+                                             ("dither", 8, 16_777_216, True), ("dither", 8, 16_777_217, False)])
+def test_server_calls_that_go_without_the_preset(gu, kind, n, D, tagged):
+    """The launch tag stands in the second status word of a call that goes without the preset; the
+    preset form leaves that word alone."""
+    import torch
+    bpc, dev = gu.bpc, gu.DEV
+    kw = dict(levels=15 if kind == "dither5" else 4, seed=5) if kind != "sign" else {}
+    prm = bpc.make_params(gu.KIND_B["dither" if kind == "dither5" else kind], 1_048_576, **kw)
+    pay = torch.zeros(bpc.payload_bytes(prm, D), dtype=torch.uint8, device=dev)
+    out = torch.zeros_like(pay)
+    ws = torch.zeros(bpc.workspace_bytes(prm, D, n), dtype=torch.uint8, device=dev)
+    s = torch.randn(D, device=dev) * 1e-4
+    bpc.bpc_server_aggregate([prm] * n, [pay] * n, prm, s, D, out, ws)
+    bpc.workspace_check(prm, D, ws)
+    at = int(bpc.lib().bpc_workspace_status_offset(ctypes.byref(prm), D))
+    assert bool(ws[at + 4:at + 8].any()) == tagged
 
 
 @pytest.mark.parametrize("kind", ["topk", "topk16"])
