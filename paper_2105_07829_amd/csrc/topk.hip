@@ -60,6 +60,7 @@ constexpr uint32_t kSelGrid = 256;                      // workgroups the select
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr int kSamplePer = 16;                          // sampled elements per thread of the sample pass
 constexpr uint32_t kSample = kThreads * kSamplePer;     // per partition: 4096
+constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
 constexpr uint32_t kNoGuess = 0xffffffffu;              // no key reaches it: nothing goes to the short list
 
 __device__ inline uint32_t key_of(float v) { return __float_as_uint(v) & 0x7fffffffu; }
@@ -160,12 +161,11 @@ __device__ inline void level2_in_registers(const uint32_t (&bits)[PER], uint32_t
   __syncthreads();
   pick_bin<kBins23, kBits23, THREADS>(h, k_rem1, b1, scan, sel);
 }
-// Levels 2 and 3: the key in sel[0], the rank left among the keys equal to it in sel[1].
+// Level 3, given level 2's (prefix2, k_rem2): the key in sel[0], the rank left among the keys equal to it
+// in sel[1].
 template <int PER, int THREADS>
-__device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
-                                             uint32_t k_rem1, uint32_t *h, uint32_t *scan, uint32_t *sel) {
-  level2_in_registers<PER, THREADS>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
-  const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
+__device__ inline void level3_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t prefix2,
+                                           uint32_t k_rem2, uint32_t *h, uint32_t *scan, uint32_t *sel) {
   __syncthreads();
   for (int b = threadIdx.x; b < kBins23; b += THREADS) h[b] = 0;
   __syncthreads();
@@ -177,6 +177,14 @@ __device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32
   }
   __syncthreads();
   pick_bin<kBins23, kBits23, THREADS>(h, k_rem2, prefix2, scan, sel);
+}
+// Levels 2 and 3.
+template <int PER, int THREADS>
+__device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
+                                             uint32_t k_rem1, uint32_t *h, uint32_t *scan, uint32_t *sel) {
+  level2_in_registers<PER, THREADS>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
+  const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
+  level3_in_registers<PER, THREADS>(bits, cnt, rounds, prefix2, k_rem2, h, scan, sel);
 }
 
 // Chunk (of eight consecutive elements) number c of the sample of a partition sampled every
@@ -419,9 +427,19 @@ __global__ __launch_bounds__(kThreads) void topk_sample_kernel(Geo g, SRC src, u
   level1_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, rank, h, scan, sel);
   const uint32_t b1 = sel[0], k_rem1 = sel[1];
   __syncthreads();
-  // (the lower end of the level-2 bin will do for a guess: it holds a thousandth of an octave)
+  // The lower end of the level-2 bin (1/8192 of an octave of magnitudes) will do for a guess as long as
+  // the bin holds few elements, which the list then takes too.  Magnitudes that lie that close
+  // together would overrun the list and leave the partition to the long form (within 2^-14 of each
+  // other, 1 M elements: 59 us for the call with the third level, 690 us without).
   level2_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, b1, k_rem1, h, scan, sel);
-  if (threadIdx.x == 0) guess[p] = sel[0] << kShift2;
+  const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
+  const uint64_t in_bin = (uint64_t)h[prefix2 & (kBins23 - 1)] * d;   // times m: elements of the partition
+  if (in_bin <= (uint64_t)kFewInBin * m) {   // (uniform)
+    if (threadIdx.x == 0) guess[p] = prefix2 << kShift2;
+    return;
+  }
+  level3_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, prefix2, k_rem2, h, scan, sel);
+  if (threadIdx.x == 0) guess[p] = sel[0];
 }
 
 template <class SRC, class = void>

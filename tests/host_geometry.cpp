@@ -31,4 +31,7 @@ void geo_block_tiles(uint64_t lo, uint64_t hi, uint64_t D, uint64_t *t0, uint64_
   *t0 = t.t0;
   *n = t.n;
 }
+// Byte offset in a workspace of the selection state of a top-k call: eight words a partition, the second
+// of them non-zero where the partition was left to the long form.
+uint64_t geo_topk_state(const bpc_params_t *p, uint64_t D) { return bpc::ws_layout(p, D).state; }
 }

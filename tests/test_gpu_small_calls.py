@@ -167,3 +167,44 @@ def test_fp16_with_the_most_runs_in_one_launch(gu, orc, n, dtype, pe):
     orc.adaptive_update_bypass(po, mask, out_ref, D, x, m, v, orc.make_opt(orc.OPT_ADAM, *hyper))
     for a, b in ((dx, x), (dm, m), (dv, v)):
         assert np.array_equal(gu.to_host(a), b)
+
+
+def _long_form(gu, geo, prm, D, ws):
+    """Which partitions of the last top-k call on `ws` were left to the long form."""
+    at = int(geo.geo_topk_state(ctypes.byref(prm), D))
+    words = gu.to_host(ws[at:at + 32 * -(-D // prm.part_elems)]).view(np.uint32).reshape(-1, 8)
+    return words[:, 1] != 0
+
+
+@pytest.mark.parametrize("kind,n", [("topk", 1), ("topk16", 1), ("topk", 3)])
+@pytest.mark.parametrize("pe,D", [(65536, 5 * 65536 + 40_001), (1_048_576, 1_048_576 + 300_007)])
+def test_topk_of_magnitudes_close_together_stays_on_the_short_list(gu, orc, geo, kind, n, pe, D):
+    """Magnitudes within 2^-14 of each other share one bin of the first two radix levels, with far more
+    of them in it than the short list holds; the guess then goes down to the key itself."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=0.01)
+    rs = np.random.default_rng(D + n)
+    v = ((1.0 + rs.random(D) * 2.0 ** -14) * rs.choice([-1.0, 1.0], D)).astype(np.float32)
+    keys = v.view(np.uint32) & 0x7fffffff
+    assert np.unique(keys >> 10).size <= 2 and pe > 32768
+    ws = gu.new_ws(pb, D, n)
+    res = np.zeros(D, np.float32)
+    pay = gu.new_payload(pb, D)
+    rd = gu.to_dev(res)
+    if n == 1:
+        ref = orc.compress(po, v, res)
+        bpc.bpc_compress(pb, gu.to_dev(v), rd, pay, ws)
+    else:   # server: everything but the last bits of Delta comes from the residual
+        res = v.copy()
+        rd = gu.to_dev(res)
+        zero = orc.compress(po, np.zeros(D, np.float32), None)
+        ref = orc.server_aggregate([po] * n, [zero] * n, po, res, D)
+        bpc.bpc_server_aggregate([pb] * n, [gu.to_dev(zero)] * n, pb, rd, D, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+    stride = orc.partition_stride(po)
+    got = gu.to_host(pay)
+    for p in range(-(-D // pe)):
+        k = max(1, int(0.01 * min(pe, D - p * pe)))
+        assert np.array_equal(got[p * stride:p * stride + 16 + 4 * k], ref[p * stride:p * stride + 16 + 4 * k]), p
+    assert not _long_form(gu, geo, pb, D, ws).any()

@@ -1,28 +1,9 @@
 """The index arithmetic of csrc/geometry.hpp, compiled for the host: what the kernels read and write
 stays inside the buffers they are given."""
 import ctypes as C
-import os
-import subprocess
 
 import numpy as np
 import pytest
-
-HERE = os.path.dirname(os.path.abspath(__file__))
-
-
-@pytest.fixture(scope="module")
-def geo(tmp_path_factory):
-    so = str(tmp_path_factory.mktemp("geo") / "host_geometry.so")
-    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-shared", "-fPIC", "-o", so,
-                    os.path.join(HERE, "host_geometry.cpp")], check=True)
-    L = C.CDLL(so)
-    for name, args, res in [("geo_tiles", [C.c_uint64], C.c_uint32), ("geo_tile_elems", [], C.c_uint32),
-                            ("geo_row_elems", [], C.c_uint32), ("geo_row_in_record", [C.c_uint32, C.c_uint64], C.c_uint32),
-                            ("geo_lans_tile", [], C.c_uint32), ("geo_find_block", [C.c_void_p, C.c_uint64, C.c_uint64], C.c_int64),
-                            ("geo_tile_edge", [C.c_uint64, C.c_uint64], C.c_uint64),
-                            ("geo_block_tiles", [C.c_uint64, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p], None)]:
-        getattr(L, name).argtypes, getattr(L, name).restype = args, res
-    return L
 
 
 # kind, levels -> (elements a read covers, its bytes); the nibble kinds are read as 32-bit words by
