@@ -132,7 +132,8 @@ struct WsLayout {
                      // slot is non-zero if a single-pass kernel of that run gave up waiting
   size_t tickets;    // u32 at every kTicketStride bytes, kTicketClasses of them: the ticket counters of the
                      // ticketed single-pass kernels
-  size_t partials;   // double[n_tiles]: per-tile partial norms
+  size_t partials;   // double[n_tiles]: per-tile partial norms (LANS with caller-defined blocks: a word for
+                     // every tile of kSTile, its first block)
   size_t dense;      // float[D]: q / Delta / decoded message when no caller buffer can hold it
   size_t hist;       // u32[P*kTopkHistWords]: top-k radix histograms (2048 + 1024 + 1024 bins)
   size_t state;      // u32[P*8 + 8]: top-k selection state; a barrier counter

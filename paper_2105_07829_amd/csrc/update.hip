@@ -737,42 +737,33 @@ __global__ __launch_bounds__(kThreads) void lans_apply_kernel(Geo g, DEC dec, fl
 // LANS with caller-defined blocks (Algorithm 5 normalises over layers G_b): two streaming passes.
 //
 //   norms  : reads m, v, x and the message, writes the new m and v, and leaves the three sums of
-//            squares of every (tile, block) pair
-//   totals : adds the pairs of each block that reaches beyond a tile up, in tile order, and turns
-//            them into the block's phi and two weights
-//   step   : reads the new m and v, x and the message again and writes x
+//            squares of every (tile, block) pair; a tile whose blocks all lie inside it has its x
+//            written here, too
+//   totals : adds the pairs of each block that reaches beyond a tile up and turns them into the
+//            block's phi and two weights
+//   step   : reads the new m and v, x and the message again and writes x (the other tiles)
 //
 // A tile is 8192 elements, 512 threads with four rows of four elements each, one workgroup a tile,
 // so nothing waits for anything inside a kernel.  Walking the pairs in element order, every step
 // raises the tile or the block or both, so pair (t, b) owns the three doubles at t + b and no
 // table of places is needed; a block that lies inside a tile is finished by the norms pass, which
 // puts its phi and weights (three floats) where the sums would go, and the totals pass does the
-// same at the first pair of each of the others.
-// What bounds it: memory, 20.5 + 16.5 bytes an element with a 4-bit message.  The form before this
-// kept a tile's x and directions in registers until its blocks were complete (24.5 bytes where
-// that worked, 16.5 more for the tiles of blocks over 2 M elements) with one workgroup of 1024
-// threads a CU and block totals exchanged inside the kernel: 33 bytes an element on average, but
-// at 3.7 TB/s.  Layer-shaped blocks, 336 M elements: 2.67 -> 2.08 ms (norms 1.14 ms at 6.1 TB/s, totals
-// 0.01 ms, step 0.89 ms at 6.2 TB/s).
+// same at the first pair of each of the others.  The first block of every tile, which the norms pass
+// has searched, is kept for the step pass; that word says as well that the tile is done.
+// The blocks of a tile go in batches: each wave sums those of its rows that a block reaches, and one
+// barrier later the waves' sums of all blocks of the batch are added up side by side.
+// What bounds it: memory, 20.5 + 16.5 bytes an element with a 4-bit message, 24.5 where the blocks
+// lie inside tiles (counters: 37.04 with layers).  Layer-shaped blocks, 336 M elements: norms 1.10 ms
+// at 6.3 TB/s, totals 0.01, step 0.92 ms at 6.1 TB/s, 2.06 ms the call.  100 M elements in blocks of
+// 8192 / 1024 / 256: 418 / 450 / 898 us; one block at a time with barriers of its own and x in the
+// second pass only it was 631 / 872 / 2001.  (The form that kept a tile's x and directions in
+// registers until its blocks were complete, one workgroup of 1024 threads a CU and block totals
+// exchanged inside the kernel, took 2.67 ms over the layers and 527 / 972 / 2268 us.)
 constexpr int kBThreads = 512;
 constexpr int kBPer = kSTile / kBThreads;   // 16
 constexpr int kBRows = kBPer / 4;
 constexpr int kBRow = kBThreads * 4;
-
-// The block that holds element i: the last one that starts at or before it.  One wave, 64 bounds
-// at a time (every wave of a workgroup does it for itself: one or two loads for the usual number
-// of layers, under way together with the tile's loads).
-__device__ inline uint32_t find_block_wave(const uint64_t *offs, uint64_t n_blocks, uint64_t i) {
-  const uint32_t lane = threadIdx.x & 63;
-  uint64_t lo = 0, n = n_blocks;   // the answer is in [lo, lo + n)
-  while (n > 1) {
-    const uint64_t stride = (n + 63) / 64;
-    const bool in = lane * stride < n;
-    const uint64_t off = offs[lo + (in ? lane * stride : 0)];
-    narrow_blocks((uint32_t)__popcll(__ballot(in && off <= i)), stride, &lo, &n);
-  }
-  return __builtin_amdgcn_readfirstlane((uint32_t)lo);
-}
+constexpr uint32_t kTileDone = 0xffffffffu;   // in place of a tile's first block: the norms pass has written its x
 
 struct LansOut { float xs[kBPer], ur[kBPer], uc[kBPer]; };
 template <class DEC>
@@ -820,56 +811,137 @@ __device__ __forceinline__ float wave_sum_f32_last(float x) {
   return x;
 }
 
-// The three sums of squares over those of the tile's elements whose position lies in [lo, hi):
-// eight elements of a thread and the 64 threads of a wave in f32 (512 squares; the same partial
-// sums as the one-pass kernel above), everything beyond that in f64.  Result in threads 0..2 (thread
-// k: the k-th sum); contains two barriers.
-template <bool ALL>
-__device__ __forceinline__ double lans_tile_sum(const LansOut &h, uint32_t lo, uint32_t hi, double *red) {
-  constexpr int kWaves = kBThreads / 64;
-  float f[2][3];
-#pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    float f_x = 0.0f, f_r = 0.0f, f_c = 0.0f;
-#pragma unroll
-    for (int e = half * (kBPer / 2); e < (half + 1) * (kBPer / 2); ++e) {
-      const uint32_t pos = (uint32_t)(e / 4 * kBRow) + threadIdx.x * 4 + e % 4;
-      const bool in = ALL || (pos >= lo && pos < hi);
-      f_x = in ? fmaf(h.xs[e], h.xs[e], f_x) : f_x;
-      f_r = in ? fmaf(h.ur[e], h.ur[e], f_r) : f_r;
-      f_c = in ? fmaf(h.uc[e], h.uc[e], f_c) : f_c;
-    }
-    f[half][0] = wave_sum_f32_last(f_x);
-    f[half][1] = wave_sum_f32_last(f_r);
-    f[half][2] = wave_sum_f32_last(f_c);
+// The blocks that meet a tile, in every wave: lane l of a window holds the offset lo + l (or the last
+// one), block number lo + first is the first that meets the tile, and `n` of them from there on are at
+// hand, at most kBatch.
+constexpr uint32_t kBatch = 32;
+struct BlockBatch {
+  uint64_t b;        // number of the first
+  uint32_t n;
+  uint32_t first, cap, rel;   // lane of the first; how many this window could hold; lane: the block's first element in the tile
+  uint64_t inside;   // bit q: block b + q lies inside the tile
+  __device__ uint32_t lo(uint32_t q) const { return __builtin_amdgcn_readlane(rel, first + q); }
+  __device__ uint32_t hi(uint32_t q) const { return __builtin_amdgcn_readlane(rel, first + q + 1); }
+};
+// Lane l's bound of a step of the search among the n blocks from lo.
+__device__ __forceinline__ uint64_t block_bound(const OptArgs &o, uint64_t lo, uint64_t n) {
+  const uint64_t k = lo + (threadIdx.x & 63) * ((n + 63) / 64);
+  return o.block_offsets[k < o.n_blocks ? k : o.n_blocks];
+}
+// `off`: the window's offsets (stride 1 from lo), `first` the lane of block b = lo + first.
+__device__ __forceinline__ BlockBatch block_batch(const OptArgs &o, uint64_t off, uint64_t lo, uint32_t first, const LansTile &t, uint64_t D) {
+  const uint32_t lane = threadIdx.x & 63;
+  const uint64_t tile_first = t.base, tile_end = t.base + t.valid, edge = tile_edge(tile_end, D);
+  BlockBatch r;
+  r.b = lo + first;
+  r.first = first;
+  r.cap = 63 - first < kBatch ? 63 - first : kBatch;
+  const uint64_t at = off > tile_first ? off : tile_first;
+  r.rel = (uint32_t)((at < tile_end ? at : tile_end) - tile_first);
+  const uint64_t meets = __ballot(lane - first < r.cap && lo + lane < o.n_blocks && off < tile_end);
+  r.n = (uint32_t)__builtin_ctzll(~(meets >> first));
+  r.inside = (__ballot(off >= tile_first) & (__ballot(off <= edge) >> 1)) >> first;
+  return r;
+}
+// The first batch of a tile: the last block that starts at or before the tile's first element and those
+// after it.  64 bounds at a time; `off` = block_bound(o, 0, n_blocks), requested before the tile's loads (one
+// more step for more than 64 blocks, two for more than 4096).
+__device__ __forceinline__ BlockBatch block_search(const OptArgs &o, uint64_t off, const LansTile &t, uint64_t D) {
+  uint64_t lo = 0, n = o.n_blocks;   // the answer is in [lo, lo + n)
+  for (;;) {
+    const uint64_t stride = (n + 63) / 64, from = lo;
+    narrow_blocks((uint32_t)__popcll(__ballot((threadIdx.x & 63) * stride < n && off <= t.base)), stride, &lo, &n);
+    if (stride == 1) return block_batch(o, off, from, __builtin_amdgcn_readfirstlane((uint32_t)(lo - from)), t, D);
+    off = block_bound(o, lo, n);
   }
-  __syncthreads();   // (red of the block before has been read)
+}
+// The batch after one that was full.
+__device__ __forceinline__ BlockBatch block_next(const OptArgs &o, uint64_t b, const LansTile &t, uint64_t D) {
+  return block_batch(o, block_bound(o, b, 1), b, 0, t, D);
+}
+// Rows of a wave that a block [lo, hi) of the tile reaches, one call of fn(u, whole) each, `whole` where
+// all of the wave's elements of the row belong to it (the same in every lane).
+template <class FN>
+__device__ __forceinline__ void for_rows(uint32_t lo, uint32_t hi, FN fn) {
+  const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 256;
+#pragma unroll
+  for (int u = 0; u < kBRows; ++u) {
+    const uint32_t r0 = u * kBRow + w0, r1 = r0 + 256;
+    if (lo <= r0 && hi >= r1) fn(u, true);
+    else if (lo < r1 && hi > r0) fn(u, false);
+  }
+}
+__device__ __forceinline__ bool in_block(int u, int c, uint32_t lo, uint32_t hi) {
+  const uint32_t pos = (uint32_t)(u * kBRow + c) + threadIdx.x * 4;
+  return pos >= lo && pos < hi;
+}
+
+// A wave's three sums of squares over its elements of the block [lo, hi), to red[0..2]: eight elements of
+// a thread and the 64 threads in f32 (512 squares; the same partial sums as the one-pass kernel above),
+// everything beyond that in f64.
+__device__ __forceinline__ void lans_wave_sums(const LansOut &h, uint32_t lo, uint32_t hi, double *red) {
+  float f[2][3] = {{0.0f, 0.0f, 0.0f}, {0.0f, 0.0f, 0.0f}};
+  bool any = false;
+  for_rows(lo, hi, [&](int u, bool whole) {
+    any = true;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int e = 4 * u + c;
+      float *s = f[u / 2];
+      const bool in = whole || in_block(u, c, lo, hi);
+      s[0] = in ? fmaf(h.xs[e], h.xs[e], s[0]) : s[0];
+      s[1] = in ? fmaf(h.ur[e], h.ur[e], s[1]) : s[1];
+      s[2] = in ? fmaf(h.uc[e], h.uc[e], s[2]) : s[2];
+    }
+  });
+  if (any) {   // (uniform)
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      f[0][k] = wave_sum_f32_last(f[0][k]);
+      f[1][k] = wave_sum_f32_last(f[1][k]);
+    }
+  }
   if ((threadIdx.x & 63) == 63) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) red[3 * (threadIdx.x >> 6) + k] = (double)f[0][k] + (double)f[1][k];
+    for (int k = 0; k < 3; ++k) red[k] = (double)f[0][k] + (double)f[1][k];
   }
-  __syncthreads();
-  double s = 0.0;
-  if (threadIdx.x < 3) {
+}
+// The step of the elements of block [lo, hi): x in place.
+__device__ __forceinline__ void lans_step_rows(LansOut &h, uint32_t lo, uint32_t hi, float lr, float phi, float w_r, float w_c) {
+  const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 256;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) s += red[3 * w + threadIdx.x];
+  for (int u = 0; u < kBRows; ++u) {
+    if (lo < u * kBRow + w0 + 256 && hi > u * kBRow + w0) {   // (uniform)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int e = 4 * u + c;
+        const float dir = phi * (w_r * h.ur[e] + w_c * h.uc[e]);
+        h.xs[e] = in_block(u, c, lo, hi) ? h.xs[e] - lr * dir : h.xs[e];
+      }
+    }
   }
-  return s;
+}
+__device__ __forceinline__ void lans_store_x(const LansTile &t, const LansOut &h, float *x) {
+#pragma unroll
+  for (int u = 0; u < kBRows; ++u)
+    row_buf(x + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(h.xs[4 * u], h.xs[4 * u + 1], h.xs[4 * u + 2], h.xs[4 * u + 3]), threadIdx.x * 16);
 }
 
 template <class DEC>
-__global__ __launch_bounds__(kBThreads) void lans_norms_kernel(Geo g, ClusterGeo cg, DEC dec, const float *x, float *m, float *v,
-                                                              OptArgs o, double *pairs) {
+__global__ __launch_bounds__(kBThreads, 4) void lans_norms_kernel(Geo g, ClusterGeo cg, DEC dec, float *x, float *m, float *v,
+                                                              OptArgs o, double *pairs, uint32_t *first_block) {
+  constexpr int kWaves = kBThreads / 64;
   __shared__ __align__(16) float lds[DEC::kLdsFloats];
-  __shared__ double red[3 * (kBThreads / 64)];
-  __shared__ double tot[3];
+  __shared__ double red[kBatch][kWaves][3], tot[kBatch][3];
+  __shared__ float wts[kBatch][3];
   if (blockIdx.x == 0 && threadIdx.x == 0) o.status[0] = 0;   // no wait in this call
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x);
   const LansTile t = lans_tile(g, cg, item);
+  const uint64_t bound = block_bound(o, 0, o.n_blocks);
   LansIn<DEC> in;
   lans_request(g, dec, t, x, m, v, in);
-  const uint64_t tile_first = (uint64_t)item * kSTile, tile_end = tile_first + t.valid;
-  const uint32_t b0 = find_block_wave(o.block_offsets, o.n_blocks, tile_first);
+  BlockBatch blk = block_search(o, bound, t, g.D);
+  const uint32_t b0 = (uint32_t)blk.b;
   const float hdr = lans_tables(dec, t, lds);
   const float omb1 = 1.0f - o.beta1, omb2 = 1.0f - o.beta2;
   const float inv_bc1 = 1.0f / o.bc1, inv_bc2 = 1.0f / o.bc2;
@@ -891,68 +963,130 @@ __global__ __launch_bounds__(kBThreads) void lans_norms_kernel(Geo g, ClusterGeo
     row_buf(m + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(mo[0], mo[1], mo[2], mo[3]), threadIdx.x * 16);
     row_buf(v + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(vo[0], vo[1], vo[2], vo[3]), threadIdx.x * 16);
   }
-  const uint64_t edge = tile_edge(tile_end, g.D);
+  bool done = true;   // every block so far lies inside the tile: its elements' steps are made
 #pragma unroll 1
-  for (uint64_t b = b0; b < o.n_blocks; ++b) {
-    const uint64_t lo = uniform_off(o.block_offsets[b]), hi = uniform_off(o.block_offsets[b + 1]);
-    if (lo >= tile_end) break;
-    const uint32_t rlo = (uint32_t)((lo > tile_first ? lo : tile_first) - tile_first);
-    const uint32_t rhi = (uint32_t)((hi < tile_end ? hi : tile_end) - tile_first);
-    const double s = rlo == 0 && rhi == (uint32_t)kSTile ? lans_tile_sum<true>(h, rlo, rhi, red) : lans_tile_sum<false>(h, rlo, rhi, red);
-    double *pair = pairs + 3 * (item + b);
-    if (lo < tile_first || hi > edge) {
-      if (threadIdx.x < 3) pair[threadIdx.x] = s;
-    } else {
-      if (threadIdx.x < 3) tot[threadIdx.x] = s;
-      __syncthreads();
-      if (threadIdx.x == 0) lans_weights(o, tot[0], tot[1], tot[2], reinterpret_cast<float *>(pair));
+  for (;;) {
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll 1
+    for (uint32_t q = 0; q < blk.n; ++q) lans_wave_sums(h, blk.lo(q), blk.hi(q), red[q][wave]);
+    __syncthreads();
+    double *pair = pairs + 3 * (item + blk.b);
+    const uint64_t all = (1ull << blk.n) - 1, inside = blk.inside & all;
+    if (threadIdx.x < 3 * blk.n) {   // thread 3 q + k: the k-th sum of block q
+      const uint32_t q = threadIdx.x / 3, k = threadIdx.x - 3 * q;
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) s += red[q][w][k];
+      if ((inside >> q) & 1) tot[q][k] = s;
+      else pair[threadIdx.x] = s;
     }
+    done = done && inside == all;
+    if (inside) {
+      __syncthreads();
+      if (threadIdx.x < blk.n && ((inside >> threadIdx.x) & 1)) {
+        const uint32_t q = threadIdx.x;
+        lans_weights(o, tot[q][0], tot[q][1], tot[q][2], wts[q]);
+        float *w = reinterpret_cast<float *>(pair + 3 * q);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = wts[q][k];
+      }
+      if (done) {
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t q = 0; q < blk.n; ++q) lans_step_rows(h, blk.lo(q), blk.hi(q), o.lr, wts[q][0], wts[q][1], wts[q][2]);
+      }
+    }
+    if (blk.n < blk.cap) break;
+    blk = block_next(o, blk.b + blk.n, t, g.D);
+    __syncthreads();   // (red, tot and wts have been read)
   }
+  if (done) lans_store_x(t, h, x);
+  if (threadIdx.x == 0) first_block[item] = done ? kTileDone : b0;
 }
 
 // phi and weights of the blocks that reach beyond a tile.  A workgroup looks at `chunk` blocks at a
-// time (one for the usual number of layers, so that every block has a workgroup; up to 64 where
-// there are many, most of which lie inside a tile and need nothing here).
+// time (one up to 256 blocks, at most 64; where there are many, most lie inside a tile and need
+// nothing here).  Blocks of up to kTotWave tiles are a wave's each, longer ones the workgroup's.
 constexpr int kTotThreads = 1024;
-constexpr uint32_t kTotGrid = 1024;
+constexpr uint32_t kTotGrid = 256;
+constexpr uint32_t kTotWave = 256;
 __global__ __launch_bounds__(kTotThreads) void lans_totals_kernel(OptArgs o, uint64_t D, double *pairs, uint32_t chunk) {
-  __shared__ double red[kTotThreads / 64];
+  constexpr int kWaves = kTotThreads / 64;
+  __shared__ double red[kWaves][3];
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  // sums over the pairs k = from, from + step, ... of n, then over the wave
+  auto sums = [](const double *first, uint32_t n, uint32_t from, uint32_t step, double a[3]) {
+    a[0] = a[1] = a[2] = 0.0;
+    for (uint32_t k = from; k < n; k += step) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) a[c] += first[3 * (uint64_t)k + c];
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) a[c] = wave_sum(a[c]);
+  };
   for (uint64_t c0 = (uint64_t)blockIdx.x * chunk; c0 < o.n_blocks; c0 += (uint64_t)gridDim.x * chunk) {
-    const uint64_t mine = c0 + (threadIdx.x & 63);
-    bool far = false;
-    if ((threadIdx.x & 63) < chunk && mine < o.n_blocks) far = block_tiles(o.block_offsets[mine], o.block_offsets[mine + 1], D).n > 1;
-    unsigned long long todo = __ballot(far);   // (the same in every wave)
-    while (todo) {
-      const uint64_t b = c0 + (uint32_t)__builtin_ctzll(todo);
-      todo &= todo - 1;
-      const BlockTiles t = block_tiles(uniform_off(o.block_offsets[b]), uniform_off(o.block_offsets[b + 1]), D);
-      double *first = pairs + 3 * (t.t0 + b);
-      const uint32_t n = (uint32_t)t.n;
-      double a0 = 0.0, a1 = 0.0, a2 = 0.0;
-      for (uint32_t k = threadIdx.x; k < n; k += kTotThreads) {
-        a0 += first[3 * (uint64_t)k];
-        a1 += first[3 * (uint64_t)k + 1];
-        a2 += first[3 * (uint64_t)k + 2];
+    const uint64_t mine = c0 + lane;
+    BlockTiles bt{0, 0};
+    if (lane < chunk && mine < o.n_blocks) bt = block_tiles(o.block_offsets[mine], o.block_offsets[mine + 1], D);
+    const uint32_t t0 = (uint32_t)bt.t0, n_mine = (uint32_t)bt.n;
+    auto block = [&](uint32_t q) { return pairs + 3 * (c0 + q + __builtin_amdgcn_readlane(t0, q)); };
+    double a[3];
+    uint32_t turn = 0;
+    for (uint64_t todo = __ballot(n_mine > 1 && n_mine <= kTotWave); todo; todo &= todo - 1, ++turn) {
+      if (turn % kWaves != wave) continue;
+      const uint32_t q = (uint32_t)__builtin_ctzll(todo);
+      double *first = block(q);
+      sums(first, __builtin_amdgcn_readlane(n_mine, q), lane, 64, a);
+      if (lane == 0) lans_weights(o, a[0], a[1], a[2], reinterpret_cast<float *>(first));
+    }
+    for (uint64_t todo = __ballot(n_mine > kTotWave); todo; todo &= todo - 1) {   // (the same in every wave)
+      const uint32_t q = (uint32_t)__builtin_ctzll(todo);
+      double *first = block(q);
+      sums(first, __builtin_amdgcn_readlane(n_mine, q), threadIdx.x, kTotThreads, a);
+      if (lane == 0) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) red[wave][c] = a[c];
       }
-      const double t0 = block_sum<kTotThreads>(a0, red);
-      const double t1 = block_sum<kTotThreads>(a1, red);
-      const double t2 = block_sum<kTotThreads>(a2, red);
-      // (every thread has read its pairs before the barriers of the sums)
-      if (threadIdx.x == 0) lans_weights(o, t0, t1, t2, reinterpret_cast<float *>(first));
+      __syncthreads();   // (and every pair of the block has been read)
+      if (threadIdx.x == 0) {
+        double s[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w)
+#pragma unroll
+          for (int c = 0; c < 3; ++c) s[c] += red[w][c];
+        lans_weights(o, s[0], s[1], s[2], reinterpret_cast<float *>(first));
+      }
+      __syncthreads();
     }
   }
 }
 
 template <class DEC>
-__global__ __launch_bounds__(kBThreads) void lans_step_kernel(Geo g, ClusterGeo cg, DEC dec, float *x, const float *m,
-                                                             const float *v, OptArgs o, const double *pairs) {
+__global__ __launch_bounds__(kBThreads, 4) void lans_step_kernel(Geo g, ClusterGeo cg, DEC dec, float *x, const float *m,
+                                                             const float *v, OptArgs o, const double *pairs,
+                                                             const uint32_t *first_block) {
   __shared__ __align__(16) float lds[DEC::kLdsFloats];
   const uint32_t item = __builtin_amdgcn_readfirstlane(blockIdx.x);
+  const uint32_t b0 = __builtin_amdgcn_readfirstlane(first_block[item]);
+  if (b0 == kTileDone) return;
   const LansTile t = lans_tile(g, cg, item);
+  const uint64_t bound = block_bound(o, b0, 1);
   LansIn<DEC> in;
   lans_request(g, dec, t, x, m, v, in);
-  const uint64_t tile_first = (uint64_t)item * kSTile, tile_end = tile_first + t.valid;
-  const uint32_t b0 = find_block_wave(o.block_offsets, o.n_blocks, tile_first);
+  BlockBatch blk = block_batch(o, bound, b0, 0, t, g.D);
+  // lane q of a batch: phi and weights of its q-th block, which stand at the block's first pair
+  float w[3];
+  auto weights = [&](uint64_t off) {
+    const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) w[k] = 0.0f;
+    if (lane < blk.n) {
+      const float *at = reinterpret_cast<const float *>(pairs + 3 * (off / kSTile + blk.b + lane));
+#pragma unroll
+      for (int k = 0; k < 3; ++k) w[k] = at[k];
+    }
+  };
+  weights(bound);
   const float hdr = lans_tables(dec, t, lds);
   const float inv_bc1 = 1.0f / o.bc1, inv_bc2 = 1.0f / o.bc2;
   LansOut h;
@@ -970,27 +1104,19 @@ __global__ __launch_bounds__(kBThreads) void lans_step_kernel(Geo g, ClusterGeo 
                   &h.ur[4 * u + c], &h.uc[4 * u + c]);
     }
   }
-  float xo[kBPer];
-#pragma unroll
-  for (int e = 0; e < kBPer; ++e) xo[e] = h.xs[e];
 #pragma unroll 1
-  for (uint64_t b = b0; b < o.n_blocks; ++b) {
-    const uint64_t lo = uniform_off(o.block_offsets[b]), hi = uniform_off(o.block_offsets[b + 1]);
-    if (lo >= tile_end) break;
-    const uint32_t rlo = (uint32_t)((lo > tile_first ? lo : tile_first) - tile_first);
-    const uint32_t rhi = (uint32_t)((hi < tile_end ? hi : tile_end) - tile_first);
-    const float *w = reinterpret_cast<const float *>(pairs + 3 * (lo / kSTile + b));
-    const float phi = uniform_load(w), w_r = uniform_load(w + 1), w_c = uniform_load(w + 2);
-#pragma unroll
-    for (int e = 0; e < kBPer; ++e) {
-      const uint32_t pos = (uint32_t)(e / 4 * kBRow) + threadIdx.x * 4 + e % 4;
-      const float dir = phi * (w_r * h.ur[e] + w_c * h.uc[e]);
-      xo[e] = pos >= rlo && pos < rhi ? h.xs[e] - o.lr * dir : xo[e];
+  for (;;) {
+#pragma unroll 1
+    for (uint32_t q = 0; q < blk.n; ++q) {
+      auto of = [&](float a) { return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(a), q)); };
+      lans_step_rows(h, blk.lo(q), blk.hi(q), o.lr, of(w[0]), of(w[1]), of(w[2]));
     }
+    if (blk.n < blk.cap) break;
+    const uint64_t b = blk.b + blk.n, off = block_bound(o, b, 1);
+    blk = block_batch(o, off, b, 0, t, g.D);
+    weights(off);
   }
-#pragma unroll
-  for (int u = 0; u < kBRows; ++u)
-    row_buf(x + t.base, t.valid, u * kBRow, kBRow).store16<kNonTemporal>(as_u32x4(xo[4 * u], xo[4 * u + 1], xo[4 * u + 2], xo[4 * u + 3]), threadIdx.x * 16);
+  lans_store_x(t, h, x);
 }
 
 // LANS with caller-defined blocks.  *used = false: shape not supported (tiles that cross
@@ -1009,9 +1135,10 @@ static hipError_t run_lans_blocks(const Geo &g, DEC dec, float *x, float *m, flo
   const uint64_t per = cdiv(o.n_blocks, kTotGrid);
   const uint32_t chunk = per < 64 ? (uint32_t)per : 64u;
   const uint64_t chunks = cdiv(o.n_blocks, chunk);
-  lans_norms_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs);
+  uint32_t *first_block = ws.at<uint32_t>(ws.lay.partials);   // a word a tile (the region has two doubles)
+  lans_norms_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs, first_block);
   lans_totals_kernel<<<chunks < kTotGrid ? (uint32_t)chunks : kTotGrid, kTotThreads, 0, stream>>>(o, g.D, pairs, chunk);
-  lans_step_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs);
+  lans_step_kernel<DEC><<<cg.n_items, kBThreads, 0, stream>>>(g, cg, dec, x, m, v, o, pairs, first_block);
   return hipGetLastError();
 }
 

@@ -9,21 +9,19 @@ uint32_t geo_row_elems() { return bpc::kThreads * 4; }
 uint32_t geo_row_in_record(uint32_t row0, uint64_t part_elems) { return bpc::row_in_record(row0, part_elems); }
 
 uint32_t geo_lans_tile() { return bpc::kSTile; }
-// The wave's block search (64 bounds at a time); -1 if it looks outside the n_blocks + 1 offsets.
+// The wave's block search: 64 bounds at a time, those past the last offset clamped to it.
 int64_t geo_find_block(const uint64_t *offs, uint64_t n_blocks, uint64_t i) {
   uint64_t lo = 0, n = n_blocks;
-  while (n > 1) {
+  for (;;) {
     const uint64_t stride = (n + 63) / 64;
     uint32_t c = 0;
-    for (uint32_t lane = 0; lane < 64; ++lane) {
-      const bool in = lane * stride < n;
-      const uint64_t at = lo + (in ? lane * stride : 0);
-      if (at > n_blocks) return -1;
-      c += in && offs[at] <= i;
+    for (uint64_t lane = 0; lane < 64; ++lane) {
+      const uint64_t k = lo + lane * stride;
+      c += lane * stride < n && offs[k < n_blocks ? k : n_blocks] <= i;
     }
     bpc::narrow_blocks(c, stride, &lo, &n);
+    if (stride == 1) return (int64_t)lo;
   }
-  return (int64_t)lo;
 }
 uint64_t geo_tile_edge(uint64_t tile_end, uint64_t D) { return bpc::tile_edge(tile_end, D); }
 void geo_block_tiles(uint64_t lo, uint64_t hi, uint64_t D, uint64_t *t0, uint64_t *n) {

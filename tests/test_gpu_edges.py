@@ -548,3 +548,50 @@ def test_lans_blocks_at_the_edges_of_tiles_and_of_the_block_search(gu, orc, kind
         assert np.array_equal(mg.view(np.uint32), m.view(np.uint32))
         assert np.array_equal(vg.view(np.uint32), v.view(np.uint32))
     assert gu.lans_step_close(xg, x, x0, blocks)
+
+
+@pytest.mark.parametrize("kind", ["dither", "fp16", "topk16"])
+@pytest.mark.parametrize("shape", ["around_a_batch", "sixty_four", "tiles_of_a_wave"])
+def test_lans_blocks_at_the_edges_of_batches_windows_and_totals(gu, orc, kind, shape):
+    """The passes look at 32 blocks of a tile at a time, out of windows of 64 offsets, write x in the first
+    pass where all of a tile's blocks lie inside it, and add the pairs of up to 256 tiles up in a
+    wave: tiles of 31, 32, 33, 64 and 65 blocks, closed ones and ones whose first or last block reaches
+    out; 64 blocks, the last over several tiles (its window ends with it); blocks of 256 and 257 tiles."""
+    import torch
+    bpc = gu.bpc
+    pe, T = 65536, 8192
+
+    def tile(t, n, lo=0, hi=T):   # n blocks of tile t, from lo to hi in it
+        return [t * T + lo + i * (hi - lo) // n for i in range(n)]
+
+    if shape == "around_a_batch":
+        offs = []
+        for t, n in enumerate((31, 32, 33, 64, 65, 1)):   # closed
+            offs += tile(t, n)
+        offs += tile(6, 32, 0, 8000)[:-1]                 # its last block reaches into tile 7
+        offs += tile(7, 31, 300) + tile(8, 32)            # tile 7: its first block comes from tile 6
+        offs += tile(9, 32, 5) + tile(10, 33, 5)          # blocks across both ends
+        offs += [11 * T + 5, 14 * T, 14 * T + 1, 16 * T - 1, 16 * T + 100]
+    elif shape == "sixty_four":
+        offs = tile(0, 60) + [T, T + 9, T + 100, T + 101, 4 * T + 777]
+    else:
+        offs = [0, 3, 3 + 255 * T + 10, 600 * T - 8, 600 * T - 8 + 255 * T + 9, 860 * T]
+    blocks = np.array(offs, dtype=np.uint64)
+    assert blocks[0] == 0 and np.all(np.diff(blocks.astype(np.int64)) > 0)
+    assert shape != "sixty_four" or len(blocks) == 65
+    D = int(blocks[-1])
+    po, pb = gu.both_params(orc, kind, pe, **KW.get(kind, {}))
+    rs = np.random.default_rng(91)
+    payload = orc.compress(po, (rs.standard_t(3.0, D) * 1e-2).astype(np.float32), None)
+    x0 = (rs.standard_normal(D) * 0.02).astype(np.float32)
+    m0 = (rs.standard_normal(D) * 1e-3).astype(np.float32)
+    v0 = (rs.random(D) * 1e-5).astype(np.float32)
+    oo = orc.make_opt(orc.OPT_LANS, 0.5, 0.9, 0.999, 1e-8, 0.01, 4, block_offsets=blocks)
+    ob = bpc.make_opt(bpc.OPT_LANS, 0.5, 0.9, 0.999, 1e-8, 0.01, 4,
+                      block_offsets=torch.from_numpy(blocks.astype(np.int64)).to(gu.DEV))
+    x, m, v = x0.copy(), m0.copy(), v0.copy()
+    orc.adaptive_update(po, payload, D, x, m, v, oo)
+    xg, mg, vg = gu.gpu_update(pb, payload, x0, m0, v0, ob)
+    assert np.array_equal(mg.view(np.uint32), m.view(np.uint32))
+    assert np.array_equal(vg.view(np.uint32), v.view(np.uint32))
+    assert gu.lans_step_close(xg, x, x0, blocks)
