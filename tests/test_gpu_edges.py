@@ -484,11 +484,10 @@ def test_fp16_server_forms_and_ragged_ends(gu, orc, n, ef):
 @pytest.mark.parametrize("kind", ["sign", "dither", "topk", "identity"])
 @pytest.mark.parametrize("lr", [1e-3, 0.5])
 def test_lans_blocks_of_every_shape_in_one_call(gu, orc, kind, lr):
-    """Caller-defined LANS blocks (Algorithm 5's layers) that stress every path of the one-pass
-    kernel: ninety small blocks inside one tile of 8192 elements (more than it keeps weights
-    for), blocks of one element, empty blocks, a block that starts exactly on a tile, blocks that
-    start and end inside tiles and span several of them, across partition boundaries, and a
-    block that runs to the ragged end."""
+    """Caller-defined LANS blocks (Algorithm 5's layers) of every shape in one call: ninety small blocks
+    inside one tile of 8192 elements (more than a batch of the passes), blocks of one element, empty
+    blocks, a block that starts exactly on a tile, blocks that start and end inside tiles and span
+    several of them, across partition boundaries, and a block that runs to the ragged end."""
     import torch
     bpc = gu.bpc
     pe = 65536

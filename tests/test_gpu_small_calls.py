@@ -99,30 +99,48 @@ def test_server_calls_that_go_without_the_preset(gu, kind, n, D, tagged):
     assert bool(ws[at + 4:at + 8].any()) == tagged
 
 
+def _long_form(gu, geo, prm, D, ws):
+    """Which partitions of the last top-k call on `ws` were left to the long form."""
+    at = int(geo.geo_topk_state(ctypes.byref(prm), D))
+    words = gu.to_host(ws[at:at + 32 * -(-D // prm.part_elems)]).view(np.uint32).reshape(-1, 8)
+    return words[:, 1] != 0
+
+
 @pytest.mark.parametrize("kind", ["topk", "topk16"])
-def test_topk_many_partitions(gu, orc, kind):
-    """More partitions than the device holds workgroups of the select kernel; some of them, spread
-    over the range, are left to the long form."""
-    pe = 4096
-    D = 1300 * pe + 1001
+@pytest.mark.parametrize("pe,P,overrun", [(4096, 1301, ()), (65536, 131, (3, 40, 77, 129)), (65536, 70, (0, 41, 69)), (65536, 20, (7, 8))])
+def test_topk_many_partitions(gu, orc, geo, kind, pe, P, overrun):
+    """The select pass with one, two and four workgroups a partition (more than 128 partitions, 65 to
+    128, fewer), and with more partitions than the device holds of its workgroups.  Partitions of equal
+    magnitudes have more tied keys than the short list has room (32768) and are left to the long
+    form, the others of the same call are not; in partitions of 4096 elements even equal
+    magnitudes or zeros fit the list."""
+    bpc = gu.bpc
+    D = (P - 1) * pe + 1001
     po, pb = gu.both_params(orc, kind, pe, k_ratio=0.01)
     rs = np.random.default_rng(23)
     g = rs.standard_normal(D).astype(np.float32)
     e = (0.3 * rs.standard_normal(D)).astype(np.float32)
-    for p in (3, 200, 257, 700, 1299):
-        g[p * pe:(p + 1) * pe] = np.where(rs.random(pe) < 0.5, -0.5, 0.5)
+    for p in overrun if overrun else (3, 200, 257, 700, 1299):
+        n = min(pe, D - p * pe)
+        g[p * pe:(p + 1) * pe] = np.where(rs.random(n) < 0.5, -0.5, 0.5)
         e[p * pe:(p + 1) * pe] = 0.0
-    g[800 * pe:801 * pe] = 0.0
-    e[800 * pe:801 * pe] = 0.0
+    zeros = 800 if not overrun else 10
+    g[zeros * pe:(zeros + 1) * pe] = 0.0
+    e[zeros * pe:(zeros + 1) * pe] = 0.0
+    full = [p for p in overrun if min(pe, D - p * pe) > 32768] + ([zeros] if overrun else [])
     res_ref = e.copy()
     pay_ref = orc.compress(po, g, res_ref)
-    pay_gpu, res_gpu = gu.gpu_compress(pb, g, e.copy())
-    assert np.array_equal(res_gpu.view(np.uint32), res_ref.view(np.uint32))
+    rd, pay, ws = gu.to_dev(e), gu.new_payload(pb, D), gu.new_ws(pb, D)
+    bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    pay_gpu = gu.to_host(pay)
+    assert np.array_equal(gu.to_host(rd).view(np.uint32), res_ref.view(np.uint32))
     stride = orc.partition_stride(po)
-    for p in range(1301):
+    for p in range(P):
         k = max(1, int(0.01 * min(pe, D - p * pe)))
         a, b = pay_gpu[p * stride:(p + 1) * stride], pay_ref[p * stride:(p + 1) * stride]
         assert np.array_equal(a[:16 + 4 * k], b[:16 + 4 * k]), p
+    assert np.flatnonzero(_long_form(gu, geo, pb, D, ws)).tolist() == sorted(full)
 
 
 @pytest.mark.parametrize("n,dtype", [(1, np.float16), (4, np.float32), (8, np.float16), (16, np.float32)])
@@ -167,13 +185,6 @@ def test_fp16_with_the_most_runs_in_one_launch(gu, orc, n, dtype, pe):
     orc.adaptive_update_bypass(po, mask, out_ref, D, x, m, v, orc.make_opt(orc.OPT_ADAM, *hyper))
     for a, b in ((dx, x), (dm, m), (dv, v)):
         assert np.array_equal(gu.to_host(a), b)
-
-
-def _long_form(gu, geo, prm, D, ws):
-    """Which partitions of the last top-k call on `ws` were left to the long form."""
-    at = int(geo.geo_topk_state(ctypes.byref(prm), D))
-    words = gu.to_host(ws[at:at + 32 * -(-D // prm.part_elems)]).view(np.uint32).reshape(-1, 8)
-    return words[:, 1] != 0
 
 
 @pytest.mark.parametrize("kind,n", [("topk", 1), ("topk16", 1), ("topk", 3)])

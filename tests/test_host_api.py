@@ -136,7 +136,7 @@ def test_update_workspace_covers_more_blocks_than_partitions(bpc):
     few = bpc.update_workspace_bytes(p, D, 2)
     many = 400
     need = bpc.update_workspace_bytes(p, D, many)
-    # per block: its totals and a counter; per tile of 8192 elements: two slots of three sums
+    # (the size that the call has always answered; the passes need three doubles a block)
     assert common <= few < need and need >= common + 20 * many + 48 * (D // 8192)
     assert need % 256 == 0
     o = bpc.make_opt(bpc.OPT_LANS, 1e-3, 0.9, 0.999, 1e-8, 0.01, 1)
