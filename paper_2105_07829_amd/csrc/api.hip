@@ -279,7 +279,8 @@ bpc_status_t bpc_compress_static_ws(const bpc_params_t *params, const void *grad
   hipError_t e = static_workspace(&ws);
   if (e != hipSuccess) return hip_status(e);
   // from here on the call is bpc_compress on that workspace (whose kernels clear the parts of it
-  // that must start from a known value: slots, status word, histograms)
+  // that must start from a known value, or tell what an earlier call left there from their own:
+  // slots, status word, histograms)
   return bpc_compress(params, grad, dtype, residual, D, payload, ws, BPC_STATIC_WS_BYTES, hip_stream);
 }
 

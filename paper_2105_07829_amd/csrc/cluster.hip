@@ -36,10 +36,6 @@ hipStream_t g_last_stream[kMaxDevices];
 bool g_have[kMaxDevices];
 }  // namespace
 
-// While `stream` is being captured into a graph nothing is chained: the graph orders its own
-// nodes, and an event recorded during capture is not one a later eager launch could wait for.
-// Keeping replays of such a graph apart from cluster kernels launched elsewhere at the same
-// time is then up to the caller.
 // A number no other launch gets: a counter that starts somewhere else in every process, through a
 // bijection of the 64-bit numbers (Steele, Lea and Flood's SplitMix64 finaliser), so that two tags
 // differ in about half their bits.
@@ -58,6 +54,10 @@ static uint64_t next_tag() {
   }
 }
 
+// While `stream` is being captured into a graph nothing is chained: the graph orders its own
+// nodes, and an event recorded during capture is not one a later eager launch could wait for.
+// Keeping replays of such a graph apart from cluster kernels launched elsewhere at the same
+// time is then up to the caller.
 static bool is_capturing(hipStream_t stream) {
   hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &st) != hipSuccess) return false;

@@ -144,7 +144,8 @@ struct WsLayout {
   size_t cand;       // u32[P * kTopkListCap] indices, then as many value bits: top-k short lists of the partitions
   size_t tilecnt;    // u32[2*n_tiles]: per-tile (greater, equal) counts, then offsets
   size_t slots;      // double[3 * tiles of kSTile]: partition-wide reductions of the single-pass kernels
-                     // (one per tile; three for the LANS block norms)
+                     // (one per tile, two words per tile in a launch with a tag; three for the LANS block norms;
+                     // LANS with caller-defined blocks: its pairs, which go on into `norms` and beyond)
   size_t norms;      // double[3*P]: LANS block norms when blocks are the partitions
   size_t total;
 };

@@ -12,8 +12,8 @@
 //                at most about 2 k elements of the partition have keys >= G
 //   load+hist1 : v_j from the source -> dense buffer; the elements with key >= G go to the
 //                partition's short list and into the histogram of key >> 20
-//   select     : one workgroup per partition runs the radix select on the short list alone
-//                and writes the record; kept slots of the buffer zeroed
+//   select     : one to four workgroups per partition run the radix select on the short list alone,
+//                each for itself, and write a share of the record; kept slots of the buffer zeroed
 // The sample only decides how much work the selection is, never its result: a partition whose
 // short list came out shorter than k or longer than kTopkListCap (the sample misled, or a
 // great many equal magnitudes, or fewer than k non-zeros) is taken by the long form below
@@ -56,7 +56,7 @@ constexpr int kBits1 = 11, kBits23 = 10;
 constexpr int kTpgLoad = 2, kTpgHist2 = 4, kTpgHist3 = 1, kTpgCount = 1;
 constexpr int kSelThreads = 1024;                       // workgroup of the select pass
 constexpr int kSelPer = kTopkListCap / kSelThreads;     // list entries a thread of it keeps
-constexpr uint32_t kSelGrid = 256;                      // workgroups the select pass is spread over when there are few partitions
+constexpr uint32_t kSelGrid = 256;                      // workgroups the select pass is spread over when there are few partitions: a fixed number, one for each compute unit of an MI355X
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr int kSamplePer = 16;                          // sampled elements per thread of the sample pass
 constexpr uint32_t kSample = kThreads * kSamplePer;     // per partition: 4096
@@ -799,10 +799,10 @@ __device__ inline void topk_write_entry(const Geo &g, uint8_t *rec, uint32_t pos
 // lanes read neighbouring words), and keeps their values in registers throughout; positions in
 // the record follow from the counts of the waves before, of the rounds before and of the lanes
 // before.  A list shorter than k or longer than its room leaves the partition to the long form.
-// Where there are fewer partitions than compute units, `shares` workgroups take a partition: each
-// works the selection out for itself and writes its share of the rounds (with the guess taken two
-// levels deep and the runs requested before the list's length is looked at: a step of 3 workers on
-// 0.3 M elements 153 -> 146 us, of 8 workers on 25.6 M elements 927 -> 911 us).
+// `shares` workgroups take a partition, four up to 64 partitions, two up to 128: each works the
+// selection out for itself and writes its share of the rounds (measured together with the guess
+// taken two levels deep and the runs requested before the list's length is looked at: a step of 3
+// workers on 0.3 M elements 153 -> 146 us, of 8 workers on 25.6 M elements 927 -> 911 us).
 template <bool HALF>
 __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, uint32_t *state,
                                                                        const uint32_t *hist, const uint32_t *groupcnt,
