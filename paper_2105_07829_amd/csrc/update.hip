@@ -754,11 +754,12 @@ __global__ __launch_bounds__(kThreads) void lans_apply_kernel(Geo g, DEC dec, fl
 // barrier later the waves' sums of all blocks of the batch are added up side by side.
 // What bounds it: memory, 20.5 + 16.5 bytes an element with a 4-bit message, 24.5 where the blocks
 // lie inside tiles (counters: 37.04 with layers).  Layer-shaped blocks, 336 M elements: norms 1.10 ms
-// at 6.3 TB/s, totals 0.01, step 0.92 ms at 6.1 TB/s, 2.06 ms the call.  100 M elements in blocks of
-// 8192 / 1024 / 256: 418 / 450 / 898 us; one block at a time with barriers of its own and x in the
-// second pass only it was 631 / 872 / 2001.  (The form that kept a tile's x and directions in
-// registers until its blocks were complete, one workgroup of 1024 threads a CU and block totals
-// exchanged inside the kernel, took 2.67 ms over the layers and 527 / 972 / 2268 us.)
+// at 6.3 TB/s, totals 0.01, step 0.92 ms at 6.1 TB/s, 2.06 to 2.13 ms the call (from process to
+// process).  100 M elements in blocks of 8192 / 1024 / 256: 418 / 450 / 898 us; one block at a time with
+// barriers of its own and x in the second pass only it was 631 / 872 / 2001.  (The form that kept a
+// tile's x and directions in registers until its blocks were complete, one workgroup of 1024 threads
+// a CU and block totals exchanged inside the kernel, took 2.67 ms over the layers and
+// 527 / 972 / 2268 us.)
 constexpr int kBThreads = 512;
 constexpr int kBPer = kSTile / kBThreads;   // 16
 constexpr int kBRows = kBPer / 4;
