@@ -64,6 +64,11 @@ static bool is_capturing(hipStream_t stream) {
   return st != hipStreamCaptureStatusNone;
 }
 
+bool launch_tag(hipStream_t stream, uint64_t *tag) {
+  *tag = next_tag();
+  return is_capturing(stream);
+}
+
 // The event is recorded only when it is needed: when a launch comes on another stream than the
 // one before, on that earlier stream (it then covers the earlier kernel and whatever that
 // stream was given since, which is more than needed and never less).  Recording one after

@@ -116,6 +116,9 @@ inline SplitGeo split_geo(const Geo &g, uint32_t tile, bool ragged_ok) {
 // `tag` (if given) receives this launch's tag, 0 while the stream is being captured.
 hipError_t cluster_launch_begin(hipStream_t stream, uint64_t *tag = nullptr);
 hipError_t cluster_launch_end(hipStream_t stream);
+// A tag for a launch that needs no resident grid, so is not chained; true if `stream` is being captured
+// (every replay then carries this tag).
+bool launch_tag(hipStream_t stream, uint64_t *tag);
 // Creates the current device's event now rather than at the first launch that needs it.
 hipError_t cluster_prepare_device();
 // Number of workgroups of `kernel` (`threads` threads, `dyn_lds` bytes of dynamic LDS) resident at once

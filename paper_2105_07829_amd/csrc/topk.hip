@@ -7,19 +7,22 @@
 // lowest index first, and the record lists its entries by ascending index.
 //
 // Short-list form (k of a full partition at most half of kTopkListCap): one pass over the data.
-//   sample     : 4096 elements of each partition (512 evenly spread chunks of eight); the key G
-//                at a rank of the sample chosen so that, but for rare cases, at least k and
-//                at most about 2 k elements of the partition have keys >= G
-//   load+hist1 : v_j from the source -> dense buffer; the elements with key >= G go to the
-//                partition's short list and into the histogram of key >> 20
-//   select     : one to four workgroups per partition run the radix select on the short list alone,
+//   guess      : 4096 elements of each partition (512 spread chunks of eight); the key G at a rank of
+//                the sample chosen so that, but for rare cases, at least k and at most about 2 k
+//                elements of the partition have keys >= G
+//   load       : v_j from the source -> dense buffer; the elements with key >= G go to the
+//                partition's short list
+//   select     : several workgroups per partition find the k-th largest key among the listed ones,
 //                each for itself, and write a share of the record; kept slots of the buffer zeroed
+// On the worker side the guess is made by the first workgroups of the load kernel itself, the others
+// have requested their elements before they wait for it; on the server side by a kernel in
+// front that also finds where each message's entries of a group of 8192 elements begin.
 // The sample only decides how much work the selection is, never its result: a partition whose
-// short list came out shorter than k or longer than kTopkListCap (the sample misled, or a
-// great many equal magnitudes, or fewer than k non-zeros) is taken by the long form below
-// instead: one more kernel, enqueued behind, which returns at once if no partition needs it
-// and else runs the long form's passes for those partitions (the rest of their level-1
-// histogram first) with its resident grid meeting between the passes.
+// short list came out shorter than k or longer than its room (the sample misled, or a great many
+// equal magnitudes, or fewer than k non-zeros) is taken by the long form below instead, run by the
+// partition's first select workgroup alone; partitions of more than kAloneElems elements by one more
+// kernel, enqueued behind, which returns at once if no partition needs it and else runs the
+// long form's passes for those partitions with its resident grid meeting between the passes.
 //
 // Long form (a k too large for a short list), five passes over the dense buffer:
 //   load+hist1 : as above, every element counted
@@ -34,8 +37,8 @@
 // Server side the vector is Delta = (sum of the n decoded messages) / n + e~.  It is never
 // scattered into a dense buffer (n k read-modify-writes at random places of HBM per partition):
 // the messages list their entries by ascending index, so the load pass sums the stretch of each
-// message that falls into its group of 8192 elements in LDS, and the sample pass collects the
-// sums of the sampled chunks in one sweep over the messages.
+// message that falls into its group of 8192 elements in LDS, and one workgroup a partition collects
+// the sums of the sampled chunks in LDS in one sweep over the messages.
 #include "cluster.hpp"
 #include "sources.hpp"
 #include "tile_rows.hpp"
@@ -56,19 +59,67 @@ constexpr int kBits1 = 11, kBits23 = 10;
 constexpr int kTpgLoad = 2, kTpgHist2 = 4, kTpgHist3 = 1, kTpgCount = 1;
 constexpr int kSelThreads = 1024;                       // workgroup of the select pass
 constexpr int kSelPer = kTopkListCap / kSelThreads;     // list entries a thread of it keeps
-constexpr uint32_t kSelGrid = 256;                      // workgroups the select pass is spread over when there are few partitions: a fixed number, one for each compute unit of an MI355X
+constexpr int kSelBins = 8192, kSelBits = 13;           // first level of the select pass: bins of 1024 keys from the guess up, an octave of magnitudes
+constexpr uint32_t kShareWords = 16384;                 // words of the bitmap of a select workgroup's share of the indices, at most
+constexpr uint32_t kXcds = 8, kCusOfXcd = 32;            // of an MI355X: the select pass is spread over one workgroup a compute unit when there are few partitions
+constexpr uint32_t kMostShares = 8;                     // ... of one partition (unless its bitmaps ask for more)
+constexpr uint32_t kAloneElems = 1u << 22;              // partitions up to this size are left to one workgroup if the short list fails
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
-constexpr int kSamplePer = 16;                          // sampled elements per thread of the sample pass
-constexpr uint32_t kSample = kThreads * kSamplePer;     // per partition: 4096
+constexpr uint32_t kSampleChunks = 1024;                // chunks of eight consecutive elements in a partition's sample, at most
 constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
 constexpr uint32_t kNoGuess = 0xffffffffu;              // no key reaches it: nothing goes to the short list
 
 __device__ inline uint32_t key_of(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
 // state words per partition: words 2L, 2L + 1 hold (prefix, rank left) after level L = 1..3;
-// word 0 the length of the short list, word 1 non-zero if the partition is left to the long form
+// word 1 non-zero if the partition is left to the long form
 enum { kStPrefix = 0, kStKRem = 1 };
-enum { kStListLen = 0, kStLong = 1 };
+enum { kStLong = 1 };
+
+// What the load pass of the short-list form hands from workgroup to workgroup, in the workspace's
+// region for it (16 KB a partition): the guesses, two words each (the guess, and its exclusive or with
+// the launch's tag, as the slots of cluster.hpp), and the lengths of the lists, a page apart since an
+// atomic on global memory holds up its memory channel for some 11 ns.
+struct TopkShared {
+  uint64_t *pairs;
+  uint32_t *lengths;
+  uint64_t tag;
+  uint32_t *status;
+  static size_t pairs_bytes(uint32_t P) { return (16ull * P + 4095) / 4096 * 4096; }
+  __device__ uint32_t *length(uint32_t p) const { return lengths + 1024ull * p; }
+  // One thread publishes partition p's guess; the list length is zero before anyone can see it.
+  __device__ void publish(uint32_t p, uint32_t guess) const {
+    __hip_atomic_store(length(p), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // (vector memory done)
+    asm volatile("" ::: "memory");
+    __hip_atomic_store(pairs + 2ull * p, (uint64_t)guess, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pairs + 2ull * p + 1, (uint64_t)guess ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ u32x4 look(uint32_t p) const { return TileBuf(pairs + 2ull * p, 16).load16<kMemorySide>(0, 0); }
+  // The guess, `w` being the first look at it.  The wait is for a workgroup with a lower index, which
+  // waits for nobody; it is bounded like those of cluster.hpp.
+  __device__ uint32_t wait(uint32_t p, u32x4 w) const {
+    int spins = 0;
+    while ((w.x ^ w.z) != (uint32_t)tag || (w.y ^ w.w) != (uint32_t)(tag >> 32)) {
+      if (++spins > kSpinLimit) {
+        if ((threadIdx.x & 63) == 0) status_give_up(status, tag);
+        return kNoGuess;
+      }
+      __builtin_amdgcn_s_sleep(4);
+      w = look(p);
+    }
+    return __builtin_amdgcn_readfirstlane(w.x);
+  }
+};
+
+// A partition's short list: the entries' indices and values, in any order.
+struct TopkLists {
+  uint32_t *base;
+  uint32_t P;
+  __device__ uint32_t *idx(uint32_t p) const { return base + (uint64_t)p * kTopkListCap; }
+  __device__ uint32_t *val(uint32_t p) const { return base + (uint64_t)(P + p) * kTopkListCap; }
+};
 
 // Whether partition p is left to the long form (uniform over the workgroup).
 __device__ inline bool long_form(const uint32_t *state, uint32_t p) {
@@ -105,12 +156,21 @@ __device__ inline void pick_bin(const uint32_t *h, uint32_t k_rem, uint32_t pref
   // thread t owns bins BINS-1 - t*kPer - i, highest first; threads past the bins own none
   uint32_t cnt[kPer];
   uint32_t local = 0;
+  if constexpr (kPer % 4 == 0) {   // (the histograms start at multiples of 16 bytes)
 #pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const uint32_t b = threadIdx.x * kPer + i;
-    cnt[i] = b < (uint32_t)BINS ? h[BINS - 1 - b] : 0u;
-    local += cnt[i];
+    for (int i = 0; i < kPer; i += 4) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(h + (BINS - 4 - (int)threadIdx.x * kPer - i));
+      cnt[i] = x.w; cnt[i + 1] = x.z; cnt[i + 2] = x.y; cnt[i + 3] = x.x;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const uint32_t b = threadIdx.x * kPer + i;
+      cnt[i] = b < (uint32_t)BINS ? h[BINS - 1 - b] : 0u;
+    }
   }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) local += cnt[i];
   uint32_t total;
   const uint32_t above = block_exclusive_scan<THREADS>(local, scan, &total);
   if (above < k_rem && k_rem <= above + local) {
@@ -130,21 +190,6 @@ __device__ inline void pick_bin(const uint32_t *h, uint32_t k_rem, uint32_t pref
 // Radix select, inside one workgroup of THREADS, among the keys of the values the threads hold
 // in registers (the low 31 bits of bits[i], i < cnt <= rounds, `rounds` the same for all
 // threads).  h: LDS, kBins1 words.
-// Level 1: the level-1 bin of the key of rank `rank` (1 = the largest) in sel[0], the rank left
-// inside it in sel[1].
-template <int PER, int THREADS>
-__device__ inline void level1_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t rank,
-                                           uint32_t *h, uint32_t *scan, uint32_t *sel) {
-  for (int b = threadIdx.x; b < kBins1; b += THREADS) h[b] = 0;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < PER; ++i) {
-    if ((uint32_t)i >= rounds) break;
-    if ((uint32_t)i < cnt) atomicAdd(&h[(bits[i] & 0x7fffffffu) >> kShift1], 1u);
-  }
-  __syncthreads();
-  pick_bin<kBins1, kBits1, THREADS>(h, rank, 0, scan, sel);
-}
 // Level 2, given level 1's (b1, k_rem1): the key's first 21 bits in sel[0], the rank left among the
 // keys that share them in sel[1].
 template <int PER, int THREADS>
@@ -178,23 +223,19 @@ __device__ inline void level3_in_registers(const uint32_t (&bits)[PER], uint32_t
   __syncthreads();
   pick_bin<kBins23, kBits23, THREADS>(h, k_rem2, prefix2, scan, sel);
 }
-// Levels 2 and 3.
-template <int PER, int THREADS>
-__device__ inline void levels23_in_registers(const uint32_t (&bits)[PER], uint32_t cnt, uint32_t rounds, uint32_t b1,
-                                             uint32_t k_rem1, uint32_t *h, uint32_t *scan, uint32_t *sel) {
-  level2_in_registers<PER, THREADS>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
-  const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
-  level3_in_registers<PER, THREADS>(bits, cnt, rounds, prefix2, k_rem2, h, scan, sel);
-}
 
-// Chunk (of eight consecutive elements) number c of the sample of a partition sampled every
-// `stride` chunks: one of the c-th stretch of `stride` chunks, at a place that moves from
-// stretch to stretch (chunks at equal distances of a power of two would all come from the same
-// few memory channels).
-__device__ inline uint32_t sample_chunk(uint32_t c, uint32_t stride) { return c * stride + (c * 37u) % stride; }
-
-// Sample chunks and their spacing for a partition of d elements.
-__device__ inline uint32_t sample_chunks(uint32_t d) { return d / 8 < kSample / 8 ? d / 8 : kSample / 8; }
+// The sample of a partition of d elements: chunk (of eight consecutive elements) number c is one of the c-th
+// stretch of 1 << shift chunks, at a place that moves from stretch to stretch (chunks at equal
+// distances of a power of two would all come from the same few memory channels).  Only whole chunks.
+struct SamplePlan {
+  uint32_t shift, chunks;
+  __device__ explicit SamplePlan(uint32_t d) {
+    shift = 0;
+    while (((d / 8) >> shift) > kSampleChunks) ++shift;
+    chunks = (d / 8) >> shift;
+  }
+  __device__ uint32_t chunk(uint32_t c) const { return (c << shift) + ((c * 37u) & ((1u << shift) - 1u)); }
+};
 
 // Workgroup of the load pass: 16 elements a thread (of 256 threads, 32 elements each: 91 registers
 // a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
@@ -244,36 +285,24 @@ struct TopkMsgs {
       out[e] = j0 + e < d ? (res ? mean + r[e] : mean) : 0.0f;
     }
   }
-  __device__ void finish8(const Geo &g, uint32_t p, uint32_t j0, uint32_t d, const float *sum, float out[8]) const {
-    float r[8];
-    load_res8(g, p, j0, d, r);
-    combine8(j0, d, sum, r, out);
-  }
 };
 
 // For t = 0 .. k: entry t is the first one of every group after the group of entry t - 1 up to
 // its own group (t = k: up to the end).  A message that is not in ascending order leaves
-// groups unset; readers clamp what they find to [0, k].
-// The same sweep adds the entries that fall into the chunks of the sample pass to `samp`
-// (zeroed before; about one entry in 250, so the global atomics do not matter, and the guess
-// needs no particular order of the sum); `samp` may be null.
-__global__ __launch_bounds__(kThreads) void topk_starts_kernel(Geo g, TopkMsgs m, uint32_t *starts, float *samp) {
-  const uint32_t p = blockIdx.y, i = blockIdx.z;
+// groups unset; readers clamp what they find to [0, k].  Entries t0, t0 + step, ... of worker i's message.
+__device__ inline void topk_starts(const Geo &g, const TopkMsgs &m, uint32_t *starts, uint32_t i, uint32_t p, uint32_t t0, uint32_t step) {
   const uint32_t k = m.k_of(i, p);
   const uint32_t *idx = m.idx(i, p);
   uint32_t *tab = starts + ((uint64_t)i * g.P + p) * (m.groups_per_part + 1);
   auto group = [&](uint32_t j) { const uint32_t q = j >> m.group_shift; return q < m.groups_per_part ? q : m.groups_per_part - 1; };
-  const uint32_t d = g.part_size(p);
-  const uint32_t chunks = sample_chunks(d), stride = chunks ? (d / 8) / chunks : 1u;
-  for (uint32_t t = blockIdx.x * kThreads + threadIdx.x; t <= k; t += gridDim.x * kThreads) {
+  for (uint32_t t = t0; t <= k; t += step) {
     const uint32_t first = t == 0 ? 0u : group(idx[t - 1]) + 1;
     const uint32_t last = t == k ? m.groups_per_part : group(idx[t]);
     for (uint32_t q = first; q <= last && q <= m.groups_per_part; ++q) tab[q] = t;
-    if (samp && t < k) {
-      const uint32_t j = idx[t], cj = j >> 3, c = cj / stride;
-      if (c < chunks && cj == sample_chunk(c, stride)) atomicAdd(&samp[(uint64_t)p * kSample + c * 8 + (j & 7u)], m.value(i, p, t));
-    }
   }
+}
+__global__ __launch_bounds__(kThreads) void topk_starts_kernel(Geo g, TopkMsgs m, uint32_t *starts) {
+  topk_starts(g, m, starts, blockIdx.z, blockIdx.y, blockIdx.x * kThreads + threadIdx.x, gridDim.x * kThreads);
 }
 
 // The load pass's view: the workgroup's group of 8192 elements summed in LDS, worker by worker
@@ -355,91 +384,123 @@ struct TopkMsgsGroupSource : TopkMsgs {
   }
 };
 
-// The sample pass's view of the same: the sums of the sampled chunks, collected by the sweep of
-// `topk_starts_kernel`.
-struct TopkMsgsSampleSource : TopkMsgs {
-  const float *samp;
-  static constexpr int kLdsFloats = 1;
-  __device__ void begin(const Geo &, uint32_t, float *) const {}
-  // j0: the first element of a sampled chunk
-  __device__ void at8(const Geo &g, uint32_t p, uint32_t j0, uint32_t d, const float *, float out[8]) const {
-    const uint32_t chunks = sample_chunks(d), stride = (d / 8) / chunks;
-    float sum[8];
-    load8_aligned(samp + (uint64_t)p * kSample + 8 * ((j0 >> 3) / stride), sum);
-    finish8(g, p, j0, d, sum, out);
-  }
-};
-
-// Zeroes the histograms and the state words; with `sample`, workgroup p < P also works out
-// partition p's guess G from a sample of 512 chunks of eight consecutive elements (else the
-// guess is "none").  Random 64-byte reads cost about as much as 16 times as many sequential
-// ones, hence chunks rather than single elements.
-template <class SRC>
-__global__ __launch_bounds__(kThreads) void topk_sample_kernel(Geo g, SRC src, uint32_t *hist, uint32_t *state,
-                                                               uint32_t *guess, int sample, uint32_t *status) {
-  __shared__ __align__(16) float lds[SRC::kLdsFloats];
-  __shared__ uint32_t h[kBins1];
-  if (blockIdx.x == 0 && threadIdx.x == 0) status[0] = 0;   // (set by a wait of the long form that gave up)
-  __shared__ uint32_t scan[kThreads];
-  __shared__ uint32_t sel[2];
-  {
-    const size_t i0 = (size_t)blockIdx.x * kThreads + threadIdx.x, step = (size_t)gridDim.x * kThreads;
-    uint4 *h16 = reinterpret_cast<uint4 *>(hist);
-    for (size_t q = i0; q < (size_t)kTopkHistWords * g.P / 4; q += step) h16[q] = make_uint4(0, 0, 0, 0);
-    for (size_t q = i0; q < 8ull * g.P + 8; q += step) state[q] = 0;   // (8 spare words: the long form's barrier counter)
-  }
-  const uint32_t p = blockIdx.x;
-  if (p >= g.P) return;
-  if (!sample) {
-    if (threadIdx.x == 0) guess[p] = kNoGuess;
-    return;
-  }
-  static_assert(kSamplePer % 8 == 0, "whole chunks");
-  constexpr uint32_t kChunksPer = kSamplePer / 8;
+// The guess for partition p, published: `load8(j0, v)` gives the eight elements from j0, the first of
+// a sampled chunk.  All threads of a workgroup of THREADS; h: LDS, kBins1 words.  Random 64-byte reads
+// cost about as much as 16 times as many sequential ones, hence chunks rather than single elements.
+template <int THREADS, class LOAD8>
+__device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh, uint32_t *h, uint32_t *scan, uint32_t *sel,
+                                  LOAD8 load8) {
+  constexpr uint32_t kChunksPer = (kSampleChunks + THREADS - 1) / THREADS;
+  constexpr int kPer = 8 * kChunksPer;
   const uint32_t d = g.part_size(p);
-  const uint32_t chunks = sample_chunks(d);                   // chunks in the sample (whole chunks of the partition only)
-  const uint32_t m = 8 * chunks;                              // elements in the sample
+  const SamplePlan plan(d);
+  const uint32_t m = 8 * plan.chunks;                         // elements in the sample
   // rank in the sample: the expected rank of the partition's k-th largest, four standard
   // deviations of a count of twice that size further down (neighbours are not independent),
   // and a little more
   const double expect = (double)k_of_device(g, p) * (double)m / (double)d;
   const uint32_t rank = (uint32_t)(expect + 4.0 * sqrt(2.0 * expect) + 3.0);
-  if (rank >= m) {   // (uniform) the whole partition would be listed
-    if (threadIdx.x == 0) guess[p] = 0;
+  if (rank >= m) {   // (uniform) the whole partition is listed
+    if (threadIdx.x == 0) sh.publish(p, 0);
     return;
   }
-  const uint32_t stride = (d / 8) / chunks;
-  src.begin(g, p, lds);
-  __syncthreads();
-  uint32_t key[kSamplePer];
+  uint32_t key[kPer];
   uint32_t cnt = 0;
   // (every load is issued, with chunk 0 standing in past the end, so that none is waited for
   // before the last is on its way)
 #pragma unroll
   for (uint32_t i = 0; i < kChunksPer; ++i) {
-    const uint32_t c = i * kThreads + threadIdx.x;
+    const uint32_t c = i * THREADS + threadIdx.x;
     float v[8];
-    source_at8(src, g, p, 8 * sample_chunk(c < chunks ? c : 0u, stride), d, lds, v);
+    load8(c < plan.chunks ? c : 0u, 8 * plan.chunk(c < plan.chunks ? c : 0u), v);
 #pragma unroll
     for (int e = 0; e < 8; ++e) key[8 * i + e] = key_of(v[e]);
-    cnt += c < chunks ? 8 : 0;
+    cnt += c < plan.chunks ? 8 : 0;
   }
-  level1_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, rank, h, scan, sel);
+  for (int b = threadIdx.x; b < kBins1; b += THREADS) h[b] = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kPer; ++i)
+    if ((uint32_t)i < cnt) atomicAdd(&h[key[i] >> kShift1], 1u);
+  __syncthreads();
+  pick_bin<kBins1, kBits1, THREADS>(h, rank, 0, scan, sel);
   const uint32_t b1 = sel[0], k_rem1 = sel[1];
   __syncthreads();
   // The lower end of the level-2 bin (1/8192 of an octave of magnitudes) will do for a guess as long as
   // the bin holds few elements, which the list then takes too.  Magnitudes that lie that close
   // together would overrun the list and leave the partition to the long form (within 2^-14 of each
   // other, 1 M elements: 59 us for the call with the third level, 690 us without).
-  level2_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, b1, k_rem1, h, scan, sel);
+  level2_in_registers<kPer, THREADS>(key, cnt, kPer, b1, k_rem1, h, scan, sel);
   const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
   const uint64_t in_bin = (uint64_t)h[prefix2 & (kBins23 - 1)] * d;   // times m: elements of the partition
   if (in_bin <= (uint64_t)kFewInBin * m) {   // (uniform)
-    if (threadIdx.x == 0) guess[p] = prefix2 << kShift2;
+    if (threadIdx.x == 0) sh.publish(p, prefix2 << kShift2);
     return;
   }
-  level3_in_registers<kSamplePer, kThreads>(key, cnt, kSamplePer, prefix2, k_rem2, h, scan, sel);
-  if (threadIdx.x == 0) guess[p] = sel[0];
+  level3_in_registers<kPer, THREADS>(key, cnt, kPer, prefix2, k_rem2, h, scan, sel);
+  if (threadIdx.x == 0) sh.publish(p, sel[0]);
+}
+
+// Server side, in front of the load pass.  Workgroup (p, 0): the guess from the sampled chunks of Delta,
+// whose sums are collected in LDS by one sweep over the messages (one entry in 128 or so falls into a chunk, so the
+// float atomics do not matter, and a guess needs no particular order of the sum); workgroup (p, 1 + i): where
+// each group's entries start in worker i's message.
+constexpr int kPrepThreads = 1024;
+__global__ __launch_bounds__(kPrepThreads) void topk_server_prep_kernel(Geo g, TopkMsgs m, uint32_t *starts, TopkShared sh, uint32_t *state,
+                                                                        int guesses) {
+  __shared__ __align__(16) float sum[kSampleChunks * 8];
+  __shared__ uint32_t h[kBins1];
+  __shared__ uint32_t scan[kPrepThreads / 64];
+  __shared__ uint32_t kept[kMaxWorkers];   // entries of a worker's message
+  __shared__ uint32_t sel[2];
+  const uint32_t p = blockIdx.x, role = blockIdx.y + (guesses ? 0u : 1u);
+  if (role != 0) {
+    topk_starts(g, m, starts, role - 1, p, threadIdx.x, kPrepThreads);
+    return;
+  }
+  if (p == 0) status_open(sh.status, sh.tag);
+  if (threadIdx.x == 0) state[p * 8 + kStLong] = 0;
+  const uint32_t d = g.part_size(p);
+  const SamplePlan plan(d);
+  // (a chunk a thread; its residual is on its way while the sums are formed)
+  static_assert(kSampleChunks == kPrepThreads, "a chunk a thread");
+  float res8[8];
+  const uint32_t mine = 8 * plan.chunk(threadIdx.x < plan.chunks ? threadIdx.x : 0u);
+  m.load_res8(g, p, mine, d, res8);
+  if (threadIdx.x < (uint32_t)m.msgs.n) kept[threadIdx.x] = m.k_of(threadIdx.x, p);
+  for (uint32_t q = threadIdx.x; q < kSampleChunks * 8; q += kPrepThreads) sum[q] = 0.0f;
+  __syncthreads();
+  // the messages in pieces of 2048 entries, a wave each; indices and values of a piece in flight at once
+  // (values fetched where an index turned out to be sampled had every wave wait for one after the other).
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t pieces = (uint32_t)cdiv(m.k_cap, 2048), mask = (1u << plan.shift) - 1u;
+  for (uint32_t piece = wave; piece < pieces * (uint32_t)m.msgs.n; piece += kPrepThreads / 64) {
+    const uint32_t i = piece / pieces, t0 = piece % pieces * 2048, k = __builtin_amdgcn_readfirstlane(kept[i]);
+    const uint8_t *vals = m.rec(i, p) + kHeaderBytes + 4 * ru4(m.k_cap);
+    const TileBuf ib(m.idx(i, p), k * 4), vb(vals, (m.half ? (k + 1) / 2 * 2 * 2 : k * 4));
+    u32x4 x[8];
+    float v[8][4];
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) x[q] = ib.load16(t0 * 4 + q * 1024 + lane * 16, 0);
+    if (m.half) {
+#pragma unroll
+      for (uint32_t q = 0; q < 8; ++q) widen4(vb.load8(t0 * 2 + q * 512 + lane * 8, 0), v[q]);
+    } else {
+#pragma unroll
+      for (uint32_t q = 0; q < 8; ++q) widen4(vb.load16(t0 * 4 + q * 1024 + lane * 16, 0), v[q]);
+    }
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) {
+      const uint32_t js[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e) {
+        const uint32_t j = js[e], cj = j >> 3, c = cj >> plan.shift;
+        if (((c * 37u ^ cj) & mask) == 0 && c < plan.chunks && t0 + q * 256 + lane * 4 + e < k) atomicAdd(&sum[c * 8 + (j & 7u)], v[q][e]);
+      }
+    }
+  }
+  __syncthreads();
+  topk_guess<kPrepThreads>(g, p, sh, h, scan, sel, [&](uint32_t c, uint32_t j0, float v[8]) { m.combine8(j0, d, sum + 8 * c, res8, v); });
 }
 
 template <class SRC, class = void>
@@ -447,44 +508,48 @@ struct has_begin_group : std::false_type {};
 template <class SRC>
 struct has_begin_group<SRC, std::void_t<decltype(&SRC::begin_group)>> : std::true_type {};
 
-// Load pass.  Besides the buffer: the elements of the workgroup's tiles whose key is at least
-// the partition's guess go to its short list, together and in index order, at the place one
-// atomic add on the list length hands out; place and count are recorded per group of tiles, so
-// the select pass can walk the list in index order whatever order the groups arrived in.
-// The level-1 histogram takes those elements only (the bin of the k-th largest key and the rank
-// inside it come out the same as long as the list holds k elements; every non-empty bin of every
-// workgroup is one atomic on global memory, and with all elements counted those atomics were
-// most of this pass on the server side); without a guess it takes all elements.
-// LISTED (every partition has a guess): only the listed elements are counted, and their bins
-// start at the guess's, so the LDS histogram is kNearBins bins from there (8 KB less LDS a
-// workgroup: a fourth workgroup per compute unit on the server side); the rare key beyond them
-// goes to the partition's histogram directly.
-constexpr int kNearBins = 64;
+// Load pass.  Besides the buffer, short-list form (LISTED): the elements of the workgroup's tiles whose
+// key is at least the partition's guess go to its short list, together, at the place one atomic
+// add on the list length hands out.  The order inside the list does not matter: the select pass puts
+// what it keeps in index order through a bitmap.  Long form: the level-1 histogram of all elements.
+// On the worker side workgroup p < P makes partition p's guess and the groups follow behind; a group has
+// its elements in registers before it waits for the guess (a kernel of its own for the guesses cost
+// 8 us of every call).
 // The group is taken as 4 rows of 2048 elements, 4 consecutive elements a thread and row: every
 // 16-byte access of a wave to the gradient, the residual and the buffer covers whole cache lines
 // and is marked non-temporal; everything goes through descriptors of the elements that exist
 // (the rest read as zero and are not written).  All loads of the group are requested before the
-// first is used.  Index order in the list is row, thread, element: a thread's place in its
-// row comes from the wave's ballots, the places of the rows and waves from one scan of their
-// 32 counts.
+// first is used.
 constexpr int kLoadRowElems = kLoadThreads * 4;
 constexpr int kLoadRows = kGroupElems / kLoadRowElems;
 template <class SRC, bool LISTED>
-__global__ __launch_bounds__(kLoadThreads) void topk_load_hist1_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state,
-                                                                   const uint32_t *guess, uint32_t *groupcnt,
-                                                                   uint32_t *cand_idx, uint32_t *cand_val) {
+__global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
+                                                                 TopkLists lists) {
+  constexpr bool kGuesses = LISTED && !has_begin_group<SRC>::value;
   __shared__ __align__(16) float lds[SRC::kLdsFloats];
-  constexpr int kLocalBins = LISTED ? kNearBins : kBins1;
   constexpr int kWaves = kLoadThreads / 64;
-  static_assert(kLoadRows * kWaves <= 64, "one wave scans the counts of all rows and waves");
-  __shared__ uint32_t h[kLocalBins];
-  __shared__ uint32_t run_cnt[kLoadRows * kWaves];   // listed elements per row and wave, then how many come before them
-  __shared__ uint32_t off_sh;
-  const GroupOf w = group_of<kTpgLoad>(g, blockIdx.x);
-  for (int b = threadIdx.x; b < kLocalBins; b += kLoadThreads) h[b] = 0;
-  src.begin(g, w.p, lds);
-  __syncthreads();
+  __shared__ uint32_t h[!LISTED || kGuesses ? kBins1 : 1];
+  __shared__ uint32_t scan[kWaves];
+  __shared__ uint32_t sel[2];
+  uint32_t blk = blockIdx.x;
+  if constexpr (kGuesses) {
+    if (blk == 0) status_open(sh.status, sh.tag);
+    if (blk < g.P) {
+      if (threadIdx.x == 0) state[blk * 8 + kStLong] = 0;
+      const uint32_t d = g.part_size(blk);
+      topk_guess<kLoadThreads>(g, blk, sh, h, scan, sel, [&](uint32_t, uint32_t j0, float v[8]) { src.at8(g, blk, j0, d, nullptr, v); });
+      return;
+    }
+    blk -= g.P;
+  }
+  const GroupOf w = group_of<kTpgLoad>(g, blk);
+  if constexpr (!LISTED) {
+    for (int b = threadIdx.x; b < kBins1; b += kLoadThreads) h[b] = 0;
+    __syncthreads();
+  }
   if (w.tile_lo >= w.tile_hi) return;  // (uniform) past the end of a shorter last partition
+  u32x4 look{};
+  if constexpr (LISTED) look = sh.look(w.p);
   const uint32_t j_lo = __builtin_amdgcn_readfirstlane(w.tile_lo * kTile);
   const uint32_t left = w.d - j_lo;
   const uint32_t valid = __builtin_amdgcn_readfirstlane(left < kGroupElems ? left : kGroupElems);
@@ -532,81 +597,56 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_hist1_kernel(Geo g, SR
       for (int c = 0; c < 4; ++c) v[u][c] = ef ? x[c] + e[c] : x[c];
     }
   }
+  // (the buffer is the residual, of which the guess's sample is read: no store before the guess is there)
+  uint32_t G = kNoGuess;
+  if constexpr (LISTED) G = sh.wait(w.p, look);
 #pragma unroll
   for (int u = 0; u < kLoadRows; ++u)
     row_buf(buf + base, valid, u * kLoadRowElems, kLoadRowElems).store16<kNonTemporal>(as_u32x4(v[u][0], v[u][1], v[u][2], v[u][3]), threadIdx.x * 16);
-  const uint32_t G = guess[w.p];
-  uint32_t mask = 0;   // bit 4 u + c: element c of row u goes to the list
+  if constexpr (!LISTED) {
 #pragma unroll
-  for (int u = 0; u < kLoadRows; ++u) {
+    for (int u = 0; u < kLoadRows; ++u)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if ((uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid) {
-        const uint32_t key = key_of(v[u][c]);
-        const bool listed = key >= G;
-        if (LISTED) {
-          if (listed) {
-            const uint32_t rel = (key >> kShift1) - (G >> kShift1);
-            if (rel < (uint32_t)kNearBins) atomicAdd(&h[rel], 1u);
-            else atomicAdd(&hist[(uint64_t)w.p * kTopkHistWords + kHist1 + (key >> kShift1)], 1u);
-          }
-        } else {
-          atomicAdd(&h[key >> kShift1], 1u);
-        }
-        mask |= (uint32_t)listed << (4 * u + c);
-      }
-    }
-  }
-  if (G != kNoGuess) {
+      for (int c = 0; c < 4; ++c)
+        if ((uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid) atomicAdd(&h[key_of(v[u][c]) >> kShift1], 1u);
+    __syncthreads();
+    uint32_t *gh = hist + (uint64_t)w.p * kTopkHistWords + kHist1;
+    for (int b = threadIdx.x; b < kBins1; b += kLoadThreads)
+      if (h[b]) atomicAdd(&gh[b], h[b]);
+  } else {
+    uint32_t mask = 0;   // bit 4 u + c: element c of row u goes to the list
+#pragma unroll
+    for (int u = 0; u < kLoadRows; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        mask |= (uint32_t)((uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid && key_of(v[u][c]) >= G) << (4 * u + c);
     const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t before[kLoadRows];   // listed elements of the row in the wave's lanes below this one
-#pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) {
-      uint32_t mine = 0, all = 0;
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const unsigned long long m = __ballot((mask >> (4 * u + c)) & 1u);
-        mine += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        all += (uint32_t)__popcll(m);
-      }
-      before[u] = mine;
-      if (lane == 0) run_cnt[u * kWaves + wave] = all;
-    }
+    const uint32_t cnt = (uint32_t)__popc(mask);
+    const uint32_t incl = wave_inclusive_scan_u32(cnt);
+    if (lane == 63) scan[wave] = incl;
     __syncthreads();
-    if (threadIdx.x < 64) {
-      const uint32_t x = threadIdx.x < (uint32_t)(kLoadRows * kWaves) ? run_cnt[threadIdx.x] : 0u;
-      const uint32_t incl = wave_inclusive_scan_u32(x);
-      if (threadIdx.x < (uint32_t)(kLoadRows * kWaves)) run_cnt[threadIdx.x] = incl - x;
-      if (threadIdx.x == 63) {
-        const uint32_t total = incl;
-        const uint32_t off = total ? atomicAdd(&state[w.p * 8 + kStListLen], total) : 0u;
-        off_sh = off;
-        groupcnt[2 * blockIdx.x] = off;
-        groupcnt[2 * blockIdx.x + 1] = total;
-      }
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) {
+      before += (uint32_t)q < wave ? scan[q] : 0u;
+      total += scan[q];
     }
+    if (threadIdx.x == 0) sel[0] = total ? atomicAdd(sh.length(w.p), total) : 0u;
     __syncthreads();
-    const uint64_t list = (uint64_t)w.p * kTopkListCap;
+    uint32_t pos = sel[0] + before + incl - cnt;
+    uint32_t *li = lists.idx(w.p), *lv = lists.val(w.p);
 #pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) {
-      uint32_t pos = off_sh + run_cnt[u * kWaves + wave] + before[u];
-      const uint32_t j0 = j_lo + u * kLoadRowElems + threadIdx.x * 4;
+    for (int u = 0; u < kLoadRows; ++u)
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
+      for (int c = 0; c < 4; ++c)
         if ((mask >> (4 * u + c)) & 1u) {
           if (pos < kTopkListCap) {
-            cand_idx[list + pos] = j0 + c;
-            cand_val[list + pos] = __float_as_uint(v[u][c]);
+            li[pos] = j_lo + u * kLoadRowElems + threadIdx.x * 4 + c;
+            lv[pos] = __float_as_uint(v[u][c]);
           }
           ++pos;
         }
-      }
-    }
   }
-  __syncthreads();
-  uint32_t *gh = hist + (uint64_t)w.p * kTopkHistWords + kHist1 + (LISTED ? (G >> kShift1) : 0u);
-  for (int b = threadIdx.x; b < kLocalBins; b += kLoadThreads)
-    if (h[b]) atomicAdd(&gh[b], h[b]);   // (LISTED: bins past the last one hold nothing)
 }
 
 // The selection state of partition p after `LEVEL` levels in sel[0] (prefix / threshold key)
@@ -646,11 +686,10 @@ __device__ inline void keys4(const float *part, uint32_t j, uint32_t d, uint32_t
 
 // LEVEL 2: keys whose top 11 bits equal the prefix, histogram of the next 10 bits.
 // LEVEL 3: keys whose top 21 bits equal the prefix, histogram of the last 10 bits.
-// LEVEL 1 (long form behind the short-list form only): the keys below the partition's guess,
-// which the load pass left out of the level-1 histogram.
+// LEVEL 1 (long form behind the short-list form only, whose load pass counts nothing): all keys.
 template <int LEVEL>
 __device__ inline void topk_hist_body(const Geo &g, const float *buf, uint32_t *hist, uint32_t *state, uint32_t n_groups,
-                                      int gated, const uint32_t *guess = nullptr) {
+                                      int gated) {
   constexpr int kBins = LEVEL == 1 ? kBins1 : kBins23;
   __shared__ uint32_t h[kBins];
   __shared__ uint32_t scan[kThreads];
@@ -660,7 +699,6 @@ __device__ inline void topk_hist_body(const Geo &g, const float *buf, uint32_t *
     if (gated && !long_form(state, w.p)) continue;
     for (int b = threadIdx.x; b < kBins; b += kThreads) h[b] = 0;
     if constexpr (LEVEL == 1) {
-      const uint32_t G = guess[w.p];
       __syncthreads();
       const float *part1 = buf + g.part_base(w.p);
       for (uint32_t tile = w.tile_lo; tile < w.tile_hi; ++tile) {
@@ -670,7 +708,7 @@ __device__ inline void topk_hist_body(const Geo &g, const float *buf, uint32_t *
           keys4(part1, tile * kTile + c * (kThreads * 4) + threadIdx.x * 4, w.d, key, &n);
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if ((uint32_t)e < n && key[e] < G) atomicAdd(&h[key[e] >> kShift1], 1u);
+            if ((uint32_t)e < n) atomicAdd(&h[key[e] >> kShift1], 1u);
         }
       }
       __syncthreads();
@@ -793,140 +831,379 @@ __device__ inline void topk_write_entry(const Geo &g, uint8_t *rec, uint32_t pos
   }
 }
 
-// Select pass: the radix select on the short list of one partition, then the record.  The list
-// in index order is the groups' runs in group order.  Wave w owns a stretch of consecutive
-// entries of that order, lane l of it the entries l, l + 64, ... of the stretch (neighbouring
-// lanes read neighbouring words), and keeps their values in registers throughout; positions in
-// the record follow from the counts of the waves before, of the rounds before and of the lanes
-// before.  A list shorter than k or longer than its room leaves the partition to the long form.
-// `shares` workgroups take a partition, four up to 64 partitions, two up to 128: each works the
-// selection out for itself and writes its share of the rounds (measured together with the guess
-// taken two levels deep and the runs requested before the list's length is looked at: a step of 3
-// workers on 0.3 M elements 153 -> 146 us, of 8 workers on 25.6 M elements 927 -> 911 us).
+// The long form of one partition by one workgroup of kSelThreads: three histogram passes, a pass that
+// counts per wave, a pass that writes; wave w takes the w-th stretch of the partition.  h: LDS,
+// kBins1 words.  Every element is read five times by one compute unit: a worker call on 1 M elements, all
+// zero or of one magnitude, takes 0.36 ms, of sixteen magnitudes 0.54 ms (the resident kernel below 0.71 ms),
+// on 64 M elements of one magnitude 0.51 ms (2.1 ms).
 template <bool HALF>
-__global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, uint32_t *state,
-                                                                       const uint32_t *hist, const uint32_t *groupcnt,
-                                                                       const uint32_t *cand_idx, const uint32_t *cand_val,
-                                                                       uint8_t *payload, int zero_selected, uint32_t shares) {
+__device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *buf_part, uint8_t *payload, int zero_selected,
+                                  uint32_t *h, uint32_t *scan, uint32_t *sel) {
   constexpr int kWaves = kSelThreads / 64;
-  __shared__ uint32_t h[kBins23];
-  __shared__ uint32_t vstart[kSelThreads + 1];  // entries of the list before group t's run
-  __shared__ uint32_t goff[kSelThreads];        // where group t's run sits in the list
-  __shared__ uint32_t scan[kWaves];
-  __shared__ uint32_t sel[2];
-  __shared__ uint32_t wave_gt[kWaves], wave_eq[kWaves];
-  const uint32_t p = __builtin_amdgcn_readfirstlane(blockIdx.x / shares), share = __builtin_amdgcn_readfirstlane(blockIdx.x % shares);
-  const uint32_t groups_per_part = (uint32_t)cdiv(g.tiles_per_part, kTpgLoad);            // at most kSelThreads
-  const uint32_t n_groups_p = (uint32_t)cdiv(cdiv(g.part_size(p), kTile), kTpgLoad);
-  // (the runs are requested together with the length, before the check of it)
-  uint2 run = make_uint2(0u, 0u);
-  if (threadIdx.x < n_groups_p) run = reinterpret_cast<const uint2 *>(groupcnt)[(uint64_t)p * groups_per_part + threadIdx.x];
-  const uint32_t n = __builtin_amdgcn_readfirstlane(state[p * 8 + kStListLen]);
-  const uint32_t k = (uint32_t)k_of_device(g, p);
-  if (n < k || n > kTopkListCap) {
-    if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
-    return;
-  }
-  {
-    const uint32_t c = run.y;
-    goff[threadIdx.x] = run.x;
-    uint32_t total;
-    vstart[threadIdx.x] = block_exclusive_scan<kSelThreads>(c, scan, &total);
-    if (threadIdx.x == 0) vstart[kSelThreads] = n;
-  }
-  __syncthreads();
-  const uint32_t rounds = (uint32_t)cdiv(n, kSelThreads);  // at most kSelPer
-  const uint32_t emit_lo = __builtin_amdgcn_readfirstlane(rounds * share / shares);
-  const uint32_t emit_hi = __builtin_amdgcn_readfirstlane(rounds * (share + 1) / shares);   // the rounds this workgroup writes
-  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const uint32_t first = wave * rounds * 64 + lane;        // the thread's entries: first + 64 i, i < rounds
-  const uint32_t cnt = first < n ? (uint32_t)cdiv(n - first, 64) < rounds ? (uint32_t)cdiv(n - first, 64) : rounds : 0u;
-  // the group whose run holds the first entry: the last one that starts at or before it
-  uint32_t group0 = 0;
-  if (cnt) {
-    uint32_t a = 0, b = kSelThreads;  // vstart[a] <= first < vstart[b] (vstart[kSelThreads] = n > first)
-    while (b - a > 1) {
-      const uint32_t m = (a + b) >> 1;
-      if (vstart[m] <= first) a = m; else b = m;
-    }
-    group0 = a;
-  }
-  const uint64_t list = (uint64_t)p * kTopkListCap;
-  // Place in the list of an entry of the order.  The run of the current group is kept in
-  // registers; LDS is read only when the walk crosses into a later group.
-  struct Walk {
-    uint32_t group, begin, end, off;  // entries [begin, end) of the order sit at off..
-  };
-  auto walk_to = [&](Walk &w, uint32_t entry) {
-    while (entry >= w.end) {
-      ++w.group;
-      w.begin = w.end;
-      w.end = vstart[w.group + 1];
-      w.off = goff[w.group];
-    }
-    return w.off + (entry - w.begin);
-  };
-  const Walk walk0{group0, vstart[group0], vstart[group0 + 1], goff[group0]};
-  // every load is issued whether or not the entry exists (entry 0 of the list stands in), so
-  // none of them is waited for before the last is on its way
-  uint32_t bits[kSelPer], where[kSelPer];   // value and index of the thread's entries
-  auto key = [&](int i) { return bits[i] & 0x7fffffffu; };
-  {
-    Walk w = walk0;
+  constexpr uint32_t kRow = 256, kAhead = 4;   // elements a wave takes at once; rows in flight
+  __shared__ uint32_t wave_cnt[2][kWaves];
+  const uint32_t d = g.part_size(p);
+  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const uint32_t seg = (uint32_t)cdiv(cdiv(d, kWaves), kRow) * kRow;
+  const uint32_t lo = wave * seg < d ? wave * seg : d, hi = lo + seg < d ? lo + seg : d;
+  const TileBuf b(buf_part, d * 4);
+  // visit(j, bits): the wave's elements in order, four consecutive ones a lane, kAhead rows requested at once
+  auto walk = [&](auto visit) {
+#pragma unroll 1
+    for (uint32_t r0 = lo; r0 < hi; r0 += kAhead * kRow) {
+      u32x4 x[kAhead];
 #pragma unroll
-    for (int i = 0; i < kSelPer; ++i) {
-      bits[i] = 0;
-      where[i] = 0;
-      if ((uint32_t)i >= rounds) continue;   // (the same for all threads)
-      const uint32_t at = (uint32_t)i < cnt ? walk_to(w, first + 64 * i) : 0u;
-      bits[i] = cand_val[list + at];
-      if ((uint32_t)i >= emit_lo && (uint32_t)i < emit_hi) where[i] = cand_idx[list + at];
-    }
-  }
-  // level 1 is known from the histogram of the whole partition
-  pick_bin<kBins1, kBits1, kSelThreads>(hist + (uint64_t)p * kTopkHistWords + kHist1, k, 0, scan, sel);
-  const uint32_t b1 = sel[0], k_rem1 = sel[1];
-  __syncthreads();
-  levels23_in_registers<kSelPer, kSelThreads>(bits, cnt, rounds, b1, k_rem1, h, scan, sel);
-  const uint32_t T = sel[0], r = sel[1];
-  if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
-  // keys above T and equal to T in the waves before this one
-  {
-    uint32_t n_gt = 0, n_eq = 0;
+      for (uint32_t q = 0; q < kAhead; ++q) x[q] = b.load16((r0 + q * kRow + lane * 4) * 4, 0);
 #pragma unroll
-    for (int i = 0; i < kSelPer; ++i) {
-      if ((uint32_t)i >= rounds) break;
-      n_gt += (uint32_t)i < cnt && key(i) > T;
-      n_eq += (uint32_t)i < cnt && key(i) == T;
+      for (uint32_t q = 0; q < kAhead; ++q) {
+        const uint32_t v[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
+        visit(r0 + q * kRow + lane * 4, v);
+      }
     }
-    n_gt = wave_sum_u32(n_gt);
-    n_eq = wave_sum_u32(n_eq);
-    if (lane == 0) { wave_gt[wave] = n_gt; wave_eq[wave] = n_eq; }
+  };
+  uint32_t prefix = 0, rem = k;
+#pragma unroll 1
+  for (int level = 1; level <= 3; ++level) {
+    const int hi_shift = level == 1 ? 31 : level == 2 ? kShift1 : kShift2, lo_shift = level == 1 ? kShift1 : level == 2 ? kShift2 : 0;
+    const uint32_t mask = level == 1 ? kBins1 - 1 : kBins23 - 1;
+    __syncthreads();
+    for (int q = threadIdx.x; q < kBins1; q += kSelThreads) h[q] = 0;
+    __syncthreads();
+    walk([&](uint32_t j, const uint32_t v[4]) {
+      // a row of one bin (zeros, equal magnitudes: the usual reasons to be here) is added at once
+      const uint32_t key0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(v[0] & 0x7fffffffu));
+      uint32_t differ = j + 3 < hi ? 0u : 1u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) differ |= ((v[e] & 0x7fffffffu) ^ key0) >> lo_shift;
+      if (__ballot(differ != 0) == 0) {
+        if (lane == 0 && (key0 >> hi_shift) == prefix) atomicAdd(&h[(key0 >> lo_shift) & mask], kRow);
+        return;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t key = v[e] & 0x7fffffffu;
+        if (j + e < hi && (key >> hi_shift) == prefix) atomicAdd(&h[(key >> lo_shift) & mask], 1u);
+      }
+    });
+    __syncthreads();
+    if (level == 1) pick_bin<kBins1, kBits1, kSelThreads>(h, rem, 0, scan, sel);
+    else pick_bin<kBins23, kBits23, kSelThreads>(h, rem, prefix, scan, sel);
+    prefix = sel[0];
+    rem = sel[1];
   }
+  const uint32_t T = prefix, r = rem;
+  uint32_t n_gt = 0, n_eq = 0;   // (the same in every lane)
+  walk([&](uint32_t j, const uint32_t v[4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t key = v[e] & 0x7fffffffu;
+      n_gt += (uint32_t)__popcll(__ballot(j + e < hi && key > T));
+      n_eq += (uint32_t)__popcll(__ballot(j + e < hi && key == T));
+    }
+  });
+  if (lane == 0) { wave_cnt[0][wave] = n_gt; wave_cnt[1][wave] = n_eq; }
   __syncthreads();
   uint32_t gt_base = 0, eq_base = 0;
-#pragma unroll
-  for (int v = 0; v < kWaves; ++v) {
-    gt_base += (uint32_t)v < wave ? wave_gt[v] : 0u;
-    eq_base += (uint32_t)v < wave ? wave_eq[v] : 0u;
-  }
+  for (uint32_t q = 0; q < wave; ++q) { gt_base += wave_cnt[0][q]; eq_base += wave_cnt[1][q]; }
   uint8_t *rec = payload + (uint64_t)p * g.stride;
-  float *buf_part = buf + g.part_base(p);
-  const uint64_t lanes_before = (1ull << lane) - 1ull;
-  // which entries are kept and where they go
+  walk([&](uint32_t j, const uint32_t v[4]) {
+    uint32_t both = 0;   // above T | equal to T << 16
 #pragma unroll
-  for (int i = 0; i < kSelPer; ++i) {
-    if ((uint32_t)i < emit_hi) {   // (the same for all threads)
-      const bool valid = (uint32_t)i < cnt;
-      const uint64_t gtm = __ballot(valid && key(i) > T), eqm = __ballot(valid && key(i) == T);
-      const uint32_t gt_before = gt_base + __popcll(gtm & lanes_before);
-      const uint32_t eq_before = eq_base + __popcll(eqm & lanes_before);
-      const bool t = valid && (key(i) > T || (key(i) == T && eq_before < r));
-      gt_base += __popcll(gtm);
-      eq_base += __popcll(eqm);
-      if (t && (uint32_t)i >= emit_lo) topk_write_entry<HALF>(g, rec, gt_before + (eq_before < r ? eq_before : r), where[i], __uint_as_float(bits[i]), buf_part, zero_selected);
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t key = v[e] & 0x7fffffffu;
+      both += j + e < hi ? (key > T ? 1u : 0u) + (key == T ? 0x10000u : 0u) : 0u;
+    }
+    if (__ballot((both & 0xffffu) != 0 || (both != 0 && eq_base < r)) == 0) return;   // nothing to write (and no tie to count any more)
+    const uint32_t incl = wave_inclusive_scan_u32(both), ex = incl - both;
+    uint32_t gt = gt_base + (ex & 0xffffu), eq = eq_base + (ex >> 16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t key = v[e] & 0x7fffffffu;
+      const bool above = j + e < hi && key > T, tie = j + e < hi && key == T;
+      if (above || (tie && eq < r)) topk_write_entry<HALF>(g, rec, gt + (eq < r ? eq : r), j + e, __uint_as_float(v[e]), buf_part, zero_selected);
+      gt += above;
+      eq += tie;
+    }
+    const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+    gt_base += all & 0xffffu;
+    eq_base += all >> 16;
+  });
+}
+
+// The entries of a list in the registers of a workgroup of kSelThreads, PER a thread of which `rounds` (a
+// multiple of 4, the same for all threads) are in use: rel[i] = magnitude key - guess + 1 and the value's
+// sign bit, 0 where there is no entry.
+constexpr uint32_t kRelMask = 0x7fffffffu;
+// body(i) for the entries in use, four at a time.
+template <int PER, class BODY>
+__device__ __forceinline__ void each_entry(uint32_t rounds, BODY body) {
+  if constexpr (PER > 4) each_entry<PER - 4>(rounds, body);
+  if ((uint32_t)(PER - 4) < rounds) {
+    body(std::integral_constant<int, PER - 4>{});
+    body(std::integral_constant<int, PER - 3>{});
+    body(std::integral_constant<int, PER - 2>{});
+    body(std::integral_constant<int, PER - 1>{});
+  }
+}
+
+// pick_bin() for a histogram of 4 bins a thread or more, with two barriers: `scan` (a word a wave) and
+// sel must not be in use.
+template <int BINS>
+__device__ inline void pick_bin_once(const uint32_t *h, uint32_t k_rem, uint32_t *scan, uint32_t *sel) {
+  constexpr int kPer = BINS / kSelThreads, kWaves = kSelThreads / 64;
+  uint32_t cnt[kPer], local = 0;
+  if constexpr (kPer % 4 == 0) {
+#pragma unroll
+    for (int i = 0; i < kPer; i += 4) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(h + (BINS - 4 - (int)threadIdx.x * kPer - i));
+      cnt[i] = x.w; cnt[i + 1] = x.z; cnt[i + 2] = x.y; cnt[i + 3] = x.x;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) cnt[i] = h[BINS - 1 - (int)threadIdx.x * kPer - i];
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) local += cnt[i];
+  const uint32_t incl = wave_inclusive_scan_u32(local), wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) scan[wave] = incl;
+  __syncthreads();
+  uint32_t run = incl - local;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) run += (uint32_t)w < wave ? scan[w] : 0u;
+  if (run < k_rem && k_rem <= run + local) {
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      if (run < k_rem && k_rem <= run + cnt[i]) {
+        sel[0] = BINS - 1 - (threadIdx.x * kPer + i);
+        sel[1] = k_rem - run;
+      }
+      run += cnt[i];
     }
   }
+  __syncthreads();
+}
+
+// LDS of a select workgroup.
+struct SelectLds {
+  uint32_t h[kSelBins];            // first level of the threshold; the passes for rarer cases
+  uint32_t h2[1024];               // second level
+  uint32_t bitmap[kShareWords];
+  uint16_t before[kShareWords];    // bits set before a word of it
+  uint32_t scan[3][kSelThreads / 64];
+  uint32_t sel[3][2];
+  uint32_t tie[64], tied;          // a few entries equal to the threshold
+};
+static_assert(kSelThreads == 1024, "a bin a thread in the levels of 1024 bins");
+
+// The rel R of rank k and the number r of entries equal to it that are kept, for all threads; *ties:
+// how many entries equal R.  Keys are rarely an octave above the guess: bins of 1024 keys from there
+// up, then the keys of one bin; else three levels over the whole range.  h and h2 are zero, and a barrier
+// has been since.
+template <int PER>
+__device__ inline void list_threshold(const uint32_t (&rel)[PER], uint32_t rounds, uint32_t k, SelectLds &l, uint32_t *R, uint32_t *r,
+                                      uint32_t *ties) {
+  each_entry<PER>(rounds, [&](auto i) {
+    const uint32_t x = rel[i] & kRelMask, bin = x >> 10;
+    if (x) atomicAdd(&l.h[bin < (uint32_t)kSelBins ? bin : kSelBins - 1u], 1u);
+  });
+  __syncthreads();
+  pick_bin_once<kSelBins>(l.h, k, l.scan[0], l.sel[0]);
+  uint32_t prefix = l.sel[0][0], rem = l.sel[0][1];
+  if (prefix == (uint32_t)kSelBins - 1) {   // (uniform) past the octave: the top 21 bits in two steps
+    rem = k;
+#pragma unroll 1
+    for (int shift = 20; shift >= 10; shift -= 10) {
+      const uint32_t above = prefix;
+      __syncthreads();
+      for (int b = threadIdx.x; b < 2048; b += kSelThreads) l.h[b] = 0;
+      __syncthreads();
+      each_entry<PER>(rounds, [&](auto i) {
+        const uint32_t x = rel[i] & kRelMask;
+        if (x && (shift == 20 || (x >> 20) == above)) atomicAdd(&l.h[(x >> shift) & (shift == 20 ? 2047u : 1023u)], 1u);
+      });
+      __syncthreads();
+      if (shift == 20) pick_bin<2048, 11, kSelThreads>(l.h, rem, 0, l.scan[1], l.sel[1]);
+      else pick_bin<1024, 10, kSelThreads>(l.h, rem, prefix, l.scan[1], l.sel[1]);
+      prefix = l.sel[1][0];
+      rem = l.sel[1][1];
+    }
+  }
+  each_entry<PER>(rounds, [&](auto i) {
+    const uint32_t x = rel[i] & kRelMask;
+    if (x && (x >> 10) == prefix) atomicAdd(&l.h2[x & 1023u], 1u);
+  });
+  __syncthreads();
+  pick_bin_once<1024>(l.h2, rem, l.scan[2], l.sel[2]);
+  *R = prefix << 10 | l.sel[2][0];
+  *r = l.sel[2][1];
+  *ties = l.h2[l.sel[2][0]];
+}
+
+// The index of the r-th of the `ties` entries equal to R in index order (r < ties).  A few of them, as
+// the sums of halves often give, are collected in LDS and each one's rank is counted; more take a
+// radix select on the indices (below 2^28: 10 + 10 + 8 bits).
+template <int PER>
+__device__ inline uint32_t last_tie(const uint32_t (&rel)[PER], const uint32_t (&where)[PER], uint32_t rounds, uint32_t R, uint32_t r,
+                                    uint32_t ties, SelectLds &l) {
+  constexpr uint32_t kFew = 64;
+  if (ties <= kFew) {   // (uniform)
+    each_entry<PER>(rounds, [&](auto i) {
+      if ((rel[i] & kRelMask) == R) l.tie[atomicAdd(&l.tied, 1u)] = where[i];
+    });
+    __syncthreads();
+    if (threadIdx.x < ties) {
+      const uint32_t mine = l.tie[threadIdx.x];
+      uint32_t rank = 1;
+      for (uint32_t t = 0; t < ties; ++t) rank += l.tie[t] < mine;
+      if (rank == r) l.sel[0][0] = mine;
+    }
+    __syncthreads();
+    return l.sel[0][0];
+  }
+  uint32_t prefix = 0, rem = ties - r + 1;   // (pick_bin counts from the largest down)
+#pragma unroll 1
+  for (int level = 0; level < 3; ++level) {
+    const int hi_shift = level == 0 ? 28 : level == 1 ? 18 : 8, lo_shift = level == 0 ? 18 : level == 1 ? 8 : 0;
+    __syncthreads();
+    l.h[threadIdx.x] = 0;
+    __syncthreads();
+    each_entry<PER>(rounds, [&](auto i) {
+      if ((rel[i] & kRelMask) == R && (where[i] >> hi_shift) == prefix)
+        atomicAdd(&l.h[(where[i] >> lo_shift) & (level == 2 ? 255u : 1023u)], 1u);
+    });
+    __syncthreads();
+    if (level == 2) pick_bin<256, 8, kSelThreads>(l.h, rem, prefix, l.scan[0], l.sel[0]);
+    else pick_bin<1024, 10, kSelThreads>(l.h, rem, prefix, l.scan[0], l.sel[0]);
+    prefix = l.sel[0][0];
+    rem = l.sel[0][1];
+  }
+  return prefix;
+}
+
+// Select pass.  `shares` workgroups take a partition: each keeps the whole list in registers and works out
+// which entries are kept, marks those of its share of the indices in a bitmap in LDS, and writes
+// them at the places that the bits before them give.  A list shorter than k or longer than its room
+// leaves the partition to the long form.  Bound by the vector instructions per entry (sixteen waves on
+// one compute unit) and some twenty barriers.  (The form before this one took the list in index
+// order, run by run of the load pass's workgroups, through a table in LDS, with three radix levels
+// and the idle long form behind it: 28 against 19 us on 25 partitions of 1 M elements, k = 1 %; 23 against
+// 15.5 us on 53 partitions of 2 M f16 elements, k = 0.1 %.)
+template <bool HALF>
+__global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, uint32_t *state, TopkShared sh, TopkLists lists,
+                                                                       uint8_t *payload, int zero_selected, uint32_t shares) {
+  __shared__ __align__(16) SelectLds l;
+  static_assert(kSelPer <= 32 && kTopkListCap < 65536, "one bit an entry, 16 bits a place");
+  // (workgroups go to the 8 XCDs in turn: the shares of a partition, which read the same list, to the same one)
+  const uint32_t at_xcd = blockIdx.x / kXcds;
+  const uint32_t p = __builtin_amdgcn_readfirstlane(at_xcd / shares * kXcds + blockIdx.x % kXcds), share = __builtin_amdgcn_readfirstlane(at_xcd % shares);
+  if (p >= g.P) return;
+  const uint32_t d = g.part_size(p);
+  const uint32_t range = (uint32_t)cdiv(cdiv(g.part_elems, shares), 32) * 32;
+  const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
+  const uint32_t n = __builtin_amdgcn_readfirstlane(*sh.length(p));
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * p]);
+  if (lo >= d) return;
+  const uint32_t k = (uint32_t)k_of_device(g, p);
+  if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
+  float *buf_part = buf + g.part_base(p);
+  if (n < k || n > kTopkListCap) {
+    if (share != 0) return;
+    if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
+    if (g.part_elems <= kAloneElems) topk_alone<HALF>(g, p, k, buf_part, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
+    return;
+  }
+  // entry 4 (i * kSelThreads + thread) + c of the list is the thread's entry 4 i + c; all loads of a kind are
+  // requested before the first is used, the values first
+  const uint32_t rounds = 4 * (uint32_t)cdiv(n, 4 * kSelThreads);   // at most kSelPer
+  uint32_t rel[kSelPer], where[kSelPer];
+  {
+    const TileBuf vb(lists.val(p), n * 4), ib(lists.idx(p), n * 4);
+    auto load = [&](const TileBuf &b, uint32_t (&to)[kSelPer]) {
+#pragma unroll
+      for (int i = 0; i < kSelPer; i += 4) {
+        u32x4 x{};
+        if ((uint32_t)i < rounds) x = b.load16(threadIdx.x * 16, i * kSelThreads * 4);   // (the same for all threads)
+        to[i] = x.x; to[i + 1] = x.y; to[i + 2] = x.z; to[i + 3] = x.w;
+      }
+    };
+    load(vb, rel);
+    load(ib, where);
+  }
+  const uint32_t words = range / 32;   // (at most kShareWords)
+  {
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    for (uint32_t b = threadIdx.x; b < kSelBins / 4; b += kSelThreads) reinterpret_cast<uint4 *>(l.h)[b] = zero;
+    l.h2[threadIdx.x] = 0;
+    if (threadIdx.x == 0) l.tied = 0;
+    for (uint32_t b = threadIdx.x; 4 * b < words; b += kSelThreads) reinterpret_cast<uint4 *>(l.bitmap)[b] = zero;
+  }
+  __syncthreads();
+  each_entry<kSelPer>(rounds, [&](auto i) {
+    constexpr uint32_t first = (i / 4) * (4 * kSelThreads) + i % 4;
+    rel[i] = first + threadIdx.x * 4 < n ? (key_of(__uint_as_float(rel[i])) - G + 1u) | (rel[i] & ~kRelMask) : 0u;
+  });
+  uint32_t R, r, ties;
+  list_threshold<kSelPer>(rel, rounds, k, l, &R, &r, &ties);
+  uint32_t last = 0xffffffffu;   // of the entries equal to R, those up to this index are kept
+  if (ties != r) last = last_tie<kSelPer>(rel, where, rounds, R, r, ties, l);
+  uint32_t below = 0;   // kept entries of the shares before this one
+  uint32_t mine = 0;    // bit i: the thread's entry i is kept and in this share
+  auto mark = [&](auto is_kept) {
+    each_entry<kSelPer>(rounds, [&](auto i) {
+      const bool kept = is_kept(rel[i] & kRelMask, where[i]);
+      const uint32_t at = where[i] - lo;
+      below += kept && where[i] < lo;
+      if (kept && at < range) {
+        mine |= 1u << i;
+        atomicOr(&l.bitmap[at >> 5], 1u << (at & 31u));
+      }
+    });
+  };
+  if (ties == r) mark([&](uint32_t x, uint32_t) { return x >= R; });
+  else mark([&](uint32_t x, uint32_t j) { return x > R || (x == R && j <= last); });
+  __syncthreads();
+  // bits before each word: thread t owns words per * t .. per * t + per - 1
+  const uint32_t per = 4 * (uint32_t)cdiv(words, 4 * kSelThreads);
+  uint32_t set = 0;
+  for (uint32_t q = 0; q < per; q += 4) {
+    const uint32_t w = threadIdx.x * per + q;
+    if (w < words) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);   // (past the last word: zeros up to the multiple of 4)
+      set += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
+    }
+  }
+  // (one scan for both: each total is at most kTopkListCap)
+  const uint32_t both = set | below << 16, incl = wave_inclusive_scan_u32(both), wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) l.scan[1][wave] = incl;
+  __syncthreads();
+  uint32_t all = 0, at = incl - both;
+#pragma unroll
+  for (uint32_t w = 0; w < kSelThreads / 64; ++w) {
+    const uint32_t x = l.scan[1][w];
+    at += w < wave ? x : 0u;
+    all += x;
+  }
+  at &= 0xffffu;
+  for (uint32_t q = 0; q < per; q += 4) {
+    const uint32_t w = threadIdx.x * per + q;
+    if (w < words) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);
+      const uint32_t a1 = at + (uint32_t)__popc(x.x), a2 = a1 + (uint32_t)__popc(x.y), a3 = a2 + (uint32_t)__popc(x.z);
+      *reinterpret_cast<uint2 *>(l.before + w) = make_uint2(at | a1 << 16, a2 | a3 << 16);
+      at = a3 + (uint32_t)__popc(x.w);
+    }
+  }
+  __syncthreads();
+  const uint32_t pos0 = all >> 16;
+  uint8_t *rec = payload + (uint64_t)p * g.stride;
+  each_entry<kSelPer>(rounds, [&](auto i) {
+    if ((mine >> i) & 1u) {
+      const uint32_t o = where[i] - lo, w = o >> 5;
+      const uint32_t pos = pos0 + l.before[w] + (uint32_t)__popc(l.bitmap[w] & ((1u << (o & 31u)) - 1u));
+      const uint32_t bits = ((rel[i] & kRelMask) - 1u + G) | (rel[i] & ~kRelMask);
+      topk_write_entry<HALF>(g, rec, pos, where[i], __uint_as_float(bits), buf_part, zero_selected);
+    }
+  });
 }
 
 // Ordered compaction of the long form.  Thread t of a tile owns 16 consecutive elements, so
@@ -1043,16 +1320,16 @@ __device__ inline void topk_grid_barrier(uint32_t *counter, uint32_t round, uint
   __threadfence();
 }
 
-// The long form behind the short-list form, as one launch: returns at once unless some
-// partition was left to it (the usual case: one launch and one read instead of four of each),
-// else completes their level-1 histograms and runs the four passes for those partitions, with
-// the whole grid meeting in between.
+// The long form behind the short-list form for partitions that are too large for one workgroup, as one
+// launch: returns at once unless some partition was left to it (the usual case: one launch and one
+// read instead of five of each), else runs the five passes for those partitions, with the whole
+// grid meeting in between.
 // The grid is resident as a whole (the host sizes it by occupancy).  `counter`: zero at launch.
 template <bool HALF>
 __global__ __launch_bounds__(kThreads) void topk_long_form_kernel(Geo g, float *buf, uint32_t *hist, uint32_t *state,
                                                                   uint32_t *tilecnt, uint8_t *payload, int zero_selected,
                                                                   uint32_t n2, uint32_t n3, uint32_t nc, uint32_t ne,
-                                                                  const uint32_t *guess, uint32_t *counter, uint32_t *status) {
+                                                                  uint32_t *counter, uint32_t *status) {
   __shared__ uint32_t any;
   if (threadIdx.x == 0) any = 0;
   __syncthreads();
@@ -1060,7 +1337,7 @@ __global__ __launch_bounds__(kThreads) void topk_long_form_kernel(Geo g, float *
     if (state[p * 8 + kStLong]) any = 1;
   __syncthreads();
   if (!any) return;   // (the same answer in every workgroup: the flags were written by the kernel before)
-  topk_hist_body<1>(g, buf, hist, state, n3, 1, guess);   // (groups of one tile, as level 3)
+  topk_hist_body<1>(g, buf, hist, state, n3, 1);   // (groups of one tile, as level 3)
   topk_grid_barrier(counter, 1, status);
   topk_hist_body<2>(g, buf, hist, state, n2, 1);
   topk_grid_barrier(counter, 2, status);
@@ -1084,7 +1361,7 @@ hipError_t topk_tile_starts(const Geo &g, const uint8_t *payload, bool half, uin
   m.stride = g.stride;
   m.half = half ? 1 : 0;
   m.group_shift = tile_shift;
-  topk_starts_kernel<<<dim3((uint32_t)cdiv(g.k_cap + 1, kThreads), g.P, 1), kThreads, 0, stream>>>(g, m, table, nullptr);
+  topk_starts_kernel<<<dim3((uint32_t)cdiv(g.k_cap + 1, kThreads), g.P, 1), kThreads, 0, stream>>>(g, m, table);
   return hipGetLastError();
 }
 
@@ -1092,67 +1369,77 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
                        uint8_t *payload, const Workspace &ws, hipStream_t stream) {
   uint32_t *hist = ws.at<uint32_t>(ws.lay.hist);
   uint32_t *state = ws.at<uint32_t>(ws.lay.state);
-  uint32_t *guess = ws.at<uint32_t>(ws.lay.guess);
-  uint32_t *tilecnt = ws.at<uint32_t>(ws.lay.tilecnt);   // also the per-group (place, count) of the short lists
+  uint32_t *tilecnt = ws.at<uint32_t>(ws.lay.tilecnt);
   float *dense = ws.at<float>(ws.lay.dense);
   // the vector being compressed ends up in the residual buffer (error feedback) or the workspace
   float *buf = src.residual ? src.residual : dense;
   const bool half = prm.kind == BPC_TOPK16;
-  uint32_t *cand_idx = ws.at<uint32_t>(ws.lay.cand);
-  uint32_t *cand_val = cand_idx + (size_t)kTopkListCap * g.P;
-  // the short-list form wants room for the k winners and as many again; the select pass gives
-  // each group of tiles of a partition one thread
-  // (and the long form behind it is one resident kernel: its grid comes from the occupancy query)
+  const int zero_selected = src.residual != nullptr;
+  const TopkLists lists{ws.at<uint32_t>(ws.lay.cand), g.P};
+  // behind the short-list form of large partitions stands the long form as one resident kernel: its grid
+  // comes from the occupancy query
   const void *long_fn = half ? reinterpret_cast<const void *>(&topk_long_form_kernel<true>)
                              : reinterpret_cast<const void *>(&topk_long_form_kernel<false>);
   static PerDevice cache[2];
-  int capacity[2] = {0, 0};
-  capacity[half] = cache[half].get([&] { return cluster_capacity(long_fn, kThreads, 0); });
-  const int short_list = g.k_cap <= kTopkListCap / 2 && cdiv(g.tiles_per_part, kTpgLoad) <= (uint64_t)kSelThreads &&
-                         capacity[half] > 0;
-  const uint32_t sample_grid = g.P > 64 ? g.P : 64, load_grid = group_count(g, kTpgLoad);
-  auto first_two = [&](auto s_sample, auto s_load) {
-    topk_sample_kernel<<<sample_grid, kThreads, 0, stream>>>(g, s_sample, hist, state, guess, short_list, ws.status());
-    using Load = decltype(s_load);
-    if (short_list) topk_load_hist1_kernel<Load, true><<<load_grid, kLoadThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
-    else topk_load_hist1_kernel<Load, false><<<load_grid, kLoadThreads, 0, stream>>>(g, s_load, buf, hist, state, guess, tilecnt, cand_idx, cand_val);
+  const bool gated = g.part_elems > kAloneElems;
+  const int capacity = gated ? cache[half].get([&] { return cluster_capacity(long_fn, kThreads, 0); }) : 0;
+  // the short-list form wants room for the k winners and as many again
+  const bool short_list = g.k_cap <= kTopkListCap / 2 && (!gated || capacity > 0);
+  const uint32_t load_grid = group_count(g, kTpgLoad);
+  TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status()};
+  sh.lengths = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(sh.pairs) + TopkShared::pairs_bytes(g.P));
+  hipError_t e = hipSuccess;
+  if (short_list) {
+    // under capture every replay would carry the same tag: the guesses are cleared in front
+    const bool captured = launch_tag(stream, &sh.tag);
+    if (captured) {
+      e = fill_zero(sh.pairs, 16ull * g.P, stream);
+      if (e == hipSuccess) e = fill_zero(sh.status, 8, stream);
+    }
+    if (e == hipSuccess && gated) e = fill_zero(hist, ws.lay.guess - ws.lay.hist, stream);   // (and the state words)
+  } else {
+    e = fill_zero(hist, ws.lay.guess - ws.lay.hist, stream);
+    if (e == hipSuccess) e = fill_zero(sh.status, 4, stream);
+  }
+  if (e != hipSuccess) return e;
+  auto load = [&](auto s) {
+    using Load = decltype(s);
+    const uint32_t guesses = has_begin_group<Load>::value ? 0u : g.P;
+    if (short_list) topk_load_kernel<Load, true><<<load_grid + guesses, kLoadThreads, 0, stream>>>(g, s, buf, hist, state, sh, lists);
+    else topk_load_kernel<Load, false><<<load_grid, kLoadThreads, 0, stream>>>(g, s, buf, hist, state, sh, lists);
   };
   if (src.grad) {
-    if (src.dtype == BPC_F16) {
-      GradSource<__half> s{(const __half *)src.grad, src.residual};
-      first_two(s, s);
-    } else {
-      GradSource<float> s{(const float *)src.grad, src.residual};
-      first_two(s, s);
-    }
+    if (src.dtype == BPC_F16) load(GradSource<__half>{(const __half *)src.grad, src.residual});
+    else load(GradSource<float>{(const float *)src.grad, src.residual});
   } else {
     // server: Delta straight from the n messages (they are taken to have the format of `prm`)
     uint32_t *starts = ws.at<uint32_t>(ws.lay.starts);
     const TopkMsgs m{src.msgs, src.residual, starts, (uint32_t)cdiv(g.tiles_per_part, kTpgLoad), g.k_cap, g.stride, half ? 1 : 0, 13};
-    float *samp = ws.at<float>(ws.lay.samp);
-    const hipError_t e = fill_zero(samp, sizeof(float) * kSample * g.P, stream);
-    if (e != hipSuccess) return e;
-    topk_starts_kernel<<<dim3((uint32_t)cdiv(g.k_cap + 1, kThreads), g.P, src.msgs.n), kThreads, 0, stream>>>(g, m, starts, samp);
-    first_two(TopkMsgsSampleSource{m, samp}, TopkMsgsGroupSource{m});
+    topk_server_prep_kernel<<<dim3(g.P, src.msgs.n + (short_list ? 1 : 0)), kPrepThreads, 0, stream>>>(g, m, starts, sh, state, short_list);
+    load(TopkMsgsGroupSource{m});
   }
-  const int zero_selected = src.residual != nullptr;
   if (short_list) {
-    // (as many workgroups as one round of them over the compute units takes, at most four a partition)
-    const uint32_t shares = 4 * g.P <= kSelGrid ? 4 : 2 * g.P <= kSelGrid ? 2 : 1;
-    if (half) topk_list_select_kernel<true><<<g.P * shares, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected, shares);
-    else topk_list_select_kernel<false><<<g.P * shares, kSelThreads, 0, stream>>>(g, buf, state, hist, tilecnt, cand_idx, cand_val, payload, zero_selected, shares);
+    // (as many workgroups as one round of them over the compute units takes)
+    const uint32_t of_xcd = (uint32_t)cdiv(g.P, kXcds);
+    uint32_t shares = 1;
+    while (shares < kMostShares && 2 * shares * of_xcd <= kCusOfXcd) shares *= 2;
+    const uint32_t least = (uint32_t)cdiv(g.part_elems, 32ull * kShareWords);
+    if (shares < least) shares = least;
+    if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, state, sh, lists, payload, zero_selected, shares);
+    else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, state, sh, lists, payload, zero_selected, shares);
+    if (!gated) return hipGetLastError();
   }
   const uint32_t n2 = group_count(g, kTpgHist2), n3 = group_count(g, kTpgHist3), nc = group_count(g, kTpgCount);
   const uint32_t ne = g.P * g.tiles_per_part;
   if (short_list) {
     // the long form for the partitions the short list could not take: one resident kernel
-    const uint32_t grid = (uint32_t)capacity[half] < kGatedGrid ? (uint32_t)capacity[half] : kGatedGrid;
+    const uint32_t grid = (uint32_t)capacity < kGatedGrid ? (uint32_t)capacity : kGatedGrid;
     uint32_t *counter = state + 8ull * g.P;
     uint32_t *status = ws.status();
-    hipError_t e = cluster_launch_begin(stream);
+    e = cluster_launch_begin(stream);
     if (e != hipSuccess) return e;
-    if (half) topk_long_form_kernel<true><<<grid, kThreads, 0, stream>>>(g, buf, hist, state, tilecnt, payload, zero_selected, n2, n3, nc, ne, guess, counter, status);
-    else topk_long_form_kernel<false><<<grid, kThreads, 0, stream>>>(g, buf, hist, state, tilecnt, payload, zero_selected, n2, n3, nc, ne, guess, counter, status);
+    if (half) topk_long_form_kernel<true><<<grid, kThreads, 0, stream>>>(g, buf, hist, state, tilecnt, payload, zero_selected, n2, n3, nc, ne, counter, status);
+    else topk_long_form_kernel<false><<<grid, kThreads, 0, stream>>>(g, buf, hist, state, tilecnt, payload, zero_selected, n2, n3, nc, ne, counter, status);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     return cluster_launch_end(stream);

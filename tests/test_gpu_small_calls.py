@@ -219,3 +219,41 @@ def test_topk_of_magnitudes_close_together_stays_on_the_short_list(gu, orc, geo,
         k = max(1, int(0.01 * min(pe, D - p * pe)))
         assert np.array_equal(got[p * stride:p * stride + 16 + 4 * k], ref[p * stride:p * stride + 16 + 4 * k]), p
     assert not _long_form(gu, geo, pb, D, ws).any()
+
+
+# partitions of one share and of several, larger than one workgroup takes alone (more than 4 M elements); values on
+# a grid give a few entries equal to the threshold (up to 64 are ranked one by one) or hundreds
+@pytest.mark.parametrize("kind", ["topk", "topk16"])
+@pytest.mark.parametrize("pe,D,grid", [(65536, 3 * 65536 + 777, 512.0), (65536, 40 * 65536 + 9, 16.0), (1_048_576, 1_048_576 + 70_001, 4096.0),
+                                       (1_048_576, 300_007, 64.0), (8_388_608, 8_388_608 + 5000, None)])
+def test_topk_select_ties_and_shares(gu, orc, geo, kind, pe, D, grid):
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=0.001)
+    rs = np.random.default_rng(D)
+    g = rs.standard_normal(D).astype(np.float32)
+    if grid is not None:
+        g = np.round(g * grid) / np.float32(grid)
+    else:
+        g[pe:] = 0.0   # the ragged last partition: zeros that fit its list
+    big = grid is None
+    for zeros in ((False, True) if big else (False,)):
+        if zeros:
+            g[:pe] = np.where(np.arange(pe) % 1000 == 0, g[:pe], 0.0)   # fewer non-zeros than k: too long for the list
+            g[:: 2000] = 0.0
+        res = np.zeros(D, np.float32)
+        ref = orc.compress(po, g, res)
+        rd, pay, ws = gu.to_dev(np.zeros(D, np.float32)), gu.new_payload(pb, D), gu.new_ws(pb, D)
+        ws.fill_(0xFF)
+        bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+        bpc.workspace_check(pb, D, ws)
+        assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+        stride, got = orc.partition_stride(po), gu.to_host(pay)
+        k_cap = max(1, int(0.001 * pe))
+        for p in range(-(-D // pe)):
+            k = max(1, int(0.001 * min(pe, D - p * pe)))
+            vals = 16 + 4 * (-(-k_cap // 4) * 4)
+            size = 4 if kind == "topk" else 2
+            for a, b in ((0, 16 + 4 * k), (vals, vals + size * k)):
+                assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
+        if big:
+            assert _long_form(gu, geo, pb, D, ws).tolist() == [zeros, False]
