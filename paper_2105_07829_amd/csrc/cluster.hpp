@@ -77,38 +77,6 @@ inline ClusterGeo make_cluster_geo(const Geo &g, uint32_t tile) {
   return c;
 }
 
-// Splits a gradient into the part the single-pass kernels take and the part left to the
-// multi-pass kernels.  `ragged_ok`: the single-pass kernel bounds its accesses to a shorter
-// last partition itself; otherwise it gets the full partitions only.
-struct SplitGeo {
-  bool single_pass;   // false: the partition size is not a multiple of the tile
-  Geo head;           // what the single-pass kernel takes (head.D may be 0)
-  Geo tail;           // the last, shorter partition as a one-partition gradient (tail.D may be 0)
-};
-inline SplitGeo split_geo(const Geo &g, uint32_t tile, bool ragged_ok) {
-  SplitGeo s;
-  s.single_pass = g.part_elems % tile == 0;
-  if (ragged_ok) {
-    s.head = g;
-    s.tail = g;
-    s.tail.D = 0;
-    s.tail.P = 0;
-    s.tail.n_tiles = 0;
-    return s;
-  }
-  const uint32_t p_full = (uint32_t)(g.D / g.part_elems);
-  s.head = g;
-  s.head.D = (uint64_t)p_full * g.part_elems;
-  s.head.P = p_full;
-  s.head.n_tiles = p_full * g.tiles_per_part;
-  s.tail = g;
-  s.tail.D = g.D - s.head.D;
-  s.tail.P = s.tail.D ? 1 : 0;
-  s.tail.n_tiles = (uint32_t)cdiv(s.tail.D, kTile);
-  s.tail.part0 = g.part0 + p_full;
-  return s;
-}
-
 // Host side: the arguments above count the resident workgroups of ONE kernel.  Two cluster
 // kernels running concurrently (different streams) would share the device, so launches are
 // chained: a launch on another stream than the one before first waits for an event recorded

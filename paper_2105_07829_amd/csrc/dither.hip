@@ -171,33 +171,20 @@ __global__ __launch_bounds__(kThreads) void dither_apply_kernel(Geo g, SRC src, 
   }
 }
 
-hipError_t dither_encode(const Geo &g_in, const bpc_params_t &prm_in, const Source &src_in, uint8_t *payload,
+hipError_t dither_encode(const Geo &g, const bpc_params_t &prm, const Source &src, uint8_t *payload,
                          const Workspace &ws, hipStream_t stream) {
-  // Full partitions that are a whole number of register tiles go to the single-pass kernel,
-  // a ragged last partition (or everything, if the shape does not fit) to the passes below.
-  // The single-pass kernels bound a shorter last partition through their buffer descriptors
-  // (dword granularity, so an odd number of f16 gradient elements is left to the passes below).
-  const bool ragged_ok = !(src_in.grad && src_in.dtype == BPC_F16 && (g_in.D & 1));
-  const SplitGeo sp = split_geo(g_in, src_in.grad ? kWTile : kSTile, ragged_ok);
-  Geo g = g_in;
-  Source src = src_in;
-  bpc_params_t prm = prm_in;
-  uint32_t *status = ws.status();
   // (the single-pass server handles up to 15 levels; beyond that it declines and the server
   // side takes the passes below)
-  const bool wide = prm_in.kind == BPC_DITHER && dither_planes(prm_in.levels) > 0;
-  if (sp.single_pass && sp.head.P > 0) {
+  const bool wide = prm.kind == BPC_DITHER && dither_planes(prm.levels) > 0;
+  // Partitions that are a whole number of register tiles go to the single-pass kernel (which bounds a
+  // shorter last one through its buffer descriptors), other shapes to the passes below.
+  if (g.part_elems % (src.grad ? kWTile : kSTile) == 0) {
     bool used = false;
-    hipError_t e = src.grad ? dither_worker_single_pass(sp.head, prm, src, payload, ws, stream, &used)
-                            : dither_server_single_pass(sp.head, prm, src, payload, ws, stream, &used);
-    if (e != hipSuccess) return e;
-    if (used) {
-      if (sp.tail.D == 0) return hipSuccess;
-      advance_to_tail(sp.head.P, g_in, &src, &payload, &prm);
-      g = sp.tail;
-      status = nullptr;
-    }
+    const hipError_t e = src.grad ? dither_worker_single_pass(g, prm, src, payload, ws, stream, &used)
+                                  : dither_server_single_pass(g, prm, src, payload, ws, stream, &used);
+    if (e != hipSuccess || used) return e;
   }
+  uint32_t *status = ws.status();
   double *partials = ws.at<double>(ws.lay.partials);
   const int linf = prm.norm == BPC_NORM_LINF;
   const bool natural = prm.kind == BPC_NATDITHER;

@@ -30,7 +30,7 @@ def test_tagged_and_preset_forms_agree(gu, kind, n, dtype, D):
     pe = 2_097_152 if dtype == "float16" else 1_048_576
     kw = dict(levels=15 if kind == "dither5" else 4, seed=5) if kind != "sign" else {}
     code = gu.KIND_B["dither" if kind == "dither5" else kind]
-    D &= ~1   # (an odd number of halves would send the last partition to the other kernels)
+    D &= ~1   # (odd numbers of halves: test_odd_numbers_of_halves_in_the_single_pass_workers)
     prm = bpc.make_params(code, pe, **kw)
     gen = torch.Generator(device=dev)
     gen.manual_seed(D + n)
@@ -257,3 +257,38 @@ def test_topk_select_ties_and_shares(gu, orc, geo, kind, pe, D, grid):
                 assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
         if big:
             assert _long_form(gu, geo, pb, D, ws).tolist() == [zeros, False]
+
+
+# the last half alone in a tile, at the start and in the middle of a thread's four, in each row of a tile
+@pytest.mark.parametrize("kind,kw", [("sign", {}), ("dither", dict(levels=4)), ("dither", dict(levels=7, norm=1)), ("dither", dict(levels=31)),
+                                     ("dither", dict(levels=15, norm=1)), ("natdither", dict(levels=4)), ("natdither", dict(levels=7, norm=1))])
+@pytest.mark.parametrize("ef", [True, False])
+def test_odd_numbers_of_halves_in_the_single_pass_workers(gu, orc, kind, kw, ef):
+    import fmt
+    bpc, pe = gu.bpc, 131072
+    po, pb = gu.both_params(orc, kind, pe, seed=9, stream_id=3, **kw)
+    rs = np.random.default_rng(17)
+    for D in (1, 3, 2047, 2049, 4099, 8191, 8193, 16387, 131071, 131073, 2 * 131072 + 8192 * 3 + 6147):
+        g = (rs.standard_t(3.0, D) * 1e-3).astype(np.float16)
+        g[-1] = np.float16(0.25)   # (the largest by far: its loss would show in every norm)
+        res = (rs.standard_normal(D) * 3e-4).astype(np.float32) if ef else None
+        rd = gu.to_dev(res) if ef else None
+        ref = orc.compress(po, g, res)
+        pay, ws = gu.new_payload(pb, D), gu.new_ws(pb, D)
+        bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+        bpc.workspace_check(pb, D, ws)
+        got, stride = gu.to_host(pay), orc.partition_stride(po)
+        for p, d in enumerate(fmt.part_sizes(D, pe)):
+            size = 16 + 4 * (-(-d // 32) if kind == "sign" else -(-d // 8))
+            spans = [(0, size)]
+            for t in range(bpc_planes(kind, kw)):
+                at = 16 + 4 * (pe // 8) + t * 4 * (pe // 32)
+                spans.append((at, at + 4 * -(-d // 32)))
+            for a, b in spans:
+                assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), (D, p, a)
+        if ef:
+            assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32)), D
+
+
+def bpc_planes(kind, kw):
+    return 0 if kind != "dither" else sum(kw["levels"] >> (3 + t) != 0 for t in range(3))
