@@ -507,7 +507,7 @@ hipError_t randk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_
         if (e != hipSuccess) return e;
       } else {
         for (int i = 0; i < src.msgs.n; ++i) {
-          e = scatter_add_sparse(g, in_prm[i], src.msgs.ptr[i], dense, stream);
+          e = scatter_add_randk(g, in_prm[i], src.msgs.ptr[i], dense, stream);
           if (e != hipSuccess) return e;
         }
       }

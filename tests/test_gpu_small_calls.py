@@ -292,3 +292,49 @@ def test_odd_numbers_of_halves_in_the_single_pass_workers(gu, orc, kind, kw, ef)
 
 def bpc_planes(kind, kw):
     return 0 if kind != "dither" else sum(kw["levels"] >> (3 + t) != 0 for t in range(3))
+
+
+# stretches of 8192 (top-k) and 32768 elements (random-k): ends inside, at and just past one, in full and ragged partitions
+@pytest.mark.parametrize("kind,ratio", [("topk", 0.01), ("topk", 1.0), ("topk", 1e-6), ("topk16", 0.03), ("randk", 0.01), ("randk", 0.3), ("randk", 1e-6)])
+@pytest.mark.parametrize("pe,D", [(1024, 5 * 1024 + 1), (40960, 40960 + 8191), (65536, 2 * 65536 + 8193), (131072, 131072 + 32768), (131072, 32769)])
+def test_decompress_of_the_sparse_kinds(gu, orc, kind, ratio, pe, D):
+    import torch
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio, seed=11, stream_id=5, value_scale=-1.0)
+    rs = np.random.default_rng(D)
+    g = rs.standard_normal(D).astype(np.float32)
+    pay = orc.compress(po, g, None)
+    out = torch.full((D + 64,), 7.0, device=gu.DEV)
+    bpc.bpc_decompress(pb, gu.to_dev(pay), out[:D])
+    got, ref = gu.to_host(out), orc.decompress(po, pay, D)
+    assert np.all(got[D:] == 7.0)
+    if kind == "randk":   # (the adds of repeated draws come in any order: a few roundings of the sum)
+        assert np.allclose(got[:D], ref, rtol=1e-6, atol=1e-6 * np.abs(ref).max())
+    else:
+        assert np.array_equal(got[:D], ref)
+
+
+@pytest.mark.parametrize("kind", ["topk", "topk16"])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("pe,D,equal", [(65536, 3 * 65536 + 777, False), (65536, 3 * 65536 + 40_001, True), (1_048_576, 300_007, True)])
+def test_topk_without_error_feedback(gu, orc, geo, kind, dtype, pe, D, equal):
+    """Nothing but the lists is stored; a list that fails (equal magnitudes) is made up for from the gradient."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=0.01)
+    rs = np.random.default_rng(D)
+    g = rs.standard_normal(D).astype(dtype)
+    if equal:
+        g = np.where(rs.random(D) < 0.5, -0.75, 0.75).astype(dtype)
+        g[-1] = 2.0
+    ref = orc.compress(po, g, None)
+    pay, ws = gu.new_payload(pb, D), gu.new_ws(pb, D)
+    ws.fill_(0xFF)
+    bpc.bpc_compress(pb, gu.to_dev(g), None, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    stride, got, k_cap = orc.partition_stride(po), gu.to_host(pay), max(1, int(0.01 * pe))
+    for p in range(-(-D // pe)):
+        k = max(1, int(0.01 * min(pe, D - p * pe)))
+        vals, size = 16 + 4 * (-(-k_cap // 4) * 4), 4 if kind == "topk" else 2
+        for a, b in ((0, 16 + 4 * k), (vals, vals + size * k)):
+            assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
+    assert _long_form(gu, geo, pb, D, ws).any() == equal
