@@ -522,6 +522,8 @@ struct has_begin_group<SRC, std::void_t<decltype(&SRC::begin_group)>> : std::tru
 // first is used.
 constexpr int kLoadRowElems = kLoadThreads * 4;
 constexpr int kLoadRows = kGroupElems / kLoadRowElems;
+// `buf` is null where the gradient itself will do (no error feedback, short-list form): nothing is stored
+// (f32 gradients, 20 M elements, k = 1 %: 65 -> 38 us).
 template <class SRC, bool LISTED>
 __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
                                                                  TopkLists lists) {
@@ -600,6 +602,7 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
   // (the buffer is the residual, of which the guess's sample is read: no store before the guess is there)
   uint32_t G = kNoGuess;
   if constexpr (LISTED) G = sh.wait(w.p, look);
+  if (!LISTED || buf)
 #pragma unroll
   for (int u = 0; u < kLoadRows; ++u)
     row_buf(buf + base, valid, u * kLoadRowElems, kLoadRowElems).store16<kNonTemporal>(as_u32x4(v[u][0], v[u][1], v[u][2], v[u][3]), threadIdx.x * 16);
@@ -836,9 +839,10 @@ __device__ inline void topk_write_entry(const Geo &g, uint8_t *rec, uint32_t pos
 // kBins1 words.  Every element is read five times by one compute unit: a worker call on 1 M elements, all
 // zero or of one magnitude, takes 0.36 ms, of sixteen magnitudes 0.54 ms (the resident kernel below 0.71 ms),
 // on 64 M elements of one magnitude 0.51 ms (2.1 ms).
+// The vector is `buf`, whose kept slots are zeroed with error feedback, or else the gradient `values` in f32 or f16.
 template <bool HALF>
-__device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *buf_part, uint8_t *payload, int zero_selected,
-                                  uint32_t *h, uint32_t *scan, uint32_t *sel) {
+__device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *buf, const void *values, int values16, uint8_t *payload,
+                                  int zero_selected, uint32_t *h, uint32_t *scan, uint32_t *sel) {
   constexpr int kWaves = kSelThreads / 64;
   constexpr uint32_t kRow = 256, kAhead = 4;   // elements a wave takes at once; rows in flight
   __shared__ uint32_t wave_cnt[2][kWaves];
@@ -846,14 +850,32 @@ __device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *b
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint32_t seg = (uint32_t)cdiv(cdiv(d, kWaves), kRow) * kRow;
   const uint32_t lo = wave * seg < d ? wave * seg : d, hi = lo + seg < d ? lo + seg : d;
-  const TileBuf b(buf_part, d * 4);
+  const uint64_t base = uniform_off(g.part_base(p));
+  float *buf_part = buf ? buf + base : nullptr;
+  const bool from16 = !buf && values16;
+  const TileBuf b(buf ? (const void *)buf_part : from16 ? (const void *)((const __half *)values + base) : (const void *)((const float *)values + base),
+                  d * (from16 ? 2 : 4));
   // visit(j, bits): the wave's elements in order, four consecutive ones a lane, kAhead rows requested at once
   auto walk = [&](auto visit) {
 #pragma unroll 1
     for (uint32_t r0 = lo; r0 < hi; r0 += kAhead * kRow) {
       u32x4 x[kAhead];
 #pragma unroll
-      for (uint32_t q = 0; q < kAhead; ++q) x[q] = b.load16((r0 + q * kRow + lane * 4) * 4, 0);
+      for (uint32_t q = 0; q < kAhead; ++q) {
+        const uint32_t j = r0 + q * kRow + lane * 4;
+        if (!from16) {
+          x[q] = b.load16(j * 4, 0);
+        } else {
+          u32x2 hw = b.load8(j * 2, 0);
+          if ((d & 1u) && d - 1 - j < 4u) {   // the last half of an odd number: its dword reads as zero
+            const uint32_t one = b.load2((d - 1) * 2, 0);
+            if (d - 1 - j == 0) hw.x = one; else hw.y = one;
+          }
+          float f[4];
+          widen4(hw, f);
+          x[q] = as_u32x4(f[0], f[1], f[2], f[3]);
+        }
+      }
 #pragma unroll
       for (uint32_t q = 0; q < kAhead; ++q) {
         const uint32_t v[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
@@ -1089,7 +1111,7 @@ __device__ inline uint32_t last_tie(const uint32_t (&rel)[PER], const uint32_t (
 // and the idle long form behind it: 28 against 19 us on 25 partitions of 1 M elements, k = 1 %; 23 against
 // 15.5 us on 53 partitions of 2 M f16 elements, k = 0.1 %.)
 template <bool HALF>
-__global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, uint32_t *state, TopkShared sh, TopkLists lists,
+__global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, const void *values, int values16, uint32_t *state, TopkShared sh, TopkLists lists,
                                                                        uint8_t *payload, int zero_selected, uint32_t shares) {
   __shared__ __align__(16) SelectLds l;
   static_assert(kSelPer <= 32 && kTopkListCap < 65536, "one bit an entry, 16 bits a place");
@@ -1105,11 +1127,10 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   if (lo >= d) return;
   const uint32_t k = (uint32_t)k_of_device(g, p);
   if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
-  float *buf_part = buf + g.part_base(p);
   if (n < k || n > kTopkListCap) {
     if (share != 0) return;
     if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
-    if (g.part_elems <= kAloneElems) topk_alone<HALF>(g, p, k, buf_part, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
+    if (g.part_elems <= kAloneElems) topk_alone<HALF>(g, p, k, buf, values, values16, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
     return;
   }
   // entry 4 (i * kSelThreads + thread) + c of the list is the thread's entry 4 i + c; all loads of a kind are
@@ -1196,6 +1217,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   __syncthreads();
   const uint32_t pos0 = all >> 16;
   uint8_t *rec = payload + (uint64_t)p * g.stride;
+  float *buf_part = zero_selected ? buf + g.part_base(p) : nullptr;
   each_entry<kSelPer>(rounds, [&](auto i) {
     if ((mine >> i) & 1u) {
       const uint32_t o = where[i] - lo, w = o >> 5;
@@ -1371,8 +1393,6 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   uint32_t *state = ws.at<uint32_t>(ws.lay.state);
   uint32_t *tilecnt = ws.at<uint32_t>(ws.lay.tilecnt);
   float *dense = ws.at<float>(ws.lay.dense);
-  // the vector being compressed ends up in the residual buffer (error feedback) or the workspace
-  float *buf = src.residual ? src.residual : dense;
   const bool half = prm.kind == BPC_TOPK16;
   const int zero_selected = src.residual != nullptr;
   const TopkLists lists{ws.at<uint32_t>(ws.lay.cand), g.P};
@@ -1385,6 +1405,9 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   const int capacity = gated ? cache[half].get([&] { return cluster_capacity(long_fn, kThreads, 0); }) : 0;
   // the short-list form wants room for the k winners and as many again
   const bool short_list = g.k_cap <= kTopkListCap / 2 && (!gated || capacity > 0);
+  // the vector being compressed ends up in the residual buffer (error feedback) or the workspace, or is
+  // the gradient as it is
+  float *buf = src.residual ? src.residual : src.grad && short_list && !gated ? nullptr : dense;
   const uint32_t load_grid = group_count(g, kTpgLoad);
   TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status()};
   sh.lengths = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(sh.pairs) + TopkShared::pairs_bytes(g.P));
@@ -1425,8 +1448,8 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     while (shares < kMostShares && 2 * shares * of_xcd <= kCusOfXcd) shares *= 2;
     const uint32_t least = (uint32_t)cdiv(g.part_elems, 32ull * kShareWords);
     if (shares < least) shares = least;
-    if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, state, sh, lists, payload, zero_selected, shares);
-    else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, state, sh, lists, payload, zero_selected, shares);
+    if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);
+    else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);
     if (!gated) return hipGetLastError();
   }
   const uint32_t n2 = group_count(g, kTpgHist2), n3 = group_count(g, kTpgHist3), nc = group_count(g, kTpgCount);
