@@ -143,7 +143,7 @@ struct WsLayout {
   size_t samp;       // 16 KB a partition: the keys from which elements go to the top-k short lists, two u64 a partition, and,
                      // 4 KB apart, the lengths of the lists
   size_t cand;       // u32[P * kTopkListCap] indices, then as many value bits: top-k short lists of the partitions
-  size_t tilecnt;    // u32[2*n_tiles]: per-tile (greater, equal) counts of the long form of top-k
+  size_t tilecnt;    // u32[2*n_tiles]: per-tile (greater, equal) counts of the long form of top-k; the lengths of its group lists
   size_t slots;      // double[3 * tiles of kSTile]: partition-wide reductions of the single-pass kernels
                      // (one per tile, two words per tile in a launch with a tag; three for the LANS block norms;
                      // LANS with caller-defined blocks: its pairs, which go on into `norms` and beyond)

@@ -14,9 +14,9 @@
 //                partition's short list
 //   select     : several workgroups per partition find the k-th largest key among the listed ones,
 //                each for itself, and write a share of the record; kept slots of the buffer zeroed
-// On the worker side the guess is made by the first workgroups of the load kernel itself, the others
-// have requested their elements before they wait for it; on the server side by a kernel in
-// front that also finds where each message's entries of a group of 8192 elements begin.
+// The guess is made by the first workgroups of the load kernel itself, the others have requested their
+// elements before they wait for it; on the server side a kernel in front sums the sampled chunks up and
+// finds where each message's entries of a group of 8192 elements begin.
 // The sample only decides how much work the selection is, never its result: a partition whose
 // short list came out shorter than k or longer than its room (the sample misled, or a great many
 // equal magnitudes, or fewer than k non-zeros) is taken by the long form below instead, run by the
@@ -24,7 +24,15 @@
 // kernel, enqueued behind, which returns at once if no partition needs it and else runs the
 // long form's passes for those partitions with its resident grid meeting between the passes.
 //
-// Long form (a k too large for a short list), five passes over the dense buffer:
+// Group-list form (larger k, up to kMostListed of a full partition, where the dense workspace is free): the
+// same guess and load pass, but every group of 8192 elements has a list of its own in the dense workspace.
+//   bins       : histogram of the listed keys' distances from the guess, 32 steps for every power of two
+//   collect    : the bin of the k-th largest key from it; per group, how many entries lie above the bin;
+//                the few entries inside it to one list a partition
+//   emit       : threshold key and ties from that list (every workgroup for itself), then (idx, val) as
+//                in the select pass
+//
+// Long form (the rest), five passes over the dense buffer:
 //   load+hist1 : as above, every element counted
 //   hist2      : bin of level 1 that holds the k-th largest key, histogram inside it
 //   hist3      : the same one level down
@@ -37,8 +45,7 @@
 // Server side the vector is Delta = (sum of the n decoded messages) / n + e~.  It is never
 // scattered into a dense buffer (n k read-modify-writes at random places of HBM per partition):
 // the messages list their entries by ascending index, so the load pass sums the stretch of each
-// message that falls into its group of 8192 elements in LDS, and one workgroup a partition collects
-// the sums of the sampled chunks in LDS in one sweep over the messages.
+// message that falls into its group of 8192 elements in LDS.
 #include "cluster.hpp"
 #include "sources.hpp"
 #include "tile_rows.hpp"
@@ -64,9 +71,12 @@ constexpr uint32_t kShareWords = 16384;                 // words of the bitmap o
 constexpr uint32_t kXcds = 8, kCusOfXcd = 32;            // of an MI355X: the select pass is spread over one workgroup a compute unit when there are few partitions
 constexpr uint32_t kMostShares = 8;                     // ... of one partition (unless its bitmaps ask for more)
 constexpr uint32_t kAloneElems = 1u << 22;              // partitions up to this size are left to one workgroup if the short list fails
+constexpr uint32_t kMostListed = 65536;                 // k of a full partition up to which the group-list form is taken
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr uint32_t kSampleChunks = 1024;                // chunks of eight consecutive elements in a partition's sample, at most
 constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
+constexpr uint32_t kNearBins = 1024;                    // group-list form: bins of the listed keys by their distance from the guess,
+constexpr uint32_t kBinWords = kNearBins + 1;           // and the number of entries in the threshold's bin
 constexpr uint32_t kNoGuess = 0xffffffffu;              // no key reaches it: nothing goes to the short list
 
 __device__ inline uint32_t key_of(float v) { return __float_as_uint(v) & 0x7fffffffu; }
@@ -85,11 +95,13 @@ struct TopkShared {
   uint32_t *lengths;
   uint64_t tag;
   uint32_t *status;
+  uint32_t *state;
   static size_t pairs_bytes(uint32_t P) { return (16ull * P + 4095) / 4096 * 4096; }
   __device__ uint32_t *length(uint32_t p) const { return lengths + 1024ull * p; }
   // One thread publishes partition p's guess; the list length is zero before anyone can see it.
   __device__ void publish(uint32_t p, uint32_t guess) const {
     __hip_atomic_store(length(p), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    state[p * 8 + kStLong] = 0;
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0F70);   // (vector memory done)
     asm volatile("" ::: "memory");
@@ -113,12 +125,26 @@ struct TopkShared {
   }
 };
 
-// A partition's short list: the entries' indices and values, in any order.
+// A partition's short list: the entries' indices and values, in any order.  In the group-list form: a list
+// for every group of the load pass, with room for half of its elements in the place of the group in the
+// dense workspace; that of a ragged last group, and the entries near the threshold, where the short list
+// would be.
 struct TopkLists {
   uint32_t *base;
   uint32_t P;
+  uint32_t *dense;      // null: one list a partition
+  uint32_t *counts;     // group lists: four words a group: entries, entries above the bin of the threshold
+  uint32_t groups;      // of a full partition
+  static constexpr uint32_t kNearCap = kTopkListCap - 8192;
   __device__ uint32_t *idx(uint32_t p) const { return base + (uint64_t)p * kTopkListCap; }
   __device__ uint32_t *val(uint32_t p) const { return base + (uint64_t)(P + p) * kTopkListCap; }
+  struct List { uint32_t *idx, *val, room; };
+  __device__ List of_group(const Geo &g, uint32_t p, uint32_t q, uint32_t d) const {
+    if (d - q * 8192u < 8192u) return List{idx(p) + kNearCap, val(p) + kNearCap, 8192u};
+    uint32_t *at = dense + g.part_base(p) + q * 8192u;
+    return List{at, at + 4096, 4096u};
+  }
+  __device__ uint32_t *count(uint32_t p, uint32_t q) const { return counts + 4ull * ((uint64_t)p * groups + q); }
 };
 
 // Whether partition p is left to the long form (uniform over the workgroup).
@@ -289,13 +315,15 @@ struct TopkMsgs {
 
 // For t = 0 .. k: entry t is the first one of every group after the group of entry t - 1 up to
 // its own group (t = k: up to the end).  A message that is not in ascending order leaves
-// groups unset; readers clamp what they find to [0, k].  Entries t0, t0 + step, ... of worker i's message.
-__device__ inline void topk_starts(const Geo &g, const TopkMsgs &m, uint32_t *starts, uint32_t i, uint32_t p, uint32_t t0, uint32_t step) {
+// groups unset; readers clamp what they find to [0, k].  Entries t0, t0 + step, ... below `end` of worker i's
+// message.
+__device__ inline void topk_starts(const Geo &g, const TopkMsgs &m, uint32_t *starts, uint32_t i, uint32_t p, uint32_t t0, uint32_t step,
+                                   uint32_t end = 0xffffffffu) {
   const uint32_t k = m.k_of(i, p);
   const uint32_t *idx = m.idx(i, p);
   uint32_t *tab = starts + ((uint64_t)i * g.P + p) * (m.groups_per_part + 1);
   auto group = [&](uint32_t j) { const uint32_t q = j >> m.group_shift; return q < m.groups_per_part ? q : m.groups_per_part - 1; };
-  for (uint32_t t = t0; t <= k; t += step) {
+  for (uint32_t t = t0; t <= k && t < end; t += step) {
     const uint32_t first = t == 0 ? 0u : group(idx[t - 1]) + 1;
     const uint32_t last = t == k ? m.groups_per_part : group(idx[t]);
     for (uint32_t q = first; q <= last && q <= m.groups_per_part; ++q) tab[q] = t;
@@ -309,6 +337,13 @@ __global__ __launch_bounds__(kThreads) void topk_starts_kernel(Geo g, TopkMsgs m
 // (a barrier in between: the order of the sum is the workers'), a thread's first entry of the
 // next worker requested before the adds of this one.
 struct TopkMsgsGroupSource : TopkMsgs {
+  const float *sums;   // of the sampled chunks, kTopkListCap words from partition to partition
+  __device__ void sampled8(const Geo &g, uint32_t p, uint32_t c, uint32_t j0, uint32_t d, float out[8]) const {
+    float sum[8], r[8];
+    load_res8(g, p, j0, d, r);
+    load8_aligned(sums + (uint64_t)p * kTopkListCap + 8 * c, sum);
+    combine8(j0, d, sum, r, out);
+  }
   static constexpr int kLdsFloats = kGroupElems + 5 * kMaxWorkers + 2;   // sums, ranges, counts before, record addresses
   __device__ void begin(const Geo &, uint32_t, float *) const {}
   __device__ void begin_group(const Geo &g, uint32_t p, uint32_t grp, float *lds) const {
@@ -441,66 +476,54 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   if (threadIdx.x == 0) sh.publish(p, sel[0]);
 }
 
-// Server side, in front of the load pass.  Workgroup (p, 0): the guess from the sampled chunks of Delta,
-// whose sums are collected in LDS by one sweep over the messages (one entry in 128 or so falls into a chunk, so the
-// float atomics do not matter, and a guess needs no particular order of the sum); workgroup (p, 1 + i): where
-// each group's entries start in worker i's message.
+// Server side, in front of the load pass.  The first kSumPieces workgroups of a partition find the sums of the
+// decoded messages in the sampled chunks, 64 chunks each, a thread searching one message for one chunk (on
+// one compute unit, by a sweep over the messages or by searches, they took 25 to 150 us); the others
+// where each group's entries start, kStartsPiece entries of one message each.
 constexpr int kPrepThreads = 1024;
-__global__ __launch_bounds__(kPrepThreads) void topk_server_prep_kernel(Geo g, TopkMsgs m, uint32_t *starts, TopkShared sh, uint32_t *state,
-                                                                        int guesses) {
-  __shared__ __align__(16) float sum[kSampleChunks * 8];
-  __shared__ uint32_t h[kBins1];
-  __shared__ uint32_t scan[kPrepThreads / 64];
-  __shared__ uint32_t kept[kMaxWorkers];   // entries of a worker's message
-  __shared__ uint32_t sel[2];
-  const uint32_t p = blockIdx.x, role = blockIdx.y + (guesses ? 0u : 1u);
-  if (role != 0) {
-    topk_starts(g, m, starts, role - 1, p, threadIdx.x, kPrepThreads);
+constexpr uint32_t kSumChunks = 64, kSumSlots = kPrepThreads / kSumChunks, kSumPieces = kSampleChunks / kSumChunks;
+constexpr uint32_t kStartsPiece = 8 * kPrepThreads;
+static_assert(kSampleChunks * 8 <= kTopkListCap, "the sums lie where the lists will");
+__global__ __launch_bounds__(kPrepThreads) void topk_server_prep_kernel(Geo g, TopkMsgs m, uint32_t *starts, float *sums, int guesses) {
+  __shared__ float part[kSumSlots][kSumChunks * 8];
+  const uint32_t p = blockIdx.x, first_starts = guesses ? kSumPieces : 0u;
+  if (blockIdx.y >= first_starts) {
+    const uint32_t pieces = (m.k_cap + kStartsPiece) / kStartsPiece;   // (of k_cap + 1 entries)
+    const uint32_t role = blockIdx.y - first_starts, t0 = role % pieces * kStartsPiece;
+    topk_starts(g, m, starts, role / pieces, p, t0 + threadIdx.x, kPrepThreads, t0 + kStartsPiece);
     return;
   }
-  if (p == 0) status_open(sh.status, sh.tag);
-  if (threadIdx.x == 0) state[p * 8 + kStLong] = 0;
   const uint32_t d = g.part_size(p);
   const SamplePlan plan(d);
-  // (a chunk a thread; its residual is on its way while the sums are formed)
-  static_assert(kSampleChunks == kPrepThreads, "a chunk a thread");
-  float res8[8];
-  const uint32_t mine = 8 * plan.chunk(threadIdx.x < plan.chunks ? threadIdx.x : 0u);
-  m.load_res8(g, p, mine, d, res8);
-  if (threadIdx.x < (uint32_t)m.msgs.n) kept[threadIdx.x] = m.k_of(threadIdx.x, p);
-  for (uint32_t q = threadIdx.x; q < kSampleChunks * 8; q += kPrepThreads) sum[q] = 0.0f;
-  __syncthreads();
-  // the messages in pieces of 2048 entries, a wave each; indices and values of a piece in flight at once
-  // (values fetched where an index turned out to be sampled had every wave wait for one after the other).
-  const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-  const uint32_t pieces = (uint32_t)cdiv(m.k_cap, 2048), mask = (1u << plan.shift) - 1u;
-  for (uint32_t piece = wave; piece < pieces * (uint32_t)m.msgs.n; piece += kPrepThreads / 64) {
-    const uint32_t i = piece / pieces, t0 = piece % pieces * 2048, k = __builtin_amdgcn_readfirstlane(kept[i]);
-    const uint8_t *vals = m.rec(i, p) + kHeaderBytes + 4 * ru4(m.k_cap);
-    const TileBuf ib(m.idx(i, p), k * 4), vb(vals, (m.half ? (k + 1) / 2 * 2 * 2 : k * 4));
-    u32x4 x[8];
-    float v[8][4];
+  const uint32_t slot = threadIdx.x / kSumChunks, mine = threadIdx.x % kSumChunks, c = blockIdx.y * kSumChunks + mine;
+  if (blockIdx.y * kSumChunks >= plan.chunks) return;   // (uniform)
+  float *acc = part[slot] + mine * 8;
 #pragma unroll
-    for (uint32_t q = 0; q < 8; ++q) x[q] = ib.load16(t0 * 4 + q * 1024 + lane * 16, 0);
-    if (m.half) {
-#pragma unroll
-      for (uint32_t q = 0; q < 8; ++q) widen4(vb.load8(t0 * 2 + q * 512 + lane * 8, 0), v[q]);
-    } else {
-#pragma unroll
-      for (uint32_t q = 0; q < 8; ++q) widen4(vb.load16(t0 * 4 + q * 1024 + lane * 16, 0), v[q]);
+  for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+  const uint32_t j0 = 8 * plan.chunk(c < plan.chunks ? c : 0u);
+  for (uint32_t i = slot; i < (uint32_t)m.msgs.n; i += kSumSlots) {
+    const uint32_t *idx = m.idx(i, p);
+    const uint32_t k = m.k_of(i, p);
+    uint32_t lo = 0, len = k;   // the first entry at or past j0 is one of [lo, lo + len]
+    while (len > 0) {
+      const uint32_t half = len >> 1;
+      const bool below = idx[lo + half] < j0;
+      lo += below ? half + 1 : 0u;
+      len = below ? len - half - 1 : half;
     }
-#pragma unroll
-    for (uint32_t q = 0; q < 8; ++q) {
-      const uint32_t js[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
-#pragma unroll
-      for (uint32_t e = 0; e < 4; ++e) {
-        const uint32_t j = js[e], cj = j >> 3, c = cj >> plan.shift;
-        if (((c * 37u ^ cj) & mask) == 0 && c < plan.chunks && t0 + q * 256 + lane * 4 + e < k) atomicAdd(&sum[c * 8 + (j & 7u)], v[q][e]);
-      }
+    for (; lo < k; ++lo) {
+      const uint32_t j = idx[lo] - j0;
+      if (j >= 8) break;
+      acc[j] += m.value(i, p, lo);
     }
   }
   __syncthreads();
-  topk_guess<kPrepThreads>(g, p, sh, h, scan, sel, [&](uint32_t c, uint32_t j0, float v[8]) { m.combine8(j0, d, sum + 8 * c, res8, v); });
+  if (threadIdx.x < kSumChunks * 8) {
+    float s = 0.0f;
+#pragma unroll
+    for (uint32_t q = 0; q < kSumSlots; ++q) s += part[q][threadIdx.x];
+    sums[(uint64_t)p * kTopkListCap + blockIdx.y * kSumChunks * 8 + threadIdx.x] = s;
+  }
 }
 
 template <class SRC, class = void>
@@ -512,7 +535,7 @@ struct has_begin_group<SRC, std::void_t<decltype(&SRC::begin_group)>> : std::tru
 // key is at least the partition's guess go to its short list, together, at the place one atomic
 // add on the list length hands out.  The order inside the list does not matter: the select pass puts
 // what it keeps in index order through a bitmap.  Long form: the level-1 histogram of all elements.
-// On the worker side workgroup p < P makes partition p's guess and the groups follow behind; a group has
+// In the short-list form workgroup p < P makes partition p's guess and the groups follow behind; a group has
 // its elements in registers before it waits for the guess (a kernel of its own for the guesses cost
 // 8 us of every call).
 // The group is taken as 4 rows of 2048 elements, 4 consecutive elements a thread and row: every
@@ -527,19 +550,24 @@ constexpr int kLoadRows = kGroupElems / kLoadRowElems;
 template <class SRC, bool LISTED>
 __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
                                                                  TopkLists lists) {
-  constexpr bool kGuesses = LISTED && !has_begin_group<SRC>::value;
+  constexpr bool kServer = has_begin_group<SRC>::value;
   __shared__ __align__(16) float lds[SRC::kLdsFloats];
   constexpr int kWaves = kLoadThreads / 64;
-  __shared__ uint32_t h[!LISTED || kGuesses ? kBins1 : 1];
+  __shared__ uint32_t own_h[kServer && LISTED ? 1 : kBins1];
+  uint32_t *h = kServer && LISTED ? reinterpret_cast<uint32_t *>(lds) : own_h;
   __shared__ uint32_t scan[kWaves];
   __shared__ uint32_t sel[2];
   uint32_t blk = blockIdx.x;
-  if constexpr (kGuesses) {
+  if constexpr (LISTED) {
     if (blk == 0) status_open(sh.status, sh.tag);
     if (blk < g.P) {
-      if (threadIdx.x == 0) state[blk * 8 + kStLong] = 0;
       const uint32_t d = g.part_size(blk);
-      topk_guess<kLoadThreads>(g, blk, sh, h, scan, sel, [&](uint32_t, uint32_t j0, float v[8]) { src.at8(g, blk, j0, d, nullptr, v); });
+      if (lists.dense)   // (the bins of the group-list form, used by later kernels)
+        for (uint32_t b = threadIdx.x; b < kBinWords; b += kLoadThreads) hist[(uint64_t)blk * kTopkHistWords + b] = 0;
+      topk_guess<kLoadThreads>(g, blk, sh, h, scan, sel, [&](uint32_t c, uint32_t j0, float v[8]) {
+        if constexpr (kServer) src.sampled8(g, blk, c, j0, d, v);
+        else src.at8(g, blk, j0, d, nullptr, v);
+      });
       return;
     }
     blk -= g.P;
@@ -559,7 +587,7 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
   const bool ef = src.res != nullptr;
   const TileBuf eb(ef ? src.res + base : nullptr, ef ? valid * 4 : 0);
   float v[kLoadRows][4];
-  if constexpr (has_begin_group<SRC>::value) {
+  if constexpr (kServer) {
     // the residual's elements are requested first, so they are on their way while the group's
     // sum is formed
     u32x4 er[kLoadRows];
@@ -634,18 +662,24 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
       before += (uint32_t)q < wave ? scan[q] : 0u;
       total += scan[q];
     }
-    if (threadIdx.x == 0) sel[0] = total ? atomicAdd(sh.length(w.p), total) : 0u;
-    __syncthreads();
-    uint32_t pos = sel[0] + before + incl - cnt;
-    uint32_t *li = lists.idx(w.p), *lv = lists.val(w.p);
+    TopkLists::List list{lists.idx(w.p), lists.val(w.p), kTopkListCap};
+    uint32_t pos = before + incl - cnt;
+    if (lists.dense) {
+      list = lists.of_group(g, w.p, w.tile_lo / kTpgLoad, w.d);
+      if (threadIdx.x == 0) *lists.count(w.p, w.tile_lo / kTpgLoad) = total;   // (more than its room: the vector itself will be read)
+    } else {
+      if (threadIdx.x == 0) sel[0] = total ? atomicAdd(sh.length(w.p), total) : 0u;
+      __syncthreads();
+      pos += sel[0];
+    }
 #pragma unroll
     for (int u = 0; u < kLoadRows; ++u)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         if ((mask >> (4 * u + c)) & 1u) {
-          if (pos < kTopkListCap) {
-            li[pos] = j_lo + u * kLoadRowElems + threadIdx.x * 4 + c;
-            lv[pos] = __float_as_uint(v[u][c]);
+          if (pos < list.room) {
+            list.idx[pos] = j_lo + u * kLoadRowElems + threadIdx.x * 4 + c;
+            list.val[pos] = __float_as_uint(v[u][c]);
           }
           ++pos;
         }
@@ -1228,6 +1262,273 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   });
 }
 
+// Group-list form.  A workgroup takes kRangeGroups groups, two waves each.
+constexpr uint32_t kRangeGroups = kSelThreads / 128;
+struct GroupRange {
+  uint32_t p, q0, q1, d;   // groups [q0, q1) of partition p
+  __device__ GroupRange(const Geo &g, const TopkLists &lists) {
+    const uint32_t ranges = (lists.groups + kRangeGroups - 1) / kRangeGroups;
+    p = blockIdx.x / ranges;
+    d = g.part_size(p);
+    const uint32_t groups = (uint32_t)cdiv(d, kGroupElems);
+    q0 = blockIdx.x % ranges * kRangeGroups;
+    q1 = q0 + kRangeGroups < groups ? q0 + kRangeGroups : groups;
+  }
+};
+// The vector that was compressed, for groups more than half of which are listed (one layer's gradient may
+// dwarf the rest of its partition): the buffer, or the gradient in f32 or f16.
+struct TopkVector {
+  const void *at;
+  int half;
+  __device__ uint32_t bits(uint64_t j) const {
+    return __float_as_uint(half ? __half2float(reinterpret_cast<const __half *>(at)[j]) : reinterpret_cast<const float *>(at)[j]);
+  }
+};
+// Entries `first`, `first` + STEP, ... below n of a list: the first four are kept in registers, so that a kernel
+// that goes over them more than once waits for them once; visit(rel, value, index), rel = key - guess.
+// Without a list (`val` null) entry e is element `at` + e of the vector, index `j0` + e.
+template <uint32_t STEP, bool IDX>
+struct EntriesOf {
+  const uint32_t *idx, *val;
+  uint32_t first, n, G;
+  TopkVector vec;
+  uint64_t at;
+  uint32_t j0, v[4], j[4];
+  __device__ void load(uint32_t e0, uint32_t (&lv)[4], uint32_t (&lj)[4]) const {
+    if (val) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t e = e0 + r * STEP;
+        lv[r] = e < n ? val[e] : 0u;
+        lj[r] = IDX && e < n ? idx[e] : 0u;
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t e = e0 + r * STEP;
+        lv[r] = e < n ? vec.bits(at + e) : 0u;
+        lj[r] = j0 + e;
+      }
+    }
+  }
+  __device__ void load_first() { load(first, v, j); }
+  template <class VISIT>
+  __device__ void each(VISIT visit) const {
+    auto one = [&](uint32_t e, uint32_t x, uint32_t y) {
+      const uint32_t key = x & 0x7fffffffu;
+      if (e < n && key >= G) visit(key - G, x, y);
+    };
+#pragma unroll
+    for (int r = 0; r < 4; ++r) one(first + r * STEP, v[r], j[r]);
+    for (uint32_t e0 = first + 4 * STEP; e0 < n; e0 += 4 * STEP) {
+      uint32_t lv[4], lj[4];
+      load(e0, lv, lj);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) one(e0 + r * STEP, lv[r], lj[r]);
+    }
+  }
+};
+// The entries of the wave's group, number q of the workgroup's range (none past its end).
+template <bool IDX>
+__device__ inline EntriesOf<128, IDX> entries_of_group(const Geo &g, const TopkLists &lists, const GroupRange &w, uint32_t q, uint32_t G,
+                                                       const TopkVector &vec) {
+  EntriesOf<128, IDX> e{};
+  e.first = threadIdx.x & 127;
+  e.G = G;
+  if (q < w.q1) {
+    const TopkLists::List list = lists.of_group(g, w.p, q, w.d);
+    e.n = __builtin_amdgcn_readfirstlane(*lists.count(w.p, q));
+    if (e.n <= list.room) {
+      e.idx = list.idx;
+      e.val = list.val;
+    } else {
+      e.j0 = q * kGroupElems;
+      e.n = w.d - e.j0 < kGroupElems ? w.d - e.j0 : kGroupElems;
+      e.vec = vec;
+      e.at = g.part_base(w.p) + e.j0;
+    }
+    e.load_first();
+  }
+  return e;
+}
+// 32 bins for every power of two of the distance from the guess, whatever the magnitudes' spread: a bin holds a
+// few per cent of the list at most (unless keys are equal).  Bins below 864; bin b starts at near_start(b).
+__device__ inline uint32_t near_bin(uint32_t rel) {
+  const uint32_t e = 31u - (uint32_t)__builtin_clz(rel | 1u);
+  return rel < 32u ? rel : (e - 4u) * 32u + ((rel >> (e - 5u)) & 31u);
+}
+__device__ inline uint32_t near_start(uint32_t b) { return b < 32u ? b : (32u + b % 32u) << (b / 32u - 1u); }
+
+__global__ __launch_bounds__(kSelThreads) void topk_bins_kernel(Geo g, uint32_t *hist, TopkShared sh, TopkLists lists, TopkVector vec) {
+  __shared__ uint32_t h[kNearBins];
+  const GroupRange w(g, lists);
+  if (w.q0 >= w.q1) return;
+  const uint32_t q = __builtin_amdgcn_readfirstlane(w.q0 + (threadIdx.x >> 7));
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  h[threadIdx.x] = 0;
+  __syncthreads();
+  entries_of_group<false>(g, lists, w, q, G, vec).each([&](uint32_t rel, uint32_t, uint32_t) { atomicAdd(&h[near_bin(rel)], 1u); });
+  __syncthreads();
+  if (h[threadIdx.x]) atomicAdd(&hist[(uint64_t)w.p * kTopkHistWords + threadIdx.x], h[threadIdx.x]);
+}
+
+// The bin of the k-th largest key of a partition in sel[0], the rank left in it in sel[1]; false if the
+// lists hold fewer than k.
+__device__ inline bool near_bin_of_k(const uint32_t *bins, uint32_t k, uint32_t *scan, uint32_t *sel) {
+  static_assert(kNearBins == kSelThreads, "a bin a thread");
+  const uint32_t mine = bins[kNearBins - 1 - threadIdx.x];
+  uint32_t total;
+  const uint32_t above = block_exclusive_scan<kSelThreads>(mine, scan, &total);
+  if (above < k && k <= above + mine) {
+    sel[0] = kNearBins - 1 - threadIdx.x;
+    sel[1] = k - above;
+  }
+  __syncthreads();
+  return total >= k;
+}
+
+__global__ __launch_bounds__(kSelThreads) void topk_collect_kernel(Geo g, uint32_t *hist, TopkShared sh, TopkLists lists, TopkVector vec) {
+  __shared__ uint32_t scan[kSelThreads / 64], sel[2], sure[kRangeGroups], near, at;
+  const GroupRange w(g, lists);
+  if (w.q0 >= w.q1) return;
+  uint32_t *bins = hist + (uint64_t)w.p * kTopkHistWords;
+  const uint32_t k = (uint32_t)k_of_device(g, w.p);
+  if (threadIdx.x < kRangeGroups) sure[threadIdx.x] = 0;
+  if (threadIdx.x == 0) near = 0;
+  if (!near_bin_of_k(bins, k, scan, sel)) return;   // (left to the long form: the next kernel finds out by itself)
+  const uint32_t bin = sel[0], slot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), q = w.q0 + slot;
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  const auto mine = entries_of_group<true>(g, lists, w, q, G, vec);
+  uint32_t above = 0, inside = 0;
+  mine.each([&](uint32_t rel, uint32_t, uint32_t) {
+    const uint32_t b = near_bin(rel);
+    above += b > bin;
+    inside += b == bin;
+  });
+  above = wave_sum_u32(above);
+  if ((threadIdx.x & 63) == 0 && above) atomicAdd(&sure[slot], above);
+  uint32_t place = inside ? atomicAdd(&near, inside) : 0u;
+  __syncthreads();
+  if (threadIdx.x == 0) at = near ? atomicAdd(&bins[kNearBins], near) : 0u;
+  if (q < w.q1 && (threadIdx.x & 127) == 0) lists.count(w.p, q)[1] = sure[slot];
+  __syncthreads();
+  place += at;
+  if (inside) {
+    uint32_t *ni = lists.idx(w.p), *nv = lists.val(w.p);
+    mine.each([&](uint32_t rel, uint32_t v, uint32_t j) {
+      if (near_bin(rel) == bin) {
+        if (place < TopkLists::kNearCap) { ni[place] = j; nv[place] = v; }
+        ++place;
+      }
+    });
+  }
+}
+
+// Emit pass of the group-list form.  The form in all, against the long form that these k took before (worker
+// calls): 20 M f16 elements, k = 1 %, 77 against 122 us (load 44, bins 5, collect 6.5, emit 20); 100 M, k =
+// 3 %, 328 against 566; 0.3 M 31 against 36.  (One workgroup a partition over lists that long, as in the
+// select pass, took 70 to 140 us by itself.)
+template <bool HALF>
+__global__ __launch_bounds__(kSelThreads) void topk_group_emit_kernel(Geo g, float *buf, TopkVector vec, uint32_t *state,
+                                                                      const uint32_t *hist, TopkShared sh, TopkLists lists, uint8_t *payload,
+                                                                      int zero_selected) {
+  constexpr uint32_t kWords = kRangeGroups * kGroupElems / 32;
+  __shared__ __align__(16) uint32_t h[2048];
+  __shared__ uint32_t bitmap[kWords];
+  __shared__ uint16_t before[kWords];
+  __shared__ uint32_t scan[kSelThreads / 64], sel[2];
+  static_assert(kWords == 2 * kSelThreads && kBins1 <= 2048, "two words of the bitmap a thread");
+  const GroupRange w(g, lists);
+  if (w.q0 >= w.q1) return;
+  const uint32_t *bins = hist + (uint64_t)w.p * kTopkHistWords;
+  const uint32_t k = (uint32_t)k_of_device(g, w.p);
+  if (w.q0 == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, w.p, payload);
+  const uint32_t near = __builtin_amdgcn_readfirstlane(bins[kNearBins]);
+  if (!near_bin_of_k(bins, k, scan, sel) || near > TopkLists::kNearCap) {
+    if (w.q0 != 0) return;
+    if (threadIdx.x == 0) state[w.p * 8 + kStLong] = 1;
+    topk_alone<HALF>(g, w.p, k, buf, vec.at, vec.half, payload, zero_selected, h, scan, sel);
+    return;
+  }
+  const uint32_t bin = sel[0];
+  uint32_t rem = sel[1];
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  EntriesOf<kSelThreads, true> near_ones{lists.idx(w.p), lists.val(w.p), threadIdx.x, near, G};
+  near_ones.load_first();
+  auto each_near = [&](auto visit) { near_ones.each([&](uint32_t rel, uint32_t, uint32_t j) { visit(rel, j); }); };
+  const uint32_t q = __builtin_amdgcn_readfirstlane(w.q0 + (threadIdx.x >> 7));
+  const auto mine = entries_of_group<true>(g, lists, w, q, G, vec);
+  // the threshold inside the bin (less than 2^26 keys: 6 + 10 + 10 bits), then, among ties, the index of the last
+  // one kept
+  const uint32_t start = near_start(bin), width = near_start(bin + 1) - start;
+  uint32_t R = 0, ties = 0;
+#pragma unroll 1
+  for (int shift = width > 1u << 20 ? 20 : width > 1u << 10 ? 10 : 0; shift >= 0; shift -= 10) {
+    const uint32_t prefix = R;
+    __syncthreads();
+    h[threadIdx.x] = 0;
+    __syncthreads();
+    each_near([&](uint32_t rel, uint32_t) {
+      if (((rel - start) >> shift >> 10) == prefix) atomicAdd(&h[((rel - start) >> shift) & 1023u], 1u);
+    });
+    __syncthreads();
+    pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
+    R = sel[0];
+    rem = sel[1];
+    ties = h[sel[0] & 1023u];
+  }
+  R += start;
+  uint32_t last = 0xffffffffu;
+  if (ties != rem) {   // (uniform) the rem-th of the ties in index order (indices below 2^28: 10 + 10 + 8 bits)
+    uint32_t prefix = 0;
+    rem = ties - rem + 1;   // (pick_bin counts from the largest down)
+#pragma unroll 1
+    for (int level = 0; level < 3; ++level) {
+      const int hi_shift = level == 0 ? 28 : level == 1 ? 18 : 8, lo_shift = level == 0 ? 18 : level == 1 ? 8 : 0;
+      __syncthreads();
+      h[threadIdx.x] = 0;
+      __syncthreads();
+      each_near([&](uint32_t rel, uint32_t j) {
+        if (rel == R && (j >> hi_shift) == prefix) atomicAdd(&h[(j >> lo_shift) & (level == 2 ? 255u : 1023u)], 1u);
+      });
+      __syncthreads();
+      if (level == 2) pick_bin<256, 8, kSelThreads>(h, rem, prefix, scan, sel);
+      else pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
+      prefix = sel[0];
+      rem = sel[1];
+    }
+    last = prefix;
+  }
+  // kept entries of the groups before the workgroup's: those above the bin, and those inside it
+  const uint32_t lo = w.q0 * kGroupElems;
+  uint32_t below = 0;
+  for (uint32_t b = threadIdx.x; b < w.q0; b += kSelThreads) below += lists.count(w.p, b)[1];
+  each_near([&](uint32_t rel, uint32_t j) { below += j < lo && (rel > R || (rel == R && j <= last)); });
+  bitmap[2 * threadIdx.x] = 0;
+  bitmap[2 * threadIdx.x + 1] = 0;
+  __syncthreads();
+  mine.each([&](uint32_t rel, uint32_t, uint32_t j) {
+    if (rel > R || (rel == R && j <= last)) atomicOr(&bitmap[(j - lo) >> 5], 1u << (j & 31u));
+  });
+  __syncthreads();
+  const uint32_t w0 = bitmap[2 * threadIdx.x], w1 = bitmap[2 * threadIdx.x + 1], c0 = (uint32_t)__popc(w0);
+  uint32_t all, all_below;
+  const uint32_t at = block_exclusive_scan<kSelThreads>(c0 + (uint32_t)__popc(w1), scan, &all);
+  block_exclusive_scan<kSelThreads>(below, scan, &all_below);
+  before[2 * threadIdx.x] = (uint16_t)at;
+  before[2 * threadIdx.x + 1] = (uint16_t)(at + c0);
+  __syncthreads();
+  uint8_t *rec = payload + (uint64_t)w.p * g.stride;
+  float *buf_part = zero_selected ? buf + g.part_base(w.p) : nullptr;
+  mine.each([&](uint32_t rel, uint32_t v, uint32_t j) {
+    if (rel > R || (rel == R && j <= last)) {
+      const uint32_t o = j - lo, word = o >> 5;
+      const uint32_t pos = all_below + before[word] + (uint32_t)__popc(bitmap[word] & ((1u << (o & 31u)) - 1u));
+      topk_write_entry<HALF>(g, rec, pos, j, __uint_as_float(v), buf_part, zero_selected);
+    }
+  });
+}
+
 // Ordered compaction of the long form.  Thread t of a tile owns 16 consecutive elements, so
 // positions follow from an exclusive scan over threads, on top of the counts of the partition's
 // earlier tiles (at most a few hundred numbers, summed by every workgroup for itself).  The
@@ -1395,7 +1696,7 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   float *dense = ws.at<float>(ws.lay.dense);
   const bool half = prm.kind == BPC_TOPK16;
   const int zero_selected = src.residual != nullptr;
-  const TopkLists lists{ws.at<uint32_t>(ws.lay.cand), g.P};
+  TopkLists lists{ws.at<uint32_t>(ws.lay.cand), g.P, nullptr, tilecnt, (uint32_t)cdiv(g.tiles_per_part, kTpgLoad)};
   // behind the short-list form of large partitions stands the long form as one resident kernel: its grid
   // comes from the occupancy query
   const void *long_fn = half ? reinterpret_cast<const void *>(&topk_long_form_kernel<true>)
@@ -1403,13 +1704,17 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   static PerDevice cache[2];
   const bool gated = g.part_elems > kAloneElems;
   const int capacity = gated ? cache[half].get([&] { return cluster_capacity(long_fn, kThreads, 0); }) : 0;
-  // the short-list form wants room for the k winners and as many again
-  const bool short_list = g.k_cap <= kTopkListCap / 2 && (!gated || capacity > 0);
+  // the short-list form wants room for the k winners and as many again; beyond, the group-list form wants the
+  // dense workspace and groups that are not listed to a large part
+  const bool group_lists = g.k_cap > kTopkListCap / 2 && g.k_cap <= kMostListed && g.part_elems >= 16ull * g.k_cap && !gated &&
+                           (src.residual || src.grad);
+  const bool short_list = group_lists || (g.k_cap <= kTopkListCap / 2 && (!gated || capacity > 0));
+  if (group_lists) lists.dense = reinterpret_cast<uint32_t *>(dense);
   // the vector being compressed ends up in the residual buffer (error feedback) or the workspace, or is
   // the gradient as it is
   float *buf = src.residual ? src.residual : src.grad && short_list && !gated ? nullptr : dense;
   const uint32_t load_grid = group_count(g, kTpgLoad);
-  TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status()};
+  TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status(), state};
   sh.lengths = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(sh.pairs) + TopkShared::pairs_bytes(g.P));
   hipError_t e = hipSuccess;
   if (short_list) {
@@ -1427,8 +1732,7 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   if (e != hipSuccess) return e;
   auto load = [&](auto s) {
     using Load = decltype(s);
-    const uint32_t guesses = has_begin_group<Load>::value ? 0u : g.P;
-    if (short_list) topk_load_kernel<Load, true><<<load_grid + guesses, kLoadThreads, 0, stream>>>(g, s, buf, hist, state, sh, lists);
+    if (short_list) topk_load_kernel<Load, true><<<load_grid + g.P, kLoadThreads, 0, stream>>>(g, s, buf, hist, state, sh, lists);
     else topk_load_kernel<Load, false><<<load_grid, kLoadThreads, 0, stream>>>(g, s, buf, hist, state, sh, lists);
   };
   if (src.grad) {
@@ -1438,8 +1742,19 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     // server: Delta straight from the n messages (they are taken to have the format of `prm`)
     uint32_t *starts = ws.at<uint32_t>(ws.lay.starts);
     const TopkMsgs m{src.msgs, src.residual, starts, (uint32_t)cdiv(g.tiles_per_part, kTpgLoad), g.k_cap, g.stride, half ? 1 : 0, 13};
-    topk_server_prep_kernel<<<dim3(g.P, src.msgs.n + (short_list ? 1 : 0)), kPrepThreads, 0, stream>>>(g, m, starts, sh, state, short_list);
-    load(TopkMsgsGroupSource{m});
+    const uint32_t rows = (short_list ? kSumPieces : 0u) + src.msgs.n * ((m.k_cap + kStartsPiece) / kStartsPiece);
+    float *sums = reinterpret_cast<float *>(lists.base);
+    topk_server_prep_kernel<<<dim3(g.P, rows), kPrepThreads, 0, stream>>>(g, m, starts, sums, short_list);
+    load(TopkMsgsGroupSource{m, sums});
+  }
+  if (group_lists) {
+    const uint32_t grid = g.P * (uint32_t)cdiv(lists.groups, kRangeGroups);
+    const TopkVector vec{buf ? buf : src.grad, !buf && src.dtype == BPC_F16};
+    topk_bins_kernel<<<grid, kSelThreads, 0, stream>>>(g, hist, sh, lists, vec);
+    topk_collect_kernel<<<grid, kSelThreads, 0, stream>>>(g, hist, sh, lists, vec);
+    if (half) topk_group_emit_kernel<true><<<grid, kSelThreads, 0, stream>>>(g, buf, vec, state, hist, sh, lists, payload, zero_selected);
+    else topk_group_emit_kernel<false><<<grid, kSelThreads, 0, stream>>>(g, buf, vec, state, hist, sh, lists, payload, zero_selected);
+    return hipGetLastError();
   }
   if (short_list) {
     // (as many workgroups as one round of them over the compute units takes)

@@ -338,3 +338,52 @@ def test_topk_without_error_feedback(gu, orc, geo, kind, dtype, pe, D, equal):
         for a, b in ((0, 16 + 4 * k), (vals, vals + size * k)):
             assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
     assert _long_form(gu, geo, pb, D, ws).any() == equal
+
+
+# k above 16384 with an error-feedback buffer or a plain gradient: a list for every 8192 elements
+@pytest.mark.parametrize("kind,ef,n", [("topk", True, 1), ("topk16", True, 1), ("topk", False, 1), ("topk", True, 3)])
+@pytest.mark.parametrize("pe,D,ratio", [(524288, 524288 + 1, 0.04), (524288, 2 * 524288 - 8192 + 5, 0.0625), (1_048_576, 300_007, 0.03), (1_048_576, 1_048_576 + 8192 * 9, 0.03)])
+@pytest.mark.parametrize("what", ["normal", "ties", "narrow", "equal", "one layer"])
+def test_topk_group_lists(gu, orc, geo, kind, ef, n, pe, D, ratio, what):
+    """Forms of the distribution: ties at the threshold, magnitudes within 2^-14 of each other, all equal (left
+    to the long form), and a stretch of a partition that holds most of what is listed (more than its groups'
+    lists have room for)."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
+    rs = np.random.default_rng(D)
+    v = rs.standard_normal(D).astype(np.float32)
+    if what == "ties":
+        v = np.round(v * 64.0) / np.float32(64.0)
+    elif what == "narrow":
+        v = ((1.0 + rs.random(D) * 2.0 ** -14) * rs.choice([-1.0, 1.0], D)).astype(np.float32)
+    elif what == "equal":
+        v = np.where(rs.random(D) < 0.5, -0.75, 0.75).astype(np.float32)
+    elif what == "one layer":
+        v[30_000:46_384] *= np.float32(100.0)
+    ws = gu.new_ws(pb, D, n)
+    ws.fill_(0xFF)
+    pay = gu.new_payload(pb, D)
+    if n == 1:
+        g = (v.astype(np.float16) if not ef and D % 2 else v)
+        res = (rs.standard_normal(D) * 1e-3).astype(np.float32) if ef and what == "normal" else np.zeros(D, np.float32) if ef else None
+        rd = gu.to_dev(res) if ef else None
+        ref = orc.compress(po, g, res)
+        bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+    else:
+        msgs = [orc.compress(po, (v * np.float32(0.5 + i)).astype(np.float32), None) for i in range(n)]
+        res = v.copy()
+        rd = gu.to_dev(res)
+        ref = orc.server_aggregate([po] * n, msgs, po, res, D)
+        bpc.bpc_server_aggregate([pb] * n, [gu.to_dev(m) for m in msgs], pb, rd, D, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    if ef:
+        assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+    stride, got, k_cap = orc.partition_stride(po), gu.to_host(pay), int(ratio * pe)
+    assert k_cap > 16384
+    for p in range(-(-D // pe)):
+        k = max(1, int(ratio * min(pe, D - p * pe)))
+        vals, size = 16 + 4 * (-(-k_cap // 4) * 4), 4 if kind == "topk" else 2
+        for a, b in ((0, 16 + 4 * k), (vals, vals + size * k)):
+            assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
+    if n == 1 and what != "ties" and not (what == "narrow" and not ef):
+        assert bool(_long_form(gu, geo, pb, D, ws)[0]) == (what == "equal")
