@@ -133,7 +133,7 @@ struct TopkLists {
   uint32_t *base;
   uint32_t P;
   uint32_t *dense;      // null: one list a partition
-  uint32_t *counts;     // group lists: four words a group: entries, entries above the bin of the threshold
+  uint32_t *counts;     // group lists: two words a group: entries, entries above the bin of the threshold
   uint32_t groups;      // of a full partition
   static constexpr uint32_t kNearCap = kTopkListCap - 8192;
   __device__ uint32_t *idx(uint32_t p) const { return base + (uint64_t)p * kTopkListCap; }
@@ -144,7 +144,7 @@ struct TopkLists {
     uint32_t *at = dense + g.part_base(p) + q * 8192u;
     return List{at, at + 4096, 4096u};
   }
-  __device__ uint32_t *count(uint32_t p, uint32_t q) const { return counts + 4ull * ((uint64_t)p * groups + q); }
+  __device__ uint32_t *count(uint32_t p, uint32_t q) const { return counts + 2ull * ((uint64_t)p * groups + q); }
 };
 
 // Whether partition p is left to the long form (uniform over the workgroup).
