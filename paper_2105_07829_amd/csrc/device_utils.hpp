@@ -219,4 +219,20 @@ __device__ inline uint32_t block_exclusive_scan(uint32_t x, uint32_t *lds /*THRE
   return before + incl - x;
 }
 
+// The first of the k ascending indices at `idx` that is at least `target`; one wave, the answer in all lanes.
+// (Whatever the message holds, the answer is at most k.)
+__device__ inline uint32_t wave_lower_bound(const uint32_t *idx, uint32_t k, uint32_t target) {
+  uint32_t lo = 0, len = k;
+  while (len > 0) {
+    const uint32_t step = (len + 63) / 64, at = (threadIdx.x & 63) * step;
+    const uint32_t below = (uint32_t)__popcll(__ballot(at < len && idx[lo + (at < len ? at : 0u)] < target));
+    // probe `below` - 1 is below the target (if any is), probe `below` is not
+    const uint32_t skip = below ? (below - 1) * step + 1 : 0u;
+    const uint32_t end = below ? (below * step < len ? below * step : len) : 0u;
+    lo += skip;
+    len = end > skip ? end - skip : 0u;
+  }
+  return lo;
+}
+
 }  // namespace bpc

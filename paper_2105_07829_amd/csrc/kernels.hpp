@@ -94,6 +94,16 @@ hipError_t dither_server_single_pass(const Geo &g, const bpc_params_t &prm, cons
 hipError_t dither_worker_single_pass(const Geo &g, const bpc_params_t &prm, const Source &src, uint8_t *payload,
                                      const Workspace &ws, hipStream_t stream, bool *used);
 
+// Random-k calls in which every workgroup (`tiles` of them, of `threads` threads) makes all draws of `messages`
+// messages of its partition again, instead of a launch in front that bins them: as long as that takes a
+// workgroup at most 32 rounds of four draws a thread (some 0.2 us each) and the device 2^20 blocks of four
+// draws (3 us) for every launch that is saved, `launches`.  Worker calls on 0.3 M / 1 M / 2 M f32 elements, k = 1 %:
+// 13.4 -> 7.0 / 7.4 / 12.0 us; server calls of 8 workers on 0.3 M 23.2 -> 13.8; Adam-style updates on 0.3 M 13.3 -> 6.7.
+inline bool randk_draws_again(const Geo &g, uint32_t tiles, uint32_t messages, uint32_t threads, uint32_t launches = 1) {
+  const uint64_t k = k_rule(g.k_ratio, g.D < g.part_elems ? g.D : g.part_elems);   // of the largest partition
+  return messages * k <= 128ull * threads && (uint64_t)tiles * messages * k <= (uint64_t)launches << 22;
+}
+
 // out = decode(payload), dense.
 // Tables for the update kernel's sparse decoder (see update.hip).
 constexpr uint32_t kRandkTableStride = 1025;

@@ -212,13 +212,59 @@ __device__ inline void randk_apply_draws(float *acc, uint32_t lo, const uint2 *l
   __syncthreads();
 }
 
+// Draw number t -> index for all draws of a partition, four a thread and round: fn(index, t).
+template <int THREADS, class FN>
+__device__ inline void randk_each_draw(const Philox &rng, uint32_t k, uint32_t d, FN fn) {
+  for (uint32_t t4 = threadIdx.x; 4 * t4 < k; t4 += THREADS) {
+    uint32_t rnd[4];
+    rng.block(t4, rnd);
+#pragma unroll
+    for (uint32_t c = 0; c < 4; ++c)
+      if (4 * t4 + c < k) fn((uint32_t)(((uint64_t)rnd[c] * d) >> 32), 4 * t4 + c);
+  }
+}
+// The draws that fall into the slice [lo, lo + len), found by drawing all of them again; those beyond the
+// room of the list are looked for again when they are needed.
+constexpr uint32_t kHitRoom = 1024;
+struct RandkHits {
+  uint2 at[kHitRoom];
+  uint32_t n;
+};
+template <int THREADS>
+__device__ inline void randk_find_hits(RandkHits &h, const Philox &rng, uint32_t k, uint32_t d, uint32_t lo, uint32_t len) {
+  randk_each_draw<THREADS>(rng, k, d, [&](uint32_t j, uint32_t t) {
+    if (j - lo < len) {
+      const uint32_t pos = atomicAdd(&h.n, 1u);
+      if (pos < kHitRoom) h.at[pos] = make_uint2(j, t);
+    }
+  });
+}
+template <int THREADS>
+__device__ inline void randk_apply_hits(float *acc, uint32_t lo, uint32_t len, const RandkHits &h, const Philox &rng, uint32_t k,
+                                        uint32_t d, float scale, float *val) {
+  __syncthreads();
+  const uint32_t n = h.n;
+  if (n <= kHitRoom) {   // (uniform)
+    randk_apply_draws<THREADS>(acc, lo, h.at, 0, n, scale, val);
+    return;
+  }
+  randk_each_draw<THREADS>(rng, k, d, [&](uint32_t j, uint32_t t) { if (j - lo < len) val[t] = acc[j - lo]; });
+  __syncthreads();
+  randk_each_draw<THREADS>(rng, k, d, [&](uint32_t j, uint32_t t) { if (j - lo < len) atomicAdd(&acc[j - lo], -(scale * val[t])); });
+  __syncthreads();
+}
+
 // Worker with error feedback in one pass over the data: a workgroup forms its tile of q = g + e
-// in LDS, serves the draws that fall into it (binned per tile by `randk_bin_kernel<true>`) and
-// writes the tile of the residual.
-template <class SRC>
+// in LDS, serves the draws that fall into it (binned per tile by `randk_bin_kernel<true>`; AGAIN, in small
+// calls: drawn again by every workgroup while its loads are on their way) and writes the tile of the
+// residual.
+struct RandkStream { uint64_t seed, stream_id; uint32_t *status; };   // of the outgoing message; the workspace's status word
+template <class SRC, bool AGAIN>
 __global__ __launch_bounds__(kThreads) void randk_tile_kernel(Geo g, SRC src, float *buf, uint8_t *payload, float value_scale,
-                                                              const uint2 *lists, const uint32_t *table) {
+                                                              const uint2 *lists, const uint32_t *table, RandkStream out) {
   __shared__ float acc[kTile];
+  __shared__ typename std::conditional<AGAIN, RandkHits, uint32_t>::type hits;
+  if (AGAIN && blockIdx.x == 0 && threadIdx.x == 0) out.status[0] = 0;   // (random-k has no waits)
   const uint32_t p = blockIdx.x / g.tiles_per_part, tile = blockIdx.x % g.tiles_per_part;
   const uint32_t d = g.part_size(p);
   const uint32_t lo = tile * kTile;
@@ -229,7 +275,12 @@ __global__ __launch_bounds__(kThreads) void randk_tile_kernel(Geo g, SRC src, fl
     hdr[0] = k; hdr[1] = 0; hdr[2] = 0; hdr[3] = 0;
   }
   const uint32_t *tab = table + (uint64_t)p * (kRbMaxBins + 1);
-  const uint32_t from = tab[tile], to = tab[tile + 1];
+  const uint32_t from = AGAIN ? 0u : tab[tile], to = AGAIN ? 0u : tab[tile + 1];
+  const Philox rng(out.seed, out.stream_id, p + g.part0);
+  if constexpr (AGAIN) {
+    if (threadIdx.x == 0) hits.n = 0;
+    __syncthreads();
+  }
   // the tile as rows of 1024 elements, 4 consecutive a thread, through descriptors of the
   // elements that exist: whole-line non-temporal accesses, all loads requested before the first
   // is used (elements past a shorter last partition read as zero and are not written back)
@@ -248,6 +299,7 @@ __global__ __launch_bounds__(kThreads) void randk_tile_kernel(Geo g, SRC src, fl
       gr[u] = tile_load4(gb, threadIdx.x * 4 * (uint32_t)sizeof(T), u * kRowElems * (uint32_t)sizeof(T), (const T *)nullptr);
       er[u] = eb.load16<kNonTemporal>(threadIdx.x * 16, u * kRowElems * 4);
     }
+    if constexpr (AGAIN) randk_find_hits<kThreads>(hits, rng, k, d, lo, valid);
     if constexpr (sizeof(T) == 2) patch_last_half<kRows, kRowElems>(gb, valid, gr);
 #pragma unroll
     for (int u = 0; u < kRows; ++u) {
@@ -260,7 +312,8 @@ __global__ __launch_bounds__(kThreads) void randk_tile_kernel(Geo g, SRC src, fl
   }
   const float scale = value_scale >= 0.0f ? value_scale : (float)d / (float)k;
   float *val = reinterpret_cast<float *>(payload + (uint64_t)p * g.stride + kHeaderBytes);
-  randk_apply_draws<kThreads>(acc, lo, lists + (uint64_t)p * g.k_cap, from < k ? from : k, to < k ? to : k, scale, val);
+  if constexpr (AGAIN) randk_apply_hits<kThreads>(acc, lo, valid, hits, rng, k, d, scale, val);
+  else randk_apply_draws<kThreads>(acc, lo, lists + (uint64_t)p * g.k_cap, from < k ? from : k, to < k ? to : k, scale, val);
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
     const float4 a = reinterpret_cast<const float4 *>(acc)[u * kThreads + threadIdx.x];
@@ -357,6 +410,75 @@ __global__ __launch_bounds__(kRbSumThreads) void randk_sum_binned_kernel(Geo g, 
       const float4 a = *reinterpret_cast<const float4 *>(acc + q);
       ob.store16<kNonTemporal>(as_u32x4(a.x, a.y, a.z, a.w), q * 4);
     }
+  }
+}
+
+// Server with a residual, small calls: the same in one launch, every workgroup drawing all messages' indices
+// and the outgoing ones again for its slice of 8192 elements.
+constexpr int kAgainThreads = 512;
+constexpr uint32_t kAgainSlice = 8192;
+__global__ __launch_bounds__(kAgainThreads) void randk_sum_again_kernel(Geo g, WorkerMsgs msgs, RandkScales sc, const float *res, float *buf,
+                                                                        uint8_t *payload, float value_scale, RandkStream out) {
+  __shared__ __align__(16) float acc[kAgainSlice];
+  __shared__ RandkHits hits;
+  const uint32_t slices_per_part = (uint32_t)cdiv(g.part_elems, kAgainSlice);
+  const uint32_t p = blockIdx.x / slices_per_part, s = blockIdx.x % slices_per_part, lo = s * kAgainSlice;
+  const uint32_t d = g.part_size(p);
+  if (blockIdx.x == 0 && threadIdx.x == 0) out.status[0] = 0;   // (random-k has no waits)
+  if (lo >= d) return;
+  const uint32_t len = d - lo < kAgainSlice ? d - lo : kAgainSlice;
+  const uint64_t at = uniform_off(g.part_base(p) + lo);
+  constexpr int kRows = kAgainSlice / (kAgainThreads * 4);
+  const TileBuf rb(res + at, len * 4);
+  u32x4 early[kRows];
+#pragma unroll
+  for (int c = 0; c < kRows; ++c) early[c] = rb.load16<kNonTemporal>((c * kAgainThreads + threadIdx.x) * 16, 0);
+  for (uint32_t q = threadIdx.x; q < kAgainSlice / 4; q += kAgainThreads) reinterpret_cast<float4 *>(acc)[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  if (threadIdx.x == 0) hits.n = 0;
+  __syncthreads();
+  // worker by worker (a barrier in between keeps the order of the sum)
+  for (int i = 0; i < msgs.n; ++i) {
+    const uint8_t *rec = msgs.ptr[i] + (uint64_t)p * g.stride;
+    uint32_t k = *reinterpret_cast<const uint32_t *>(rec);
+    k = __builtin_amdgcn_readfirstlane(k > g.k_cap ? g.k_cap : k);
+    const TileBuf vb(rec + kHeaderBytes, k * 4);
+    const float scale = sc.value_scale[i] >= 0.0f ? sc.value_scale[i] : (float)d / (float)k;
+    const Philox rng(msgs.seed[i], msgs.stream_id[i], p + g.part0);
+    for (uint32_t t4 = threadIdx.x; 4 * t4 < k; t4 += kAgainThreads) {
+      // (all four values are requested before it is known which are wanted)
+      float v[4];
+      widen4(vb.load16(t4 * 16, 0), v);
+      uint32_t rnd[4];
+      rng.block(t4, rnd);
+#pragma unroll
+      for (uint32_t c = 0; c < 4; ++c) {
+        const uint32_t rel = (uint32_t)(((uint64_t)rnd[c] * d) >> 32) - lo;
+        if (rel < len && 4 * t4 + c < k) atomicAdd(&acc[rel], scale * v[c]);
+      }
+    }
+    __syncthreads();
+  }
+  const uint32_t k = (uint32_t)k_of_device(g, p);
+  const Philox rng(out.seed, out.stream_id, p + g.part0);
+  randk_find_hits<kAgainThreads>(hits, rng, k, d, lo, len);
+#pragma unroll
+  for (int c = 0; c < kRows; ++c) {
+    float4 *a = reinterpret_cast<float4 *>(acc) + c * kAgainThreads + threadIdx.x;
+    float r[4];
+    widen4(early[c], r);
+    *a = make_float4(a->x * msgs.inv_n + r[0], a->y * msgs.inv_n + r[1], a->z * msgs.inv_n + r[2], a->w * msgs.inv_n + r[3]);
+  }
+  if (s == 0 && threadIdx.x == 0) {
+    uint32_t *hdr = reinterpret_cast<uint32_t *>(payload + (uint64_t)p * g.stride);
+    hdr[0] = k; hdr[1] = 0; hdr[2] = 0; hdr[3] = 0;
+  }
+  const float scale = value_scale >= 0.0f ? value_scale : (float)d / (float)k;
+  randk_apply_hits<kAgainThreads>(acc, lo, len, hits, rng, k, d, scale, reinterpret_cast<float *>(payload + (uint64_t)p * g.stride + kHeaderBytes));
+  const TileBuf ob(buf + at, len * 4);
+#pragma unroll
+  for (int c = 0; c < kRows; ++c) {
+    const float4 a = reinterpret_cast<const float4 *>(acc)[c * kAgainThreads + threadIdx.x];
+    ob.store16<kNonTemporal>(as_u32x4(a.x, a.y, a.z, a.w), (c * kAgainThreads + threadIdx.x) * 16);
   }
 }
 
@@ -469,6 +591,16 @@ hipError_t randk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_
                                                                payload, prm.seed, prm.stream_id);
       return hipGetLastError();
     }
+    const RandkStream out{prm.seed, prm.stream_id, status};
+    if (randk_draws_again(g, g.n_tiles, 1, kThreads)) {
+      if (src.dtype == BPC_F16)
+        randk_tile_kernel<GradSource<__half>, true><<<g.n_tiles, kThreads, 0, stream>>>(
+            g, GradSource<__half>{(const __half *)src.grad, src.residual}, buf, payload, prm.value_scale, nullptr, nullptr, out);
+      else
+        randk_tile_kernel<GradSource<float>, true><<<g.n_tiles, kThreads, 0, stream>>>(
+            g, GradSource<float>{(const float *)src.grad, src.residual}, buf, payload, prm.value_scale, nullptr, nullptr, out);
+      return hipGetLastError();
+    }
     if (g.tiles_per_part <= kRbMaxBins && one_list + one_table <= sizeof(float) * g.D) {
       // one pass over the data (q goes to the residual buffer, so the dense workspace is free for the list)
       uint2 *lists = reinterpret_cast<uint2 *>(dense);
@@ -476,11 +608,11 @@ hipError_t randk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_
       hipError_t e = launch_randk_bin<true>(g, out_stream, out_scale, 1, 12, lists, table, stream, status);
       if (e != hipSuccess) return e;
       if (src.dtype == BPC_F16)
-        randk_tile_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, GradSource<__half>{(const __half *)src.grad, src.residual}, buf,
-                                                              payload, prm.value_scale, lists, table);
+        randk_tile_kernel<GradSource<__half>, false><<<g.n_tiles, kThreads, 0, stream>>>(
+            g, GradSource<__half>{(const __half *)src.grad, src.residual}, buf, payload, prm.value_scale, lists, table, out);
       else
-        randk_tile_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, GradSource<float>{(const float *)src.grad, src.residual}, buf,
-                                                              payload, prm.value_scale, lists, table);
+        randk_tile_kernel<GradSource<float>, false><<<g.n_tiles, kThreads, 0, stream>>>(
+            g, GradSource<float>{(const float *)src.grad, src.residual}, buf, payload, prm.value_scale, lists, table, out);
       return hipGetLastError();
     }
     hipError_t e0 = fill_zero(status, 16, stream);
@@ -515,6 +647,13 @@ hipError_t randk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_
     } else {
       RandkScales sc;
       for (int i = 0; i < src.msgs.n; ++i) sc.value_scale[i] = in_prm[i].value_scale;
+      const uint32_t per_part = (uint32_t)cdiv(g.part_elems, kAgainSlice);
+      const uint32_t again_slices = (g.P - 1) * per_part + (uint32_t)cdiv(g.D - (uint64_t)(g.P - 1) * g.part_elems, kAgainSlice);
+      if (src.residual && randk_draws_again(g, again_slices, src.msgs.n + 1, kAgainThreads, 2)) {
+        randk_sum_again_kernel<<<again_slices, kAgainThreads, 0, stream>>>(g, src.msgs, sc, src.residual, buf, payload, prm.value_scale,
+                                                                           RandkStream{prm.seed, prm.stream_id, status});
+        return hipGetLastError();
+      }
       // slices of 8192 elements, larger (up to what LDS holds) if a partition would have more than kRbMaxBins of them
       uint32_t slice_shift = 13;
       while (slice_shift < 15 && cdiv(g.part_elems, 1ull << slice_shift) > kRbMaxBins) ++slice_shift;

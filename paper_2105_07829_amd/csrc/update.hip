@@ -239,7 +239,8 @@ struct DenseDec {
 // are one stretch of a list (top-k: of the record itself, whose entries come by ascending
 // index; random-k: of the record's draws binned per tile beforehand), found through a table of
 // where each tile's stretch starts, and laid out in LDS by the workgroup that has the tile.
-template <int TILE, int THREADS>
+// OWN (small calls): no table; the workgroup searches the record (top-k) or makes all draws again (random-k).
+template <int TILE, int THREADS, bool OWN = false>
 struct SparseTileDec {
   const uint8_t *payload;
   uint64_t stride;
@@ -248,6 +249,8 @@ struct SparseTileDec {
   const uint32_t *starts;    // [partition][tile .. ], `starts_stride` words a partition
   uint32_t starts_stride;
   const uint2 *pairs;        // random-k: [partition][k_cap]
+  struct Draws { uint64_t seed, stream_id, D, part_elems; uint32_t part0; float value_scale; };
+  Draws draws;               // random-k, OWN
   __device__ const float *dense_base() const { return nullptr; }
   static constexpr int kLdsFloats = TILE;
   __device__ void begin(uint32_t, float *) const {}
@@ -257,12 +260,46 @@ struct SparseTileDec {
     const uint8_t *rec = payload + (uint64_t)p * stride;
     uint32_t k = *reinterpret_cast<const uint32_t *>(rec);
     k = k > k_cap ? k_cap : k;
-    const uint32_t *tab = starts + (uint64_t)p * starts_stride;
-    uint32_t s = tab[tile], e = tab[tile + 1];
-    s = s < k ? s : k;
-    e = e < k ? e : k;
     const uint32_t lo = tile * TILE;
-    __syncthreads();
+    uint32_t s, e;
+    if constexpr (OWN) {
+      __shared__ uint32_t ends[2];
+      const uint32_t wave = threadIdx.x >> 6;
+      if (mode != 2 && wave < 2) {
+        const uint32_t at = wave_lower_bound(reinterpret_cast<const uint32_t *>(rec + kHeaderBytes), k, lo + wave * TILE);
+        if ((threadIdx.x & 63) == 0) ends[wave] = at;
+      }
+      __syncthreads();
+      if (mode == 2) {
+        const uint64_t rest = draws.D - (uint64_t)p * draws.part_elems;
+        const uint32_t d = (uint32_t)(rest < draws.part_elems ? rest : draws.part_elems);
+        const float scale = draws.value_scale >= 0.0f ? draws.value_scale : (float)d / (float)k;
+        const Philox rng(draws.seed, draws.stream_id, p + draws.part0);
+        const TileBuf vb(rec + kHeaderBytes, k * 4);
+        for (uint32_t t4 = threadIdx.x; 4 * t4 < k; t4 += THREADS) {
+          const u32x4 v = vb.load16(t4 * 16, 0);   // (before it is known which are wanted)
+          const uint32_t vs[4] = {v.x, v.y, v.z, v.w};
+          uint32_t rnd[4];
+          rng.block(t4, rnd);
+#pragma unroll
+          for (uint32_t c = 0; c < 4; ++c) {
+            const uint32_t rel = (uint32_t)(((uint64_t)rnd[c] * d) >> 32) - lo;
+            if (rel < (uint32_t)TILE && 4 * t4 + c < k) atomicAdd(&lds[rel], scale * __uint_as_float(vs[c]));   // an index may repeat
+          }
+        }
+        __syncthreads();
+        return;
+      }
+      s = ends[0];
+      e = ends[1];
+    } else {
+      const uint32_t *tab = starts + (uint64_t)p * starts_stride;
+      s = tab[tile];
+      e = tab[tile + 1];
+      s = s < k ? s : k;
+      e = e < k ? e : k;
+      __syncthreads();
+    }
     if (mode == 2) {
       const uint2 *list = pairs + (uint64_t)p * k_cap;
       for (uint32_t q = s + threadIdx.x; q < e; q += THREADS) {
@@ -298,6 +335,8 @@ template <class DEC, class = void>
 struct has_begin_tile : std::false_type {};
 template <class DEC>
 struct has_begin_tile<DEC, std::void_t<decltype(&DEC::begin_tile)>> : std::true_type {};
+
+constexpr uint32_t kOwnTiles = 512;   // tiles of an update call that goes without tables, at most
 
 struct OptArgs {
   float lr, beta1, beta2, eps, wd, bc1, bc2, phi_lo, phi_hi;
@@ -1223,6 +1262,26 @@ hipError_t adaptive_update(const Geo &g, const bpc_params_t &prm, const uint8_t 
     const uint32_t tiles = (uint32_t)cdiv(g.part_elems, 1ull << shift);
     const uint32_t *table = nullptr;
     const uint2 *pairs = nullptr;
+    // small calls go without the launch that makes the table (top-k, Adam-style: 0.3 M elements 13.5 -> 6.7 us, 2 M
+    // 13.3 -> 9.7; LANS over the partitions, 4 M, 26.3 -> 24.2)
+    const uint32_t tiles_all = (uint32_t)cdiv(g.D, 1ull << shift);
+    if (tiles_all <= kOwnTiles && (prm.kind != BPC_RANDK || randk_draws_again(g, tiles_all, 1, lans ? kBThreads : kThreads))) {
+      const int mode = prm.kind == BPC_RANDK ? 2 : prm.kind == BPC_TOPK16 ? 1 : 0;
+      auto run = [&](auto dec, auto call) {
+        return call(decltype(dec){payload, g.stride, g.k_cap, mode, nullptr, 0, nullptr,
+                                  {prm.seed, prm.stream_id, g.D, g.part_elems, g.part0, prm.value_scale}});
+      };
+      if (!lans)
+        return run(SparseTileDec<kTile, kThreads, true>{}, [&](auto dec) {
+          adam_update_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, dec, x, m, v, o);
+          return hipGetLastError();
+        });
+      bool used = false;
+      const hipError_t e = opt.block_offsets
+          ? run(SparseTileDec<kSTile, kBThreads, true>{}, [&](auto dec) { return run_lans_blocks(g, dec, x, m, v, o, ws, stream, &used); })
+          : run(SparseTileDec<kSTile, kLThreads, true>{}, [&](auto dec) { return run_lans_single(g, dec, x, m, v, o, ws, stream, &used); });
+      if (e != hipSuccess || used) return e;
+    }
     uint32_t table_stride = 0;
     int mode = -1;
     if (prm.kind == BPC_RANDK) {
@@ -1244,13 +1303,13 @@ hipError_t adaptive_update(const Geo &g, const bpc_params_t &prm, const uint8_t 
     }
     if (mode >= 0) {
       if (!lans) {
-        adam_update_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, SparseTileDec<kTile, kThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs}, x, m, v, o);
+        adam_update_kernel<<<g.n_tiles, kThreads, 0, stream>>>(g, SparseTileDec<kTile, kThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs, {}}, x, m, v, o);
         return hipGetLastError();
       }
       bool used = false;
       hipError_t e = opt.block_offsets
-          ? run_lans_blocks(g, SparseTileDec<kSTile, kBThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs}, x, m, v, o, ws, stream, &used)
-          : run_lans_single(g, SparseTileDec<kSTile, kLThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs}, x, m, v, o, ws, stream, &used);
+          ? run_lans_blocks(g, SparseTileDec<kSTile, kBThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs, {}}, x, m, v, o, ws, stream, &used)
+          : run_lans_single(g, SparseTileDec<kSTile, kLThreads>{payload, g.stride, g.k_cap, mode, table, table_stride, pairs, {}}, x, m, v, o, ws, stream, &used);
       if (e != hipSuccess || used) return e;
       // (the single-pass kernel declined the shape: the dense decode below overwrites the lists)
     }

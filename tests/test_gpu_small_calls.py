@@ -387,3 +387,89 @@ def test_topk_group_lists(gu, orc, geo, kind, ef, n, pe, D, ratio, what):
             assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), p
     if n == 1 and what != "ties" and not (what == "narrow" and not ef):
         assert bool(_long_form(gu, geo, pb, D, ws)[0]) == (what == "equal")
+
+
+# small random-k calls make their draws again in every workgroup: one tile and several partitions, more hits in a
+# tile than its list has room (k = d / 2), and sizes on either side of the rule (2 M / 4 M elements)
+@pytest.mark.parametrize("pe,D,ratio,n", [(1024, 1000, 0.01, 2), (16384, 5 * 16384 + 4099, 0.5, 2), (16384, 8193, 1.0, 1), (131072, 131072 + 8192 * 3 + 1, 0.03, 8),
+                                          (1_048_576, 1_048_576 + 70_001, 0.01, 3), (1_048_576, 4 * 1_048_576 + 3, 0.01, 3)])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_randk_small_and_large_calls(gu, orc, pe, D, ratio, n, dtype):
+    import torch
+    bpc = gu.bpc
+    rs = np.random.default_rng(D)
+    prm = [gu.both_params(orc, "randk", pe, k_ratio=ratio, seed=3, stream_id=100 + i, value_scale=1.0 if i == n else -1.0) for i in range(n + 1)]
+    ws = gu.new_ws(prm[0][1], D, n)
+    ws.fill_(0xFF)
+    pays, close = [], lambda a, b: np.all(np.abs(a - b) <= 1e-6 * (np.abs(b) + np.abs(b).mean()))
+    for i in range(n):
+        g = (rs.standard_normal(D) * 1e-2).astype(dtype)
+        res = (rs.standard_normal(D) * 1e-3).astype(np.float32)
+        rd, pay = gu.to_dev(res), gu.new_payload(prm[i][1], D)
+        bpc.bpc_compress(prm[i][1], gu.to_dev(g), rd, pay, ws)
+        bpc.workspace_check(prm[i][1], D, ws)
+        ref = orc.compress(prm[i][0], g, res)
+        pays.append(ref)
+        _equal_randk(orc, prm[i][0], gu.to_host(pay), ref, pe, D, ratio, exact=True)
+        # (repeated draws: many differences of one element in any order)
+        assert close(gu.to_host(rd), res) if ratio < 0.5 else np.abs(gu.to_host(rd) - res).max() <= 1e-5 * max(1.0, 1.0 / ratio)
+    s = (rs.standard_normal(D) * 1e-3).astype(np.float32)
+    sd, out = gu.to_dev(s), gu.new_payload(prm[n][1], D)
+    bpc.bpc_server_aggregate([p[1] for p in prm[:n]], [gu.to_dev(p) for p in pays], prm[n][1], sd, D, out, ws)
+    bpc.workspace_check(prm[n][1], D, ws)
+    ref = orc.server_aggregate([p[0] for p in prm[:n]], pays, prm[n][0], s, D)
+    _equal_randk(orc, prm[n][0], gu.to_host(out), ref, pe, D, ratio, exact=False)
+    assert np.abs(gu.to_host(sd) - s).max() <= 1e-6 * 40 * np.abs(s).max()
+    x, m, v = [(rs.standard_normal(D) * c).astype(np.float32) for c in (0.02, 3e-4, 1e-3)]
+    v = v * v
+    dx, dm, dv = gu.to_dev(x), gu.to_dev(m), gu.to_dev(v)
+    hyper = (1e-3, 0.9, 0.999, 1e-8, 0.01, 3)
+    bpc.bpc_adaptive_update(prm[n][1], gu.to_dev(ref), dx, dm, dv, bpc.make_opt(bpc.OPT_ADAM, *hyper), ws)
+    bpc.workspace_check(prm[n][1], D, ws)
+    orc.adaptive_update(prm[n][0], ref, D, x, m, v, orc.make_opt(orc.OPT_ADAM, *hyper))
+    for a, b in ((dx, x), (dm, m), (dv, v)):
+        assert close(gu.to_host(a), b)
+
+
+def _equal_randk(orc, po, got, ref, pe, D, ratio, exact):
+    stride = orc.partition_stride(po)
+    for p in range(-(-D // pe)):
+        k = max(1, int(ratio * min(pe, D - p * pe)))
+        a, b = got[p * stride:p * stride + 16 + 4 * k], ref[p * stride:p * stride + 16 + 4 * k]
+        assert np.array_equal(a[:16], b[:16]), p
+        va, vb = a[16:].view(np.float32), b[16:].view(np.float32)
+        assert np.array_equal(va, vb) if exact else np.abs(va - vb).max() <= 1e-6 * 40 * np.abs(vb).max(), p
+
+
+# the search of an update call without a table, tiles of 4096 and 8192 elements: ends inside and on a tile, and a call
+# of more tiles than the rule takes
+@pytest.mark.parametrize("kind,ratio", [("topk", 0.01), ("topk16", 0.03), ("topk", 1.0), ("randk", 0.02)])
+@pytest.mark.parametrize("pe,D", [(8192, 3 * 8192 + 1), (131072, 131072 + 4096), (131072, 32769), (1_048_576, 5 * 1_048_576 + 77)])
+@pytest.mark.parametrize("opt", ["adam", "lans", "blocks"])
+def test_sparse_updates_with_and_without_a_table(gu, orc, kind, ratio, pe, D, opt):
+    import torch
+    bpc = gu.bpc
+    if ratio == 1.0 and D > 10 ** 6:
+        pytest.skip("a message as large as the gradient adds nothing here")
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio, seed=2, stream_id=7)
+    rs = np.random.default_rng(D)
+    pay = orc.compress(po, rs.standard_normal(D).astype(np.float32), None)
+    x, m, v = [(rs.standard_normal(D) * c).astype(np.float32) for c in (0.02, 3e-4, 1e-3)]
+    v = v * v
+    x0 = x.copy()
+    dx, dm, dv = gu.to_dev(x), gu.to_dev(m), gu.to_dev(v)
+    offs = np.unique(np.array([0, 1000, 9000, 9001, 30000, D], dtype=np.uint64).clip(0, D)) if opt == "blocks" else None
+    nb = 0 if offs is None else len(offs) - 1
+    hyper = (1e-3, 0.9, 0.999, 1e-8, 0.01, 3)
+    kind_b, kind_o = (bpc.OPT_ADAM, orc.OPT_ADAM) if opt == "adam" else (bpc.OPT_LANS, orc.OPT_LANS)
+    ob = bpc.make_opt(kind_b, *hyper, block_offsets=None if offs is None else torch.from_numpy(offs.astype("int64")).to(gu.DEV))
+    oo = orc.make_opt(kind_o, *hyper) if offs is None else orc.make_opt(kind_o, *hyper, block_offsets=offs)
+    ws = torch.full((max(bpc.workspace_bytes(pb, D, 1), bpc.update_workspace_bytes(pb, D, nb)),), 0xFF, dtype=torch.uint8, device=gu.DEV)
+    bpc.bpc_adaptive_update(pb, gu.to_dev(pay), dx, dm, dv, ob, ws)
+    bpc.workspace_check(pb, D, ws)
+    orc.adaptive_update(po, pay, D, x, m, v, oo)
+    tol = lambda a, b: np.all(np.abs(gu.to_host(a) - b) <= 1e-6 * (np.abs(b) + np.abs(b).mean()))
+    assert tol(dm, m) and tol(dv, v) and tol(dx, x)
+    if opt != "adam":
+        edges = offs if offs is not None else np.unique(np.append(np.arange(0, D, pe), D))
+        assert gu.lans_step_close(gu.to_host(dx), x, x0, blocks=edges)
