@@ -173,8 +173,6 @@ __global__ __launch_bounds__(kThreads) void dither_apply_kernel(Geo g, SRC src, 
 
 hipError_t dither_encode(const Geo &g, const bpc_params_t &prm, const Source &src, uint8_t *payload,
                          const Workspace &ws, hipStream_t stream) {
-  // (the single-pass server handles up to 15 levels; beyond that it declines and the server
-  // side takes the passes below)
   const bool wide = prm.kind == BPC_DITHER && dither_planes(prm.levels) > 0;
   // Partitions that are a whole number of register tiles go to the single-pass kernel (which bounds a
   // shorter last one through its buffer descriptors), other shapes to the passes below.

@@ -44,9 +44,17 @@ __device__ inline uint32_t byte_and(uint32_t x, uint32_t mask) {
 // WIDE: linear levels 8..15 (the 5-bit form): one bit plane beside the nibbles, on the way in
 // and on the way out; a worker's table then has 32 entries, index = plane bit << 4 | nibble,
 // and the workers come in groups of four so that their words and plane bytes fit the registers.
+// WIDE with NW == 0: any number of linear levels beyond 7 (up to three planes) and of workers.  A worker's
+// table holds the 64 magnitudes, index = plane bits << 3 | low level bits; the sign is put on the value.
+// Bound by its vector instructions; in place of the three passes over the messages' planes (whose sums are
+// formed twice, a plane's bits picked one by one): 31 levels, 5 workers, 1 M / 3 M elements 27 -> 12 / 41 -> 18 us;
+// 63 levels, 4 workers, 100 M 888 -> 290; 15 levels, 5 workers, 100 M f16 800 -> 311.  The forms with NW > 0 stay for
+// 15 levels (8 workers, 100 M: 279 us): their tables hold signed values.
 template <bool EF, bool LINF, int NW, bool NAT, bool WIDE = false>
 struct DitherServerOp {
-  static constexpr int kThreads = NW > 0 ? 512 : kSThreads;
+  static constexpr bool kAnyWide = WIDE && NW == 0;
+  static constexpr int kPlanes = !WIDE ? 0 : kAnyWide ? 3 : 1;   // planes of the output at most
+  static constexpr int kThreads = NW > 0 || WIDE ? 512 : kSThreads;
   static constexpr int kDSRows = kSTile / (kThreads * 8);   // 2 or 4
   static constexpr int kPerThread = 8 * kDSRows;
   struct Raw { u32x4 e[2 * kDSRows]; };
@@ -54,14 +62,16 @@ struct DitherServerOp {
   struct Ctx { float nu, top_over_nu; int mode; const float *mag; };
   static constexpr bool kMax = LINF;
   static constexpr int kRowsPerTile = kDSRows;
-  static constexpr int kLutStride = WIDE ? 32 : 16;
+  static constexpr int kLutStride = kAnyWide ? 64 : WIDE ? 32 : 16;
   // decode tables (at most 1024 floats), the output magnitudes, and (WIDE) the spread table:
   // for each value of a plane byte, its even bits at bit 6 of the four bytes of one word and its
   // odd bits likewise in a second word, i.e. where the "plane bit << 4" of a table index falls
   // once a word's nibbles sit at bits 2..5 of its bytes
-  static constexpr int kSpreadAt = kMaxWorkers * 16 + 16;
-  static constexpr int kTableFloats = kSpreadAt + (WIDE ? 512 : 0);
-  static_assert(!WIDE || (NW > 0 && NW * 32 <= kMaxWorkers * 16), "tables of the wide form must fit");
+  // (any width: at most 4096 floats of tables and 64 output magnitudes; no spread table)
+  static constexpr int kMagAt = kMaxWorkers * (kAnyWide ? 64 : 16);
+  static constexpr int kSpreadAt = kMagAt + (kAnyWide ? 64 : 16);
+  static constexpr int kTableFloats = kSpreadAt + (WIDE && !kAnyWide ? 512 : 0);
+  static_assert(!WIDE || NW * 32 <= kMaxWorkers * 16, "tables of the wide form must fit");
   static constexpr bool kPersistent = false;
   static constexpr int kWavesPerSimd = (NW > 8 && !WIDE) ? 6 : 4;
   static constexpr uint64_t kTaggedTenths = (NW > 8 && !WIDE) ? 26 : 40;
@@ -103,15 +113,15 @@ struct DitherServerOp {
   }
 
   // Decode tables of all workers for partition p: lut[i*16 + nibble], or (WIDE)
-  // lut[i*32 + (plane bit << 4 | nibble)].
+  // lut[i*32 + (plane bit << 4 | nibble)], or (any width) lut[i*64 + level].
   __device__ void fill_luts(uint32_t p, float *lut) const {
     __syncthreads();
     for (int e = threadIdx.x; e < msgs.n * kLutStride; e += kThreads) {
       const int i = e / kLutStride, code = e % kLutStride;
       const float nu = *reinterpret_cast<const float *>(msgs.ptr[i] + (uint64_t)p * g.stride);
-      const uint32_t level = (code & 7) | ((code >> 4) << 3);
+      const uint32_t level = kAnyWide ? (uint32_t)code : (code & 7) | ((code >> 4) << 3);
       const float mag = level <= levels ? dither_mag(nu, level, levels, NAT) : 0.0f;
-      lut[e] = (code & 8) ? -mag : mag;
+      lut[e] = !kAnyWide && (code & 8) ? -mag : mag;
     }
     __syncthreads();
   }
@@ -130,8 +140,49 @@ struct DitherServerOp {
 #pragma unroll
     for (int u = 0; u < kDSRows; ++u) out[u] = plane[u * kThreads + threadIdx.x];
   }
+  // Any width: the bytes of all planes that cover this thread's 8 elements of each row.
+  __device__ void load_all_planes(uint32_t item, int i, uint32_t out[3][kDSRows]) const {
+    const uint32_t planes = dither_planes(levels);
+    const uint64_t plane_bytes = dither_plane_bytes(g.part_elems);
+    const uint8_t *plane = msgs.ptr[i] + uniform_off((uint64_t)part_of(item) * g.stride + dither_plane0(g.part_elems) + (tile_off(item) >> 3));
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int u = 0; u < kDSRows; ++u) out[t][u] = t < (int)planes ? (plane + t * plane_bytes)[u * kThreads + threadIdx.x] : 0u;
+  }
+  // Any width: the table offset level*4 of an element is one byte of two words (even and odd elements):
+  // the low level bits at bits 2..4 of the bytes, plane t's bit at bit 5 + t.  Bits 0, 2, 4, 6 of a plane byte
+  // come to bits 0, 8, 16, 24 by one 24-bit multiplication (copies 6 places apart: the products' other bits
+  // meet in pairs whose carries stay between them).
+  __device__ static uint32_t spread_even(uint32_t b) { return __umul24(b & 0x55u, 0x41041u) & 0x01010101u; }
+  __device__ static void add_worker_any(const uint32_t word[kDSRows], const uint32_t pb[3][kDSRows], const float *lut_i,
+                                        float acc[kPerThread]) {
+    const char *lut_b = reinterpret_cast<const char *>(lut_i);
+#pragma unroll
+    for (int u = 0; u < kDSRows; ++u) {
+      uint32_t even = (word[u] << 2) & 0x1c1c1c1cu, odd = (word[u] >> 2) & 0x1c1c1c1cu;
+#pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        even |= spread_even(pb[t][u]) << (5 + t);
+        odd |= spread_even(pb[t][u] >> 1) << (5 + t);
+      }
+      float v[8];
+      v[0] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(even, 0xfcu));
+      v[1] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(odd, 0xfcu));
+      v[2] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(even, 0xfcu));
+      v[3] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(odd, 0xfcu));
+      v[4] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(even, 0xfcu));
+      v[5] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(odd, 0xfcu));
+      v[6] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(even, 0xfcu));
+      v[7] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(odd, 0xfcu));
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        acc[8 * u + c] = acc[8 * u + c] + __uint_as_float(__float_as_uint(v[c]) | ((word[u] << (28 - 4 * c)) & 0x80000000u));
+    }
+  }
+
   // WIDE, once per workgroup: the spread table.
-  template <bool W = WIDE, std::enable_if_t<W, int> = 0>
+  template <bool W = WIDE && !kAnyWide, std::enable_if_t<W, int> = 0>
   __device__ void init(float *table) const {
     if (threadIdx.x < 256) {
       uint32_t even = 0, odd = 0;
@@ -197,7 +248,24 @@ struct DitherServerOp {
     float acc[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) acc[k] = 0.0f;
-    if (WIDE) {
+    if (kAnyWide) {
+      // four workers at a time (a last group asks for its last worker again in place of those it lacks)
+      constexpr int kGroup = 4;
+#pragma unroll 1
+      for (int i0 = 0; i0 < msgs.n; i0 += kGroup) {
+        uint32_t word[kGroup][kDSRows], pb[kGroup][3][kDSRows];
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+          const int i = i0 + k < msgs.n ? i0 + k : msgs.n - 1;
+          load_words(item, i, word[k]);
+          load_all_planes(item, i, pb[k]);
+        }
+        if (i0 == 0) fill_luts(p, table);
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k)
+          if (i0 + k < msgs.n) add_worker_any(word[k], pb[k], table + (i0 + k) * 64, acc);
+      }
+    } else if (WIDE) {
       // groups of four workers, each requested in one go (more in flight would not fit the
       // registers next to the tile of the older partition)
       constexpr int kGroup = NW > 4 ? 4 : (NW > 0 ? NW : 1);
@@ -280,7 +348,7 @@ struct DitherServerOp {
       hdr[0] = __float_as_uint(nu);
       hdr[1] = 0; hdr[2] = 0; hdr[3] = 0;
     }
-    float *mag = table + kMaxWorkers * 16;
+    float *mag = table + kMagAt;
     dither_fill_table(nu, levels, NAT, mag);
     const float top_over_nu = dither_top(levels, NAT) / nu;
     return Ctx{nu, top_over_nu, dither_mode(nu, top_over_nu), mag};
@@ -292,13 +360,17 @@ struct DitherServerOp {
     const Philox rng(seed, stream_id, p + g.part0);
     const uint32_t j0 = tile_off(item) + (u * kThreads + threadIdx.x) * 8;
     float r[8];
-    uint32_t hi = 0;
-    const uint32_t word = dither_row<MODE, NAT, WIDE>(&h.delta[8 * u], ctx.nu, ctx.top_over_nu, dither_top(levels, NAT), levels, rng, j0, ctx.mag, r, &hi);
+    uint32_t hi[kPlanes > 0 ? kPlanes : 1];
+    const uint32_t word = dither_row<MODE, NAT, kPlanes>(&h.delta[8 * u], ctx.nu, ctx.top_over_nu, dither_top(levels, NAT), levels, rng, j0, ctx.mag, r, hi);
     uint32_t *nibs = reinterpret_cast<uint32_t *>(payload + (uint64_t)p * g.stride + kHeaderBytes);
     (nibs + uniform_off((tile_off(item) + u * (kThreads * 8)) >> 3))[threadIdx.x] = word;
     if (WIDE) {
       uint8_t *plane = payload + (uint64_t)p * g.stride + dither_plane0(g.part_elems);
-      (plane + uniform_off((tile_off(item) + u * (kThreads * 8)) >> 3))[threadIdx.x] = (uint8_t)hi;
+      const uint32_t planes = kAnyWide ? dither_planes(levels) : 1u;
+      const uint64_t plane_bytes = dither_plane_bytes(g.part_elems);
+#pragma unroll
+      for (int t = 0; t < kPlanes; ++t)
+        if (t < (int)planes) (plane + t * plane_bytes + uniform_off((tile_off(item) + u * (kThreads * 8)) >> 3))[threadIdx.x] = (uint8_t)hi[t];
     }
     if (EF) {
       const TileBuf ob = row_buf(res + base(item), valid_of(item), u * (kThreads * 8), kThreads * 8);
@@ -324,18 +396,14 @@ static hipError_t launch_dither_server(const Geo &g, const ClusterGeo &cg, const
   return launch_cluster(DitherServerOp<EF, LINF, NW, NAT, WIDE>{g, cg, mp, res, payload, prm.norm_override, prm.levels, \
                                                            prm.seed, prm.stream_id},                        \
                         cg, slots, status, tickets, stream, used)
-  switch (mp.n) {
-    case 4: BPC_DS(4);
-    case 8: BPC_DS(8);
-    case 16: BPC_DS(16);
-    default:
-      if constexpr (WIDE) {
-        *used = false;   // the wide form is built for 4, 8 and 16 workers; others take the passes
-        return hipSuccess;
-      } else {
-        BPC_DS(0);
-      }
+  if (!WIDE || dither_planes(prm.levels) == 1) {
+    switch (mp.n) {
+      case 4: BPC_DS(4);
+      case 8: BPC_DS(8);
+      case 16: BPC_DS(16);
+    }
   }
+  BPC_DS(0);
 #undef BPC_DS
 }
 
@@ -347,14 +415,10 @@ hipError_t dither_server_single_pass(const Geo &g, const bpc_params_t &prm, cons
   uint32_t *tickets = ws.tickets();
   const bool linf = prm.norm == BPC_NORM_LINF, nat = prm.kind == BPC_NATDITHER;
   const uint32_t planes = nat ? 0u : dither_planes(prm.levels);
-  if (planes > 1) {   // 6 and 7 bits: the multi-pass kernels
-    *used = false;
-    return hipSuccess;
-  }
 #define BPC_DSL(EF)                                                                                              \
   do {                                                                                                           \
-    if (planes == 1 && linf) return launch_dither_server<EF, true, false, true>(g, cg, prm, src, payload, slots, status, tickets, stream, used);  \
-    if (planes == 1) return launch_dither_server<EF, false, false, true>(g, cg, prm, src, payload, slots, status, tickets, stream, used);         \
+    if (planes > 0 && linf) return launch_dither_server<EF, true, false, true>(g, cg, prm, src, payload, slots, status, tickets, stream, used);  \
+    if (planes > 0) return launch_dither_server<EF, false, false, true>(g, cg, prm, src, payload, slots, status, tickets, stream, used);         \
     if (linf && nat) return launch_dither_server<EF, true, true, false>(g, cg, prm, src, payload, slots, status, tickets, stream, used);   \
     if (linf) return launch_dither_server<EF, true, false, false>(g, cg, prm, src, payload, slots, status, tickets, stream, used);         \
     if (nat) return launch_dither_server<EF, false, true, false>(g, cg, prm, src, payload, slots, status, tickets, stream, used);          \

@@ -473,3 +473,45 @@ def test_sparse_updates_with_and_without_a_table(gu, orc, kind, ratio, pe, D, op
     if opt != "adam":
         edges = offs if offs is not None else np.unique(np.append(np.arange(0, D, pe), D))
         assert gu.lans_step_close(gu.to_host(dx), x, x0, blocks=edges)
+
+
+# bit planes on the server: one to three planes, worker counts below, at and above the groups of four, ragged
+# ends inside a thread's eight elements; the same call recorded into a graph (preset form) gives the same bytes
+@pytest.mark.parametrize("n", [1, 3, 5, 16, 64])
+@pytest.mark.parametrize("kw", [dict(levels=8), dict(levels=15, norm=1), dict(levels=16, norm=1), dict(levels=31), dict(levels=32), dict(levels=63, norm=1)])
+@pytest.mark.parametrize("ef", [True, False])
+def test_bit_planes_in_the_single_pass_server(gu, orc, n, kw, ef):
+    import fmt
+    import torch
+    bpc, pe = gu.bpc, 16384
+    po, pb = gu.both_params(orc, "dither", pe, seed=21, stream_id=4, **kw)
+    rs = np.random.default_rng(n)
+    for D in (1, 8191, 8193, 2 * 16384 + 8192 + 4099):
+        msgs = [orc.compress(po, (rs.standard_normal(D) * 1e-3 * (i + 1)).astype(np.float32), None) for i in range(n)]
+        res = (rs.standard_normal(D) * 3e-4).astype(np.float32) if ef else None
+        rd, pays = gu.to_dev(res) if ef else None, [gu.to_dev(m) for m in msgs]
+        res0 = rd.clone() if ef else None
+        pay, ws = gu.new_payload(pb, D), gu.new_ws(pb, D, n)
+        ws.fill_(0xFF)
+        bpc.bpc_server_aggregate([pb] * n, pays, pb, rd, D, pay, ws)
+        bpc.workspace_check(pb, D, ws)
+        ref = orc.server_aggregate([po] * n, msgs, po, res, D)
+        got, stride = gu.to_host(pay), orc.partition_stride(po)
+        for p, d in enumerate(fmt.part_sizes(D, pe)):
+            spans = [(0, 16 + 4 * -(-d // 8))] + [(16 + 4 * (pe // 8) + t * 4 * (pe // 32),) * 2 for t in range(bpc_planes("dither", kw))]
+            for a, b in [spans[0]] + [(a, a + 4 * -(-d // 32)) for a, _ in spans[1:]]:
+                assert np.array_equal(got[p * stride + a:p * stride + b], ref[p * stride + a:p * stride + b]), (D, p, a)
+        if ef:
+            assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32)), D
+    res1, pay1 = rd.clone() if ef else None, pay.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        bpc.bpc_server_aggregate([pb] * n, pays, pb, rd, D, pay, ws)
+    for _ in range(3):
+        if ef:
+            rd.copy_(res0)
+        pay.copy_(gu.new_payload(pb, D))
+        graph.replay()
+        torch.cuda.synchronize()
+        bpc.workspace_check(pb, D, ws)
+        assert torch.equal(pay, pay1) and (not ef or torch.equal(rd, res1))
