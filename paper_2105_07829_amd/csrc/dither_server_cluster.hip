@@ -40,6 +40,21 @@ __device__ inline uint32_t byte_and(uint32_t x, uint32_t mask) {
   return r;
 }
 
+// The float in LDS at the uniform address `base` + byte B of `offsets`, plus `fixed` (a constant: it goes into
+// the read): one instruction for the address.
+template <int B>
+__device__ inline float lds_at(uint32_t base, uint32_t offsets, uint32_t fixed = 0) {
+  uint32_t a;
+  if (B == 0) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_0" : "=v"(a) : "v"(base), "v"(offsets));
+  else if (B == 1) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(a) : "v"(base), "v"(offsets));
+  else if (B == 2) asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_2" : "=v"(a) : "v"(base), "v"(offsets));
+  else asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_3" : "=v"(a) : "v"(base), "v"(offsets));
+  return *(const __attribute__((address_space(3))) float *)(a + fixed);
+}
+__device__ inline uint32_t lds_address(const float *p) {
+  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
+}
+
 // NW > 0: number of workers known at compile time (unrolled); NW == 0: rolled loop.
 // WIDE: linear levels 8..15 (the 5-bit form): one bit plane beside the nibbles, on the way in
 // and on the way out; a worker's table then has 32 entries, index = plane bit << 4 | nibble,
@@ -47,9 +62,9 @@ __device__ inline uint32_t byte_and(uint32_t x, uint32_t mask) {
 // WIDE with NW == 0: any number of linear levels beyond 7 (up to three planes) and of workers.  A worker's
 // table holds the 64 magnitudes, index = plane bits << 3 | low level bits; the sign is put on the value.
 // Bound by its vector instructions; in place of the three passes over the messages' planes (whose sums are
-// formed twice, a plane's bits picked one by one): 31 levels, 5 workers, 1 M / 3 M elements 27 -> 12 / 41 -> 18 us;
-// 63 levels, 4 workers, 100 M 888 -> 290; 15 levels, 5 workers, 100 M f16 800 -> 311.  The forms with NW > 0 stay for
-// 15 levels (8 workers, 100 M: 279 us): their tables hold signed values.
+// formed twice, a plane's bits picked one by one): 31 levels, 5 workers, 1 M / 3 M elements 27 -> 11 / 41 -> 16 us;
+// 63 levels, 4 workers, 100 M 888 -> 260; 31 levels, 16 workers, 100 M 1678 -> 462; 15 levels, 5 workers, 100 M f16
+// 801 -> 276.  The forms with NW > 0 stay for 15 levels (8 workers, 100 M: 273 us): their tables hold signed values.
 template <bool EF, bool LINF, int NW, bool NAT, bool WIDE = false>
 struct DitherServerOp {
   static constexpr bool kAnyWide = WIDE && NW == 0;
@@ -67,10 +82,11 @@ struct DitherServerOp {
   // for each value of a plane byte, its even bits at bit 6 of the four bytes of one word and its
   // odd bits likewise in a second word, i.e. where the "plane bit << 4" of a table index falls
   // once a word's nibbles sit at bits 2..5 of its bytes
-  // (any width: at most 4096 floats of tables and 64 output magnitudes; no spread table)
+  // (any width: at most 4096 floats of tables and 64 output magnitudes; spread to bit 5)
   static constexpr int kMagAt = kMaxWorkers * (kAnyWide ? 64 : 16);
   static constexpr int kSpreadAt = kMagAt + (kAnyWide ? 64 : 16);
-  static constexpr int kTableFloats = kSpreadAt + (WIDE && !kAnyWide ? 512 : 0);
+  static constexpr int kSpreadBit = kAnyWide ? 5 : 6;
+  static constexpr int kTableFloats = kSpreadAt + (WIDE ? 512 : 0);
   static_assert(!WIDE || NW * 32 <= kMaxWorkers * 16, "tables of the wide form must fit");
   static constexpr bool kPersistent = false;
   static constexpr int kWavesPerSimd = (NW > 8 && !WIDE) ? 6 : 4;
@@ -141,55 +157,68 @@ struct DitherServerOp {
     for (int u = 0; u < kDSRows; ++u) out[u] = plane[u * kThreads + threadIdx.x];
   }
   // Any width: the bytes of all planes that cover this thread's 8 elements of each row.
+  template <int PLANES>
   __device__ void load_all_planes(uint32_t item, int i, uint32_t out[3][kDSRows]) const {
-    const uint32_t planes = dither_planes(levels);
     const uint64_t plane_bytes = dither_plane_bytes(g.part_elems);
     const uint8_t *plane = msgs.ptr[i] + uniform_off((uint64_t)part_of(item) * g.stride + dither_plane0(g.part_elems) + (tile_off(item) >> 3));
 #pragma unroll
-    for (int t = 0; t < 3; ++t)
+    for (int t = 0; t < PLANES; ++t)
 #pragma unroll
-      for (int u = 0; u < kDSRows; ++u) out[t][u] = t < (int)planes ? (plane + t * plane_bytes)[u * kThreads + threadIdx.x] : 0u;
+      for (int u = 0; u < kDSRows; ++u) out[t][u] = (plane + t * plane_bytes)[u * kThreads + threadIdx.x];
   }
   // Any width: the table offset level*4 of an element is one byte of two words (even and odd elements):
-  // the low level bits at bits 2..4 of the bytes, plane t's bit at bit 5 + t.  Bits 0, 2, 4, 6 of a plane byte
-  // come to bits 0, 8, 16, 24 by one 24-bit multiplication (copies 6 places apart: the products' other bits
-  // meet in pairs whose carries stay between them).
-  __device__ static uint32_t spread_even(uint32_t b) { return __umul24(b & 0x55u, 0x41041u) & 0x01010101u; }
+  // the low level bits at bits 2..4 of the bytes, plane t's bit at bit 5 + t (the spread table's, shifted).
+  template <int PLANES>
   __device__ static void add_worker_any(const uint32_t word[kDSRows], const uint32_t pb[3][kDSRows], const float *lut_i,
-                                        float acc[kPerThread]) {
-    const char *lut_b = reinterpret_cast<const char *>(lut_i);
+                                        const float *table, float acc[kPerThread]) {
+    const uint32_t lut = lds_address(lut_i);
+    const u32x2 *spread = reinterpret_cast<const u32x2 *>(table + kSpreadAt);
 #pragma unroll
     for (int u = 0; u < kDSRows; ++u) {
       uint32_t even = (word[u] << 2) & 0x1c1c1c1cu, odd = (word[u] >> 2) & 0x1c1c1c1cu;
 #pragma unroll
-      for (int t = 0; t < 3; ++t) {
-        even |= spread_even(pb[t][u]) << (5 + t);
-        odd |= spread_even(pb[t][u] >> 1) << (5 + t);
+      for (int t = 0; t < PLANES; ++t) {
+        const u32x2 bits = spread[pb[t][u]];
+        even |= bits.x << t;
+        odd |= bits.y << t;
       }
-      float v[8];
-      v[0] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(even, 0xfcu));
-      v[1] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(odd, 0xfcu));
-      v[2] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(even, 0xfcu));
-      v[3] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(odd, 0xfcu));
-      v[4] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(even, 0xfcu));
-      v[5] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(odd, 0xfcu));
-      v[6] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(even, 0xfcu));
-      v[7] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(odd, 0xfcu));
+      const float v[8] = {lds_at<0>(lut, even), lds_at<0>(lut, odd), lds_at<1>(lut, even), lds_at<1>(lut, odd),
+                          lds_at<2>(lut, even), lds_at<2>(lut, odd), lds_at<3>(lut, even), lds_at<3>(lut, odd)};
 #pragma unroll
       for (int c = 0; c < 8; ++c)
         acc[8 * u + c] = acc[8 * u + c] + __uint_as_float(__float_as_uint(v[c]) | ((word[u] << (28 - 4 * c)) & 0x80000000u));
     }
   }
 
+  // Any width: four workers at a time (a last group asks for its last worker again in place of those it lacks).
+  template <int PLANES>
+  __device__ void sum_any(uint32_t item, uint32_t p, float *table, float acc[kPerThread]) const {
+    constexpr int kGroup = 4;
+#pragma unroll 1
+    for (int i0 = 0; i0 < msgs.n; i0 += kGroup) {
+      uint32_t word[kGroup][kDSRows], pb[kGroup][3][kDSRows];
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        const int i = i0 + k < msgs.n ? i0 + k : msgs.n - 1;
+        load_words(item, i, word[k]);
+        load_all_planes<PLANES>(item, i, pb[k]);
+      }
+      if (i0 == 0) fill_luts(p, table);
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k)
+        if (i0 + k < msgs.n) add_worker_any<PLANES>(word[k], pb[k], table + (i0 + k) * 64, table, acc);
+    }
+  }
+
   // WIDE, once per workgroup: the spread table.
-  template <bool W = WIDE && !kAnyWide, std::enable_if_t<W, int> = 0>
+  template <bool W = WIDE, std::enable_if_t<W, int> = 0>
   __device__ void init(float *table) const {
     if (threadIdx.x < 256) {
       uint32_t even = 0, odd = 0;
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        even |= ((threadIdx.x >> (2 * k)) & 1u) << (8 * k + 6);
-        odd |= ((threadIdx.x >> (2 * k + 1)) & 1u) << (8 * k + 6);
+        even |= ((threadIdx.x >> (2 * k)) & 1u) << (8 * k + kSpreadBit);
+        odd |= ((threadIdx.x >> (2 * k + 1)) & 1u) << (8 * k + kSpreadBit);
       }
       u32x2 e;
       e.x = even; e.y = odd;
@@ -198,23 +227,17 @@ struct DitherServerOp {
   }
   // WIDE: table offset = (plane bit << 4 | nibble) * 4: the nibbles at bits 2..5 of the bytes of
   // two words as in add_worker, the plane bits or-ed in at bit 6 through the spread table.
-  __device__ static void add_worker_wide(const uint32_t word[kDSRows], const uint32_t pb[kDSRows], const float *lut_i,
+  // (the bytes' other bits are zero, so the byte picked is the offset: add_worker_at)
+  __device__ static void add_worker_wide(const uint32_t word[kDSRows], const uint32_t pb[kDSRows], uint32_t base, int k,
                                          const float *table, float acc[kPerThread]) {
-    const char *lut_b = reinterpret_cast<const char *>(lut_i);
+    const uint32_t f = k * 128;
     const u32x2 *spread = reinterpret_cast<const u32x2 *>(table + kSpreadAt);
 #pragma unroll
     for (int u = 0; u < kDSRows; ++u) {
       const u32x2 bits = spread[pb[u]];
       const uint32_t even = ((word[u] << 2) & 0x3c3c3c3cu) | bits.x, odd = ((word[u] >> 2) & 0x3c3c3c3cu) | bits.y;
-      float v[8];
-      v[0] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(even, 0x7cu));
-      v[1] = *reinterpret_cast<const float *>(lut_b + byte_and<0>(odd, 0x7cu));
-      v[2] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(even, 0x7cu));
-      v[3] = *reinterpret_cast<const float *>(lut_b + byte_and<1>(odd, 0x7cu));
-      v[4] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(even, 0x7cu));
-      v[5] = *reinterpret_cast<const float *>(lut_b + byte_and<2>(odd, 0x7cu));
-      v[6] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(even, 0x7cu));
-      v[7] = *reinterpret_cast<const float *>(lut_b + byte_and<3>(odd, 0x7cu));
+      const float v[8] = {lds_at<0>(base, even, f), lds_at<0>(base, odd, f), lds_at<1>(base, even, f), lds_at<1>(base, odd, f),
+                          lds_at<2>(base, even, f), lds_at<2>(base, odd, f), lds_at<3>(base, even, f), lds_at<3>(base, odd, f)};
 #pragma unroll
       for (int c = 0; c < 8; ++c) acc[8 * u + c] = acc[8 * u + c] + v[c];
     }
@@ -241,6 +264,22 @@ struct DitherServerOp {
     }
   }
 
+  // The same from a table whose place only the loop knows, k tables after `base`: the nibbles are masked in the
+  // words (two instructions for eight of them), so that the byte picked is the offset and the instruction
+  // that picks it adds the base (a byte and-ed with its mask needed a second instruction an element for that:
+  // 16 workers, 17 M / 100 M / 336 M elements 65.7 -> 62.6 / 363 -> 352 / 1056 -> 1050 us; 64 workers, 100 M 961 -> 944).
+  __device__ static void add_worker_at(const uint32_t word[kDSRows], uint32_t base, int k, float acc[kPerThread]) {
+    const uint32_t f = k * 64;
+#pragma unroll
+    for (int u = 0; u < kDSRows; ++u) {
+      const uint32_t even = (word[u] << 2) & 0x3c3c3c3cu, odd = (word[u] >> 2) & 0x3c3c3c3cu;
+      const float v[8] = {lds_at<0>(base, even, f), lds_at<0>(base, odd, f), lds_at<1>(base, even, f), lds_at<1>(base, odd, f),
+                          lds_at<2>(base, even, f), lds_at<2>(base, odd, f), lds_at<3>(base, even, f), lds_at<3>(base, odd, f)};
+#pragma unroll
+      for (int c = 0; c < 8; ++c) acc[8 * u + c] = acc[8 * u + c] + v[c];
+    }
+  }
+
   __device__ double phase1(uint32_t item, Raw &raw, Held &h, float *table) const {
     const uint32_t p = part_of(item);
 #pragma unroll
@@ -249,22 +288,10 @@ struct DitherServerOp {
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) acc[k] = 0.0f;
     if (kAnyWide) {
-      // four workers at a time (a last group asks for its last worker again in place of those it lacks)
-      constexpr int kGroup = 4;
-#pragma unroll 1
-      for (int i0 = 0; i0 < msgs.n; i0 += kGroup) {
-        uint32_t word[kGroup][kDSRows], pb[kGroup][3][kDSRows];
-#pragma unroll
-        for (int k = 0; k < kGroup; ++k) {
-          const int i = i0 + k < msgs.n ? i0 + k : msgs.n - 1;
-          load_words(item, i, word[k]);
-          load_all_planes(item, i, pb[k]);
-        }
-        if (i0 == 0) fill_luts(p, table);
-#pragma unroll
-        for (int k = 0; k < kGroup; ++k)
-          if (i0 + k < msgs.n) add_worker_any(word[k], pb[k], table + (i0 + k) * 64, acc);
-      }
+      const uint32_t planes = dither_planes(levels);
+      if (planes == 1) sum_any<1>(item, p, table, acc);
+      else if (planes == 2) sum_any<2>(item, p, table, acc);
+      else sum_any<3>(item, p, table, acc);
     } else if (WIDE) {
       // groups of four workers, each requested in one go (more in flight would not fit the
       // registers next to the tile of the older partition)
@@ -279,21 +306,21 @@ struct DitherServerOp {
         }
         if (i0 == 0) fill_luts(p, table);
 #pragma unroll
-        for (int k = 0; k < kGroup; ++k) add_worker_wide(word[k], pb[k], table + (i0 + k) * 32, table, acc);
+        for (int k = 0; k < kGroup; ++k) add_worker_wide(word[k], pb[k], lds_address(table + i0 * 32), k, table, acc);
       }
     } else if (NW > 8) {
       // many workers: groups of four, so that a lane stays within 80 registers and three
       // workgroups share a CU (n = 16: 1.31 -> 1.18 ms at 336 M elements; with 4 or 8 workers
       // everything in one go, below, was as fast or faster)
       constexpr int kGroup = 4;
-#pragma unroll 1   // (unrolled, the loads of all groups are hoisted to the front)
+#pragma unroll 1   // (unrolled, the loads of all groups are hoisted to the front, and spill behind a barrier for the compiler)
       for (int i0 = 0; i0 < NW; i0 += kGroup) {
         uint32_t word[kGroup][kDSRows];
 #pragma unroll
         for (int k = 0; k < kGroup; ++k) load_words(item, i0 + k, word[k]);
         if (i0 == 0) fill_luts(p, table);
 #pragma unroll
-        for (int k = 0; k < kGroup; ++k) add_worker(word[k], table + (i0 + k) * 16, acc);
+        for (int k = 0; k < kGroup; ++k) add_worker_at(word[k], lds_address(table + i0 * 16), k, acc);
       }
     } else if (NW > 0) {
       // every word of every worker is requested before the tables are built
@@ -308,7 +335,7 @@ struct DitherServerOp {
       for (int i = 0; i < msgs.n; ++i) {
         uint32_t word[kDSRows];
         load_words(item, i, word);
-        add_worker(word, table + i * 16, acc);
+        add_worker_at(word, lds_address(table + i * 16), 0, acc);
       }
     }
     const uint32_t valid = valid_of(item);
