@@ -142,17 +142,17 @@ struct DitherServerOp {
     __syncthreads();
   }
 
-  // The word of worker i's nibbles that covers this thread's 8 elements of each row.
-  __device__ void load_words(uint32_t item, int i, uint32_t out[kDSRows]) const {
+  // The word of a worker's nibbles that covers this thread's 8 elements of each row.
+  __device__ void load_words(uint32_t item, const uint8_t *msg, uint32_t out[kDSRows]) const {
     const uint32_t *nibs = reinterpret_cast<const uint32_t *>(
-        msgs.ptr[i] + uniform_off((uint64_t)part_of(item) * g.stride + kHeaderBytes + (tile_off(item) >> 1)));
+        msg + uniform_off((uint64_t)part_of(item) * g.stride + kHeaderBytes + (tile_off(item) >> 1)));
 #pragma unroll
     for (int u = 0; u < kDSRows; ++u) out[u] = nibs[u * kThreads + threadIdx.x];
   }
 
-  // The byte of worker i's bit plane that covers this thread's 8 elements of each row.
-  __device__ void load_planes(uint32_t item, int i, uint32_t out[kDSRows]) const {
-    const uint8_t *plane = msgs.ptr[i] + uniform_off((uint64_t)part_of(item) * g.stride + dither_plane0(g.part_elems) + (tile_off(item) >> 3));
+  // The byte of a worker's bit plane that covers this thread's 8 elements of each row.
+  __device__ void load_planes(uint32_t item, const uint8_t *msg, uint32_t out[kDSRows]) const {
+    const uint8_t *plane = msg + uniform_off((uint64_t)part_of(item) * g.stride + dither_plane0(g.part_elems) + (tile_off(item) >> 3));
 #pragma unroll
     for (int u = 0; u < kDSRows; ++u) out[u] = plane[u * kThreads + threadIdx.x];
   }
@@ -200,7 +200,7 @@ struct DitherServerOp {
 #pragma unroll
       for (int k = 0; k < kGroup; ++k) {
         const int i = i0 + k < msgs.n ? i0 + k : msgs.n - 1;
-        load_words(item, i, word[k]);
+        load_words(item, msgs.ptr[i], word[k]);
         load_all_planes<PLANES>(item, i, pb[k]);
       }
       if (i0 == 0) fill_luts(p, table);
@@ -282,8 +282,12 @@ struct DitherServerOp {
 
   __device__ double phase1(uint32_t item, Raw &raw, Held &h, float *table) const {
     const uint32_t p = part_of(item);
+    auto issue = [&] {
 #pragma unroll
-    for (int u = 0; u < kDSRows; ++u) issue_row(item, u, raw);
+      for (int u = 0; u < kDSRows; ++u) issue_row(item, u, raw);
+    };
+    constexpr bool kLate = WIDE && NW > 4;
+    if (!kLate) issue();
     float acc[kPerThread];
 #pragma unroll
     for (int k = 0; k < kPerThread; ++k) acc[k] = 0.0f;
@@ -293,21 +297,33 @@ struct DitherServerOp {
       else if (planes == 2) sum_any<2>(item, p, table, acc);
       else sum_any<3>(item, p, table, acc);
     } else if (WIDE) {
-      // groups of four workers, each requested in one go (more in flight would not fit the
-      // registers next to the tile of the older partition)
+      // four workers in flight (more would not fit the registers next to the tile of the older partition): a
+      // worker's words are requested as soon as those of the worker four before it are used up, and e~ behind the
+      // last of them (8 / 16 workers, 15 levels, 100 M elements: 273 -> 262 / 383 -> 362 us; the nibbles alone of 16
+      // workers spill at three workgroups a CU: 1050 -> 1074 at 336 M, and the form for any width: 462 -> 543)
       constexpr int kGroup = NW > 4 ? 4 : (NW > 0 ? NW : 1);
+      uint32_t word[kGroup][kDSRows], pb[kGroup][kDSRows];
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) {
+        load_words(item, msgs.ptr[k], word[k]);
+        load_planes(item, msgs.ptr[k], pb[k]);
+      }
+      fill_luts(p, table);
 #pragma unroll 1   // (unrolled, the loads of all groups are hoisted to the front)
-      for (int i0 = 0; i0 < NW; i0 += kGroup) {
-        uint32_t word[kGroup][kDSRows], pb[kGroup][kDSRows];
+      for (int i0 = 0; i0 < NW - kGroup; i0 += kGroup) {
+        const uint8_t *next[kGroup];
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) next[k] = msgs.ptr[i0 + kGroup + k];
 #pragma unroll
         for (int k = 0; k < kGroup; ++k) {
-          load_words(item, i0 + k, word[k]);
-          load_planes(item, i0 + k, pb[k]);
+          add_worker_wide(word[k], pb[k], lds_address(table + i0 * 32), k, table, acc);
+          load_words(item, next[k], word[k]);
+          load_planes(item, next[k], pb[k]);
         }
-        if (i0 == 0) fill_luts(p, table);
-#pragma unroll
-        for (int k = 0; k < kGroup; ++k) add_worker_wide(word[k], pb[k], lds_address(table + i0 * 32), k, table, acc);
       }
+      if (kLate) issue();
+#pragma unroll
+      for (int k = 0; k < kGroup; ++k) add_worker_wide(word[k], pb[k], lds_address(table + (NW - kGroup) * 32), k, table, acc);
     } else if (NW > 8) {
       // many workers: groups of four, so that a lane stays within 80 registers and three
       // workgroups share a CU (n = 16: 1.31 -> 1.18 ms at 336 M elements; with 4 or 8 workers
@@ -317,7 +333,7 @@ struct DitherServerOp {
       for (int i0 = 0; i0 < NW; i0 += kGroup) {
         uint32_t word[kGroup][kDSRows];
 #pragma unroll
-        for (int k = 0; k < kGroup; ++k) load_words(item, i0 + k, word[k]);
+        for (int k = 0; k < kGroup; ++k) load_words(item, msgs.ptr[i0 + k], word[k]);
         if (i0 == 0) fill_luts(p, table);
 #pragma unroll
         for (int k = 0; k < kGroup; ++k) add_worker_at(word[k], lds_address(table + i0 * 16), k, acc);
@@ -326,7 +342,7 @@ struct DitherServerOp {
       // every word of every worker is requested before the tables are built
       uint32_t word[NW > 0 ? NW : 1][kDSRows];
 #pragma unroll
-      for (int i = 0; i < NW; ++i) load_words(item, i, word[i]);
+      for (int i = 0; i < NW; ++i) load_words(item, msgs.ptr[i], word[i]);
       fill_luts(p, table);
 #pragma unroll
       for (int i = 0; i < NW; ++i) add_worker(word[i], table + i * 16, acc);
@@ -334,7 +350,7 @@ struct DitherServerOp {
       fill_luts(p, table);
       for (int i = 0; i < msgs.n; ++i) {
         uint32_t word[kDSRows];
-        load_words(item, i, word);
+        load_words(item, msgs.ptr[i], word);
         add_worker_at(word, lds_address(table + i * 16), 0, acc);
       }
     }
