@@ -84,8 +84,9 @@ inline ClusterGeo make_cluster_geo(const Geo &g, uint32_t tile) {
 // `tag` (if given) receives this launch's tag, 0 while the stream is being captured.
 hipError_t cluster_launch_begin(hipStream_t stream, uint64_t *tag = nullptr);
 hipError_t cluster_launch_end(hipStream_t stream);
-// A tag for a launch that needs no resident grid, so is not chained; true if `stream` is being captured
-// (every replay then carries this tag).
+// A tag for a launch none of whose workgroups waits for one that may not be running (it need not be
+// resident as a whole, and is not chained); true if `stream` is being captured (every replay then carries
+// this tag).
 bool launch_tag(hipStream_t stream, uint64_t *tag);
 // Creates the current device's event now rather than at the first launch that needs it.
 hipError_t cluster_prepare_device();

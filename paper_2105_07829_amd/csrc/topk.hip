@@ -15,8 +15,9 @@
 //   select     : several workgroups per partition find the k-th largest key among the listed ones,
 //                each for itself, and write a share of the record; kept slots of the buffer zeroed
 // The guess is made by the first workgroups of the load kernel itself, the others have requested their
-// elements before they wait for it; on the server side a kernel in front sums the sampled chunks up and
-// finds where each message's entries of a group of 8192 elements begin.
+// elements before they wait for it (none of them for a workgroup that may not be running: TopkShared); on
+// the server side a kernel in front sums the sampled chunks up and finds where each message's entries of a
+// group of 8192 elements begin.
 // The sample only decides how much work the selection is, never its result: a partition whose
 // short list came out shorter than k or longer than its room (the sample misled, or a great many
 // equal magnitudes, or fewer than k non-zeros) is taken by the long form below instead, run by the
@@ -49,6 +50,12 @@
 #include "cluster.hpp"
 #include "sources.hpp"
 #include "tile_rows.hpp"
+
+// Whether the workgroups that are there for it make the guesses; a test compiles the pass without, as if they
+// were kept from running (test_gpu_late_guess.py).
+#ifndef BPC_TOPK_FIRST_GUESS
+#define BPC_TOPK_FIRST_GUESS 1
+#endif
 
 namespace bpc {
 
@@ -87,17 +94,33 @@ enum { kStPrefix = 0, kStKRem = 1 };
 enum { kStLong = 1 };
 
 // What the load pass of the short-list form hands from workgroup to workgroup, in the workspace's
-// region for it (16 KB a partition): the guesses, two words each (the guess, and its exclusive or with
-// the launch's tag, as the slots of cluster.hpp), and the lengths of the lists, a page apart since an
-// atomic on global memory holds up its memory channel for some 11 ns.
+// region for it (16 KB a partition): the guesses, four words each (the guess, its exclusive or with
+// the launch's tag, as the slots of cluster.hpp, and the tag once a workgroup has taken the guess on), and
+// the lengths of the lists, a page apart since an atomic on global memory holds up its memory channel for
+// some 11 ns.
+//
+// The first workgroups of the launch make the guesses, and the others wait for them.  Its grid is not resident
+// as a whole, and workgroups are bound to an XCD by their index: beside another kernel that waits (a second
+// top-k call, a single-pass kernel, on another stream), waiting workgroups of either could fill the XCD that a
+// guess's workgroup is bound to, and hold each other up.  So nobody waits long for a workgroup that may not
+// have started: after kPatience looks (some 0.2 ms) a waiting workgroup makes the guess itself.  The one that
+// takes it on first publishes it; the others drop theirs and wait for that one, which is running and waits
+// for nobody.  Whoever publishes it, it is the same guess: nothing is stored to the vector that is sampled
+// before a guess is there.
+constexpr int kPatience = 128;
 struct TopkShared {
   uint64_t *pairs;
   uint32_t *lengths;
   uint64_t tag;
   uint32_t *status;
   uint32_t *state;
-  static size_t pairs_bytes(uint32_t P) { return (16ull * P + 4095) / 4096 * 4096; }
+  static size_t pairs_bytes(uint32_t P) { return (32ull * P + 4095) / 4096 * 4096; }
   __device__ uint32_t *length(uint32_t p) const { return lengths + 1024ull * p; }
+  __device__ uint64_t *pair(uint32_t p) const { return pairs + 4ull * p; }
+  // One thread takes the guess on; the tag if another one has.
+  __device__ uint64_t take(uint32_t p) const {
+    return __hip_atomic_exchange(pair(p) + 2, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
   // One thread publishes partition p's guess; the list length is zero before anyone can see it.
   __device__ void publish(uint32_t p, uint32_t guess) const {
     __hip_atomic_store(length(p), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -105,23 +128,19 @@ struct TopkShared {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0F70);   // (vector memory done)
     asm volatile("" ::: "memory");
-    __hip_atomic_store(pairs + 2ull * p, (uint64_t)guess, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(pairs + 2ull * p + 1, (uint64_t)guess ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pair(p), (uint64_t)guess, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pair(p) + 1, (uint64_t)guess ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  __device__ u32x4 look(uint32_t p) const { return TileBuf(pairs + 2ull * p, 16).load16<kMemorySide>(0, 0); }
-  // The guess, `w` being the first look at it.  The wait is for a workgroup with a lower index, which
-  // waits for nobody; it is bounded like those of cluster.hpp.
-  __device__ uint32_t wait(uint32_t p, u32x4 w) const {
-    int spins = 0;
+  __device__ u32x4 look(uint32_t p) const { return TileBuf(pair(p), 16).load16<kMemorySide>(0, 0); }
+  // One wave waits for the guess, `w` being its first look at it, for `looks` more; false if it is not there.
+  __device__ bool wait(uint32_t p, u32x4 w, int looks, uint32_t *guess) const {
     while ((w.x ^ w.z) != (uint32_t)tag || (w.y ^ w.w) != (uint32_t)(tag >> 32)) {
-      if (++spins > kSpinLimit) {
-        if ((threadIdx.x & 63) == 0) status_give_up(status, tag);
-        return kNoGuess;
-      }
+      if (--looks < 0) return false;
       __builtin_amdgcn_s_sleep(4);
       w = look(p);
     }
-    return __builtin_amdgcn_readfirstlane(w.x);
+    *guess = w.x;
+    return true;
   }
 };
 
@@ -266,7 +285,9 @@ struct SamplePlan {
 // Workgroup of the load pass: 16 elements a thread (of 256 threads, 32 elements each: 91 registers
 // a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
 // 135 us, of 8 workers on 25.6 M elements 911 -> 892 us, of 16 workers on 110 M f16 elements 4275 ->
-// 4202 us.  (1024 threads: 131, 908 and 4402 us.)
+// 4202 us.  (1024 threads: 131, 908 and 4402 us.  With the guess a second time, for workgroups that waited too
+// long, it is 66 to 78 registers and six waves, and these steps take what they took: 104.6 -> 104.9, 779 -> 773
+// and 3932 -> 3913 us; in one copy for both uses, 56 registers: 107.2, 777.)
 constexpr int kLoadThreads = 512;
 constexpr uint32_t kGroupElems = kTpgLoad * kTile;   // elements a workgroup of the load pass takes: 8192
 static_assert(kGroupElems == 8192, "the workspace is laid out for groups of 8192 elements");
@@ -419,12 +440,16 @@ struct TopkMsgsGroupSource : TopkMsgs {
   }
 };
 
-// The guess for partition p, published: `load8(j0, v)` gives the eight elements from j0, the first of
+// The guess for partition p, published unless another workgroup has taken it on (`taken`, what TopkShared::take
+// gave thread 0): `load8(j0, v)` gives the eight elements from j0, the first of
 // a sampled chunk.  All threads of a workgroup of THREADS; h: LDS, kBins1 words.  Random 64-byte reads
 // cost about as much as 16 times as many sequential ones, hence chunks rather than single elements.
 template <int THREADS, class LOAD8>
-__device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh, uint32_t *h, uint32_t *scan, uint32_t *sel,
-                                  LOAD8 load8) {
+__device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh, uint64_t taken, uint32_t *h, uint32_t *scan,
+                                  uint32_t *sel, LOAD8 load8) {
+  auto publish = [&](uint32_t guess) {
+    if (threadIdx.x == 0 && taken != sh.tag) sh.publish(p, guess);
+  };
   constexpr uint32_t kChunksPer = (kSampleChunks + THREADS - 1) / THREADS;
   constexpr int kPer = 8 * kChunksPer;
   const uint32_t d = g.part_size(p);
@@ -436,7 +461,7 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   const double expect = (double)k_of_device(g, p) * (double)m / (double)d;
   const uint32_t rank = (uint32_t)(expect + 4.0 * sqrt(2.0 * expect) + 3.0);
   if (rank >= m) {   // (uniform) the whole partition is listed
-    if (threadIdx.x == 0) sh.publish(p, 0);
+    publish(0);
     return;
   }
   uint32_t key[kPer];
@@ -469,11 +494,11 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
   const uint64_t in_bin = (uint64_t)h[prefix2 & (kBins23 - 1)] * d;   // times m: elements of the partition
   if (in_bin <= (uint64_t)kFewInBin * m) {   // (uniform)
-    if (threadIdx.x == 0) sh.publish(p, prefix2 << kShift2);
+    publish(prefix2 << kShift2);
     return;
   }
   level3_in_registers<kPer, THREADS>(key, cnt, kPer, prefix2, k_rem2, h, scan, sel);
-  if (threadIdx.x == 0) sh.publish(p, sel[0]);
+  publish(sel[0]);
 }
 
 // Server side, in front of the load pass.  The first kSumPieces workgroups of a partition find the sums of the
@@ -536,8 +561,8 @@ struct has_begin_group<SRC, std::void_t<decltype(&SRC::begin_group)>> : std::tru
 // add on the list length hands out.  The order inside the list does not matter: the select pass puts
 // what it keeps in index order through a bitmap.  Long form: the level-1 histogram of all elements.
 // In the short-list form workgroup p < P makes partition p's guess and the groups follow behind; a group has
-// its elements in registers before it waits for the guess (a kernel of its own for the guesses cost
-// 8 us of every call).
+// its elements in registers before one of its waves waits for the guess (a kernel of its own for the guesses
+// cost 8 us of every call).
 // The group is taken as 4 rows of 2048 elements, 4 consecutive elements a thread and row: every
 // 16-byte access of a wave to the gradient, the residual and the buffer covers whole cache lines
 // and is marked non-temporal; everything goes through descriptors of the elements that exist
@@ -557,29 +582,30 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
   uint32_t *h = kServer && LISTED ? reinterpret_cast<uint32_t *>(lds) : own_h;
   __shared__ uint32_t scan[kWaves];
   __shared__ uint32_t sel[2];
-  uint32_t blk = blockIdx.x;
-  if constexpr (LISTED) {
-    if (blk == 0) status_open(sh.status, sh.tag);
-    if (blk < g.P) {
-      const uint32_t d = g.part_size(blk);
-      if (lists.dense)   // (the bins of the group-list form, used by later kernels)
-        for (uint32_t b = threadIdx.x; b < kBinWords; b += kLoadThreads) hist[(uint64_t)blk * kTopkHistWords + b] = 0;
-      topk_guess<kLoadThreads>(g, blk, sh, h, scan, sel, [&](uint32_t c, uint32_t j0, float v[8]) {
-        if constexpr (kServer) src.sampled8(g, blk, c, j0, d, v);
-        else src.at8(g, blk, j0, d, nullptr, v);
-      });
-      return;
-    }
-    blk -= g.P;
+  auto make_guess = [&](uint32_t p, uint32_t d) {
+    topk_guess<kLoadThreads>(g, p, sh, threadIdx.x == 0 ? sh.take(p) : 0, h, scan, sel, [&](uint32_t c, uint32_t j0, float x[8]) {
+      if constexpr (kServer) src.sampled8(g, p, c, j0, d, x);
+      else src.at8(g, p, j0, d, nullptr, x);
+    });
+  };
+  const bool first = LISTED && blockIdx.x < g.P;   // is here for the guess of a partition
+  GroupOf w;
+  if (first) {
+    w = GroupOf{blockIdx.x, 0, 0, g.part_size(blockIdx.x)};
+    if (blockIdx.x == 0) status_open(sh.status, sh.tag);
+    if (lists.dense)   // (the bins of the group-list form, used by later kernels)
+      for (uint32_t b = threadIdx.x; b < kBinWords; b += kLoadThreads) hist[(uint64_t)w.p * kTopkHistWords + b] = 0;
+    if (BPC_TOPK_FIRST_GUESS) make_guess(blockIdx.x, w.d);
+    return;
+  } else {
+    w = group_of<kTpgLoad>(g, blockIdx.x - (LISTED ? g.P : 0u));
+    if (w.tile_lo >= w.tile_hi) return;  // (uniform) past the end of a shorter last partition
   }
-  const GroupOf w = group_of<kTpgLoad>(g, blk);
   if constexpr (!LISTED) {
     for (int b = threadIdx.x; b < kBins1; b += kLoadThreads) h[b] = 0;
     __syncthreads();
   }
-  if (w.tile_lo >= w.tile_hi) return;  // (uniform) past the end of a shorter last partition
-  u32x4 look{};
-  if constexpr (LISTED) look = sh.look(w.p);
+  const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const uint32_t j_lo = __builtin_amdgcn_readfirstlane(w.tile_lo * kTile);
   const uint32_t left = w.d - j_lo;
   const uint32_t valid = __builtin_amdgcn_readfirstlane(left < kGroupElems ? left : kGroupElems);
@@ -587,49 +613,74 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
   const bool ef = src.res != nullptr;
   const TileBuf eb(ef ? src.res + base : nullptr, ef ? valid * 4 : 0);
   float v[kLoadRows][4];
-  if constexpr (kServer) {
-    // the residual's elements are requested first, so they are on their way while the group's
-    // sum is formed
-    u32x4 er[kLoadRows];
+  auto fetch = [&] {
+    if constexpr (kServer) {
+      // the residual's elements are requested first, so they are on their way while the group's
+      // sum is formed
+      u32x4 er[kLoadRows];
 #pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) er[u] = eb.load16<kNonTemporal>(threadIdx.x * 16, u * kLoadRowElems * 4);
-    src.begin_group(g, w.p, w.tile_lo / kTpgLoad, lds);
+      for (int u = 0; u < kLoadRows; ++u) er[u] = eb.load16<kNonTemporal>(threadIdx.x * 16, u * kLoadRowElems * 4);
+      src.begin_group(g, w.p, w.tile_lo / kTpgLoad, lds);
 #pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) {
-      const float4 sum = reinterpret_cast<const float4 *>(lds)[u * kLoadThreads + threadIdx.x];
-      const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
-      float e[4];
-      widen4(er[u], e);
+      for (int u = 0; u < kLoadRows; ++u) {
+        const float4 sum = reinterpret_cast<const float4 *>(lds)[u * kLoadThreads + threadIdx.x];
+        const float sv[4] = {sum.x, sum.y, sum.z, sum.w};
+        float e[4];
+        widen4(er[u], e);
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const float mean = sv[c] * src.msgs.inv_n;
-        const float delta = ef ? mean + e[c] : mean;
-        v[u][c] = (uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid ? delta : 0.0f;
+        for (int c = 0; c < 4; ++c) {
+          const float mean = sv[c] * src.msgs.inv_n;
+          const float delta = ef ? mean + e[c] : mean;
+          v[u][c] = (uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid ? delta : 0.0f;
+        }
+      }
+    } else {
+      using T = typename SRC::Elem;
+      const TileBuf gb(src.grad + base, valid * (uint32_t)sizeof(T));
+      typename Vec4Of<T>::type gr[kLoadRows];
+      u32x4 er[kLoadRows];
+#pragma unroll
+      for (int u = 0; u < kLoadRows; ++u) {
+        gr[u] = tile_load4(gb, threadIdx.x * 4 * (uint32_t)sizeof(T), u * kLoadRowElems * (uint32_t)sizeof(T), (const T *)nullptr);
+        er[u] = eb.load16<kNonTemporal>(threadIdx.x * 16, u * kLoadRowElems * 4);
+      }
+      if constexpr (sizeof(T) == 2) patch_last_half<kLoadRows, kLoadRowElems>(gb, valid, gr);
+#pragma unroll
+      for (int u = 0; u < kLoadRows; ++u) {
+        float x[4], e[4];
+        widen4(gr[u], x);
+        widen4(er[u], e);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[u][c] = ef ? x[c] + e[c] : x[c];
       }
     }
+  };
+  uint32_t G = kNoGuess;
+  if constexpr (!LISTED) {
+    fetch();
   } else {
-    using T = typename SRC::Elem;
-    const TileBuf gb(src.grad + base, valid * (uint32_t)sizeof(T));
-    typename Vec4Of<T>::type gr[kLoadRows];
-    u32x4 er[kLoadRows];
-#pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) {
-      gr[u] = tile_load4(gb, threadIdx.x * 4 * (uint32_t)sizeof(T), u * kLoadRowElems * (uint32_t)sizeof(T), (const T *)nullptr);
-      er[u] = eb.load16<kNonTemporal>(threadIdx.x * 16, u * kLoadRowElems * 4);
-    }
-    if constexpr (sizeof(T) == 2) patch_last_half<kLoadRows, kLoadRowElems>(gb, valid, gr);
-#pragma unroll
-    for (int u = 0; u < kLoadRows; ++u) {
-      float x[4], e[4];
-      widen4(gr[u], x);
-      widen4(er[u], e);
-#pragma unroll
-      for (int c = 0; c < 4; ++c) v[u][c] = ef ? x[c] + e[c] : x[c];
+    // (the buffer is the residual, of which the guess's sample is read: no store before the guess is there)
+    // (one wave looks for all: eight times fewer reads of one address)
+    auto wait = [&](u32x4 look, int looks) {
+      if (wave == 0) {
+        uint32_t guess = kNoGuess;
+        const bool there = sh.wait(w.p, look, looks, &guess);
+        if (lane == 0) { sel[0] = guess; sel[1] = there; }
+      }
+      __syncthreads();
+      G = __builtin_amdgcn_readfirstlane(sel[0]);
+      return __builtin_amdgcn_readfirstlane(sel[1]) != 0;
+    };
+    u32x4 look{};
+    if (wave == 0) look = sh.look(w.p);
+    fetch();
+    if (!wait(look, kPatience)) {
+      __syncthreads();
+      make_guess(w.p, w.d);
+      __syncthreads();
+      if (!wait(sh.look(w.p), kSpinLimit) && threadIdx.x == 0) status_give_up(sh.status, sh.tag);
     }
   }
-  // (the buffer is the residual, of which the guess's sample is read: no store before the guess is there)
-  uint32_t G = kNoGuess;
-  if constexpr (LISTED) G = sh.wait(w.p, look);
   if (!LISTED || buf)
 #pragma unroll
   for (int u = 0; u < kLoadRows; ++u)
@@ -651,7 +702,6 @@ __global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src,
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         mask |= (uint32_t)((uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid && key_of(v[u][c]) >= G) << (4 * u + c);
-    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const uint32_t cnt = (uint32_t)__popc(mask);
     const uint32_t incl = wave_inclusive_scan_u32(cnt);
     if (lane == 63) scan[wave] = incl;
@@ -1157,7 +1207,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   const uint32_t range = (uint32_t)cdiv(cdiv(g.part_elems, shares), 32) * 32;
   const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
   const uint32_t n = __builtin_amdgcn_readfirstlane(*sh.length(p));
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * p]);
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(p)[0]);
   if (lo >= d) return;
   const uint32_t k = (uint32_t)k_of_device(g, p);
   if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
@@ -1364,7 +1414,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_bins_kernel(Geo g, uint32_t 
   const GroupRange w(g, lists);
   if (w.q0 >= w.q1) return;
   const uint32_t q = __builtin_amdgcn_readfirstlane(w.q0 + (threadIdx.x >> 7));
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(w.p)[0]);
   h[threadIdx.x] = 0;
   __syncthreads();
   entries_of_group<false>(g, lists, w, q, G, vec).each([&](uint32_t rel, uint32_t, uint32_t) { atomicAdd(&h[near_bin(rel)], 1u); });
@@ -1397,7 +1447,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_collect_kernel(Geo g, uint32
   if (threadIdx.x == 0) near = 0;
   if (!near_bin_of_k(bins, k, scan, sel)) return;   // (left to the long form: the next kernel finds out by itself)
   const uint32_t bin = sel[0], slot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), q = w.q0 + slot;
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(w.p)[0]);
   const auto mine = entries_of_group<true>(g, lists, w, q, G, vec);
   uint32_t above = 0, inside = 0;
   mine.each([&](uint32_t rel, uint32_t, uint32_t) {
@@ -1452,7 +1502,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_group_emit_kernel(Geo g, flo
   }
   const uint32_t bin = sel[0];
   uint32_t rem = sel[1];
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pairs[2ull * w.p]);
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(w.p)[0]);
   EntriesOf<kSelThreads, true> near_ones{lists.idx(w.p), lists.val(w.p), threadIdx.x, near, G};
   near_ones.load_first();
   auto each_near = [&](auto visit) { near_ones.each([&](uint32_t rel, uint32_t, uint32_t j) { visit(rel, j); }); };
@@ -1721,7 +1771,7 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     // under capture every replay would carry the same tag: the guesses are cleared in front
     const bool captured = launch_tag(stream, &sh.tag);
     if (captured) {
-      e = fill_zero(sh.pairs, 16ull * g.P, stream);
+      e = fill_zero(sh.pairs, 32ull * g.P, stream);
       if (e == hipSuccess) e = fill_zero(sh.status, 8, stream);
     }
     if (e == hipSuccess && gated) e = fill_zero(hist, ws.lay.guess - ws.lay.hist, stream);   // (and the state words)

@@ -115,3 +115,40 @@ def test_overlapped_workers_at_the_resnet50_shape(env):
             for lo, hi in fmt.defined_bytes("topk", d, fmt.k_of(w["k_ratio"], d), k_cap):
                 assert np.array_equal(fmt.record(a, p, strd)[lo:hi], fmt.record(b, p, strd)[lo:hi]), (i, p)
         assert torch.equal(outs[False][1][i].view(torch.int32), outs[True][1][i].view(torch.int32)), i
+
+
+@pytest.mark.parametrize("beside", ["sign", "dither", "topk"])
+def test_topk_beside_another_call_that_waits(env, beside):
+    """A top-k worker call, whose load pass waits for the guess of a partition's key, and a call whose workgroups wait
+    for each other (or a second top-k call), started at once on two streams that waited for one event."""
+    gu, synth, torch = env
+    bpc = gu.bpc
+    pe, D = 1 << 20, 24 * (1 << 20) + 4097
+    prms = [bpc.make_params(bpc.TOPK, pe, k_ratio=0.01, stream_id=1),
+            bpc.make_params(gu.KIND_B[beside], pe, k_ratio=0.01, levels=4, seed=3, stream_id=2)]
+    grads = [synth.device_gradient("normal", D, "f32", worker=i, device="cuda") for i in range(2)]
+    res0 = [synth.device_gradient("normal", D, "f32", worker=100 + i, device="cuda") * 0.3 for i in range(2)]
+    wss = [torch.empty(bpc.workspace_bytes(p, D, 1), dtype=torch.uint8, device="cuda") for p in prms]
+    want = None
+    main, side = torch.cuda.current_stream(), [torch.cuda.Stream(), torch.cuda.Stream()]
+    for rounds in range(6):
+        res = [r.clone() for r in res0]
+        pays = [torch.zeros(bpc.payload_bytes(p, D), dtype=torch.uint8, device="cuda") for p in prms]
+        torch.cuda.synchronize()
+        order = (0, 1) if rounds % 2 else (1, 0)
+        if rounds:
+            torch.cuda._sleep(400000)   # (both calls are enqueued behind it)
+            for s in side:
+                s.wait_stream(main)
+        for i in order:
+            with torch.cuda.stream(side[i] if rounds else main):
+                bpc.bpc_compress(prms[i], grads[i], res[i], pays[i], wss[i])
+        for s in side:
+            main.wait_stream(s)
+        torch.cuda.synchronize()
+        for i in range(2):
+            bpc.workspace_check(prms[i], D, wss[i])
+        got = [t.view(torch.int32) for t in res] + pays
+        if want is None:
+            want = got
+        assert all(torch.equal(a, b) for a, b in zip(got, want)), rounds
