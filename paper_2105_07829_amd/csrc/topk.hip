@@ -1207,7 +1207,10 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   const uint32_t range = (uint32_t)cdiv(cdiv(g.part_elems, shares), 32) * 32;
   const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
   const uint32_t n = __builtin_amdgcn_readfirstlane(*sh.length(p));
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(p)[0]);
+  // (the highest key is taken for the one below it: less a guess of 0, plus one, it would read as no entry, and a
+  // threshold would be looked for among fewer than k of them)
+  constexpr uint32_t kTopKey = kRelMask - 1;
+  const uint32_t guess = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(p)[0]), G = guess < kTopKey ? guess : kTopKey;
   if (lo >= d) return;
   const uint32_t k = (uint32_t)k_of_device(g, p);
   if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
@@ -1245,7 +1248,8 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   __syncthreads();
   each_entry<kSelPer>(rounds, [&](auto i) {
     constexpr uint32_t first = (i / 4) * (4 * kSelThreads) + i % 4;
-    rel[i] = first + threadIdx.x * 4 < n ? (key_of(__uint_as_float(rel[i])) - G + 1u) | (rel[i] & ~kRelMask) : 0u;
+    const uint32_t key = rel[i] & kRelMask;
+    rel[i] = first + threadIdx.x * 4 < n ? ((key < kTopKey ? key : kTopKey) - G + 1u) | (rel[i] & ~kRelMask) : 0u;
   });
   uint32_t R, r, ties;
   list_threshold<kSelPer>(rel, rounds, k, l, &R, &r, &ties);

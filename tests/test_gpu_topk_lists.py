@@ -1,0 +1,58 @@
+"""Top-k lists at the edges: keys at the top of the range, many messages of very many entries, equal magnitudes
+beside the lists."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gu():
+    import torch
+    assert torch.cuda.is_available()
+    import gpu_util
+    gpu_util.bpc.lib()
+    return gpu_util
+
+
+def same_records(orc, po, kind, got, ref, pe, D, ratio, nan=False):
+    """Indices and values of every record."""
+    stride, k_cap = orc.partition_stride(po), max(1, int(ratio * pe))
+    for p in range(-(-D // pe)):
+        k = max(1, int(ratio * min(pe, D - p * pe)))
+        vals, size = 16 + 4 * (-(-k_cap // 4) * 4), 4 if kind == "topk" else 2
+        a, b = got[p * stride:(p + 1) * stride], ref[p * stride:(p + 1) * stride]
+        assert np.array_equal(a[:16 + 4 * k], b[:16 + 4 * k]), p
+        va, vb = a[vals:vals + size * k], b[vals:vals + size * k]
+        if nan:   # (which NaN is not said)
+            t = np.float32 if kind == "topk" else np.float16
+            assert np.array_equal(va.view(t), vb.view(t), equal_nan=True), p
+        else:
+            assert np.array_equal(va, vb), p
+
+
+@pytest.mark.parametrize("kind", ["topk", "topk16"])
+@pytest.mark.parametrize("ef", [True, False])
+@pytest.mark.parametrize("pe,D,ratio,share", [(8192, 100, 0.05, 0.03), (8192, 8192 + 700, 1.0, 1.0), (32768, 32768, 0.25, 0.01), (32768, 32768, 0.25, 0.5)])
+def test_topk_keys_at_the_top_of_the_range(gu, orc, kind, ef, pe, D, ratio, share):
+    """Bit patterns 0x7fffffff and 0xffffffff in partitions whose guess is 0 (listed whole: all of a small one, or
+    all but zeros).  They sort first like every NaN, and nothing is written past the records."""
+    import torch
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
+    rs = np.random.default_rng(D)
+    bits = np.zeros(D, np.uint32)
+    at = rs.choice(D, max(1, int(share * D)), replace=False)
+    bits[at] = np.where(rs.random(at.size) < 0.5, 0x7fffffff, 0xffffffff)
+    bits[rs.choice(D, 9, replace=False)] = np.float32(3.0).view(np.uint32)
+    g, res = bits.view(np.float32), np.zeros(D, np.float32) if ef else None
+    ref_res = None if res is None else res.copy()
+    ref = orc.compress(po, g, ref_res)
+    size, rd = bpc.payload_bytes(pb, D), gu.to_dev(res)
+    pay, ws = torch.full((size + (1 << 20),), 0xA5, dtype=torch.uint8, device=gu.DEV), gu.new_ws(pb, D)
+    bpc.bpc_compress(pb, gu.to_dev(g), rd, pay[:size], ws)
+    bpc.workspace_check(pb, D, ws)
+    assert bool((pay[size:] == 0xA5).all())
+    same_records(orc, po, kind, gu.to_host(pay)[:size], ref, pe, D, ratio, nan=True)
+    if ef:   # (a kept NaN leaves 0 behind, or what the difference of two NaNs is)
+        assert np.array_equal(gu.to_host(rd)[~np.isnan(ref_res)], ref_res[~np.isnan(ref_res)])
