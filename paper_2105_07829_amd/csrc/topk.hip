@@ -286,8 +286,9 @@ struct SamplePlan {
 // a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
 // 135 us, of 8 workers on 25.6 M elements 911 -> 892 us, of 16 workers on 110 M f16 elements 4275 ->
 // 4202 us.  (1024 threads: 131, 908 and 4402 us.  With the guess a second time, for workgroups that waited too
-// long, it is 66 to 78 registers and six waves, and these steps take what they took: 104.6 -> 104.9, 779 -> 773
-// and 3932 -> 3913 us; in one copy for both uses, 56 registers: 107.2, 777.)
+// long, a worker's is held to 64 registers, since calls of many small partitions want the eight waves: 16 M elements
+// in partitions of 1024, 590 us a call so, 621 with 74 registers; these steps take what they took.  In one copy
+// for both uses, 56 registers, the guess takes longer: steps of 3 workers 104.6 -> 107.2 us.)
 constexpr int kLoadThreads = 512;
 constexpr uint32_t kGroupElems = kTpgLoad * kTile;   // elements a workgroup of the load pass takes: 8192
 static_assert(kGroupElems == 8192, "the workspace is laid out for groups of 8192 elements");
@@ -573,7 +574,7 @@ constexpr int kLoadRows = kGroupElems / kLoadRowElems;
 // `buf` is null where the gradient itself will do (no error feedback, short-list form): nothing is stored
 // (f32 gradients, 20 M elements, k = 1 %: 65 -> 38 us).
 template <class SRC, bool LISTED>
-__global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
+__global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::value ? 8 : 1)) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
                                                                  TopkLists lists) {
   constexpr bool kServer = has_begin_group<SRC>::value;
   __shared__ __align__(16) float lds[SRC::kLdsFloats];
