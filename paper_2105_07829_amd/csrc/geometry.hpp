@@ -84,6 +84,42 @@ BPC_HD inline uint32_t row_in_record(uint32_t row0, uint64_t part_elems) {
   return row0 < last ? row0 : last;
 }
 
+// The sample of a top-k partition of d elements: up to kSampleChunks whole chunks of eight consecutive
+// elements, one of every 1 << shift (up to a quarter of them in small partitions, of which calls have many: servers
+// of 4 workers on 16 M elements, partitions of 8192 / 65536, 171 -> 129 and 69 -> 56 us).
+constexpr uint32_t kSampleChunks = 1024, kSmallPartition = 65536;
+BPC_HD inline uint32_t sample_shift(uint32_t d) {
+  uint32_t shift = 0;
+  while (((d / 8) >> shift) > (d <= kSmallPartition ? kSampleChunks / 4 : kSampleChunks)) ++shift;
+  return shift;
+}
+BPC_HD inline uint32_t sample_chunks(uint32_t d) { return (d / 8) >> sample_shift(d); }
+
+// What the rows of workgroups (the second grid dimension) of the kernel in front of a top-k server's load pass
+// do for a partition.  Rows of sums: `slots` messages side by side, a thread searching one message for one of
+// `chunks` sampled chunks.  Rows of starts: eight entries a thread (and the end) of one message, or all of
+// `messages` short ones; the launch has `starts` rows of them, of which each takes every starts-th of the
+// `roles`.  (A grid has at most 65535 rows.)  Long messages take larger workgroups (16 messages of 31 K
+// entries, 60 M elements: 434 us a call with 1024 threads, 444 with 256; 8 messages of 10 K, 26 M: a step 778, 770).
+constexpr uint32_t kPrepThreads = 256, kPrepMostThreads = 1024, kPrepSlots = 16, kPrepMostStarts = 32768;
+struct PrepRows { uint32_t threads, slots, chunks, chunk_bits, sums, messages, pieces, roles, starts; };
+// n messages of partitions of `d` elements at most and k_cap entries.
+BPC_HD inline PrepRows prep_rows(uint32_t n, uint32_t k_cap, uint32_t d, bool guesses) {
+  PrepRows r;
+  r.threads = k_cap > kTopkListCap / 2 ? kPrepMostThreads : kPrepThreads;
+  r.slots = 1;
+  while (r.slots < n && r.slots < kPrepSlots) r.slots *= 2;
+  r.chunks = r.threads / r.slots;   // (a power of two)
+  r.chunk_bits = 0;
+  while (1u << r.chunk_bits < r.chunks) ++r.chunk_bits;
+  r.sums = guesses ? (uint32_t)cdiv(sample_chunks(d), r.chunks) : 0u;
+  r.pieces = (uint32_t)cdiv((uint64_t)k_cap + 1, 8 * r.threads);
+  r.messages = r.pieces == 1 ? 8 * r.threads / (k_cap + 1) : 1u;
+  r.roles = r.pieces == 1 ? (uint32_t)cdiv(n, r.messages) : n * r.pieces;
+  r.starts = r.roles < kPrepMostStarts ? r.roles : kPrepMostStarts;
+  return r;
+}
+
 // Bit planes that follow the nibbles of a linear-dithering record: level bits 3, 4, 5.
 BPC_HD inline uint32_t dither_planes(uint32_t levels) {
   uint32_t planes = 0;

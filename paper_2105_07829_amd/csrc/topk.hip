@@ -80,7 +80,6 @@ constexpr uint32_t kMostShares = 8;                     // ... of one partition 
 constexpr uint32_t kAloneElems = 1u << 22;              // partitions up to this size are left to one workgroup if the short list fails
 constexpr uint32_t kMostListed = 65536;                 // k of a full partition up to which the group-list form is taken
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
-constexpr uint32_t kSampleChunks = 1024;                // chunks of eight consecutive elements in a partition's sample, at most
 constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
 constexpr uint32_t kNearBins = 1024;                    // group-list form: bins of the listed keys by their distance from the guess,
 constexpr uint32_t kBinWords = kNearBins + 1;           // and the number of entries in the threshold's bin
@@ -274,11 +273,7 @@ __device__ inline void level3_in_registers(const uint32_t (&bits)[PER], uint32_t
 // distances of a power of two would all come from the same few memory channels).  Only whole chunks.
 struct SamplePlan {
   uint32_t shift, chunks;
-  __device__ explicit SamplePlan(uint32_t d) {
-    shift = 0;
-    while (((d / 8) >> shift) > kSampleChunks) ++shift;
-    chunks = (d / 8) >> shift;
-  }
+  __device__ explicit SamplePlan(uint32_t d) : shift(sample_shift(d)), chunks(sample_chunks(d)) {}
   __device__ uint32_t chunk(uint32_t c) const { return (c << shift) + ((c * 37u) & ((1u << shift) - 1u)); }
 };
 
@@ -345,10 +340,23 @@ __device__ inline void topk_starts(const Geo &g, const TopkMsgs &m, uint32_t *st
   const uint32_t *idx = m.idx(i, p);
   uint32_t *tab = starts + ((uint64_t)i * g.P + p) * (m.groups_per_part + 1);
   auto group = [&](uint32_t j) { const uint32_t q = j >> m.group_shift; return q < m.groups_per_part ? q : m.groups_per_part - 1; };
-  for (uint32_t t = t0; t <= k && t < end; t += step) {
-    const uint32_t first = t == 0 ? 0u : group(idx[t - 1]) + 1;
-    const uint32_t last = t == k ? m.groups_per_part : group(idx[t]);
-    for (uint32_t q = first; q <= last && q <= m.groups_per_part; ++q) tab[q] = t;
+  constexpr uint32_t kAhead = 4;   // entries requested before the first is looked at
+  for (uint32_t t = t0; t <= k && t < end; t += kAhead * step) {
+    uint32_t before[kAhead], here[kAhead];
+#pragma unroll
+    for (uint32_t r = 0; r < kAhead; ++r) {
+      const uint32_t e = t + r * step;
+      before[r] = e > 0 && e <= k && e < end ? idx[e - 1] : 0u;
+      here[r] = e < k && e < end ? idx[e] : 0u;
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kAhead; ++r) {
+      const uint32_t e = t + r * step;
+      if (e > k || e >= end) break;
+      const uint32_t first = e == 0 ? 0u : group(before[r]) + 1;
+      const uint32_t last = e == k ? m.groups_per_part : group(here[r]);
+      for (uint32_t q = first; q <= last && q <= m.groups_per_part; ++q) tab[q] = e;
+    }
   }
 }
 __global__ __launch_bounds__(kThreads) void topk_starts_kernel(Geo g, TopkMsgs m, uint32_t *starts) {
@@ -502,32 +510,40 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   publish(sel[0]);
 }
 
-// Server side, in front of the load pass.  The first kSumPieces workgroups of a partition find the sums of the
-// decoded messages in the sampled chunks, 64 chunks each, a thread searching one message for one chunk (on
+// Server side, in front of the load pass.  The first rows of workgroups of a partition find the sums of the
+// decoded messages in the sampled chunks, a thread searching one message for one chunk (on
 // one compute unit, by a sweep over the messages or by searches, they took 25 to 150 us); the others
-// where each group's entries start, kStartsPiece entries of one message each.
-constexpr int kPrepThreads = 1024;
-constexpr uint32_t kSumChunks = 64, kSumSlots = kPrepThreads / kSumChunks, kSumPieces = kSampleChunks / kSumChunks;
-constexpr uint32_t kStartsPiece = 8 * kPrepThreads;
+// where each group's entries start.  (With workgroups of 1024 threads for 16 messages whatever their number, and
+// one for every message however short, calls of many partitions spent more time here than in the passes
+// behind: 4 workers, 16 M elements, partitions of 8192 / 65536, 138 to 266 and 65 to 85 us a call; 129 and 56 so.)
 static_assert(kSampleChunks * 8 <= kTopkListCap, "the sums lie where the lists will");
-__global__ __launch_bounds__(kPrepThreads) void topk_server_prep_kernel(Geo g, TopkMsgs m, uint32_t *starts, float *sums, int guesses) {
-  __shared__ float part[kSumSlots][kSumChunks * 8];
-  const uint32_t p = blockIdx.x, first_starts = guesses ? kSumPieces : 0u;
-  if (blockIdx.y >= first_starts) {
-    const uint32_t pieces = (m.k_cap + kStartsPiece) / kStartsPiece;   // (of k_cap + 1 entries)
-    const uint32_t role = blockIdx.y - first_starts, t0 = role % pieces * kStartsPiece;
-    topk_starts(g, m, starts, role / pieces, p, t0 + threadIdx.x, kPrepThreads, t0 + kStartsPiece);
+__global__ __launch_bounds__(kPrepMostThreads) void topk_server_prep_kernel(Geo g, TopkMsgs m, PrepRows rows, uint32_t *starts, float *sums) {
+  extern __shared__ float part[];   // eight words a thread
+  const uint32_t p = blockIdx.x, n = (uint32_t)m.msgs.n;
+  if (blockIdx.y >= rows.sums) {
+    for (uint32_t role = blockIdx.y - rows.sums; role < rows.roles; role += rows.starts) {
+      if (rows.pieces > 1) {
+        const uint32_t t0 = role % rows.pieces * 8 * rows.threads;
+        topk_starts(g, m, starts, role / rows.pieces, p, t0 + threadIdx.x, rows.threads, t0 + 8 * rows.threads);
+      } else {
+        const uint32_t i0 = role * rows.messages, per = m.k_cap + 1;
+        const uint32_t all = (n - i0 < rows.messages ? n - i0 : rows.messages) * per;
+        for (uint32_t q = threadIdx.x; q < all; q += rows.threads) {
+          const uint32_t t = q % per;
+          topk_starts(g, m, starts, i0 + q / per, p, t, 1, t + 1);
+        }
+      }
+    }
     return;
   }
-  const uint32_t d = g.part_size(p);
-  const SamplePlan plan(d);
-  const uint32_t slot = threadIdx.x / kSumChunks, mine = threadIdx.x % kSumChunks, c = blockIdx.y * kSumChunks + mine;
-  if (blockIdx.y * kSumChunks >= plan.chunks) return;   // (uniform)
-  float *acc = part[slot] + mine * 8;
+  const SamplePlan plan(g.part_size(p));
+  const uint32_t slot = threadIdx.x >> rows.chunk_bits, c = blockIdx.y * rows.chunks + (threadIdx.x & (rows.chunks - 1));
+  if (blockIdx.y * rows.chunks >= plan.chunks) return;   // (uniform)
+  float *acc = part + threadIdx.x * 8;   // [slot][chunk][element]
 #pragma unroll
   for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
   const uint32_t j0 = 8 * plan.chunk(c < plan.chunks ? c : 0u);
-  for (uint32_t i = slot; i < (uint32_t)m.msgs.n; i += kSumSlots) {
+  for (uint32_t i = slot; i < n; i += rows.slots) {
     const uint32_t *idx = m.idx(i, p);
     const uint32_t k = m.k_of(i, p);
     uint32_t lo = 0, len = k;   // the first entry at or past j0 is one of [lo, lo + len]
@@ -544,11 +560,12 @@ __global__ __launch_bounds__(kPrepThreads) void topk_server_prep_kernel(Geo g, T
     }
   }
   __syncthreads();
-  if (threadIdx.x < kSumChunks * 8) {
+  const uint32_t words = rows.chunks * 8;
+  for (uint32_t w = threadIdx.x; w < words; w += rows.threads) {
     float s = 0.0f;
 #pragma unroll
-    for (uint32_t q = 0; q < kSumSlots; ++q) s += part[q][threadIdx.x];
-    sums[(uint64_t)p * kTopkListCap + blockIdx.y * kSumChunks * 8 + threadIdx.x] = s;
+    for (uint32_t q = 0; q < kPrepSlots; ++q) s += q < rows.slots ? part[(q < rows.slots ? q : 0u) * words + w] : 0.0f;
+    sums[(uint64_t)p * kTopkListCap + blockIdx.y * words + w] = s;
   }
 }
 
@@ -1797,9 +1814,9 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     // server: Delta straight from the n messages (they are taken to have the format of `prm`)
     uint32_t *starts = ws.at<uint32_t>(ws.lay.starts);
     const TopkMsgs m{src.msgs, src.residual, starts, (uint32_t)cdiv(g.tiles_per_part, kTpgLoad), g.k_cap, g.stride, half ? 1 : 0, 13};
-    const uint32_t rows = (short_list ? kSumPieces : 0u) + src.msgs.n * ((m.k_cap + kStartsPiece) / kStartsPiece);
+    const PrepRows rows = prep_rows((uint32_t)src.msgs.n, g.k_cap, g.part_size(0), short_list);
     float *sums = reinterpret_cast<float *>(lists.base);
-    topk_server_prep_kernel<<<dim3(g.P, rows), kPrepThreads, 0, stream>>>(g, m, starts, sums, short_list);
+    topk_server_prep_kernel<<<dim3(g.P, rows.sums + rows.starts), rows.threads, rows.threads * 32, stream>>>(g, m, rows, starts, sums);
     load(TopkMsgsGroupSource{m, sums});
   }
   if (group_lists) {

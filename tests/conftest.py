@@ -33,6 +33,8 @@ def geo(tmp_path_factory):
                             ("geo_lans_tile", [], C.c_uint32), ("geo_find_block", [C.c_void_p, C.c_uint64, C.c_uint64], C.c_int64),
                             ("geo_tile_edge", [C.c_uint64, C.c_uint64], C.c_uint64),
                             ("geo_block_tiles", [C.c_uint64, C.c_uint64, C.c_uint64, C.c_void_p, C.c_void_p], None),
-                            ("geo_topk_state", [C.c_void_p, C.c_uint64], C.c_uint64)]:
+                            ("geo_topk_state", [C.c_void_p, C.c_uint64], C.c_uint64),
+                            ("geo_prep_rows", [C.c_uint32, C.c_uint32, C.c_uint32, C.c_int, C.c_void_p], None),
+                            ("geo_sample_chunks", [C.c_uint32], C.c_uint32)]:
         getattr(L, name).argtypes, getattr(L, name).restype = args, res
     return L

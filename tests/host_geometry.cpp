@@ -32,4 +32,11 @@ void geo_block_tiles(uint64_t lo, uint64_t hi, uint64_t D, uint64_t *t0, uint64_
 // Byte offset in a workspace of the selection state of a top-k call: eight words a partition, the second
 // of them non-zero where the partition was left to the long form.
 uint64_t geo_topk_state(const bpc_params_t *p, uint64_t D) { return bpc::ws_layout(p, D).state; }
+// The rows of workgroups in front of a top-k server's load pass: threads, slots, chunks, sums, messages, pieces, roles, starts.
+void geo_prep_rows(uint32_t n, uint32_t k_cap, uint32_t d, int guesses, uint32_t out[8]) {
+  const bpc::PrepRows r = bpc::prep_rows(n, k_cap, d, guesses != 0);
+  const uint32_t v[8] = {r.threads, r.slots, r.chunks, r.sums, r.messages, r.pieces, r.roles, r.starts};
+  for (int i = 0; i < 8; ++i) out[i] = v[i];
+}
+uint32_t geo_sample_chunks(uint32_t d) { return bpc::sample_chunks(d); }
 }

@@ -56,3 +56,24 @@ def test_topk_keys_at_the_top_of_the_range(gu, orc, kind, ef, pe, D, ratio, shar
     same_records(orc, po, kind, gu.to_host(pay)[:size], ref, pe, D, ratio, nan=True)
     if ef:   # (a kept NaN leaves 0 behind, or what the difference of two NaNs is)
         assert np.array_equal(gu.to_host(rd)[~np.isnan(ref_res)], ref_res[~np.isnan(ref_res)])
+
+
+@pytest.mark.parametrize("kind,pe,ratio,n,D", [("topk", 8_390_656, 1.0, 64, 3001), ("topk16", 8_390_656, 1.0, 63, 8193), ("topk", 8192, 0.01, 4, 300 * 8192 + 5),
+                                               ("topk", 1024, 0.02, 64, 50 * 1024 + 77), ("topk16", 65536, 0.03, 17, 5 * 65536 + 9), ("topk", 1_048_576, 0.0019, 3, 1_048_576 + 8192)])
+def test_topk_server_rows_of_sums_and_starts(gu, orc, kind, pe, ratio, n, D):
+    """Messages of more entries than the rows of one launch take at once (64 messages of 8.4 M entries each at most; the
+    gradient itself is short), of few entries (several to a row), and of just under and over a row's."""
+    import torch
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
+    rs = np.random.default_rng(n)
+    kinds = [orc.compress(po, rs.standard_normal(D).astype(np.float32), None) for _ in range(min(n, 3))]
+    dev = [gu.to_dev(m) for m in kinds]
+    res = (rs.standard_normal(D) * 0.1).astype(np.float32)
+    rd, pay = gu.to_dev(res), gu.new_payload(pb, D)
+    ws = torch.empty(bpc.workspace_bytes(pb, D, n), dtype=torch.uint8, device=gu.DEV)
+    bpc.bpc_server_aggregate([pb] * n, [dev[i % len(dev)] for i in range(n)], pb, rd, D, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    ref = orc.server_aggregate([po] * n, [kinds[i % len(kinds)] for i in range(n)], po, res, D)
+    assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+    same_records(orc, po, kind, gu.to_host(pay), ref, pe, D, ratio)

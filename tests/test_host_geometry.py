@@ -80,3 +80,24 @@ def test_lans_blocks_stay_inside_their_pairs_whatever_the_offsets(geo, name, D):
         if n.value > 1:
             touched += [t0.value + b, t0.value + n.value - 1 + b]
     assert not touched or (min(touched) >= 0 and max(touched) <= tiles + n_blocks - 2)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 16, 17, 20, 63, 64])
+@pytest.mark.parametrize("d", [1, 9, 1024, 8192, 9000, 300_007, 1 << 20, (1 << 23) + 1024, 1 << 28])
+@pytest.mark.parametrize("ratio", [1e-9, 1e-3, 0.01, 0.1, 1.0])
+def test_rows_in_front_of_the_topk_server_cover_everything_and_fit_a_grid(geo, n, d, ratio):
+    """Every sampled chunk and every entry of every message (and its end) belong to one row; a grid has at most
+    65535 rows, however many entries the messages have."""
+    k_cap, out = max(1, int(ratio * d)), (C.c_uint32 * 8)()
+    for guesses in (0, 1):
+        geo.geo_prep_rows(n, k_cap, d, guesses, out)
+        threads, slots, chunks, sums, messages, pieces, roles, starts = out
+        entries = 8 * threads
+        assert sums + starts <= 65535 and 1 <= starts <= roles
+        assert slots * chunks == threads and (slots >= n or slots == 16)
+        assert sums * chunks >= geo.geo_sample_chunks(d) * guesses
+        assert pieces * entries >= k_cap + 1
+        if pieces > 1:
+            assert messages == 1 and roles == n * pieces
+        else:
+            assert messages * (k_cap + 1) <= entries and roles * messages >= n > (roles - 1) * messages
