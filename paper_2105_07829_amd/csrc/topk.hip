@@ -6,9 +6,10 @@
 // bits(v) & 0x7fffffff (11 + 10 + 10 bits); elements equal to the threshold key are admitted
 // lowest index first, and the record lists its entries by ascending index.
 //
-// Short-list form (k of a full partition at most half of kTopkListCap): one pass over the data.
-//   guess      : 4096 elements of each partition (512 spread chunks of eight); the key G at a rank of
-//                the sample chosen so that, but for rare cases, at least k and at most about 2 k
+// Short-list form (k of a full partition at most half of kTopkListCap, partitions of up to 8 M elements):
+// one pass over the data.
+//   guess      : up to 8192 elements of each partition (1024 spread chunks of eight); the key G at a rank of
+//                the sample chosen so that, but for rare cases, at least k and no more than a few k
 //                elements of the partition have keys >= G
 //   load       : v_j from the source -> dense buffer; the elements with key >= G go to the
 //                partition's short list
@@ -78,6 +79,7 @@ constexpr uint32_t kShareWords = 16384;                 // words of the bitmap o
 constexpr uint32_t kXcds = 8, kCusOfXcd = 32;            // of an MI355X: the select pass is spread over one workgroup a compute unit when there are few partitions
 constexpr uint32_t kMostShares = 8;                     // ... of one partition (unless its bitmaps ask for more)
 constexpr uint32_t kAloneElems = 1u << 22;              // partitions up to this size are left to one workgroup if the short list fails
+constexpr uint32_t kMostOfList = 1u << 23;              // elements of a partition in the short-list form, at most
 constexpr uint32_t kMostListed = 65536;                 // k of a full partition up to which the group-list form is taken
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
@@ -113,6 +115,7 @@ struct TopkShared {
   uint64_t tag;
   uint32_t *status;
   uint32_t *state;
+  bool limited;   // the lists' room is (that of the group lists is not)
   static size_t pairs_bytes(uint32_t P) { return (32ull * P + 4095) / 4096 * 4096; }
   __device__ uint32_t *length(uint32_t p) const { return lengths + 1024ull * p; }
   __device__ uint64_t *pair(uint32_t p) const { return pairs + 4ull * p; }
@@ -464,11 +467,7 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   const uint32_t d = g.part_size(p);
   const SamplePlan plan(d);
   const uint32_t m = 8 * plan.chunks;                         // elements in the sample
-  // rank in the sample: the expected rank of the partition's k-th largest, four standard
-  // deviations of a count of twice that size further down (neighbours are not independent),
-  // and a little more
-  const double expect = (double)k_of_device(g, p) * (double)m / (double)d;
-  const uint32_t rank = (uint32_t)(expect + 4.0 * sqrt(2.0 * expect) + 3.0);
+  const uint32_t rank = m ? sample_rank(k_of_device(g, p), m, d, sh.limited) : 0;
   if (rank >= m) {   // (uniform) the whole partition is listed
     publish(0);
     return;
@@ -1222,7 +1221,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   const uint32_t p = __builtin_amdgcn_readfirstlane(at_xcd / shares * kXcds + blockIdx.x % kXcds), share = __builtin_amdgcn_readfirstlane(at_xcd % shares);
   if (p >= g.P) return;
   const uint32_t d = g.part_size(p);
-  const uint32_t range = (uint32_t)cdiv(cdiv(g.part_elems, shares), 32) * 32;
+  const uint32_t range = (uint32_t)cdiv(cdiv(g.part_size(0), shares), 32) * 32;
   const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
   const uint32_t n = __builtin_amdgcn_readfirstlane(*sh.length(p));
   // (the highest key is taken for the one below it: less a guess of 0, plus one, it would read as no entry, and a
@@ -1235,7 +1234,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   if (n < k || n > kTopkListCap) {
     if (share != 0) return;
     if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
-    if (g.part_elems <= kAloneElems) topk_alone<HALF>(g, p, k, buf, values, values16, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
+    if (g.part_size(0) <= kAloneElems) topk_alone<HALF>(g, p, k, buf, values, values16, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
     return;
   }
   // entry 4 (i * kSelThreads + thread) + c of the list is the thread's entry 4 i + c; all loads of a kind are
@@ -1774,19 +1773,22 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
   const void *long_fn = half ? reinterpret_cast<const void *>(&topk_long_form_kernel<true>)
                              : reinterpret_cast<const void *>(&topk_long_form_kernel<false>);
   static PerDevice cache[2];
-  const bool gated = g.part_elems > kAloneElems;
+  const uint32_t most = g.part_size(0);   // elements of the largest partition
+  const bool gated = most > kAloneElems;
   const int capacity = gated ? cache[half].get([&] { return cluster_capacity(long_fn, kThreads, 0); }) : 0;
-  // the short-list form wants room for the k winners and as many again; beyond, the group-list form wants the
-  // dense workspace and groups that are not listed to a large part
-  const bool group_lists = g.k_cap > kTopkListCap / 2 && g.k_cap <= kMostListed && g.part_elems >= 16ull * g.k_cap && !gated &&
-                           (src.residual || src.grad);
-  const bool short_list = group_lists || (g.k_cap <= kTopkListCap / 2 && (!gated || capacity > 0));
+  // the short-list form wants a list that its sample is unlikely to make too long, and partitions of up to 8 M
+  // elements (beyond, its few workgroups a partition take longer than the passes of the long form: one
+  // partition of 64 M elements 1590 against 440 us); the group-list form wants the dense workspace and groups that
+  // are not listed to a large part
+  const bool fits = g.k_cap <= kTopkListCap / 2 && topk_list_fits(k_rule(g.k_ratio, most), most);
+  const bool group_lists = !fits && g.k_cap <= kMostListed && g.part_elems >= 16ull * g.k_cap && !gated && (src.residual || src.grad);
+  const bool short_list = group_lists || (fits && (!gated || (most <= kMostOfList && capacity > 0)));
   if (group_lists) lists.dense = reinterpret_cast<uint32_t *>(dense);
   // the vector being compressed ends up in the residual buffer (error feedback) or the workspace, or is
   // the gradient as it is
   float *buf = src.residual ? src.residual : src.grad && short_list && !gated ? nullptr : dense;
   const uint32_t load_grid = group_count(g, kTpgLoad);
-  TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status(), state};
+  TopkShared sh{ws.at<uint64_t>(ws.lay.samp), nullptr, 0, ws.status(), state, !group_lists};
   sh.lengths = reinterpret_cast<uint32_t *>(reinterpret_cast<uint8_t *>(sh.pairs) + TopkShared::pairs_bytes(g.P));
   hipError_t e = hipSuccess;
   if (short_list) {
@@ -1833,7 +1835,7 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     const uint32_t of_xcd = (uint32_t)cdiv(g.P, kXcds);
     uint32_t shares = 1;
     while (shares < kMostShares && 2 * shares * of_xcd <= kCusOfXcd) shares *= 2;
-    const uint32_t least = (uint32_t)cdiv(g.part_elems, 32ull * kShareWords);
+    const uint32_t least = (uint32_t)cdiv(most, 32ull * kShareWords);
     if (shares < least) shares = least;
     if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);
     else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);

@@ -1,5 +1,7 @@
 """Top-k lists at the edges: keys at the top of the range, many messages of very many entries, equal magnitudes
 beside the lists."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -77,3 +79,29 @@ def test_topk_server_rows_of_sums_and_starts(gu, orc, kind, pe, ratio, n, D):
     ref = orc.server_aggregate([po] * n, [kinds[i % len(kinds)] for i in range(n)], po, res, D)
     assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
     same_records(orc, po, kind, gu.to_host(pay), ref, pe, D, ratio)
+
+
+def state_words(gu, geo, prm, D, ws):
+    """Word 1 of every partition's selection state after a call on `ws`: non-zero where the list did not do."""
+    at = int(geo.geo_topk_state(ctypes.byref(prm), D))
+    return gu.to_host(ws[at:at + 32 * -(-D // prm.part_elems)]).view(np.uint32).reshape(-1, 8)[:, 1]
+
+
+@pytest.mark.parametrize("kind,dtype,ef", [("topk", np.float32, True), ("topk16", np.float16, False)])
+@pytest.mark.parametrize("pe,D,ratio", [(1 << 20, (1 << 20) + 77, 1 / 64), (1 << 21, 1 << 21, 14_000.5 / (1 << 21)), (1 << 22, (1 << 22) + 8193, 1 / 256),
+                                        (1 << 23, 1 << 23, 0.001), (1 << 23, 1 << 23, 0.0015), (1 << 23, (1 << 23) + 1, 1e-4), (12 << 20, 12 << 20, 0.001), (1 << 26, 5_000_011, 2e-4)])
+def test_topk_on_either_side_of_what_a_list_holds(gu, orc, geo, kind, dtype, ef, pe, D, ratio):
+    """Ordinary vectors whose lists would be too long are not left to the fallback: they take another form."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
+    rs = np.random.default_rng(int(1 / ratio))
+    g = rs.standard_normal(D).astype(dtype)
+    res = (rs.standard_normal(D) * 0.1).astype(np.float32) if ef else None
+    rd, pay, ws = gu.to_dev(res), gu.new_payload(pb, D), gu.new_ws(pb, D)
+    bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    ref = orc.compress(po, g, res)
+    if ef:
+        assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+    same_records(orc, po, kind, gu.to_host(pay), ref, pe, D, ratio)
+    assert not state_words(gu, geo, pb, D, ws).any()

@@ -101,3 +101,22 @@ def test_rows_in_front_of_the_topk_server_cover_everything_and_fit_a_grid(geo, n
             assert messages == 1 and roles == n * pieces
         else:
             assert messages * (k_cap + 1) <= entries and roles * messages >= n > (roles - 1) * messages
+
+
+@pytest.mark.parametrize("k,d,fits", [(3000, 300_007, 1), (10_485, 1 << 20, 1), (16_384, 1 << 20, 1), (2097, 1 << 21, 1), (14_000, 1 << 21, 1),
+                                      (4194, 1 << 22, 1), (16_384, 1 << 22, 0), (8388, 1 << 23, 1), (9500, 1 << 23, 0), (838, 1 << 23, 1),
+                                      (12_582, 12 << 20, 0), (16_384, 65_536, 1), (16_384, 32_768, 1), (16_000, 16_200, 1), (30, 100, 1), (1, 7, 1)])
+def test_topk_lists_are_taken_where_they_fit(geo, k, d, fits):
+    """The length of a list: how many elements of a partition lie at or above the key of a rank of the sample.  Where the
+    rule says that it fits, it does, and holds at least k, in draws of a sample from elements in no order but
+    for some 0.3 % on either side (2.75 standard deviations): 200 draws, five or fewer (mean 1.2)."""
+    assert geo.geo_topk_list_fits(k, d) == fits
+    m = 8 * geo.geo_sample_chunks(d)
+    rank = geo.geo_sample_rank(k, m, d)
+    assert rank * d >= k * m
+    if not fits or rank >= m:
+        return
+    rs, cap = np.random.default_rng(k + d), geo.geo_topk_list_cap()
+    # (elements numbered from the largest)
+    lengths = np.array([np.sort(rs.choice(d, m, replace=False))[rank - 1] + 1 for _ in range(200)])
+    assert np.count_nonzero((lengths < k) | (lengths > cap)) <= 5
