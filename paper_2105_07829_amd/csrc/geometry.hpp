@@ -125,7 +125,7 @@ struct PrepRows { uint32_t threads, slots, chunks, chunk_bits, sums, messages, p
 BPC_HD inline PrepRows prep_rows(uint32_t n, uint32_t k_cap, uint32_t d, bool guesses) {
   PrepRows r;
   r.threads = k_cap > kTopkListCap / 2 ? kPrepMostThreads : kPrepThreads;
-  r.slots = 1;
+  r.slots = r.threads == kPrepThreads ? 1 : kPrepSlots;   // (long messages: rows of as few chunks as there can be)
   while (r.slots < n && r.slots < kPrepSlots) r.slots *= 2;
   r.chunks = r.threads / r.slots;   // (a power of two)
   r.chunk_bits = 0;

@@ -20,17 +20,21 @@
 // the server side a kernel in front sums the sampled chunks up and finds where each message's entries of a
 // group of 8192 elements begin.
 // The sample only decides how much work the selection is, never its result: a partition whose
-// short list came out shorter than k or longer than its room (the sample misled, or a great many
-// equal magnitudes, or fewer than k non-zeros) is taken by the long form below instead, run by the
+// short list came out shorter than k or longer than its room (the sample misled) is taken by the long form below
+// instead, run by the
 // partition's first select workgroup alone; partitions of more than kAloneElems elements by one more
 // kernel, enqueued behind, which returns at once if no partition needs it and else runs the
 // long form's passes for those partitions with its resident grid meeting between the passes.
+// A key that a great many elements share (zeros, magnitudes of few values) is left off the list, which starts
+// above it; if the list then holds fewer than k, it is kept whole, and ties of that key make up for the rest,
+// lowest index first: the load pass has counted them per group of 8192 elements, so every select workgroup knows how
+// far they are kept and reads its part of the vector again as far as that.
 //
 // Group-list form (larger k, up to kMostListed of a full partition, where the dense workspace is free): the
 // same guess and load pass, but every group of 8192 elements has a list of its own in the dense workspace.
 //   bins       : histogram of the listed keys' distances from the guess, 32 steps for every power of two
 //   collect    : the bin of the k-th largest key from it; per group, how many entries lie above the bin;
-//                the few entries inside it to one list a partition
+//                the few entries inside it to one list a partition, and whether they are all of one key
 //   emit       : threshold key and ties from that list (every workgroup for itself), then (idx, val) as
 //                in the select pass
 //
@@ -78,24 +82,31 @@ constexpr int kSelBins = 8192, kSelBits = 13;           // first level of the se
 constexpr uint32_t kShareWords = 16384;                 // words of the bitmap of a select workgroup's share of the indices, at most
 constexpr uint32_t kXcds = 8, kCusOfXcd = 32;            // of an MI355X: the select pass is spread over one workgroup a compute unit when there are few partitions
 constexpr uint32_t kMostShares = 8;                     // ... of one partition (unless its bitmaps ask for more)
-constexpr uint32_t kAloneElems = 1u << 22;              // partitions up to this size are left to one workgroup if the short list fails
+constexpr uint32_t kAloneElems = 1u << 21;              // partitions up to this size are left to one workgroup if the short list fails
 constexpr uint32_t kMostOfList = 1u << 23;              // elements of a partition in the short-list form, at most
 constexpr uint32_t kMostListed = 65536;                 // k of a full partition up to which the group-list form is taken
 constexpr uint32_t kGatedGrid = 1024;                   // grid of the long-form kernel behind the short-list form, at most
 constexpr uint32_t kFewInBin = kTopkListCap / 16;       // elements of a bin that the list can take unasked
+// Elements of one key stay off the list from so many on (the select pass's counts of them meet in one place: 0.3 M
+// elements of 16 magnitudes 80 us a call, 30 beside the list) if they are one in so many at least (the vector
+// is searched for them: 4 M elements of 256 magnitudes 74 us on the list, 130 beside it).
+constexpr uint32_t kTiesOffList = kTopkListCap / 8, kTiesDensity = 64;
+constexpr uint32_t kFewNear = 512;                      // entries of one key in the threshold's bin that every workgroup ranks for itself
 constexpr uint32_t kNearBins = 1024;                    // group-list form: bins of the listed keys by their distance from the guess,
-constexpr uint32_t kBinWords = kNearBins + 1;           // and the number of entries in the threshold's bin
+constexpr uint32_t kBinWords = kNearBins + 3;           // the number of entries in the threshold's bin, and their highest and lowest keys
 constexpr uint32_t kNoGuess = 0xffffffffu;              // no key reaches it: nothing goes to the short list
 
 __device__ inline uint32_t key_of(float v) { return __float_as_uint(v) & 0x7fffffffu; }
 
 // state words per partition: words 2L, 2L + 1 hold (prefix, rank left) after level L = 1..3;
-// word 1 non-zero if the partition is left to the long form
+// word 1 is kLongForm if the partition is left to the long form, kTiesBeside if elements beside its list are kept
 enum { kStPrefix = 0, kStKRem = 1 };
 enum { kStLong = 1 };
+enum : uint32_t { kLongForm = 1, kTiesBeside = 2 };
 
 // What the load pass of the short-list form hands from workgroup to workgroup, in the workspace's
-// region for it (16 KB a partition): the guesses, four words each (the guess, its exclusive or with
+// region for it (16 KB a partition): the guesses, four words each (the guess and whether there are ties beside
+// the list, its exclusive or with
 // the launch's tag, as the slots of cluster.hpp, and the tag once a workgroup has taken the guess on), and
 // the lengths of the lists, a page apart since an atomic on global memory holds up its memory channel for
 // some 11 ns.
@@ -104,11 +115,12 @@ enum { kStLong = 1 };
 // as a whole, and workgroups are bound to an XCD by their index: beside another kernel that waits (a second
 // top-k call, a single-pass kernel, on another stream), waiting workgroups of either could fill the XCD that a
 // guess's workgroup is bound to, and hold each other up.  So nobody waits long for a workgroup that may not
-// have started: after kPatience looks (some 0.2 ms) a waiting workgroup makes the guess itself.  The one that
-// takes it on first publishes it; the others drop theirs and wait for that one, which is running and waits
-// for nobody.  Whoever publishes it, it is the same guess: nothing is stored to the vector that is sampled
-// before a guess is there.
-constexpr int kPatience = 128;
+// have started: after kPatience looks (some 2 ms) a waiting workgroup takes the guess on itself and publishes that
+// there is none, which leaves the partition to the long form.  If one that is running has taken it on before,
+// it waits for that one, which waits for nobody.  The guess of a workgroup that comes too late is dropped.
+// (A second copy of the guess there instead took a worker's kernel from 40 to 64 registers and its call on 0.3 M
+// elements from 21.2 to 22.4 us.)
+constexpr int kPatience = 1024;
 struct TopkShared {
   uint64_t *pairs;
   uint32_t *lengths;
@@ -124,24 +136,26 @@ struct TopkShared {
     return __hip_atomic_exchange(pair(p) + 2, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   // One thread publishes partition p's guess; the list length is zero before anyone can see it.
-  __device__ void publish(uint32_t p, uint32_t guess) const {
+  __device__ void publish(uint32_t p, uint32_t guess, bool ties) const {
+    const uint64_t word = (uint64_t)(ties ? 1 : 0) << 32 | guess;
     __hip_atomic_store(length(p), 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     state[p * 8 + kStLong] = 0;
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0x0F70);   // (vector memory done)
     asm volatile("" ::: "memory");
-    __hip_atomic_store(pair(p), (uint64_t)guess, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(pair(p) + 1, (uint64_t)guess ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pair(p), word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(pair(p) + 1, word ^ tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   __device__ u32x4 look(uint32_t p) const { return TileBuf(pair(p), 16).load16<kMemorySide>(0, 0); }
   // One wave waits for the guess, `w` being its first look at it, for `looks` more; false if it is not there.
-  __device__ bool wait(uint32_t p, u32x4 w, int looks, uint32_t *guess) const {
+  __device__ bool wait(uint32_t p, u32x4 w, int looks, uint32_t *guess, uint32_t *ties) const {
     while ((w.x ^ w.z) != (uint32_t)tag || (w.y ^ w.w) != (uint32_t)(tag >> 32)) {
       if (--looks < 0) return false;
       __builtin_amdgcn_s_sleep(4);
       w = look(p);
     }
     *guess = w.x;
+    *ties = w.y;
     return true;
   }
 };
@@ -154,7 +168,8 @@ struct TopkLists {
   uint32_t *base;
   uint32_t P;
   uint32_t *dense;      // null: one list a partition
-  uint32_t *counts;     // group lists: two words a group: entries, entries above the bin of the threshold
+  uint32_t *counts;     // two words a group: entries of its list (group lists); ties beside the list, or (group
+                        // lists that hold k entries) entries above the bin of the threshold and, in the upper half, inside it
   uint32_t groups;      // of a full partition
   static constexpr uint32_t kNearCap = kTopkListCap - 8192;
   __device__ uint32_t *idx(uint32_t p) const { return base + (uint64_t)p * kTopkListCap; }
@@ -170,7 +185,7 @@ struct TopkLists {
 
 // Whether partition p is left to the long form (uniform over the workgroup).
 __device__ inline bool long_form(const uint32_t *state, uint32_t p) {
-  return __builtin_amdgcn_readfirstlane(state[p * 8 + kStLong]) != 0;
+  return __builtin_amdgcn_readfirstlane(state[p * 8 + kStLong]) == kLongForm;
 }
 
 // Group `blk` of TPG consecutive tiles of one partition.
@@ -283,10 +298,7 @@ struct SamplePlan {
 // Workgroup of the load pass: 16 elements a thread (of 256 threads, 32 elements each: 91 registers
 // a lane and five waves a SIMD where this has 44 and eight): steps of 3 workers on 0.3 M elements 146 ->
 // 135 us, of 8 workers on 25.6 M elements 911 -> 892 us, of 16 workers on 110 M f16 elements 4275 ->
-// 4202 us.  (1024 threads: 131, 908 and 4402 us.  With the guess a second time, for workgroups that waited too
-// long, a worker's is held to 64 registers, since calls of many small partitions want the eight waves: 16 M elements
-// in partitions of 1024, 590 us a call so, 621 with 74 registers; these steps take what they took.  In one copy
-// for both uses, 56 registers, the guess takes longer: steps of 3 workers 104.6 -> 107.2 us.)
+// 4202 us.  (1024 threads: 131, 908 and 4402 us.)
 constexpr int kLoadThreads = 512;
 constexpr uint32_t kGroupElems = kTpgLoad * kTile;   // elements a workgroup of the load pass takes: 8192
 static_assert(kGroupElems == 8192, "the workspace is laid out for groups of 8192 elements");
@@ -459,8 +471,8 @@ struct TopkMsgsGroupSource : TopkMsgs {
 template <int THREADS, class LOAD8>
 __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh, uint64_t taken, uint32_t *h, uint32_t *scan,
                                   uint32_t *sel, LOAD8 load8) {
-  auto publish = [&](uint32_t guess) {
-    if (threadIdx.x == 0 && taken != sh.tag) sh.publish(p, guess);
+  auto publish = [&](uint32_t guess, bool ties) {
+    if (threadIdx.x == 0 && taken != sh.tag) sh.publish(p, guess, ties);
   };
   constexpr uint32_t kChunksPer = (kSampleChunks + THREADS - 1) / THREADS;
   constexpr int kPer = 8 * kChunksPer;
@@ -469,7 +481,7 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   const uint32_t m = 8 * plan.chunks;                         // elements in the sample
   const uint32_t rank = m ? sample_rank(k_of_device(g, p), m, d, sh.limited) : 0;
   if (rank >= m) {   // (uniform) the whole partition is listed
-    publish(0);
+    publish(0, false);
     return;
   }
   uint32_t key[kPer];
@@ -502,11 +514,20 @@ __device__ inline void topk_guess(const Geo &g, uint32_t p, const TopkShared &sh
   const uint32_t prefix2 = sel[0], k_rem2 = sel[1];
   const uint64_t in_bin = (uint64_t)h[prefix2 & (kBins23 - 1)] * d;   // times m: elements of the partition
   if (in_bin <= (uint64_t)kFewInBin * m) {   // (uniform)
-    publish(prefix2 << kShift2);
+    publish(prefix2 << kShift2, false);
     return;
   }
   level3_in_registers<kPer, THREADS>(key, cnt, kPer, prefix2, k_rem2, h, scan, sel);
-  publish(sel[0]);
+  // One key that so many elements share that they would overrun the list (zeros, gradients of few magnitudes) stays
+  // off it: the list starts above, and where it then holds fewer than k, ties of that key are kept beside it.
+  // (Left to one workgroup or the resident kernel instead, calls on such data took up to thirty times as long as
+  // ordinary ones: partitions of 2 M f16 elements of 16 magnitudes, 16 M in all, k = 0.1 % / 1 %, 1117 -> 58 and
+  // 1205 -> 72 us; 0.3 M zeros, k = 1 % / 6 %, 140 -> 35 and 245 -> 55.)
+  const uint64_t equal = h[sel[0] & (kBins23 - 1)], listed = rank - sel[1] + equal;   // of the sample
+  const bool ties = d > kTopkListCap &&   // (smaller partitions fit the list whole)
+                    ((equal * d > kTiesOffList * (uint64_t)m && equal * kTiesDensity > m) ||
+                     (sh.limited && listed * d > 3ull * kTopkListCap / 4 * m));
+  publish(sel[0] + (ties ? 1u : 0u), ties);
 }
 
 // Server side, in front of the load pass.  The first rows of workgroups of a partition find the sums of the
@@ -590,7 +611,7 @@ constexpr int kLoadRows = kGroupElems / kLoadRowElems;
 // `buf` is null where the gradient itself will do (no error feedback, short-list form): nothing is stored
 // (f32 gradients, 20 M elements, k = 1 %: 65 -> 38 us).
 template <class SRC, bool LISTED>
-__global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::value ? 8 : 1)) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
+__global__ __launch_bounds__(kLoadThreads) void topk_load_kernel(Geo g, SRC src, float *buf, uint32_t *hist, uint32_t *state, TopkShared sh,
                                                                  TopkLists lists) {
   constexpr bool kServer = has_begin_group<SRC>::value;
   __shared__ __align__(16) float lds[SRC::kLdsFloats];
@@ -599,12 +620,6 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
   uint32_t *h = kServer && LISTED ? reinterpret_cast<uint32_t *>(lds) : own_h;
   __shared__ uint32_t scan[kWaves];
   __shared__ uint32_t sel[2];
-  auto make_guess = [&](uint32_t p, uint32_t d) {
-    topk_guess<kLoadThreads>(g, p, sh, threadIdx.x == 0 ? sh.take(p) : 0, h, scan, sel, [&](uint32_t c, uint32_t j0, float x[8]) {
-      if constexpr (kServer) src.sampled8(g, p, c, j0, d, x);
-      else src.at8(g, p, j0, d, nullptr, x);
-    });
-  };
   const bool first = LISTED && blockIdx.x < g.P;   // is here for the guess of a partition
   GroupOf w;
   if (first) {
@@ -612,7 +627,11 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
     if (blockIdx.x == 0) status_open(sh.status, sh.tag);
     if (lists.dense)   // (the bins of the group-list form, used by later kernels)
       for (uint32_t b = threadIdx.x; b < kBinWords; b += kLoadThreads) hist[(uint64_t)w.p * kTopkHistWords + b] = 0;
-    if (BPC_TOPK_FIRST_GUESS) make_guess(blockIdx.x, w.d);
+    if (BPC_TOPK_FIRST_GUESS)
+      topk_guess<kLoadThreads>(g, w.p, sh, threadIdx.x == 0 ? sh.take(w.p) : 0, h, scan, sel, [&](uint32_t c, uint32_t j0, float x[8]) {
+        if constexpr (kServer) src.sampled8(g, w.p, c, j0, w.d, x);
+        else src.at8(g, w.p, j0, w.d, nullptr, x);
+      });
     return;
   } else {
     w = group_of<kTpgLoad>(g, blockIdx.x - (LISTED ? g.P : 0u));
@@ -673,6 +692,7 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
     }
   };
   uint32_t G = kNoGuess;
+  bool ties = false;
   if constexpr (!LISTED) {
     fetch();
   } else {
@@ -680,20 +700,21 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
     // (one wave looks for all: eight times fewer reads of one address)
     auto wait = [&](u32x4 look, int looks) {
       if (wave == 0) {
-        uint32_t guess = kNoGuess;
-        const bool there = sh.wait(w.p, look, looks, &guess);
-        if (lane == 0) { sel[0] = guess; sel[1] = there; }
+        uint32_t guess = kNoGuess, beside = 0;
+        const bool there = sh.wait(w.p, look, looks, &guess, &beside);
+        if (lane == 0) { sel[0] = guess; sel[1] = there ? 1u + beside : 0u; }
       }
       __syncthreads();
       G = __builtin_amdgcn_readfirstlane(sel[0]);
-      return __builtin_amdgcn_readfirstlane(sel[1]) != 0;
+      const uint32_t there = __builtin_amdgcn_readfirstlane(sel[1]);
+      ties = there > 1u;
+      return there != 0;
     };
     u32x4 look{};
     if (wave == 0) look = sh.look(w.p);
     fetch();
-    if (!wait(look, kPatience)) {
-      __syncthreads();
-      make_guess(w.p, w.d);
+    if (!wait(look, kPatience)) {   // (uniform)
+      if (threadIdx.x == 0 && sh.take(w.p) != sh.tag) sh.publish(w.p, kNoGuess, false);
       __syncthreads();
       if (!wait(sh.look(w.p), kSpinLimit) && threadIdx.x == 0) status_give_up(sh.status, sh.tag);
     }
@@ -719,7 +740,14 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
 #pragma unroll
       for (int c = 0; c < 4; ++c)
         mask |= (uint32_t)((uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid && key_of(v[u][c]) >= G) << (4 * u + c);
-    const uint32_t cnt = (uint32_t)__popc(mask);
+    uint32_t cnt = (uint32_t)__popc(mask);
+    if (ties) {   // (uniform) ties beside the list are counted in the upper half
+#pragma unroll
+      for (int u = 0; u < kLoadRows; ++u)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          cnt += (uint32_t)(u * kLoadRowElems + c) + threadIdx.x * 4 < valid && key_of(v[u][c]) == G - 1u ? 0x10000u : 0u;
+    }
     const uint32_t incl = wave_inclusive_scan_u32(cnt);
     if (lane == 63) scan[wave] = incl;
     __syncthreads();
@@ -729,8 +757,10 @@ __global__ __launch_bounds__(kLoadThreads, (LISTED && !has_begin_group<SRC>::val
       before += (uint32_t)q < wave ? scan[q] : 0u;
       total += scan[q];
     }
+    if (ties && threadIdx.x == 0) lists.count(w.p, w.tile_lo / kTpgLoad)[1] = total >> 16;
+    total &= 0xffffu;
     TopkLists::List list{lists.idx(w.p), lists.val(w.p), kTopkListCap};
-    uint32_t pos = before + incl - cnt;
+    uint32_t pos = (before + incl - cnt) & 0xffffu;
     if (lists.dense) {
       list = lists.of_group(g, w.p, w.tile_lo / kTpgLoad, w.d);
       if (threadIdx.x == 0) *lists.count(w.p, w.tile_lo / kTpgLoad) = total;   // (more than its room: the vector itself will be read)
@@ -935,11 +965,38 @@ __device__ inline void topk_write_entry(const Geo &g, uint8_t *rec, uint32_t pos
   }
 }
 
+// The vector that was compressed, of one partition: the buffer, or the gradient in f32 or f16.  at(j): the f32 bits
+// of four elements from j on, a multiple of four; zeros past the end.
+struct PartValues {
+  TileBuf b;
+  uint32_t d;
+  bool half;
+  __device__ PartValues(const void *part, uint32_t elems, bool halves) : b(part, elems * (halves ? 2 : 4)), d(elems), half(halves) {}
+  __device__ u32x4 at(uint32_t j) const {
+    if (!half) return b.load16(j * 4, 0);
+    u32x2 hw = b.load8(j * 2, 0);
+    if ((d & 1u) && d - 1 - j < 4u) {   // the last half of an odd number: its dword reads as zero
+      const uint32_t one = b.load2((d - 1) * 2, 0);
+      if (d - 1 - j == 0) hw.x = one; else hw.y = one;
+    }
+    float f[4];
+    widen4(hw, f);
+    return as_u32x4(f[0], f[1], f[2], f[3]);
+  }
+};
+__device__ inline PartValues part_values(const Geo &g, uint32_t p, const float *buf, const void *values, int values16) {
+  const uint64_t base = uniform_off(g.part_base(p));
+  const bool half = !buf && values16;
+  return PartValues(buf ? (const void *)(buf + base) : half ? (const void *)((const __half *)values + base) : (const void *)((const float *)values + base),
+                    g.part_size(p), half);
+}
+
 // The long form of one partition by one workgroup of kSelThreads: three histogram passes, a pass that
 // counts per wave, a pass that writes; wave w takes the w-th stretch of the partition.  h: LDS,
-// kBins1 words.  Every element is read five times by one compute unit: a worker call on 1 M elements, all
-// zero or of one magnitude, takes 0.36 ms, of sixteen magnitudes 0.54 ms (the resident kernel below 0.71 ms),
-// on 64 M elements of one magnitude 0.51 ms (2.1 ms).
+// kBins1 words.  Every element is read five times by one compute unit, in the rare case that the sample misled: a worker
+// call on partitions of 1 M f32 elements that all do takes 0.57 to 0.59 ms (the resident kernel below 0.68 to
+// 0.80), of 2 M f16 1.05 to 1.23 (0.91, and 4.7 us more in every ordinary call), of 4 M f32 2.02 (0.68 to 1.06):
+// hence kAloneElems.  (Group lists of 1 M elements, k = 3 %: 1.25 ms.)
 // The vector is `buf`, whose kept slots are zeroed with error feedback, or else the gradient `values` in f32 or f16.
 template <bool HALF>
 __device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *buf, const void *values, int values16, uint8_t *payload,
@@ -951,32 +1008,15 @@ __device__ inline void topk_alone(const Geo &g, uint32_t p, uint32_t k, float *b
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const uint32_t seg = (uint32_t)cdiv(cdiv(d, kWaves), kRow) * kRow;
   const uint32_t lo = wave * seg < d ? wave * seg : d, hi = lo + seg < d ? lo + seg : d;
-  const uint64_t base = uniform_off(g.part_base(p));
-  float *buf_part = buf ? buf + base : nullptr;
-  const bool from16 = !buf && values16;
-  const TileBuf b(buf ? (const void *)buf_part : from16 ? (const void *)((const __half *)values + base) : (const void *)((const float *)values + base),
-                  d * (from16 ? 2 : 4));
+  float *buf_part = buf ? buf + uniform_off(g.part_base(p)) : nullptr;
+  const PartValues x_of = part_values(g, p, buf, values, values16);
   // visit(j, bits): the wave's elements in order, four consecutive ones a lane, kAhead rows requested at once
   auto walk = [&](auto visit) {
 #pragma unroll 1
     for (uint32_t r0 = lo; r0 < hi; r0 += kAhead * kRow) {
       u32x4 x[kAhead];
 #pragma unroll
-      for (uint32_t q = 0; q < kAhead; ++q) {
-        const uint32_t j = r0 + q * kRow + lane * 4;
-        if (!from16) {
-          x[q] = b.load16(j * 4, 0);
-        } else {
-          u32x2 hw = b.load8(j * 2, 0);
-          if ((d & 1u) && d - 1 - j < 4u) {   // the last half of an odd number: its dword reads as zero
-            const uint32_t one = b.load2((d - 1) * 2, 0);
-            if (d - 1 - j == 0) hw.x = one; else hw.y = one;
-          }
-          float f[4];
-          widen4(hw, f);
-          x[q] = as_u32x4(f[0], f[1], f[2], f[3]);
-        }
-      }
+      for (uint32_t q = 0; q < kAhead; ++q) x[q] = x_of.at(r0 + q * kRow + lane * 4);
 #pragma unroll
       for (uint32_t q = 0; q < kAhead; ++q) {
         const uint32_t v[4] = {x[q].x, x[q].y, x[q].z, x[q].w};
@@ -1203,17 +1243,161 @@ __device__ inline uint32_t last_tie(const uint32_t (&rel)[PER], const uint32_t (
   return prefix;
 }
 
+// Ties beside the list of a partition: the listed elements, all above one key, are fewer than k, and the rest of
+// the k are elements of that key, lowest index first.  The load pass has counted them per group, so a workgroup
+// of kSelThreads finds from the counts which group holds the last one that is kept.
+struct TieCut {
+  uint32_t all, before;    // of them in the partition, in groups before the workgroup's
+  uint32_t group, rest;    // the group of the last kept one, and how many of that group are kept
+};
+// `need` of them are kept; the workgroup's first group is q0 (below `groups`).
+__device__ __forceinline__ TieCut tie_cut(const TopkLists &lists, uint32_t p, uint32_t groups, uint32_t need, uint32_t q0, uint32_t *scan,
+                                 uint32_t *sel, uint32_t shift = 0) {
+  static_assert(kMostOfList / kGroupElems <= kSelThreads && kAloneElems <= kMostOfList, "a group a thread");
+  TieCut c;
+  const uint32_t mine = threadIdx.x < groups ? lists.count(p, threadIdx.x)[1] >> shift : 0u;
+  const uint32_t before = block_exclusive_scan<kSelThreads>(mine, scan, &c.all);
+  if (before < need && need <= before + mine) { sel[0] = threadIdx.x; sel[1] = need - before; }
+  if (threadIdx.x == q0) scan[0] = before;
+  __syncthreads();
+  c.group = __builtin_amdgcn_readfirstlane(sel[0]);
+  c.rest = __builtin_amdgcn_readfirstlane(sel[1]);
+  c.before = __builtin_amdgcn_readfirstlane(scan[0]);
+  __syncthreads();
+  return c;
+}
+// Ties (elements of key T) of [lo, hi), whole groups or up to the partition's end, are kept up to the index returned.
+__device__ __forceinline__ uint32_t tie_end(const PartValues &x, uint32_t T, const TieCut &c, uint32_t lo, uint32_t hi, uint32_t *scan, uint32_t *sel) {
+  static_assert(kGroupElems == 8 * kSelThreads, "eight elements a thread");
+  const uint32_t at = c.group * kGroupElems;
+  if (at < lo) return lo;
+  if (at >= hi) return hi;
+  const uint32_t j0 = at + threadIdx.x * 8;
+  const u32x4 a = x.at(j0), b = x.at(j0 + 4);
+  const uint32_t v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  uint32_t mask = 0;
+#pragma unroll
+  for (uint32_t e = 0; e < 8; ++e) mask |= (uint32_t)(j0 + e < x.d && (v[e] & 0x7fffffffu) == T) << e;
+  uint32_t all;
+  const uint32_t before = block_exclusive_scan<kSelThreads>((uint32_t)__popc(mask), scan, &all);
+  if (before < c.rest && c.rest <= before + (uint32_t)__popc(mask)) {
+    for (uint32_t skip = c.rest - before; skip > 1; --skip) mask &= mask - 1;
+    sel[0] = j0 + (uint32_t)__builtin_ctz(mask) + 1;
+  }
+  __syncthreads();
+  const uint32_t end = __builtin_amdgcn_readfirstlane(sel[0]);
+  __syncthreads();
+  return end;
+}
+// visit(j, bits) for the elements of key T in [lo, hi), lo a multiple of four.
+template <class VISIT>
+__device__ __forceinline__ void each_tie(const PartValues &x, uint32_t T, uint32_t lo, uint32_t hi, VISIT visit) {
+  constexpr uint32_t kAhead = 4;
+  for (uint32_t j0 = lo + threadIdx.x * 4; j0 < hi; j0 += kAhead * 4 * kSelThreads) {
+    u32x4 r[kAhead];
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q) r[q] = x.at(j0 + q * 4 * kSelThreads);
+#pragma unroll
+    for (uint32_t q = 0; q < kAhead; ++q) {
+      const uint32_t v[4] = {r[q].x, r[q].y, r[q].z, r[q].w}, j = j0 + q * 4 * kSelThreads;
+#pragma unroll
+      for (uint32_t e = 0; e < 4; ++e)
+        if (j + e < hi && (v[e] & 0x7fffffffu) == T) visit(j + e, v[e]);
+    }
+  }
+}
+
+// The bits before every word of the bitmap, in l.before; the sum of the threads' `below` (at most kTopkListCap, as
+// the number of bits).
+__device__ __forceinline__ uint32_t bits_before_words(SelectLds &l, uint32_t words, uint32_t below) {
+  // bits before each word: thread t owns words per * t .. per * t + per - 1
+  const uint32_t per = 4 * (uint32_t)cdiv(words, 4 * kSelThreads);
+  uint32_t set = 0;
+  for (uint32_t q = 0; q < per; q += 4) {
+    const uint32_t w = threadIdx.x * per + q;
+    if (w < words) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);   // (past the last word: zeros up to the multiple of 4)
+      set += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
+    }
+  }
+  // (one scan for both: each total is at most kTopkListCap)
+  const uint32_t both = set | below << 16, incl = wave_inclusive_scan_u32(both), wave = threadIdx.x >> 6;
+  if ((threadIdx.x & 63) == 63) l.scan[1][wave] = incl;
+  __syncthreads();
+  uint32_t all = 0, at = incl - both;
+#pragma unroll
+  for (uint32_t w = 0; w < kSelThreads / 64; ++w) {
+    const uint32_t x = l.scan[1][w];
+    at += w < wave ? x : 0u;
+    all += x;
+  }
+  at &= 0xffffu;
+  for (uint32_t q = 0; q < per; q += 4) {
+    const uint32_t w = threadIdx.x * per + q;
+    if (w < words) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);
+      const uint32_t a1 = at + (uint32_t)__popc(x.x), a2 = a1 + (uint32_t)__popc(x.y), a3 = a2 + (uint32_t)__popc(x.z);
+      *reinterpret_cast<uint2 *>(l.before + w) = make_uint2(at | a1 << 16, a2 | a3 << 16);
+      at = a3 + (uint32_t)__popc(x.w);
+    }
+  }
+  __syncthreads();
+  return all >> 16;
+}
+
+// A share of the select pass where ties of key T beside the list make its n entries up to k: all entries are kept, and
+// ties as far as they go; the share's indices are [lo, hi).  false if there are not enough of them.
+template <bool HALF>
+__device__ __forceinline__ bool select_with_ties(const Geo &g, uint32_t p, uint32_t share, uint32_t lo, uint32_t hi, uint32_t n, uint32_t k, uint32_t T,
+                                        float *buf, const void *values, int values16, uint32_t *state, const TopkLists &lists,
+                                        uint8_t *payload, int zero_selected, SelectLds &l) {
+  const TieCut cut = tie_cut(lists, p, (g.part_size(p) + kGroupElems - 1) / kGroupElems, k - n, lo / kGroupElems, l.scan[0], l.sel[0]);
+  if (cut.all < k - n) return false;
+  if (share == 0 && threadIdx.x == 0) state[p * 8 + kStLong] = kTiesBeside;
+  const PartValues x_of = part_values(g, p, buf, values, values16);
+  const uint32_t ties_to = tie_end(x_of, T, cut, lo, hi, l.scan[0], l.sel[0]);
+  const uint32_t words = (hi - lo + 31) / 32;
+  for (uint32_t w = threadIdx.x; w < (words + 3) / 4 * 4; w += kSelThreads) l.bitmap[w] = 0;
+  __syncthreads();
+  const uint32_t *idx = lists.idx(p), *val = lists.val(p);
+  uint32_t below = 0;
+  for (uint32_t e = threadIdx.x; e < n; e += kSelThreads) {
+    const uint32_t j = idx[e];
+    below += j < lo;
+    if (j >= lo && j < hi) atomicOr(&l.bitmap[(j - lo) >> 5], 1u << (j & 31u));
+  }
+  each_tie(x_of, T, lo, ties_to, [&](uint32_t j, uint32_t) { atomicOr(&l.bitmap[(j - lo) >> 5], 1u << (j & 31u)); });
+  __syncthreads();
+  const uint32_t pos0 = bits_before_words(l, words, below) + (cut.before < k - n ? cut.before : k - n);
+  uint8_t *rec = payload + (uint64_t)p * g.stride;
+  float *buf_part = zero_selected ? buf + g.part_base(p) : nullptr;
+  auto write = [&](uint32_t j, uint32_t bits) {
+    const uint32_t o = j - lo, w = o >> 5;
+    const uint32_t pos = pos0 + l.before[w] + (uint32_t)__popc(l.bitmap[w] & ((1u << (o & 31u)) - 1u));
+    topk_write_entry<HALF>(g, rec, pos, j, __uint_as_float(bits), buf_part, zero_selected);
+  };
+  each_tie(x_of, T, lo, ties_to, write);
+  __syncthreads();   // (a listed element's slot of the buffer, once zeroed, could pass for a tie)
+  for (uint32_t e = threadIdx.x; e < n; e += kSelThreads) {
+    const uint32_t j = idx[e];
+    if (j >= lo && j < hi) write(j, val[e]);
+  }
+  return true;
+}
+
 // Select pass.  `shares` workgroups take a partition: each keeps the whole list in registers and works out
 // which entries are kept, marks those of its share of the indices in a bitmap in LDS, and writes
 // them at the places that the bits before them give.  A list shorter than k or longer than its room
-// leaves the partition to the long form.  Bound by the vector instructions per entry (sixteen waves on
+// leaves the partition to the long form, unless ties beside it make it up to k: a share then reads its indices
+// of the vector as far as ties are kept.  Bound by the vector instructions per entry (sixteen waves on
 // one compute unit) and some twenty barriers.  (The form before this one took the list in index
 // order, run by run of the load pass's workgroups, through a table in LDS, with three radix levels
 // and the idle long form behind it: 28 against 19 us on 25 partitions of 1 M elements, k = 1 %; 23 against
 // 15.5 us on 53 partitions of 2 M f16 elements, k = 0.1 %.)
+struct ShareRanges { uint32_t list, ties; };   // indices a share takes: multiples of 32, and (with ties beside the list) of kGroupElems
 template <bool HALF>
 __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, float *buf, const void *values, int values16, uint32_t *state, TopkShared sh, TopkLists lists,
-                                                                       uint8_t *payload, int zero_selected, uint32_t shares) {
+                                                                       uint8_t *payload, int zero_selected, uint32_t shares, ShareRanges ranges) {
   __shared__ __align__(16) SelectLds l;
   static_assert(kSelPer <= 32 && kTopkListCap < 65536, "one bit an entry, 16 bits a place");
   // (workgroups go to the 8 XCDs in turn: the shares of a partition, which read the same list, to the same one)
@@ -1221,19 +1405,22 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   const uint32_t p = __builtin_amdgcn_readfirstlane(at_xcd / shares * kXcds + blockIdx.x % kXcds), share = __builtin_amdgcn_readfirstlane(at_xcd % shares);
   if (p >= g.P) return;
   const uint32_t d = g.part_size(p);
-  const uint32_t range = (uint32_t)cdiv(cdiv(g.part_size(0), shares), 32) * 32;
-  const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
   const uint32_t n = __builtin_amdgcn_readfirstlane(*sh.length(p));
+  const uint64_t pair = sh.pair(p)[0];
   // (the highest key is taken for the one below it: less a guess of 0, plus one, it would read as no entry, and a
   // threshold would be looked for among fewer than k of them)
   constexpr uint32_t kTopKey = kRelMask - 1;
-  const uint32_t guess = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(p)[0]), G = guess < kTopKey ? guess : kTopKey;
-  if (lo >= d) return;
+  const uint32_t guess = __builtin_amdgcn_readfirstlane((uint32_t)pair), G = guess < kTopKey ? guess : kTopKey;
   const uint32_t k = (uint32_t)k_of_device(g, p);
+  const bool beside = n < k && __builtin_amdgcn_readfirstlane((uint32_t)(pair >> 32)) != 0;   // ties of the key below the guess are kept
+  const uint32_t range = beside ? ranges.ties : ranges.list;
+  const uint32_t lo = share * range, hi = lo + range < d ? lo + range : d;
+  if (lo >= d) return;
   if (share == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, p, payload);
   if (n < k || n > kTopkListCap) {
+    if (beside && select_with_ties<HALF>(g, p, share, lo, hi, n, k, guess - 1u, buf, values, values16, state, lists, payload, zero_selected, l)) return;
     if (share != 0) return;
-    if (threadIdx.x == 0) state[p * 8 + kStLong] = 1;
+    if (threadIdx.x == 0) state[p * 8 + kStLong] = kLongForm;
     if (g.part_size(0) <= kAloneElems) topk_alone<HALF>(g, p, k, buf, values, values16, payload, zero_selected, l.h, l.scan[0], l.sel[0]);
     return;
   }
@@ -1288,39 +1475,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_list_select_kernel(Geo g, fl
   if (ties == r) mark([&](uint32_t x, uint32_t) { return x >= R; });
   else mark([&](uint32_t x, uint32_t j) { return x > R || (x == R && j <= last); });
   __syncthreads();
-  // bits before each word: thread t owns words per * t .. per * t + per - 1
-  const uint32_t per = 4 * (uint32_t)cdiv(words, 4 * kSelThreads);
-  uint32_t set = 0;
-  for (uint32_t q = 0; q < per; q += 4) {
-    const uint32_t w = threadIdx.x * per + q;
-    if (w < words) {
-      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);   // (past the last word: zeros up to the multiple of 4)
-      set += (uint32_t)(__popc(x.x) + __popc(x.y) + __popc(x.z) + __popc(x.w));
-    }
-  }
-  // (one scan for both: each total is at most kTopkListCap)
-  const uint32_t both = set | below << 16, incl = wave_inclusive_scan_u32(both), wave = threadIdx.x >> 6;
-  if ((threadIdx.x & 63) == 63) l.scan[1][wave] = incl;
-  __syncthreads();
-  uint32_t all = 0, at = incl - both;
-#pragma unroll
-  for (uint32_t w = 0; w < kSelThreads / 64; ++w) {
-    const uint32_t x = l.scan[1][w];
-    at += w < wave ? x : 0u;
-    all += x;
-  }
-  at &= 0xffffu;
-  for (uint32_t q = 0; q < per; q += 4) {
-    const uint32_t w = threadIdx.x * per + q;
-    if (w < words) {
-      const uint4 x = *reinterpret_cast<const uint4 *>(l.bitmap + w);
-      const uint32_t a1 = at + (uint32_t)__popc(x.x), a2 = a1 + (uint32_t)__popc(x.y), a3 = a2 + (uint32_t)__popc(x.z);
-      *reinterpret_cast<uint2 *>(l.before + w) = make_uint2(at | a1 << 16, a2 | a3 << 16);
-      at = a3 + (uint32_t)__popc(x.w);
-    }
-  }
-  __syncthreads();
-  const uint32_t pos0 = all >> 16;
+  const uint32_t pos0 = bits_before_words(l, words, below);
   uint8_t *rec = payload + (uint64_t)p * g.stride;
   float *buf_part = zero_selected ? buf + g.part_base(p) : nullptr;
   each_entry<kSelPer>(rounds, [&](auto i) {
@@ -1365,7 +1520,7 @@ struct EntriesOf {
   TopkVector vec;
   uint64_t at;
   uint32_t j0, v[4], j[4];
-  __device__ void load(uint32_t e0, uint32_t (&lv)[4], uint32_t (&lj)[4]) const {
+  __device__ __forceinline__ void load(uint32_t e0, uint32_t (&lv)[4], uint32_t (&lj)[4]) const {
     if (val) {
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
@@ -1382,9 +1537,9 @@ struct EntriesOf {
       }
     }
   }
-  __device__ void load_first() { load(first, v, j); }
+  __device__ __forceinline__ void load_first() { load(first, v, j); }
   template <class VISIT>
-  __device__ void each(VISIT visit) const {
+  __device__ __forceinline__ void each(VISIT visit) const {
     auto one = [&](uint32_t e, uint32_t x, uint32_t y) {
       const uint32_t key = x & 0x7fffffffu;
       if (e < n && key >= G) visit(key - G, x, y);
@@ -1401,7 +1556,7 @@ struct EntriesOf {
 };
 // The entries of the wave's group, number q of the workgroup's range (none past its end).
 template <bool IDX>
-__device__ inline EntriesOf<128, IDX> entries_of_group(const Geo &g, const TopkLists &lists, const GroupRange &w, uint32_t q, uint32_t G,
+__device__ __forceinline__ EntriesOf<128, IDX> entries_of_group(const Geo &g, const TopkLists &lists, const GroupRange &w, uint32_t q, uint32_t G,
                                                        const TopkVector &vec) {
   EntriesOf<128, IDX> e{};
   e.first = threadIdx.x & 127;
@@ -1443,9 +1598,9 @@ __global__ __launch_bounds__(kSelThreads) void topk_bins_kernel(Geo g, uint32_t 
   if (h[threadIdx.x]) atomicAdd(&hist[(uint64_t)w.p * kTopkHistWords + threadIdx.x], h[threadIdx.x]);
 }
 
-// The bin of the k-th largest key of a partition in sel[0], the rank left in it in sel[1]; false if the
-// lists hold fewer than k.
-__device__ inline bool near_bin_of_k(const uint32_t *bins, uint32_t k, uint32_t *scan, uint32_t *sel) {
+// The bin of the k-th largest key of a partition in sel[0], the rank left in it in sel[1] (neither if the lists
+// hold fewer than k); how many they hold.
+__device__ __forceinline__ uint32_t near_bin_of_k(const uint32_t *bins, uint32_t k, uint32_t *scan, uint32_t *sel) {
   static_assert(kNearBins == kSelThreads, "a bin a thread");
   const uint32_t mine = bins[kNearBins - 1 - threadIdx.x];
   uint32_t total;
@@ -1455,32 +1610,41 @@ __device__ inline bool near_bin_of_k(const uint32_t *bins, uint32_t k, uint32_t 
     sel[1] = k - above;
   }
   __syncthreads();
-  return total >= k;
+  return total;
 }
 
 __global__ __launch_bounds__(kSelThreads) void topk_collect_kernel(Geo g, uint32_t *hist, TopkShared sh, TopkLists lists, TopkVector vec) {
-  __shared__ uint32_t scan[kSelThreads / 64], sel[2], sure[kRangeGroups], near, at;
+  __shared__ uint32_t scan[kSelThreads / 64], sel[2], sure[kRangeGroups], near, at, ends[2];
   const GroupRange w(g, lists);
   if (w.q0 >= w.q1) return;
   uint32_t *bins = hist + (uint64_t)w.p * kTopkHistWords;
   const uint32_t k = (uint32_t)k_of_device(g, w.p);
   if (threadIdx.x < kRangeGroups) sure[threadIdx.x] = 0;
-  if (threadIdx.x == 0) near = 0;
-  if (!near_bin_of_k(bins, k, scan, sel)) return;   // (left to the long form: the next kernel finds out by itself)
+  if (threadIdx.x == 0) { near = 0; ends[0] = 0; ends[1] = 0; }
+  if (near_bin_of_k(bins, k, scan, sel) < k) return;   // (ties beside the lists, or the long form: the next kernel finds out by itself)
   const uint32_t bin = sel[0], slot = __builtin_amdgcn_readfirstlane(threadIdx.x >> 7), q = w.q0 + slot;
   const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(w.p)[0]);
   const auto mine = entries_of_group<true>(g, lists, w, q, G, vec);
-  uint32_t above = 0, inside = 0;
+  uint32_t above = 0, inside = 0, most = 0, least = 0;   // (of the keys inside, one more than the highest; not the lowest)
   mine.each([&](uint32_t rel, uint32_t, uint32_t) {
     const uint32_t b = near_bin(rel);
     above += b > bin;
     inside += b == bin;
+    if (b == bin) {
+      most = most > rel + 1 ? most : rel + 1;
+      least = least > ~rel ? least : ~rel;
+    }
   });
-  above = wave_sum_u32(above);
-  if ((threadIdx.x & 63) == 0 && above) atomicAdd(&sure[slot], above);
+  if (inside) {   // (few threads' business, unless keys are equal)
+    atomicMax(&ends[0], most);
+    atomicMax(&ends[1], least);
+  }
+  const uint32_t both = wave_sum_u32(above | inside << 16);   // (a group has 8192 elements)
+  if ((threadIdx.x & 63) == 0 && both) atomicAdd(&sure[slot], both);
   uint32_t place = inside ? atomicAdd(&near, inside) : 0u;
   __syncthreads();
   if (threadIdx.x == 0) at = near ? atomicAdd(&bins[kNearBins], near) : 0u;
+  if (threadIdx.x < 2 && near) atomicMax(&bins[kNearBins + 1 + threadIdx.x], ends[threadIdx.x]);
   if (q < w.q1 && (threadIdx.x & 127) == 0) lists.count(w.p, q)[1] = sure[slot];
   __syncthreads();
   place += at;
@@ -1495,6 +1659,57 @@ __global__ __launch_bounds__(kSelThreads) void topk_collect_kernel(Geo g, uint32
   }
 }
 
+constexpr uint32_t kRangeWords = kRangeGroups * kGroupElems / 32;   // of a workgroup's bitmap
+static_assert(kRangeWords == 2 * kSelThreads, "two words of the bitmap a thread");
+// The bits before every word of the bitmap, in `before`; the sum of the threads' `below`.
+__device__ __forceinline__ uint32_t range_bits_before(const uint32_t *bitmap, uint16_t *before, uint32_t below, uint32_t *scan) {
+  const uint32_t w0 = bitmap[2 * threadIdx.x], w1 = bitmap[2 * threadIdx.x + 1], c0 = (uint32_t)__popc(w0);
+  uint32_t all, all_below;
+  const uint32_t at = block_exclusive_scan<kSelThreads>(c0 + (uint32_t)__popc(w1), scan, &all);
+  block_exclusive_scan<kSelThreads>(below, scan, &all_below);
+  before[2 * threadIdx.x] = (uint16_t)at;
+  before[2 * threadIdx.x + 1] = (uint16_t)(at + c0);
+  __syncthreads();
+  return all_below;
+}
+
+// Emit pass of the group-list form where ties of the key below the guess, beside the lists, make their `listed` entries up
+// to k: a workgroup writes all entries of its groups, and its ties as far as they go.  false if there are not enough.
+template <bool HALF>
+__device__ __forceinline__ bool emit_with_ties(const Geo &g, const GroupRange &w, uint32_t k, uint32_t listed, uint32_t G, float *buf, const TopkVector &vec,
+                                      uint32_t *state, const TopkLists &lists, uint8_t *payload, int zero_selected, uint32_t *bitmap,
+                                      uint16_t *before, uint32_t *scan, uint32_t *sel) {
+  const uint32_t need = k - listed;
+  const TieCut cut = tie_cut(lists, w.p, (w.d + kGroupElems - 1) / kGroupElems, need, w.q0, scan, sel);
+  if (cut.all < need) return false;
+  if (w.q0 == 0 && threadIdx.x == 0) state[w.p * 8 + kStLong] = kTiesBeside;
+  const uint32_t lo = w.q0 * kGroupElems, hi = w.q1 * kGroupElems < w.d ? w.q1 * kGroupElems : w.d;
+  const PartValues x_of = part_values(g, w.p, buf, vec.at, vec.half);
+  const uint32_t ties_to = tie_end(x_of, G - 1u, cut, lo, hi, scan, sel);
+  const auto mine = entries_of_group<true>(g, lists, w, __builtin_amdgcn_readfirstlane(w.q0 + (threadIdx.x >> 7)), G, vec);
+  uint32_t below = threadIdx.x == 0 ? (cut.before < need ? cut.before : need) : 0u;
+  for (uint32_t b = threadIdx.x; b < w.q0; b += kSelThreads) below += lists.count(w.p, b)[0];
+  bitmap[2 * threadIdx.x] = 0;
+  bitmap[2 * threadIdx.x + 1] = 0;
+  __syncthreads();
+  auto mark = [&](uint32_t j) { atomicOr(&bitmap[(j - lo) >> 5], 1u << (j & 31u)); };
+  mine.each([&](uint32_t, uint32_t, uint32_t j) { mark(j); });
+  each_tie(x_of, G - 1u, lo, ties_to, [&](uint32_t j, uint32_t) { mark(j); });
+  __syncthreads();
+  const uint32_t all_below = range_bits_before(bitmap, before, below, scan);
+  uint8_t *rec = payload + (uint64_t)w.p * g.stride;
+  float *buf_part = zero_selected ? buf + g.part_base(w.p) : nullptr;
+  auto write = [&](uint32_t j, uint32_t v) {
+    const uint32_t o = j - lo, word = o >> 5;
+    const uint32_t pos = all_below + before[word] + (uint32_t)__popc(bitmap[word] & ((1u << (o & 31u)) - 1u));
+    topk_write_entry<HALF>(g, rec, pos, j, __uint_as_float(v), buf_part, zero_selected);
+  };
+  each_tie(x_of, G - 1u, lo, ties_to, write);
+  __syncthreads();   // (a listed element's slot of the buffer, once zeroed, could pass for a tie)
+  mine.each([&](uint32_t, uint32_t v, uint32_t j) { write(j, v); });
+  return true;
+}
+
 // Emit pass of the group-list form.  The form in all, against the long form that these k took before (worker
 // calls): 20 M f16 elements, k = 1 %, 77 against 122 us (load 44, bins 5, collect 6.5, emit 20); 100 M, k =
 // 3 %, 328 against 566; 0.3 M 31 against 36.  (One workgroup a partition over lists that long, as in the
@@ -1503,27 +1718,38 @@ template <bool HALF>
 __global__ __launch_bounds__(kSelThreads) void topk_group_emit_kernel(Geo g, float *buf, TopkVector vec, uint32_t *state,
                                                                       const uint32_t *hist, TopkShared sh, TopkLists lists, uint8_t *payload,
                                                                       int zero_selected) {
-  constexpr uint32_t kWords = kRangeGroups * kGroupElems / 32;
   __shared__ __align__(16) uint32_t h[2048];
-  __shared__ uint32_t bitmap[kWords];
-  __shared__ uint16_t before[kWords];
+  __shared__ uint32_t bitmap[kRangeWords];
+  __shared__ uint16_t before[kRangeWords];
   __shared__ uint32_t scan[kSelThreads / 64], sel[2];
-  static_assert(kWords == 2 * kSelThreads && kBins1 <= 2048, "two words of the bitmap a thread");
+  static_assert(kBins1 <= 2048, "h holds the bins of a level");
   const GroupRange w(g, lists);
   if (w.q0 >= w.q1) return;
   const uint32_t *bins = hist + (uint64_t)w.p * kTopkHistWords;
   const uint32_t k = (uint32_t)k_of_device(g, w.p);
   if (w.q0 == 0 && threadIdx.x == 0) topk_write_header<HALF>(g, w.p, payload);
-  const uint32_t near = __builtin_amdgcn_readfirstlane(bins[kNearBins]);
-  if (!near_bin_of_k(bins, k, scan, sel) || near > TopkLists::kNearCap) {
+  uint32_t near = __builtin_amdgcn_readfirstlane(bins[kNearBins]);
+  const uint32_t most = __builtin_amdgcn_readfirstlane(bins[kNearBins + 1]), least = __builtin_amdgcn_readfirstlane(bins[kNearBins + 2]);
+  const uint32_t listed = near_bin_of_k(bins, k, scan, sel), bin = sel[0];
+  uint32_t rem = sel[1];
+  const uint64_t pair = sh.pair(w.p)[0];
+  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)pair);
+  const bool beside = listed < k && __builtin_amdgcn_readfirstlane((uint32_t)(pair >> 32)) != 0;   // ties of the key below the guess are kept
+  // many entries in the threshold's bin (more, maybe, than their list has room for), but all of one key: that is the
+  // threshold, and its ties are dealt with as those beside a list
+  const bool one_key = listed >= k && near > kFewNear && most - 1u == ~least;
+  if (listed < k || (near > TopkLists::kNearCap && !one_key)) {
+    if (beside && emit_with_ties<HALF>(g, w, k, listed, G, buf, vec, state, lists, payload, zero_selected, bitmap, before, scan, sel)) return;
     if (w.q0 != 0) return;
-    if (threadIdx.x == 0) state[w.p * 8 + kStLong] = 1;
+    if (threadIdx.x == 0) state[w.p * 8 + kStLong] = kLongForm;
     topk_alone<HALF>(g, w.p, k, buf, vec.at, vec.half, payload, zero_selected, h, scan, sel);
     return;
   }
-  const uint32_t bin = sel[0];
-  uint32_t rem = sel[1];
-  const uint32_t G = __builtin_amdgcn_readfirstlane((uint32_t)sh.pair(w.p)[0]);
+  TieCut cut{};
+  if (one_key) {
+    cut = tie_cut(lists, w.p, (w.d + kGroupElems - 1) / kGroupElems, rem, w.q0, scan, sel, 16);
+    near = 0;
+  }
   EntriesOf<kSelThreads, true> near_ones{lists.idx(w.p), lists.val(w.p), threadIdx.x, near, G};
   near_ones.load_first();
   auto each_near = [&](auto visit) { near_ones.each([&](uint32_t rel, uint32_t, uint32_t j) { visit(rel, j); }); };
@@ -1531,49 +1757,58 @@ __global__ __launch_bounds__(kSelThreads) void topk_group_emit_kernel(Geo g, flo
   const auto mine = entries_of_group<true>(g, lists, w, q, G, vec);
   // the threshold inside the bin (less than 2^26 keys: 6 + 10 + 10 bits), then, among ties, the index of the last
   // one kept
-  const uint32_t start = near_start(bin), width = near_start(bin + 1) - start;
-  uint32_t R = 0, ties = 0;
+  uint32_t R = 0, last = 0xffffffffu;
+  if (!one_key) {
+    const uint32_t start = near_start(bin), width = near_start(bin + 1) - start;
+    uint32_t ties = 0;
 #pragma unroll 1
-  for (int shift = width > 1u << 20 ? 20 : width > 1u << 10 ? 10 : 0; shift >= 0; shift -= 10) {
-    const uint32_t prefix = R;
-    __syncthreads();
-    h[threadIdx.x] = 0;
-    __syncthreads();
-    each_near([&](uint32_t rel, uint32_t) {
-      if (((rel - start) >> shift >> 10) == prefix) atomicAdd(&h[((rel - start) >> shift) & 1023u], 1u);
-    });
-    __syncthreads();
-    pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
-    R = sel[0];
-    rem = sel[1];
-    ties = h[sel[0] & 1023u];
-  }
-  R += start;
-  uint32_t last = 0xffffffffu;
-  if (ties != rem) {   // (uniform) the rem-th of the ties in index order (indices below 2^28: 10 + 10 + 8 bits)
-    uint32_t prefix = 0;
-    rem = ties - rem + 1;   // (pick_bin counts from the largest down)
-#pragma unroll 1
-    for (int level = 0; level < 3; ++level) {
-      const int hi_shift = level == 0 ? 28 : level == 1 ? 18 : 8, lo_shift = level == 0 ? 18 : level == 1 ? 8 : 0;
+    for (int shift = width > 1u << 20 ? 20 : width > 1u << 10 ? 10 : 0; shift >= 0; shift -= 10) {
+      const uint32_t prefix = R;
       __syncthreads();
       h[threadIdx.x] = 0;
       __syncthreads();
-      each_near([&](uint32_t rel, uint32_t j) {
-        if (rel == R && (j >> hi_shift) == prefix) atomicAdd(&h[(j >> lo_shift) & (level == 2 ? 255u : 1023u)], 1u);
+      each_near([&](uint32_t rel, uint32_t) {
+        if (((rel - start) >> shift >> 10) == prefix) atomicAdd(&h[((rel - start) >> shift) & 1023u], 1u);
       });
       __syncthreads();
-      if (level == 2) pick_bin<256, 8, kSelThreads>(h, rem, prefix, scan, sel);
-      else pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
-      prefix = sel[0];
+      pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
+      R = sel[0];
       rem = sel[1];
+      ties = h[sel[0] & 1023u];
     }
-    last = prefix;
+    R += start;
+    if (ties != rem) {   // (uniform) the rem-th of the ties in index order (indices below 2^28: 10 + 10 + 8 bits)
+      uint32_t prefix = 0;
+      rem = ties - rem + 1;   // (pick_bin counts from the largest down)
+#pragma unroll 1
+      for (int level = 0; level < 3; ++level) {
+        const int hi_shift = level == 0 ? 28 : level == 1 ? 18 : 8, lo_shift = level == 0 ? 18 : level == 1 ? 8 : 0;
+        __syncthreads();
+        h[threadIdx.x] = 0;
+        __syncthreads();
+        each_near([&](uint32_t rel, uint32_t j) {
+          if (rel == R && (j >> hi_shift) == prefix) atomicAdd(&h[(j >> lo_shift) & (level == 2 ? 255u : 1023u)], 1u);
+        });
+        __syncthreads();
+        if (level == 2) pick_bin<256, 8, kSelThreads>(h, rem, prefix, scan, sel);
+        else pick_bin<1024, 10, kSelThreads>(h, rem, prefix, scan, sel);
+        prefix = sel[0];
+        rem = sel[1];
+      }
+      last = prefix;
+    }
   }
   // kept entries of the groups before the workgroup's: those above the bin, and those inside it
   const uint32_t lo = w.q0 * kGroupElems;
   uint32_t below = 0;
-  for (uint32_t b = threadIdx.x; b < w.q0; b += kSelThreads) below += lists.count(w.p, b)[1];
+  if (one_key) {
+    const uint32_t hi = w.q1 * kGroupElems < w.d ? w.q1 * kGroupElems : w.d;
+    R = most - 1u;
+    // (the index after the last tie kept is 0 for no workgroup: the first one's group has some, or a later one)
+    last = tie_end(part_values(g, w.p, buf, vec.at, vec.half), G + R, cut, lo, hi, scan, sel) - 1u;
+    if (threadIdx.x == 0) below = cut.before < rem ? cut.before : rem;
+  }
+  for (uint32_t b = threadIdx.x; b < w.q0; b += kSelThreads) below += lists.count(w.p, b)[1] & 0xffffu;
   each_near([&](uint32_t rel, uint32_t j) { below += j < lo && (rel > R || (rel == R && j <= last)); });
   bitmap[2 * threadIdx.x] = 0;
   bitmap[2 * threadIdx.x + 1] = 0;
@@ -1582,13 +1817,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_group_emit_kernel(Geo g, flo
     if (rel > R || (rel == R && j <= last)) atomicOr(&bitmap[(j - lo) >> 5], 1u << (j & 31u));
   });
   __syncthreads();
-  const uint32_t w0 = bitmap[2 * threadIdx.x], w1 = bitmap[2 * threadIdx.x + 1], c0 = (uint32_t)__popc(w0);
-  uint32_t all, all_below;
-  const uint32_t at = block_exclusive_scan<kSelThreads>(c0 + (uint32_t)__popc(w1), scan, &all);
-  block_exclusive_scan<kSelThreads>(below, scan, &all_below);
-  before[2 * threadIdx.x] = (uint16_t)at;
-  before[2 * threadIdx.x + 1] = (uint16_t)(at + c0);
-  __syncthreads();
+  const uint32_t all_below = range_bits_before(bitmap, before, below, scan);
   uint8_t *rec = payload + (uint64_t)w.p * g.stride;
   float *buf_part = zero_selected ? buf + g.part_base(w.p) : nullptr;
   mine.each([&](uint32_t rel, uint32_t v, uint32_t j) {
@@ -1728,7 +1957,7 @@ __global__ __launch_bounds__(kThreads) void topk_long_form_kernel(Geo g, float *
   if (threadIdx.x == 0) any = 0;
   __syncthreads();
   for (uint32_t p = threadIdx.x; p < g.P; p += kThreads)
-    if (state[p * 8 + kStLong]) any = 1;
+    if (state[p * 8 + kStLong] == kLongForm) any = 1;
   __syncthreads();
   if (!any) return;   // (the same answer in every workgroup: the flags were written by the kernel before)
   topk_hist_body<1>(g, buf, hist, state, n3, 1);   // (groups of one tile, as level 3)
@@ -1837,8 +2066,9 @@ hipError_t topk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_t
     while (shares < kMostShares && 2 * shares * of_xcd <= kCusOfXcd) shares *= 2;
     const uint32_t least = (uint32_t)cdiv(most, 32ull * kShareWords);
     if (shares < least) shares = least;
-    if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);
-    else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares);
+    const ShareRanges ranges{(uint32_t)cdiv(cdiv(most, shares), 32) * 32, (uint32_t)cdiv(cdiv(most, kGroupElems), shares) * kGroupElems};
+    if (half) topk_list_select_kernel<true><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares, ranges);
+    else topk_list_select_kernel<false><<<of_xcd * shares * kXcds, kSelThreads, 0, stream>>>(g, buf, src.grad, src.dtype == BPC_F16, state, sh, lists, payload, zero_selected, shares, ranges);
     if (!gated) return hipGetLastError();
   }
   const uint32_t n2 = group_count(g, kTpgHist2), n3 = group_count(g, kTpgHist3), nc = group_count(g, kTpgCount);

@@ -1,6 +1,6 @@
 // The top-k passes without the workgroups that are there for the guesses (BPC_TOPK_FIRST_GUESS), as if
-// something else on the device kept them from running: every guess is then made by a workgroup that waited
-// for it.  Built by __graft_entry__.build(), used by test_gpu_late_guess.py.
+// something else on the device kept them from running: workgroups that have waited leave every partition to the
+// long form.  Built by __graft_entry__.build(), used by test_gpu_late_guess.py.
 #define BPC_TOPK_FIRST_GUESS 0
 #define bpc bpc_late
 #include "../paper_2105_07829_amd/csrc/cluster.hip"

@@ -1,7 +1,8 @@
-"""Top-k calls whose guesses come late.  The workgroups of the load pass wait for the guess of the key that lists
+"""Top-k calls whose guesses do not come.  The workgroups of the load pass wait for the guess of the key that lists
 start from; the workgroup that is there to make it may be kept from running by another kernel that waits on
 another stream.  Here the passes are compiled without those workgroups (late_guess.hip), so that every
-guess is made by a workgroup that waited: the calls end, nothing gives up, and what they give is the oracle's."""
+partition is left to the long form by a workgroup that waited: the calls end, nothing gives up, and what they
+give is the oracle's."""
 import ctypes as C
 import os
 
@@ -37,7 +38,7 @@ def late():
                                              ("topk", np.float32, True, 3), ("topk16", np.float32, False, 2)])
 @pytest.mark.parametrize("pe,D,ratio", [(8192, 5000, 0.02), (65536, 40 * 65536 + 777, 0.01), (1_048_576, 2 * 1_048_576 + 70_001, 0.01),
                                         (1_048_576, 1_048_576 + 8192 * 9 + 1, 0.03), (8_388_608, 8_388_608 + 5001, 0.001)])
-def test_guesses_made_by_workgroups_that_waited(gu, orc, late, kind, dtype, ef, n, pe, D, ratio):
+def test_calls_whose_guesses_do_not_come(gu, orc, late, kind, dtype, ef, n, pe, D, ratio):
     import torch
     bpc = gu.bpc
     po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)

@@ -105,3 +105,73 @@ def test_topk_on_either_side_of_what_a_list_holds(gu, orc, geo, kind, dtype, ef,
         assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
     same_records(orc, po, kind, gu.to_host(pay), ref, pe, D, ratio)
     assert not state_words(gu, geo, pb, D, ws).any()
+
+
+def few_magnitudes(what, D, rs, k, pe):
+    """Vectors of which more elements share one key than a list has room for, and that key decides what is kept."""
+    v = np.where(rs.random(D) < 0.5, -0.75, 0.75).astype(np.float32)
+    if what == "zeros":
+        v[:] = 0.0
+        v[::7] = -0.0
+    elif what == "sixteen":
+        v = (rs.integers(1, 17, D) * 0.0625 * rs.choice([-1.0, 1.0], D)).astype(np.float32)
+    elif what == "rows":      # of 64 elements, few of them touched: fewer non-zeros than k
+        v = np.where(np.repeat(rs.random(-(-D // 64)) < 0.4 * k / pe, 64)[:D], rs.standard_normal(D), 0.0).astype(np.float32)
+    elif what == "below":      # the deciding key is met well before the sample's rank: its elements are listed with lower ones
+        v = np.where(rs.random(D) < 1.25 * k / pe, 0.5, 0.25).astype(np.float32) * rs.choice(np.float32([-1.0, 1.0]), D)
+        v[rs.choice(D, 50, replace=False)] = 2.0
+    elif what == "group end":  # the last of the k is the last element of a group, with larger ones before and behind
+        larger = min(k // 2, 100)
+        v[:] = 0.25
+        at = (k // 8192 + 1) * 8192
+        keep = rs.choice(at - 1, k - larger - 1, replace=False)
+        v[:at] = 0.125
+        v[keep] = 0.25
+        v[at - 1] = -0.25
+        v[rs.choice(np.setdiff1d(np.arange(at + 8192), np.append(keep, at - 1)), larger, replace=False)] = 3.0
+    return v
+
+
+@pytest.mark.parametrize("kind,dtype,ef", [("topk", np.float32, True), ("topk16", np.float16, True), ("topk", np.float16, False), ("topk16", np.float32, False)])
+@pytest.mark.parametrize("pe,D,ratio", [(65536, 3 * 65536 + 40_777, 0.01), (1 << 20, (1 << 20) + 300_007, 0.01), (1 << 21, (1 << 21) + 9, 0.001),
+                                        (1 << 20, (1 << 20) + 300_007, 0.03), (1 << 19, (1 << 19) + 8192 * 5, 0.0625), (1 << 23, 1 << 23, 0.0005)])
+@pytest.mark.parametrize("what", ["equal", "zeros", "sixteen", "rows", "below", "group end"])
+def test_topk_ties_beside_the_lists(gu, orc, geo, kind, dtype, ef, pe, D, ratio, what):
+    """One list a partition and a list a group, partitions of one share of the select pass and of several, of more than 4 M
+    elements; the same vector twice, so that the second call starts from what the first left in the workspace."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
+    rs = np.random.default_rng(D)
+    v = few_magnitudes(what, D, rs, int(ratio * pe), pe).astype(dtype)
+    ref_res = np.zeros(D, np.float32) if ef else None
+    ref = orc.compress(po, v, ref_res)
+    g, ws = gu.to_dev(v), gu.new_ws(pb, D)
+    ws.fill_(0xFF)
+    for _ in range(2):
+        rd, pay = gu.to_dev(np.zeros(D, np.float32)) if ef else None, gu.new_payload(pb, D)
+        bpc.bpc_compress(pb, g, rd, pay, ws)
+        bpc.workspace_check(pb, D, ws)
+        same_records(orc, po, kind, gu.to_host(pay), ref, pe, D, ratio)
+        if ef:
+            assert np.array_equal(gu.to_host(rd).view(np.uint32), ref_res.view(np.uint32))
+        # kept beside the list or lists, or on them; not left to the long form
+        assert state_words(gu, geo, pb, D, ws)[0] in ((0, 2) if what in ("sixteen", "below") else (2,))
+
+
+@pytest.mark.parametrize("pe,D,ratio", [(1 << 20, (1 << 20) + 300_007, 0.01), (1 << 20, (1 << 20) + 300_007, 0.03), (1 << 23, 1 << 23, 0.0005)])
+@pytest.mark.parametrize("what", ["equal", "zeros", "sixteen"])
+def test_topk_server_ties_beside_the_lists(gu, orc, geo, pe, D, ratio, what):
+    """Delta of few magnitudes: two messages whose entries cancel, and the residual."""
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, "topk", pe, k_ratio=ratio)
+    rs = np.random.default_rng(D)
+    g = rs.standard_normal(D).astype(np.float32)
+    msgs = [orc.compress(po, s * g, None) for s in (np.float32(1.0), np.float32(-1.0))]
+    res = few_magnitudes(what, D, rs, int(ratio * pe), pe)
+    rd, pay, ws = gu.to_dev(res), gu.new_payload(pb, D), gu.new_ws(pb, D, 2)
+    bpc.bpc_server_aggregate([pb] * 2, [gu.to_dev(m) for m in msgs], pb, rd, D, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    ref = orc.server_aggregate([po] * 2, msgs, po, res, D)
+    assert np.array_equal(gu.to_host(rd).view(np.uint32), res.view(np.uint32))
+    same_records(orc, po, "topk", gu.to_host(pay), ref, pe, D, ratio)
+    assert state_words(gu, geo, pb, D, ws)[0] == 2
