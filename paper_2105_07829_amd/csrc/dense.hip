@@ -137,14 +137,13 @@ __global__ __launch_bounds__(kThreads) void decode_randk_kernel(Geo g, const uin
 
 // bpc_decompress() of the sparse kinds in one launch: a workgroup lays the entries of its stretch of the output
 // out in LDS and writes the stretch as whole lines.  (A zero fill and a scatter behind it, each entry a
-// 4-byte store or a float atomic at a random place: random-k, 138 M f32 elements, k = 1 %: 218 us, 90 so,
+// 4-byte store or a float atomic at a random place: random-k, 138 M f32 elements, k = 1 %: 222 us, 93 so,
 // of which writing the output is 89; top-k, 100 M f16 elements, k = 3 %: 178 and 68 us.)
 
-// Top-k: the entries of a stretch of kDecodeTile elements are one stretch of the record, found by a search.
-// HALF: the values are halves.
-constexpr int kDecodeThreads = 512;
-constexpr uint32_t kDecodeTile = 8192;
-template <bool HALF>
+// Top-k: the entries of a stretch of the output are one stretch of the record, found by a search.
+// HALF: the values are halves.  Stretches of 8192 elements; of 1024 where partitions are that small (16 M elements
+// in partitions of 1024 / 2048, k = 1 %: 33 -> 14 / 20 -> 14 us, fill and scatter 24 / 20).
+template <bool HALF, uint32_t kDecodeTile, int kDecodeThreads>
 __global__ __launch_bounds__(kDecodeThreads) void decode_topk_tile_kernel(Geo g, uint32_t tiles, const uint8_t *payload, float *out) {
   __shared__ __align__(16) float acc[kDecodeTile];
   __shared__ uint32_t ends[2];
@@ -178,11 +177,10 @@ __global__ __launch_bounds__(kDecodeThreads) void decode_topk_tile_kernel(Geo g,
 }
 
 // Random-k: a workgroup draws all of its partition's indices again and keeps those of its stretch.  Repeated
-// indices add equal values, so the order of the adds does not matter.  (One large workgroup a compute unit:
-// with stretches of 16384 elements, two workgroups, every draw is made twice as often: k = 3 % 162
-// against 123 us, k = 1 % 89.6 against 90.8.)
-constexpr int kDrawThreads = 1024;
-constexpr uint32_t kDrawTile = 32768;
+// indices add equal values, so the order of the adds does not matter.  Small stretches where there are few draws (many
+// workgroups a compute unit: one clears its LDS while another stores), large ones where there are many, and
+// fill and scatter where drawing again takes longer than both: randk_decode_form().
+template <uint32_t kDrawTile, int kDrawThreads>
 __global__ __launch_bounds__(kDrawThreads) void decode_randk_tile_kernel(Geo g, uint32_t tiles, const uint8_t *payload, float *out,
                                                                          float value_scale, uint64_t seed, uint64_t stream_id) {
   __shared__ __align__(16) float acc[kDrawTile];
@@ -255,16 +253,34 @@ hipError_t scatter_add_randk(const Geo &g, const bpc_params_t &prm, const uint8_
 
 hipError_t decode_dense(const Geo &g, const bpc_params_t &prm, const uint8_t *payload, float *out,
                         hipStream_t stream) {
+  const uint32_t most = g.part_size(0);   // elements of the largest partition
   if (prm.kind == BPC_TOPK || prm.kind == BPC_TOPK16) {
-    const uint32_t tiles = (uint32_t)cdiv(g.part_elems, kDecodeTile);
-    if (prm.kind == BPC_TOPK16) decode_topk_tile_kernel<true><<<g.P * tiles, kDecodeThreads, 0, stream>>>(g, tiles, payload, out);
-    else decode_topk_tile_kernel<false><<<g.P * tiles, kDecodeThreads, 0, stream>>>(g, tiles, payload, out);
-    return hipGetLastError();
+    auto decode = [&](auto tile, auto threads) {
+      constexpr uint32_t kDecodeTile = decltype(tile)::value;
+      constexpr int kDecodeThreads = decltype(threads)::value;
+      const uint32_t tiles = (uint32_t)cdiv(most, kDecodeTile);
+      if (prm.kind == BPC_TOPK16) decode_topk_tile_kernel<true, kDecodeTile, kDecodeThreads><<<g.P * tiles, kDecodeThreads, 0, stream>>>(g, tiles, payload, out);
+      else decode_topk_tile_kernel<false, kDecodeTile, kDecodeThreads><<<g.P * tiles, kDecodeThreads, 0, stream>>>(g, tiles, payload, out);
+      return hipGetLastError();
+    };
+    using std::integral_constant;
+    if (most <= 2048) return decode(integral_constant<uint32_t, 1024>{}, integral_constant<int, 128>{});
+    return decode(integral_constant<uint32_t, 8192>{}, integral_constant<int, 512>{});
   }
   if (prm.kind == BPC_RANDK) {
-    const uint32_t tiles = (uint32_t)cdiv(g.part_elems, kDrawTile);
-    decode_randk_tile_kernel<<<g.P * tiles, kDrawThreads, 0, stream>>>(g, tiles, payload, out, prm.value_scale, prm.seed, prm.stream_id);
-    return hipGetLastError();
+    auto decode = [&](auto tile, auto threads) {
+      constexpr uint32_t kDrawTile = decltype(tile)::value;
+      constexpr int kDrawThreads = decltype(threads)::value;
+      const uint32_t tiles = (uint32_t)cdiv(most, kDrawTile);
+      decode_randk_tile_kernel<kDrawTile, kDrawThreads><<<g.P * tiles, kDrawThreads, 0, stream>>>(g, tiles, payload, out, prm.value_scale, prm.seed, prm.stream_id);
+      return hipGetLastError();
+    };
+    using std::integral_constant;
+    const DrawForm form = randk_decode_form(g.P, most, k_rule(g.k_ratio, most));
+    if (form == kDrawsSmall) return decode(integral_constant<uint32_t, kSmallDrawTile>{}, integral_constant<int, kSmallDrawThreads>{});
+    if (form == kDrawsLarge) return decode(integral_constant<uint32_t, kLargeDrawTile>{}, integral_constant<int, kLargeDrawThreads>{});
+    const hipError_t e = fill_zero(out, sizeof(float) * g.D, stream);
+    return e != hipSuccess ? e : scatter_add_randk(g, prm, payload, out, stream);
   }
   const bool natural = prm.kind == BPC_NATDITHER;
   if (prm.kind == BPC_SIGN) decode_packed_kernel<BPC_SIGN><<<g.n_tiles, kThreads, 0, stream>>>(g, prm.levels, false, payload, out);

@@ -113,6 +113,27 @@ inline bool topk_list_fits(uint64_t k, uint32_t d) {
   return sqrt((double)kTopkListCap * m / d) - sqrt((double)k * m / d) >= 2.75;
 }
 
+// How bpc_decompress() lays a random-k message out: drawn again for every stretch of 4096 or of 32768 elements, or
+// by a zero fill and a scatter.  The draws of a stretch are those of its partition, so a call makes (stretches *
+// k) of them where the scatter makes k: what each costs beyond writing the output, in us, fitted to calls of
+// 0.3 M to 256 M elements.  Small / large / scatter, whole calls, k = 1 % unless stated: 16 M elements in partitions of
+// 1024 18 / 157 / 23 us, of 64 K 14 / 17 / 24, of 1 M 27 / 19 / 24, of 4 M 94 / 27 / 24, of 1 M with k = 0.1 %
+// 15 / 17 / 17, with k = 10 % 202 / 46 / 96; 1 M with k = 100 % 275 / 135 / 59; 256 M, one partition, - / 11 220 / 462.
+constexpr uint32_t kSmallDrawTile = 4096, kLargeDrawTile = 32768;
+constexpr int kSmallDrawThreads = 256, kLargeDrawThreads = 1024;
+enum DrawForm { kDrawsSmall, kDrawsLarge, kDrawsScattered };
+inline DrawForm randk_decode_form(uint64_t P, uint64_t d, uint64_t k) {   // P partitions of d elements at most
+  const double draws = (double)P * (double)k;
+  // the device's rate of draws (of many small workgroups, beside their stores), or, with few workgroups, a workgroup's
+  // rounds of four draws a thread one after the other
+  const double small = fmax(0.6e-6 * draws * (double)cdiv(d, kSmallDrawTile) - 0.5e-6 * (double)P * (double)d,
+                            0.26 * (double)cdiv(k, 4 * kSmallDrawThreads));
+  const double large = 2.5 + fmax(0.5e-6 * draws * (double)cdiv(d, kLargeDrawTile), 0.5 * (double)cdiv(k, 4 * kLargeDrawThreads));
+  const double scatter = 2.3 + 48e-6 * draws;
+  if (small <= large && small <= scatter) return kDrawsSmall;
+  return large <= scatter ? kDrawsLarge : kDrawsScattered;
+}
+
 // What the rows of workgroups (the second grid dimension) of the kernel in front of a top-k server's load pass
 // do for a partition.  Rows of sums: `slots` messages side by side, a thread searching one message for one of
 // `chunks` sampled chunks.  Rows of starts: eight entries a thread (and the end) of one message, or all of

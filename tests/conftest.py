@@ -37,6 +37,7 @@ def geo(tmp_path_factory):
                             ("geo_prep_rows", [C.c_uint32, C.c_uint32, C.c_uint32, C.c_int, C.c_void_p], None),
                             ("geo_sample_chunks", [C.c_uint32], C.c_uint32),
                             ("geo_topk_list_fits", [C.c_uint64, C.c_uint32], C.c_int),
+                            ("geo_randk_decode_form", [C.c_uint64, C.c_uint64, C.c_uint64], C.c_int),
                             ("geo_sample_rank", [C.c_uint64, C.c_uint32, C.c_uint32], C.c_uint32), ("geo_topk_list_cap", [], C.c_uint32)]:
         getattr(L, name).argtypes, getattr(L, name).restype = args, res
     return L

@@ -38,6 +38,7 @@ void geo_prep_rows(uint32_t n, uint32_t k_cap, uint32_t d, int guesses, uint32_t
   const uint32_t v[8] = {r.threads, r.slots, r.chunks, r.sums, r.messages, r.pieces, r.roles, r.starts};
   for (int i = 0; i < 8; ++i) out[i] = v[i];
 }
+int geo_randk_decode_form(uint64_t P, uint64_t d, uint64_t k) { return (int)bpc::randk_decode_form(P, d, k); }
 int geo_topk_list_fits(uint64_t k, uint32_t d) { return bpc::topk_list_fits(k, d); }
 uint32_t geo_sample_rank(uint64_t k, uint32_t m, uint32_t d) { return bpc::sample_rank(k, m, d, true); }
 uint32_t geo_topk_list_cap() { return bpc::kTopkListCap; }

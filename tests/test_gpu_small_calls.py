@@ -515,3 +515,24 @@ def test_bit_planes_in_the_single_pass_server(gu, orc, n, kw, ef):
         torch.cuda.synchronize()
         bpc.workspace_check(pb, D, ws)
         assert torch.equal(pay, pay1) and (not ef or torch.equal(rd, res1))
+
+
+# every form of the decode, on either side of its rules: partitions of 1024 to 4 M elements, few draws and many
+@pytest.mark.parametrize("kind,ratio,pe,D", [("topk", 0.02, 1024, 9 * 1024 + 77), ("topk16", 0.5, 2048, 5 * 2048 + 1025), ("topk", 0.01, 3072, 3072 + 2049),
+                                             ("randk", 0.01, 1024, 9 * 1024 + 77), ("randk", 0.01, 1 << 20, (1 << 20) + 4097), ("randk", 1.0, 5120, 3 * 5120 + 4095),
+                                             ("randk", 0.01, 1 << 20, 5 * (1 << 20) + 77), ("randk", 0.1, 1 << 18, 9 * (1 << 18) + 32769),
+                                             ("randk", 0.01, 1 << 22, 2 * (1 << 22) + 5), ("randk", 1.0, 1 << 20, (1 << 20) + 1), ("randk", 0.001, 1 << 26, 5_000_003)])
+def test_decompress_forms(gu, orc, kind, ratio, pe, D):
+    import torch
+    bpc = gu.bpc
+    po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio, seed=13, stream_id=6, value_scale=-1.0)
+    g = np.random.default_rng(D).standard_normal(D).astype(np.float32)
+    pay = orc.compress(po, g, None)
+    out = torch.full((D + 64,), 7.0, device=gu.DEV)
+    bpc.bpc_decompress(pb, gu.to_dev(pay), out[:D])
+    got, ref = gu.to_host(out), orc.decompress(po, pay, D)
+    assert np.all(got[D:] == 7.0)
+    if kind == "randk":   # (repeated draws add in any order)
+        assert np.allclose(got[:D], ref, rtol=1e-6, atol=1e-6 * np.abs(ref).max())
+    else:
+        assert np.array_equal(got[:D], ref)

@@ -120,3 +120,15 @@ def test_topk_lists_are_taken_where_they_fit(geo, k, d, fits):
     # (elements numbered from the largest)
     lengths = np.array([np.sort(rs.choice(d, m, replace=False))[rank - 1] + 1 for _ in range(200)])
     assert np.count_nonzero((lengths < k) | (lengths > cap)) <= 5
+
+
+@pytest.mark.parametrize("part,D,ratio,form", [(1024, 1 << 24, 0.001, 0), (1024, 1 << 24, 1.0, 0), (16_384, 1 << 24, 0.1, 0), (65_536, 1 << 24, 0.01, 0),
+                                               (1 << 20, 1 << 24, 0.001, 0), (1 << 20, 300_007, 0.01, 0), (1 << 20, 1 << 24, 0.01, 1), (1 << 20, 1 << 22, 0.01, 1), (1 << 20, 50_000_000, 0.001, 0),
+                                               (1 << 20, 138_357_544, 0.01, 1), (1 << 20, 1 << 24, 1.0, 1), (1 << 21, 1 << 24, 0.1, 1),
+                                               (1 << 22, 1 << 24, 0.01, 2), (1 << 22, 1 << 24, 1.0, 2), (1 << 26, 1 << 26, 0.01, 2), (1 << 28, 1 << 28, 0.01, 2),
+                                               (1 << 28, 1 << 28, 1.0, 2), (1 << 20, 1 << 20, 1.0, 2), (1 << 21, 1 << 21, 0.1, 2), (1 << 28, 300_007, 0.01, 0)])
+def test_form_of_the_random_k_decode(geo, part, D, ratio, form):
+    """The form that measured fastest (or within a few per cent of it) at these shapes: draws made again for
+    stretches of 4096 or 32768 elements, or a fill and a scatter where that would grow with the square of the partition."""
+    most = min(part, D)
+    assert geo.geo_randk_decode_form(-(-D // part), most, max(1, int(ratio * most))) == form
