@@ -592,7 +592,14 @@ hipError_t randk_encode(const Geo &g, const bpc_params_t &prm, const bpc_params_
       return hipGetLastError();
     }
     const RandkStream out{prm.seed, prm.stream_id, status};
-    if (randk_draws_again(g, g.n_tiles, 1, kThreads)) {
+    // A tile with more hits than its list has room for (k from a quarter of the partition on) makes the draws three
+    // times, some 0.6 us a round of 1024 of them; the launch in front then costs 4 us and 38 ns for 1000 draws
+    // more than it.  (0.3 M elements in partitions of 16384 / 32768, k = 100 %: 35 / 70 us so, 30 / 30 with that launch; 1 M in
+    // partitions of 8192: 23 and 67.)
+    const uint32_t d = g.part_size(0), tile = d < (uint32_t)kTile ? d : (uint32_t)kTile;
+    const double k = (double)k_rule(g.k_ratio, d);
+    const bool overrun = k * tile > 0.9 * kHitRoom * d, worth = !overrun || 0.6 * 3.0 / 1024 * k <= 4.0 + 38e-6 * k * g.P;
+    if (worth && randk_draws_again(g, g.n_tiles, 1, kThreads)) {
       if (src.dtype == BPC_F16)
         randk_tile_kernel<GradSource<__half>, true><<<g.n_tiles, kThreads, 0, stream>>>(
             g, GradSource<__half>{(const __half *)src.grad, src.residual}, buf, payload, prm.value_scale, nullptr, nullptr, out);

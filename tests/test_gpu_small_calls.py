@@ -405,14 +405,14 @@ def test_randk_small_and_large_calls(gu, orc, pe, D, ratio, n, dtype):
     for i in range(n):
         g = (rs.standard_normal(D) * 1e-2).astype(dtype)
         res = (rs.standard_normal(D) * 1e-3).astype(np.float32)
+        res0 = res.copy()
         rd, pay = gu.to_dev(res), gu.new_payload(prm[i][1], D)
         bpc.bpc_compress(prm[i][1], gu.to_dev(g), rd, pay, ws)
         bpc.workspace_check(prm[i][1], D, ws)
         ref = orc.compress(prm[i][0], g, res)
         pays.append(ref)
         _equal_randk(orc, prm[i][0], gu.to_host(pay), ref, pe, D, ratio, exact=True)
-        # (repeated draws: many differences of one element in any order)
-        assert close(gu.to_host(rd), res) if ratio < 0.5 else np.abs(gu.to_host(rd) - res).max() <= 1e-5 * max(1.0, 1.0 / ratio)
+        assert _randk_residual_close(g.astype(np.float32) + res0, gu.to_host(rd), res, pe, ratio)
     s = (rs.standard_normal(D) * 1e-3).astype(np.float32)
     sd, out = gu.to_dev(s), gu.new_payload(prm[n][1], D)
     bpc.bpc_server_aggregate([p[1] for p in prm[:n]], [gu.to_dev(p) for p in pays], prm[n][1], sd, D, out, ws)
@@ -429,6 +429,37 @@ def test_randk_small_and_large_calls(gu, orc, pe, D, ratio, n, dtype):
     orc.adaptive_update(prm[n][0], ref, D, x, m, v, orc.make_opt(orc.OPT_ADAM, *hyper))
     for a, b in ((dx, x), (dm, m), (dv, v)):
         assert close(gu.to_host(a), b)
+
+
+def _randk_residual_close(q, got, ref, pe, ratio):
+    """The residual of random-k with scale d / k, got and the oracle's.  An element drawn m times has scale * q taken off
+    it m times, on either side in some order: each difference rounds at 2^-24 of a partial result, of which none is
+    larger than |q| + m scale |q|, and so does the product (2^-24 of scale |q|, m times the same)."""
+    q = q.astype(np.float64)
+    sizes = np.array([min(pe, q.size - p) for p in range(0, q.size, pe)])
+    scale = np.repeat([d / max(1, int(ratio * d)) for d in sizes], sizes)
+    off = np.abs(q - ref)                                   # m scale |q|
+    m = np.round(off / np.maximum(scale * np.abs(q), 1e-45))
+    bound = 2.0 ** -24 * (2 * m * (np.abs(q) + off) + off + np.abs(q)) * 1.01 + 1e-45
+    return bool(np.all(np.abs(got.astype(np.float64) - ref) <= bound))
+
+
+# k from a quarter of the partition on: tiles with more hits than their list has room for, which make their draws three
+# times where that is worth it, and sizes that take the launch in front instead
+@pytest.mark.parametrize("pe,D,ratio", [(8192, 9 * 8192 + 7, 1.0), (16384, 3 * 16384 + 5, 1.0), (16384, 40 * 16384 + 1, 1.0), (32768, 2 * 32768 + 100, 0.25),
+                                        (4096, 5 * 4096 + 4095, 0.3)])
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+def test_randk_tiles_with_many_hits(gu, orc, pe, D, ratio, dtype):
+    bpc = gu.bpc
+    rs = np.random.default_rng(D)
+    po, pb = gu.both_params(orc, "randk", pe, k_ratio=ratio, seed=3, stream_id=9, value_scale=-1.0)
+    g, res = (rs.standard_normal(D) * 1e-2).astype(dtype), (rs.standard_normal(D) * 1e-3).astype(np.float32)
+    q, rd, pay, ws = g.astype(np.float32) + res, gu.to_dev(res), gu.new_payload(pb, D), gu.new_ws(pb, D)
+    bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+    bpc.workspace_check(pb, D, ws)
+    ref = orc.compress(po, g, res)
+    _equal_randk(orc, po, gu.to_host(pay), ref, pe, D, ratio, exact=True)
+    assert _randk_residual_close(q, gu.to_host(rd), res, pe, ratio)
 
 
 def _equal_randk(orc, po, got, ref, pe, D, ratio, exact):
