@@ -262,13 +262,14 @@ def test_topk_heavy_tail(gu, orc, kind):
     assert np.array_equal(res_gpu.view(np.uint32), res_ref.view(np.uint32))
 
 
-def test_topk_sample_that_misleads(gu, orc):
-    """The short list is built from a guess taken from a sample of the partition (512 chunks of
+def test_topk_sample_that_misleads(gu, orc, geo):
+    """The short list is built from a guess taken from a sample of the partition (1024 chunks of
     eight elements; chunk c is chunk c*stride + (c*37) % stride of the partition, stride =
-    (d/8)/512).  Large values planted on 100 sampled elements only put the guess above all but
-    those 100, so the list comes out shorter than k and the selection has to fall back on the
-    whole partition; the record must be the oracle's all the same.  (Mirrors the sampling rule
-    of the kernel: if that changes, this test still passes but no longer takes that branch.)"""
+    (d/8)/1024).  Large values planted on 200 sampled elements only, more than the rank that is looked
+    for in the sample, put the guess above all but those 200, so the list comes out shorter than k and
+    the selection has to fall back on the whole partition; the record must be the oracle's all the
+    same."""
+    import ctypes
     pe = BIG_PE
     D = 2 * pe
     ratio = 0.011
@@ -276,17 +277,23 @@ def test_topk_sample_that_misleads(gu, orc):
     rs = np.random.default_rng(23)
     g = (0.5 * rs.random(D) - 0.25).astype(np.float32)
     e = np.zeros(D, np.float32)
-    stride = (pe // 8) // 512
-    c = np.arange(512)
+    chunks = int(geo.geo_sample_chunks(pe))
+    stride = (pe // 8) // chunks
+    c = np.arange(chunks)
     chunk = c * stride + (c * 37) % stride
     sampled = (8 * chunk[:, None] + np.arange(8)[None, :]).ravel()
-    planted = rs.choice(sampled, 100, replace=False)
-    g[planted] = (10.0 + rs.random(100)).astype(np.float32)          # partition 0 only
+    planted = rs.choice(sampled, 200, replace=False)
+    assert geo.geo_sample_rank(int(ratio * pe), 8 * chunks, pe) < 200 < int(ratio * pe)
+    g[planted] = (10.0 + rs.random(200)).astype(np.float32)          # partition 0 only
     res_ref = e.copy()
     pay_ref = orc.compress(po, g, res_ref)
-    pay_gpu, res_gpu = gu.gpu_compress(pb, g, e.copy())
-    assert defined_equal("topk", pay_gpu, pay_ref, po, orc, D, pe, dict(k_ratio=ratio))
-    assert np.array_equal(res_gpu.view(np.uint32), res_ref.view(np.uint32))
+    rd, pay, ws = gu.to_dev(e), gu.new_payload(pb, D), gu.new_ws(pb, D)
+    gu.bpc.bpc_compress(pb, gu.to_dev(g), rd, pay, ws)
+    gu.bpc.workspace_check(pb, D, ws)
+    assert defined_equal("topk", gu.to_host(pay), pay_ref, po, orc, D, pe, dict(k_ratio=ratio))
+    assert np.array_equal(gu.to_host(rd).view(np.uint32), res_ref.view(np.uint32))
+    at = int(geo.geo_topk_state(ctypes.byref(pb), D))
+    assert gu.to_host(ws[at:at + 64]).view(np.uint32).reshape(2, 8)[:, 1].tolist() == [1, 0]   # (left to the long form)
 
 
 @pytest.mark.parametrize("kind", ["dither", "natdither"])
