@@ -9,7 +9,8 @@
 // +-(nu_i * level) / s (16 consecutive floats: lanes never conflict on a bank).  With the
 // number of workers known at compile time the workgroup has 512 threads and two rows, so that
 // all its words of all workers are requested at once and still fit the register file next to
-// e~ and the sums; otherwise 256 threads, four rows and a rolled loop over the workers.
+// e~ and the sums; otherwise a rolled loop over the workers, with 256 threads and four rows, or, where there
+// are bit planes, 512 threads and two rows.
 #include "dither_common.hpp"
 #include "sources.hpp"
 
@@ -64,7 +65,7 @@ __device__ inline uint32_t lds_address(const float *p) {
 // Bound by its vector instructions; in place of the three passes over the messages' planes (whose sums are
 // formed twice, a plane's bits picked one by one): 31 levels, 5 workers, 1 M / 3 M elements 27 -> 11 / 41 -> 16 us;
 // 63 levels, 4 workers, 100 M 888 -> 260; 31 levels, 16 workers, 100 M 1678 -> 462; 15 levels, 5 workers, 100 M f16
-// 801 -> 276.  The forms with NW > 0 stay for 15 levels (8 workers, 100 M: 273 us): their tables hold signed values.
+// 801 -> 276.  The forms with NW > 0 stay for 15 levels (8 workers, 100 M: 256 to 262 us): their tables hold signed values.
 template <bool EF, bool LINF, int NW, bool NAT, bool WIDE = false>
 struct DitherServerOp {
   static constexpr bool kAnyWide = WIDE && NW == 0;

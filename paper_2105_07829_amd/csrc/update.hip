@@ -1263,7 +1263,9 @@ hipError_t adaptive_update(const Geo &g, const bpc_params_t &prm, const uint8_t 
     const uint32_t *table = nullptr;
     const uint2 *pairs = nullptr;
     // small calls go without the launch that makes the table (top-k, Adam-style: 0.3 M elements 13.5 -> 6.7 us, 2 M
-    // 13.3 -> 9.7; LANS over the partitions, 4 M, 26.3 -> 24.2)
+    // 13.3 -> 9.7; LANS over the partitions, 4 M, 26.3 -> 24.2; LANS over blocks, whose two passes search or draw each for
+    // itself, at the largest sizes that go without it: top-k, 4 M, 37.1 -> 32.7, random-k, 1 M, k = 3 %, 47.6 -> 28.2, and 2 M,
+    // k = 1 %, 29.4 -> 24.3)
     const uint32_t tiles_all = (uint32_t)cdiv(g.D, 1ull << shift);
     if (tiles_all <= kOwnTiles && (prm.kind != BPC_RANDK || randk_draws_again(g, tiles_all, 1, lans ? kBThreads : kThreads))) {
       const int mode = prm.kind == BPC_RANDK ? 2 : prm.kind == BPC_TOPK16 ? 1 : 0;
