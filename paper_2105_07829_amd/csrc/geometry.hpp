@@ -215,10 +215,11 @@ struct WsLayout {
   size_t guess;      // u32[P]: not used (the sizes stay what bpc_workspace_bytes() has always answered)
   size_t starts;     // u32[kMaxWorkers * P * (groups of 8192 elements per partition + 1)]: where each group's
                      // entries start in each worker's top-k message (server side)
-  size_t samp;       // 16 KB a partition: the keys from which elements go to the top-k short lists, two u64 a partition, and,
+  size_t samp;       // 16 KB a partition: the keys from which elements go to the top-k short lists, four u64 a partition, and,
                      // 4 KB apart, the lengths of the lists
   size_t cand;       // u32[P * kTopkListCap] indices, then as many value bits: top-k short lists of the partitions
-  size_t tilecnt;    // u32[2*n_tiles]: per-tile (greater, equal) counts of the long form of top-k; the lengths of its group lists
+  size_t tilecnt;    // u32[2*n_tiles]: per-tile (greater, equal) counts of the long form of top-k; the lengths of its group lists,
+                     // and the ties beside its lists
   size_t slots;      // double[3 * tiles of kSTile]: partition-wide reductions of the single-pass kernels
                      // (one per tile, two words per tile in a launch with a tag; three for the LANS block norms;
                      // LANS with caller-defined blocks: its pairs, which go on into `norms` and beyond)

@@ -20,18 +20,18 @@
 // the server side a kernel in front sums the sampled chunks up and finds where each message's entries of a
 // group of 8192 elements begin.
 // The sample only decides how much work the selection is, never its result: a partition whose
-// short list came out shorter than k or longer than its room (the sample misled) is taken by the long form below
-// instead, run by the
-// partition's first select workgroup alone; partitions of more than kAloneElems elements by one more
-// kernel, enqueued behind, which returns at once if no partition needs it and else runs the
-// long form's passes for those partitions with its resident grid meeting between the passes.
+// short list came out shorter than k or longer than its room (the sample misled) is taken by the long form
+// below instead, run by the partition's first select workgroup alone; partitions of more than kAloneElems
+// elements by one more kernel, enqueued behind, which returns at once if no partition needs it and else runs
+// the long form's passes for those partitions with its resident grid meeting between the passes.
 // A key that a great many elements share (zeros, magnitudes of few values) is left off the list, which starts
 // above it; if the list then holds fewer than k, it is kept whole, and ties of that key make up for the rest,
 // lowest index first: the load pass has counted them per group of 8192 elements, so every select workgroup knows how
 // far they are kept and reads its part of the vector again as far as that.
 //
-// Group-list form (larger k, up to kMostListed of a full partition, where the dense workspace is free): the
-// same guess and load pass, but every group of 8192 elements has a list of its own in the dense workspace.
+// Group-list form (larger k, up to kMostListed of a full partition, or lists that would be too long, in partitions
+// of up to kAloneElems elements, where the dense workspace is free): the same guess and load pass, but every
+// group of 8192 elements has a list of its own in the dense workspace.
 //   bins       : histogram of the listed keys' distances from the guess, 32 steps for every power of two
 //   collect    : the bin of the k-th largest key from it; per group, how many entries lie above the bin;
 //                the few entries inside it to one list a partition, and whether they are all of one key
@@ -106,10 +106,9 @@ enum : uint32_t { kLongForm = 1, kTiesBeside = 2 };
 
 // What the load pass of the short-list form hands from workgroup to workgroup, in the workspace's
 // region for it (16 KB a partition): the guesses, four words each (the guess and whether there are ties beside
-// the list, its exclusive or with
-// the launch's tag, as the slots of cluster.hpp, and the tag once a workgroup has taken the guess on), and
-// the lengths of the lists, a page apart since an atomic on global memory holds up its memory channel for
-// some 11 ns.
+// the list, its exclusive or with the launch's tag, as the slots of cluster.hpp, and the tag once a workgroup
+// has taken the guess on), and the lengths of the lists, a page apart since an atomic on global memory holds
+// up its memory channel for some 11 ns.
 //
 // The first workgroups of the launch make the guesses, and the others wait for them.  Its grid is not resident
 // as a whole, and workgroups are bound to an XCD by their index: beside another kernel that waits (a second

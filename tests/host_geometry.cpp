@@ -30,7 +30,7 @@ void geo_block_tiles(uint64_t lo, uint64_t hi, uint64_t D, uint64_t *t0, uint64_
   *n = t.n;
 }
 // Byte offset in a workspace of the selection state of a top-k call: eight words a partition, the second
-// of them non-zero where the partition was left to the long form.
+// of them 1 where the partition was left to the long form, 2 where ties beside its list are kept.
 uint64_t geo_topk_state(const bpc_params_t *p, uint64_t D) { return bpc::ws_layout(p, D).state; }
 // The rows of workgroups in front of a top-k server's load pass: threads, slots, chunks, sums, messages, pieces, roles, starts.
 void geo_prep_rows(uint32_t n, uint32_t k_cap, uint32_t d, int guesses, uint32_t out[8]) {

@@ -100,7 +100,8 @@ def test_server_calls_that_go_without_the_preset(gu, kind, n, D, tagged):
 
 
 def _long_form(gu, geo, prm, D, ws):
-    """Which partitions of the last top-k call on `ws` were left to the long form."""
+    """For which partitions of the last top-k call on `ws` the list alone did not do (ties are kept beside it, or the
+    partition was left to the long form)."""
     at = int(geo.geo_topk_state(ctypes.byref(prm), D))
     words = gu.to_host(ws[at:at + 32 * -(-D // prm.part_elems)]).view(np.uint32).reshape(-1, 8)
     return words[:, 1] != 0
@@ -111,8 +112,8 @@ def _long_form(gu, geo, prm, D, ws):
 def test_topk_many_partitions(gu, orc, geo, kind, pe, P, overrun):
     """The select pass with one, two and four workgroups a partition (more than 128 partitions, 65 to
     128, fewer), and with more partitions than the device holds of its workgroups.  Partitions of equal
-    magnitudes have more tied keys than the short list has room (32768) and are left to the long
-    form, the others of the same call are not; in partitions of 4096 elements even equal
+    magnitudes have more tied keys than the short list has room (32768), so their list alone does not
+    do, that of the others of the same call does; in partitions of 4096 elements even equal
     magnitudes or zeros fit the list."""
     bpc = gu.bpc
     D = (P - 1) * pe + 1001
@@ -345,8 +346,8 @@ def test_topk_without_error_feedback(gu, orc, geo, kind, dtype, pe, D, equal):
 @pytest.mark.parametrize("pe,D,ratio", [(524288, 524288 + 1, 0.04), (524288, 2 * 524288 - 8192 + 5, 0.0625), (1_048_576, 300_007, 0.03), (1_048_576, 1_048_576 + 8192 * 9, 0.03)])
 @pytest.mark.parametrize("what", ["normal", "ties", "narrow", "equal", "one layer"])
 def test_topk_group_lists(gu, orc, geo, kind, ef, n, pe, D, ratio, what):
-    """Forms of the distribution: ties at the threshold, magnitudes within 2^-14 of each other, all equal (left
-    to the long form), and a stretch of a partition that holds most of what is listed (more than its groups'
+    """Forms of the distribution: ties at the threshold, magnitudes within 2^-14 of each other, all equal (kept
+    beside the lists), and a stretch of a partition that holds most of what is listed (more than its groups'
     lists have room for)."""
     bpc = gu.bpc
     po, pb = gu.both_params(orc, kind, pe, k_ratio=ratio)
